@@ -11,17 +11,12 @@
 // transpose is needed anywhere.  One workgroup = 8 waves = 4 vocabulary tiles x 2 halves of the
 // contraction, producing a [128 vocab x 128 rows] block; the two halves are added through LDS.
 // With up to 128 rows (a verification batch) the weight matrix is read exactly once and the kernel
-// is bound by that read.  More rows go to a second kernel (below) whose row blocks are scheduled
-// next to each other on one XCD so that a weight tile is served by that XCD's L2.
+// is bound by that read.  More rows go to a second kernel (below).
 //
 // Both operands are staged global -> registers -> LDS in 64-wide slices of the contraction
 // (rows padded to 144 bytes: conflict-free 16-byte operand reads), the weights three slices ahead,
 // one barrier per slice.  Weight slices are private to their wave; hidden slices are shared by the four waves of a
 // half.
-#include <stdlib.h>
-
-#include <type_traits>
-
 #include "common.h"
 #include "kernels.h"
 
@@ -42,14 +37,12 @@ constexpr int kLmWBuf = 32 * kLmPitch;              // one weight slice of one w
 constexpr int kLmHidBytes = 2 * 2 * kLmHidBuf;      // 2 halves x 2 buffers
 constexpr int kLmWBytes = 8 * 2 * kLmWBuf;          // 8 waves x 2 buffers
 constexpr int kLmLds = kLmHidBytes + kLmWBytes;     // 147456 bytes
-constexpr int kLmBlocksPerSeg = 8192 / kLmVB;       // block statistics per statistics segment
 static_assert(4 * 64 * 64 * 4 <= kLmHidBytes, "split-K hand-over fits the hidden buffers");
-static_assert(kLmBlocksPerSeg == 64, "one wave merges one segment");
+static_assert(8192 / kLmVB <= kWave, "one wave merges one segment");
 
 struct LmParams {
   int rows, K, V;
   int nvb, nrb, total, per_xcd;
-  int panel;               // wide kernel: vocabulary blocks per panel (0: row blocks of a vocabulary block adjacent)
   float c;
   const uint16_t* hidden;
   const uint16_t* weight;
@@ -260,318 +253,283 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_kernel(LmParams P) {
 }
 
 // ----------------------------------------------------------------------------------
-// More than 128 rows: the product is bound by the matrix cores, and what limits them is operand
-// delivery.  Each wave owns a [128 vocab x 64 rows] tile (8 accumulator tiles); the eight waves of a
-// workgroup (two per SIMD, one workgroup per CU) share one 128-entry weight slice in LDS (each
-// weight operand read feeds two matrix instructions) and cover 512 rows, so the slice is fetched and
-// staged once per 512 rows.  The hidden operands never touch LDS: a small pre-pass re-lays
-// the hidden states out in the order the matrix instruction reads them, so that one load
-// instruction fetches 1 KB of contiguous memory (8 cache lines instead of 64 for a row-major
-// operand, whose lanes walk down 32 different rows - the L1 tag rate, one line per clock, is what
-// bounds such loads).  Inside a 64-wide slice the contraction index is permuted (lane half h, step
-// j, element i  <->  k = 32 h + 8 j + i) in both operands alike.
+// More than 128 rows.  A workgroup of 8 waves (two per SIMD, one workgroup per CU) computes [256 vocab x 16 NT2 rows];
+// wave w owns 64 vocabulary entries, and the waves w and w + 4 (one SIMD) share the row tiles between them.  Both
+// operands go from memory to LDS directly (global_load_lds, 16 bytes per lane, no registers) in 64-wide slices of the
+// contraction, weights two slices ahead (they come from HBM).  The rows of a slice are 128 bytes without padding;
+// 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7), so the 16 rows one operand read touches spread over all
+// banks.
 //
-// Packed hidden states: [row tile of 32][slice][step j = 0..3][lane 0..63] x 16 bytes,
-// lane L holding hidden[32 tile + L % 32][64 slice + 32 (L / 32) + 8 j .. + 8]; rows past the end
-// are zero.
-//
-// A last row block with few rows costs more than its rows: it needs one more pass over the weight
-// matrix (from the memory-side cache at best), so the row count at which the product is cheapest per
-// row is a multiple of 512.  Up to 32 remaining rows are handled by splitting the contraction over
-// the waves of the workgroup (below); more than that keeps the ordinary path with some waves idle.
+// Matrix work never waits for a barrier: the operands of a 32-deep step are read from LDS into registers while the
+// step before is multiplied, across the slice boundary too.  The one barrier of a slice sits between its two steps:
+// behind it every wave has read slice i completely (its buffers are refilled at once) and slice i + 1 has landed.
 // ----------------------------------------------------------------------------------
-constexpr int kLwThreads = 512;
-constexpr int kLwRB = kLwThreads;                   // hidden rows per workgroup (64 per wave)
-constexpr int kLwStage = kLmVB * 8 / kLwThreads;     // 16-byte loads per thread and weight slice (128 rows x 8)
-constexpr int kLwStageRows = kLwThreads / 8;        // rows covered by one such load of the workgroup
-static_assert(kLwStage * kLwStageRows == kLmVB && kLwStage * kLwThreads * 16 == kLmVB * kLmKC * 2, "staging covers one weight slice exactly");
-constexpr int kLwLds = 8 * kLmHidBuf;               // two shared weight slices; a partial last row block: one per wave
-static_assert(8 * 64 * 64 * 4 <= kLwLds, "the partial tiles of a split contraction fit");
+constexpr int kTlThreads = 512;
+constexpr int kTlVB = 256;                          // vocabulary entries per workgroup
+constexpr int kTlSlice = 128;                       // bytes of a row per slice (64 bf16)
+constexpr int kTlABuf = kTlVB * kTlSlice;           // one weight slice
+constexpr int kTlABufs = 3;
+constexpr int kTlOutPitch = kTlVB * 2 + 16;         // bytes per row of the output tile in LDS
+// hidden slices: two ahead like the weights where the LDS (160 KB) allows, else one (they stay in L2)
+constexpr int tl_bbufs(int NT2) { return NT2 <= 10 ? 3 : 2; }
+constexpr int tl_lds(int NT2) {
+  const int loop = kTlABufs * kTlABuf + tl_bbufs(NT2) * 16 * NT2 * kTlSlice;
+  const int epi = 16 * NT2 * (kTlOutPitch + 4 * 8);          // output tile, then (max, sum) per row and vocabulary quarter
+  return loop > epi ? loop : epi;
+}
+static_assert(tl_lds(16) <= 160 * 1024 && tl_lds(10) <= 160 * 1024, "one workgroup per compute unit");
 
-__global__ __launch_bounds__(256) void lm_pack_hidden_kernel(const uint16_t* __restrict__ hidden, int rows, int K,
-                                                             int64_t n_items, lm_u32x4* __restrict__ packed) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (idx >= n_items) return;
-  const int nch = K / kLmKC;
-  const int L = static_cast<int>(idx & 63);
-  const int j = static_cast<int>((idx >> 6) & 3);
-  const int64_t blk = idx >> 8;                      // tile * nch + slice
-  const int c = static_cast<int>(blk % nch);
-  const int64_t row = (blk / nch) * 32 + (L & 31);
-  lm_u32x4 v = {0u, 0u, 0u, 0u};
-  if (row < rows) v = *reinterpret_cast<const lm_u32x4*>(hidden + row * K + c * kLmKC + 32 * (L >> 5) + 8 * j);
-  packed[idx] = v;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float lm_f32x4;
+
+// 16 bytes per lane from base + off to LDS: lane i's land at byte lds_at + 16 i.  Not tracked by the compiler: the
+// loop counts these loads itself (vmcnt).
+__device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned off, unsigned lds_at) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds_at), "v"(off), "s"(base) : "memory", "m0");
 }
 
-template <int PF2>
-__global__ __launch_bounds__(kLwThreads) void lm_head_wide_kernel(LmParams P, const lm_u32x4* __restrict__ packed) {
-  extern __shared__ __align__(16) unsigned char lm_lds[];
-  const int id = blockIdx.x;
-  int rbk, vb;
-  if (P.panel > 0) {
-    // vocabulary panels small enough for the memory-side cache: inside a panel all workgroups of row
-    // block 0 come first, then row block 1 ... (consecutive ids spread over all XCDs), so that the
-    // panel's weights are read from HBM once and by the later row blocks from that cache
-    if (id >= P.total) return;
-    const int per_panel = P.panel * P.nrb;
-    const int pn = id / per_panel, rem = id - pn * per_panel;
-    const int width = min(P.panel, P.nvb - pn * P.panel);
-    rbk = rem / width;
-    vb = pn * P.panel + rem - rbk * width;
-  } else {
-    const int logical = (id & 7) * P.per_xcd + (id >> 3);
-    if (logical >= P.total) return;
-    rbk = logical % P.nrb; vb = logical / P.nrb;
-  }
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ln = lane & 31, lh = lane >> 5;
-  const int v0 = vb * kLmVB;
-  const int r0 = rbk * kLwRB + wave * 64;             // this wave's first row
-  const int left = P.rows - r0;
-  // row tiles of this wave that hold rows; in a scalar register, so that the branches on it are scalar
-  const int ntc = __builtin_amdgcn_readfirstlane(left >= 64 ? 2 : (left <= 0 ? 0 : (left + 31) >> 5));
-  const int nch = P.K / kLmKC;
+// The product of one wave with NT row tiles of the workgroup's NT2, up to the rounded output tile and the per-row
+// statistics of its 64 vocabulary entries in LDS.  Waves of a workgroup may run it with different NT: every copy
+// passes the same barriers and issues the same loads.
+//
+// What bounds it: the matrix cores under the chip's power limit (1024 x 4096 x 128256: busy 70 % of the cycles at
+// 1.67 GHz).  A [64 vocab x 128 rows] tile per wave reads 12 KB of LDS per 32 matrix instructions (a third of the LDS
+// rate) and a workgroup fetches 64 KB per 2048 matrix cycles; 16-row granularity keeps padded rows out of the products
+// (1040 rows: 5 x 208).  Measured against the kernel this replaces (hidden operands packed by a kernel of their own and
+// read from L2 by every wave, weights through registers): 1040 x 4096 x 128256 1095 -> 856 us (1.28 PFLOP/s), 429 x
+// 8192 x 128256 909 -> 734 us, 512 x 4096 x 128256 506 -> 439 us, 224 x 4096 x 32000 89 -> 82 us, 200 x 8192 x 128256
+// 563 -> 427 us (5.0 TB/s: bound by the weights from here down), 150 x 2048 x 8000 36 -> 19 us.
+template <int NT2, int NT>
+__device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* lm_lds, int wave, int v0, int r0) {
+  constexpr int kRows = 16 * NT2;
+  constexpr int kBBufs = tl_bbufs(NT2);
+  constexpr int kBBuf = kRows * kTlSlice;
+  constexpr int kBLoads = kRows / 8;                // load instructions per hidden slice (8 rows each), dealt to 8 waves
+  constexpr int kBPer = (kBLoads + 7) / 8;          // ... at most per wave
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  const int wm = wave & 3, row0 = (wave >> 2) * 16 * ((NT2 + 1) / 2);      // this wave's first row in the tile
+  const int nch = P.K / 64, last = nch - 1;
 
-  // weight slice: 128 entries x 128 bytes, 8 lanes per row
-  const uint16_t* wsrc[kLwStage];
-  int wdst[kLwStage];
+  // ---- loads: instruction j of a wave covers 8 rows, 8 lanes per row ----
+  const int lr = lane >> 3, lp = lane & 7;
+  unsigned aoff[4], boff[kBPer];
 #pragma unroll
-  for (int j = 0; j < kLwStage; ++j) {
-    int vrow = v0 + (tid >> 3) + kLwStageRows * j;
-    vrow = vrow < P.V ? vrow : P.V - 1;
-    wsrc[j] = P.weight + static_cast<int64_t>(vrow) * P.K + (tid & 7) * 8;
-    wdst[j] = ((tid >> 3) + kLwStageRows * j) * kLmPitch + (tid & 7) * 16;
+  for (int j = 0; j < 4; ++j) {
+    const int ra = wave * 32 + j * 8 + lr;
+    aoff[j] = static_cast<unsigned>(min(ra, P.V - 1 - v0)) * static_cast<unsigned>(P.K) * 2u + ((lp ^ ((ra >> 1) & 7)) << 4);
   }
-  // packed hidden operands of this wave's two row tiles (a wave without rows reads tile 0)
-  const int tile0 = ntc > 0 ? (r0 >> 5) : 0;
-  const lm_u32x4* hsrc[2];
-  hsrc[0] = packed + static_cast<int64_t>(tile0) * nch * 256 + lane;
-  hsrc[1] = packed + static_cast<int64_t>(ntc > 1 ? tile0 + 1 : tile0) * nch * 256 + lane;
+#pragma unroll
+  for (int j = 0; j < kBPer; ++j) {
+    const int rb = (wave + 8 * j) * 8 + lr;
+    boff[j] = static_cast<unsigned>(min(rb, P.rows - 1 - r0)) * static_cast<unsigned>(P.K) * 2u + ((lp ^ ((rb >> 1) & 7)) << 4);
+  }
+  const unsigned char* abase = reinterpret_cast<const unsigned char*>(P.weight + static_cast<int64_t>(v0) * P.K);
+  const unsigned char* bbase = reinterpret_cast<const unsigned char*>(P.hidden + static_cast<int64_t>(r0) * P.K);
+  const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>(
+      (__attribute__((address_space(3))) unsigned char*)lm_lds));
+  // slices past the end repeat the last one into a buffer nobody reads any more: every slice issues the same loads
+  auto load_a = [&](int s, int buf, int j) __attribute__((always_inline)) {
+    load_to_lds(abase + min(s, last) * kTlSlice, aoff[j], lds0 + buf * kTlABuf + (wave * 32 + j * 8) * kTlSlice);
+  };
+  auto load_b = [&](int s, int buf, int j) __attribute__((always_inline)) {
+    if (8 * j + 7 < kBLoads || wave + 8 * j < kBLoads)
+      load_to_lds(bbase + min(s, last) * kTlSlice, boff[j], lds0 + kTlABufs * kTlABuf + buf * kBBuf + (wave + 8 * j) * 8 * kTlSlice);
+  };
 
-  lm_f32x16 acc[4][2];
+  // ---- operand reads: lane l holds row l % 16 of a 16-row tile, contraction entries 8 (l / 16) .. + 8 of a 32-deep step ----
+  const int pos0 = ((lane >> 4) ^ ((lane & 15) >> 1)) << 4;                  // step 0; step 1 is the same with bit 6 flipped
+  const int a_lane = (wm * 64 + (lane & 15)) * kTlSlice + pos0;
+  const int b_lane = kTlABufs * kTlABuf + (row0 + (lane & 15)) * kTlSlice + pos0;
+  lm_u32x4 a0[4], b0[NT], a1[4], b1[NT];
+  auto read_op = [&](int at, int t) { return *reinterpret_cast<const lm_u32x4*>(lm_lds + at + t * 16 * kTlSlice); };
+
+  lm_f32x4 acc[4][NT];
 #pragma unroll
   for (int mi = 0; mi < 4; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
+    for (int ni = 0; ni < NT; ++ni)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0.f;
 
-  // The whole slice loop exists three times - two, one or no row tile in this wave - and one scalar
-  // branch picks the copy: branches inside the loop would split the accumulators' live ranges.
-  // Every copy passes the same barriers.
-  auto slice_loop = [&](auto n_tiles, auto ahead) {
-    constexpr int NT = decltype(n_tiles)::value;
-    // Weight slices are fetched PF slices ahead into a ring of PF - 1 register sets (8 registers per
-    // set).  With up to 256 rows the product is bound by streaming the weights from HBM and two slices
-    // ahead is a load latency short (kernel instance PF2 = 4); with more rows it is bound by the
-    // matrix cores and the shorter ring measured faster (PF2 = 2).  Waves of a partial block have
-    // little matrix work per slice to hide a load behind and always use the deep ring.  Hidden
-    // operands: one set per HB slices ahead.
-    constexpr int PF = decltype(ahead)::value;
-    constexpr int R = PF - 1;
-    constexpr int HB = NT == 2 ? 1 : R;
-    lm_u32x4 wring[R][kLwStage];
-    auto load_weight = [&](int c, lm_u32x4 (&w)[kLwStage]) {
+  // slices 0, 1, 2 of the weights and 0, 1 (2) of the hidden rows; then wait for slice 0
 #pragma unroll
-      for (int j = 0; j < kLwStage; ++j) w[j] = *reinterpret_cast<const lm_u32x4*>(wsrc[j] + c * kLmKC);
-    };
-    auto store_weight = [&](int buf, const lm_u32x4 (&w)[kLwStage]) {
+  for (int s = 0; s < 3; ++s) {
+    if (s < kBBufs)
 #pragma unroll
-      for (int j = 0; j < kLwStage; ++j) *reinterpret_cast<lm_u32x4*>(lm_lds + buf * kLmHidBuf + wdst[j]) = w[j];
-    };
-    const int last = nch - 1;
-    // Hidden operands: slice s lives in set s mod HB.  With two row tiles there is one set, reloaded
-    // step by step with the next slice; with one tile there are three, so that this wave, which has
-    // half the matrix work per slice, does not wait a load latency per slice either.
-    lm_u32x4 b[HB][2][4];
-    {
-      lm_u32x4 w0[kLwStage];
-      load_weight(0, w0);
-      if constexpr (NT > 0) {
+      for (int j = 0; j < kBPer; ++j) load_b(s, s, j);
 #pragma unroll
-        for (int r = 0; r < HB; ++r) {
-          const int cs = r < last ? r : last;
+    for (int j = 0; j < 4; ++j) load_a(s, s, j);
+  }
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(8 + (kBBufs - 1) * (kBLoads / 8)) : "memory");
+  __builtin_amdgcn_s_barrier();
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+  for (int mi = 0; mi < 4; ++mi) a0[mi] = read_op(a_lane, mi);
 #pragma unroll
-            for (int ni = 0; ni < NT; ++ni) b[r][ni][j] = hsrc[ni][(cs * 4 + j) * 64];
+  for (int ni = 0; ni < NT; ++ni) b0[ni] = read_op(b_lane, ni);
+
+  // One 32-deep step: the products of (a, b) with the reads of the next step's operands (an, bn) between them.
+  auto step = [&](const lm_u32x4 (&a)[4], const lm_u32x4 (&b)[NT], lm_u32x4 (&an)[4], lm_u32x4 (&bn)[NT], int a_at, int b_at,
+                  auto&& extra) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ni = 0; ni < NT; ++ni) {
+      // the 4 + NT operand reads spread over the first NT - 1 groups of four products
+#pragma unroll
+      for (int u = 0; u < 4 + NT; ++u)
+        if (u * (NT - 1) / (4 + NT) == ni) {
+          if (u < 4) an[u] = read_op(a_at, u);
+          else bn[u - 4] = read_op(b_at, u - 4);
         }
-      }
-      store_weight(0, w0);
-    }
+      extra(ni);
 #pragma unroll
-    for (int r = 0; r < R; ++r) load_weight(1 + r < last ? 1 + r : last, wring[r]);
-    __syncthreads();
-    // Loads and stores for the slices ahead are issued unconditionally (past the end they repeat the
-    // last slice and are never used): a branch around a load would make every wait count after it
-    // pessimistic.  The ring slot of a slice is static: R slices per trip.
-    for (int c0 = 0; c0 < nch; c0 += R) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int c = c0 + r;
-        if (c < nch) {
-          const int buf = c & 1;
-          const int cb = c + HB < last ? c + HB : last;
-          const int cp = c + PF < last ? c + PF : last;
-          if constexpr (NT > 0) {
-            const unsigned char* wrd = lm_lds + buf * kLmHidBuf + ln * kLmPitch + lh * 64;
-            // weight operands are read one step ahead; a step's hidden operands are dead after its
-            // matrix instructions and are reloaded at once with those of HB slices later
-            lm_u32x4 a[2][4];
-#pragma unroll
-            for (int mi = 0; mi < 4; ++mi) a[0][mi] = *reinterpret_cast<const lm_u32x4*>(wrd + mi * 32 * kLmPitch);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              if (j < 3) {
-#pragma unroll
-                for (int mi = 0; mi < 4; ++mi)
-                  a[(j + 1) & 1][mi] = *reinterpret_cast<const lm_u32x4*>(wrd + mi * 32 * kLmPitch + 16 * (j + 1));
-              }
-#pragma unroll
-              for (int mi = 0; mi < 4; ++mi) {
-                acc[mi][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(lm_bf16x8, a[j & 1][mi]),
-                                                                     __builtin_bit_cast(lm_bf16x8, b[r % HB][0][j]), acc[mi][0], 0, 0, 0);
-                if constexpr (NT > 1)
-                  acc[mi][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(lm_bf16x8, a[j & 1][mi]),
-                                                                       __builtin_bit_cast(lm_bf16x8, b[r % HB][1][j]), acc[mi][1], 0, 0, 0);
-              }
-#pragma unroll
-              for (int ni = 0; ni < NT; ++ni) b[r % HB][ni][j] = hsrc[ni][(cb * 4 + j) * 64];
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-          store_weight(buf ^ 1, wring[r]);      // slice c + 1
-          load_weight(cp, wring[r]);            // slice c + PF takes its place
-          __syncthreads();
-        }
-      }
+      for (int mi = 0; mi < 4; ++mi)
+        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lm_bf16x8, a[mi]),
+                                                              __builtin_bit_cast(lm_bf16x8, b[ni]), acc[mi][ni], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // A row block of at most 32 rows (the remainder of rows / 512) would keep seven waves idle while
-  // the workgroup crawls through its 64 slices one load latency at a time.  Instead the eight waves
-  // split the contraction: wave w takes slices w, w + 8, ..., stages each in a weight buffer of its
-  // own (no workgroup barrier in the loop) and accumulates the same row tile; the eight partial
-  // tiles are then added through LDS into wave 0, which runs the ordinary epilogue.
-  const bool tail_block = __builtin_amdgcn_readfirstlane(P.rows - rbk * kLwRB) <= 32;     // the same in every wave
-  if (tail_block) {
-    unsigned char* mine = lm_lds + wave * kLmHidBuf;
-    const lm_u32x4* hs = packed + static_cast<int64_t>((rbk * kLwRB) >> 5) * nch * 256 + lane;
-    const int wrow = lane >> 3, wseg = lane & 7;
-    lm_u32x4 wl[16];
-    auto issue = [&](int c) {
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        int vrow = v0 + wrow + 8 * j;
-        vrow = vrow < P.V ? vrow : P.V - 1;
-        wl[j] = *reinterpret_cast<const lm_u32x4*>(P.weight + static_cast<int64_t>(vrow) * P.K + c * kLmKC + wseg * 8);
-      }
-    };
-    // slices of this wave: wave, wave + 8, ...; a wave without slices (d_model < 512) loads slice 0 and
-    // multiplies nothing.  (Two slices in flight per wave were no faster: what the remainder costs is
-    // one more pass over the weights.)
-    const int n_mine = wave < nch ? (nch - wave + 7) / 8 : 0;
-    issue(wave < nch ? wave : 0);
-    for (int i = 0; i < n_mine; ++i) {
-      const int c = wave + 8 * i;
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        *reinterpret_cast<lm_u32x4*>(mine + (wrow + 8 * j) * kLmPitch + wseg * 16) = wl[j];
-      lm_u32x4 b[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = hs[(c * 4 + j) * 64];
-      issue(c + 8 < nch ? c + 8 : c);                   // unconditional: the last one repeats this slice
-      const unsigned char* wrd = mine + ln * kLmPitch + lh * 64;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
-          const lm_u32x4 a = *reinterpret_cast<const lm_u32x4*>(wrd + mi * 32 * kLmPitch + 16 * j);
-          acc[mi][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(lm_bf16x8, a),
-                                                               __builtin_bit_cast(lm_bf16x8, b[j]), acc[mi][0], 0, 0, 0);
-        }
-      }
-    }
-    // add the eight partial tiles: 64 floats per lane and wave, 16 KB each
-    __syncthreads();
-    float* red = reinterpret_cast<float*>(lm_lds) + wave * (64 * 64);
-    if (wave > 0) {
-#pragma unroll
-      for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) red[(mi * 16 + r) * 64 + lane] = acc[mi][0][r];
-    }
-    __syncthreads();
-    if (wave == 0) {
-      for (int w = 1; w < kLwThreads / 64; ++w) {
-        const float* rw = reinterpret_cast<const float*>(lm_lds) + w * (64 * 64);
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[mi][0][r] += rw[(mi * 16 + r) * 64 + lane];
-      }
-    } else {
-      // the other waves hold partial sums of wave 0's rows, not tiles of their own
-#pragma unroll
-      for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mi][0][r] = 0.f;
-    }
-  } else {
-    using Deep = std::integral_constant<int, 4>;
-    if (ntc == 2) slice_loop(std::integral_constant<int, 2>{}, std::integral_constant<int, PF2>{});
-    else if (ntc == 1) slice_loop(std::integral_constant<int, 1>{}, Deep{});
-    else slice_loop(std::integral_constant<int, 0>{}, Deep{});
-  }
 
-  // each wave holds all 128 vocabulary entries of the block for its rows: statistics need no LDS
-  const bool aligned = (P.V & 7) == 0 && (reinterpret_cast<uintptr_t>(P.logits) & 15) == 0;
+  int abuf = 0, bbuf = 0;                           // buffers of slice i
+  for (int i = 0; i < nch; ++i) {
+    const int anext = abuf == 2 ? 0 : abuf + 1;
+    const int bnext = bbuf == kBBufs - 1 ? 0 : bbuf + 1;
+    step(a0, b0, a1, b1, (a_lane + abuf * kTlABuf) ^ 64, (b_lane + bbuf * kBBuf) ^ 64, [](int) {});
+    // this wave has read all of slice i (lgkmcnt) and its part of slice i + 1 is in LDS (vmcnt: the youngest loads,
+    // of slice i + 2, may still be on their way)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(4 + (kBBufs - 2) * (kBLoads / 8)) : "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    step(a1, b1, a0, b0, a_lane + anext * kTlABuf, b_lane + bnext * kBBuf, [&](int ni) __attribute__((always_inline)) {
 #pragma unroll
-  for (int ni = 0; ni < 2; ++ni) {
-    const int row = r0 + ni * 32 + ln;
-    const bool row_ok = row < P.rows;
-    uint16_t* out = P.logits + static_cast<int64_t>(row_ok ? row : 0) * P.V;
+      for (int j = 0; j < 4 + kBPer; ++j)
+        if (j * NT / (4 + kBPer) == ni) {
+          if (j < kBPer) load_b(i + kBBufs, bbuf, j);
+          else load_a(i + 3, abuf, j - kBPer);
+        }
+    });
+    abuf = anext;
+    bbuf = bnext;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();                      // the slice buffers are free
+
+  // ---- round, statistics of the rounded values, output tile to LDS ----
+  float2* sh_stat = reinterpret_cast<float2*>(lm_lds + kRows * kTlOutPitch);       // [4 vocabulary quarters][kRows]
+  const int vg0 = wm * 64 + 4 * (lane >> 4);         // this lane's entries of tile mi: vg0 + 16 mi + 0..3
+#pragma unroll
+  for (int ni = 0; ni < NT; ++ni) {
+    const int row = row0 + ni * 16 + (lane & 15);
+    float x[4][4];
     float m = -INFINITY;
-    float x[4][16];
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi) {
-      uint32_t b[16];
+      uint32_t b[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int vg = v0 + 32 * mi + 8 * g + 4 * lh;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = 4 * g + i;
-          b[r] = f32_to_bf16_rne(acc[mi][ni][r]);
-          x[mi][r] = (vg + i < P.V) ? __uint_as_float(b[r] << 16) : -INFINITY;
-          m = fmaxf(m, x[mi][r]);
-        }
+      for (int r = 0; r < 4; ++r) {
+        b[r] = f32_to_bf16_rne(acc[mi][ni][r]);
+        x[mi][r] = (v0 + vg0 + 16 * mi + r < P.V) ? __uint_as_float(b[r] << 16) : -INFINITY;
+        m = fmaxf(m, x[mi][r]);
       }
-      store_logit_tile(out, v0 + 32 * mi, lh, b, row_ok, aligned && v0 + 32 * mi + 32 <= P.V, P.V);
+      lm_u32x2 w;
+      w.x = b[0] | (b[1] << 16);
+      w.y = b[2] | (b[3] << 16);
+      *reinterpret_cast<lm_u32x2*>(lm_lds + row * kTlOutPitch + (vg0 + 16 * mi) * 2) = w;
     }
+    m = fmaxf(m, __shfl_xor(m, 16, kWave));
+    m = fmaxf(m, __shfl_xor(m, 32, kWave));
     const float mm = (m == -INFINITY) ? 0.f : m;
     float s = 0.f;
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s += fast_exp2((x[mi][r] - mm) * P.c);
-    const float mo = __shfl_xor(m, 32, kWave);
-    const float so = __shfl_xor(s, 32, kWave);
-    const float M = fmaxf(m, mo);
-    const float MM = (M == -INFINITY) ? 0.f : M;
-    const float mmo = (mo == -INFINITY) ? 0.f : mo;
-    const float S = s * fast_exp2((mm - MM) * P.c) + so * fast_exp2((mmo - MM) * P.c);
-    if (lh == 0 && row_ok) P.bstats[static_cast<int64_t>(row) * P.nvb + vb] = make_float2(M, S);
+      for (int r = 0; r < 4; ++r) s += fast_exp2((x[mi][r] - mm) * P.c);
+    s += __shfl_xor(s, 16, kWave);
+    s += __shfl_xor(s, 32, kWave);
+    if (lane < 16) sh_stat[wm * kRows + row] = make_float2(m, s);
   }
 }
 
-// One wave per (row, 8192-class segment): the 64 block statistics of the segment become the entry
-// the acceptance walk reads.
-__global__ __launch_bounds__(kWave) void lm_stats_merge_kernel(const float2* __restrict__ bstats, int nvb, int nseg,
+template <int NT2>
+__global__ __launch_bounds__(kTlThreads) void lm_head_tile_kernel(LmParams P) {
+  extern __shared__ __align__(16) unsigned char lm_lds[];
+  constexpr int kRows = 16 * NT2;
+  // the row blocks of one vocabulary block run next to each other on one XCD: its L2 serves the weights to all of them
+  const int id = blockIdx.x;
+  const int logical = (id & 7) * P.per_xcd + (id >> 3);
+  if (logical >= P.total) return;
+  const int rbk = logical % P.nrb, vb = logical / P.nrb;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int v0 = vb * kTlVB, r0 = rbk * kRows;
+  if constexpr (NT2 % 2 == 0) {
+    lm_tile_wave<NT2, NT2 / 2>(P, lm_lds, wave, v0, r0);
+  } else {
+    if (wave < 4) lm_tile_wave<NT2, (NT2 + 1) / 2>(P, lm_lds, wave, v0, r0);
+    else lm_tile_wave<NT2, NT2 / 2>(P, lm_lds, wave, v0, r0);
+  }
+  __syncthreads();
+  const float2* sh_stat = reinterpret_cast<const float2*>(lm_lds + kRows * kTlOutPitch);
+  const int rows_here = min(kRows, P.rows - r0), cols = min(kTlVB, P.V - v0);
+  if (tid < rows_here) {
+    float M = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) M = fmaxf(M, sh_stat[i * kRows + tid].x);
+    const float MM = (M == -INFINITY) ? 0.f : M;
+    float S = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float2 st = sh_stat[i * kRows + tid];
+      S += st.y * fast_exp2(((st.x == -INFINITY ? 0.f : st.x) - MM) * P.c);
+    }
+    P.bstats[static_cast<int64_t>(r0 + tid) * P.nvb + vb] = make_float2(M, S);
+  }
+  uint16_t* out = P.logits + static_cast<int64_t>(r0) * P.V + v0;
+  if (cols == kTlVB && (P.V & 7) == 0 && (reinterpret_cast<uintptr_t>(P.logits) & 15) == 0) {
+    for (int row = tid >> 5; row < rows_here; row += kTlThreads / 32)
+      *reinterpret_cast<lm_u32x4*>(out + static_cast<int64_t>(row) * P.V + (tid & 31) * 8) =
+          *reinterpret_cast<const lm_u32x4*>(lm_lds + row * kTlOutPitch + (tid & 31) * 16);
+  } else {
+    for (int i = tid; i < rows_here * kTlVB; i += kTlThreads) {
+      const int row = i / kTlVB, v = i % kTlVB;
+      if (v < cols) out[static_cast<int64_t>(row) * P.V + v] = *reinterpret_cast<const uint16_t*>(lm_lds + row * kTlOutPitch + v * 2);
+    }
+  }
+}
+
+template <int NT2>
+static int launch_lm_tile(const LmParams& P, hipStream_t stream) {
+  static std::atomic<uint64_t> attr_done{0};
+  if (set_lds_once(&lm_head_tile_kernel<NT2>, tl_lds(NT2), attr_done) != 0) return -1;
+  hipLaunchKernelGGL((lm_head_tile_kernel<NT2>), dim3(P.per_xcd * 8), dim3(kTlThreads), tl_lds(NT2), stream, P);
+  return 0;
+}
+
+// Row tiles per workgroup: the split of the rows whose rounds over the chip cost least.  A slice costs its matrix work,
+// proportional to the row tiles, plus a part that does not depend on them (weight traffic, barrier), about three tiles'
+// worth.  Measured over all choices (us): 1040 x 4096 x 128256 13 tiles 856, 14 896, 12 943, 16 988, 10 972; 429 x 8192 x
+// 128256 14 tiles 736, 15 771, 16 810, 10 831, 13 984; 224 x 4096 x 32000 8 tiles 81, 10 89, 14 92, 2 171; 150 x 2048 x
+// 8000 2 tiles 19, 4 22, 14 42: the rule takes the fastest each time.
+constexpr int kTlFixed = 3;
+static int lm_tile_rows(int rows, int V, int n_cu) {
+  static constexpr int kChoices[] = {16, 15, 14, 13, 12, 11, 10, 8, 6, 4, 2};
+  const int64_t nvb = (V + kTlVB - 1) / kTlVB;
+  int best = 16;
+  int64_t best_cost = -1;
+  for (const int nt2 : kChoices) {
+    const int64_t nrb = (rows + 16 * nt2 - 1) / (16 * nt2);
+    const int64_t cost = ((nvb * nrb + n_cu - 1) / n_cu) * (nt2 + kTlFixed);
+    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = nt2; }
+  }
+  return best;
+}
+
+// One wave per (row, 8192-class segment): the block statistics of the segment (per_seg <= 64 of them) become the
+// entry the acceptance walk reads.
+__global__ __launch_bounds__(kWave) void lm_stats_merge_kernel(const float2* __restrict__ bstats, int nvb, int per_seg, int nseg,
                                                                float c, SegStat* __restrict__ stats) {
   const int seg = blockIdx.x, row = blockIdx.y, lane = threadIdx.x;
-  const int i = seg * kLmBlocksPerSeg + lane;
+  const int i = seg * per_seg + lane;
   float m = -INFINITY, s = 0.f;
-  if (i < nvb) {
+  if (lane < per_seg && i < nvb) {
     const float2 b = bstats[static_cast<int64_t>(row) * nvb + i];
     m = b.x; s = b.y;
   }
@@ -586,70 +544,59 @@ __global__ __launch_bounds__(kWave) void lm_stats_merge_kernel(const float2* __r
   }
 }
 
-// Workspace: [block statistics rows x ceil(V/128) x 8 bytes][packed hidden states, more than 128 rows only]
+// Workspace: block statistics, rows x ceil(V / 128) x 8 bytes (the kernel for more rows uses half of it)
 static size_t lm_bstats_bytes(int rows, int V) {
   const size_t nvb = (static_cast<size_t>(V) + kLmVB - 1) / kLmVB;
   return (static_cast<size_t>(rows) * nvb * sizeof(float2) + 255) / 256 * 256;
 }
 
 size_t lm_head_workspace_bytes(int rows, int d_model, int V) {
-  size_t n = lm_bstats_bytes(rows, V) + 256;
-  if (rows > kLmRB) n += static_cast<size_t>((rows + 31) / 32) * 32 * d_model * sizeof(uint16_t);
-  return n;
+  (void)d_model;
+  return lm_bstats_bytes(rows, V) + 256;
 }
 
 size_t row_stats_bytes(int rows, int V) { return static_cast<size_t>(rows) * stats_segments(V) * sizeof(SegStat); }
 
 int launch_lm_head(const LmHeadArgs& a, hipStream_t stream) {
   if (a.rows <= 0) return 0;
-  static bool attr_set = false;
-  if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(lm_head_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kLmLds) != hipSuccess)
-      return -1;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(lm_head_wide_kernel<2>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kLwLds) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(lm_head_wide_kernel<4>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kLwLds) != hipSuccess)
-      return -1;
-    attr_set = true;
-  }
-  const bool wide = a.rows > kLmRB;
   LmParams P;
   P.rows = a.rows; P.K = a.d_model; P.V = a.V;
-  P.nvb = (a.V + kLmVB - 1) / kLmVB;
-  P.nrb = (a.rows + (wide ? kLwRB : kLmRB) - 1) / (wide ? kLwRB : kLmRB);
-  P.total = P.nvb * P.nrb;
-  P.per_xcd = (P.total + 7) / 8;
-  // Several row blocks: panels of 128 vocabulary blocks (134 MB of weights at d_model = 4096), every
-  // row block of a panel in turn, measured 5-10 % faster than keeping the row blocks of one
-  // vocabulary block adjacent when the last row block is partial, and equal otherwise.
-  P.panel = (wide && P.nrb > 1) ? 128 : 0;
-#ifdef SPECV_DEV_KNOBS
-  if (const char* e = getenv("SPECV_LM_PANEL")) {                       // sweeps only; normal builds read no environment
-    const int v = atoi(e);
-    if (v >= 0 && v <= 65536) P.panel = v;
-  }
-#endif
   P.c = kLog2e / a.temperature;
   P.hidden = static_cast<const uint16_t*>(a.hidden);
   P.weight = static_cast<const uint16_t*>(a.weight);
   P.logits = static_cast<uint16_t*>(a.logits);
   P.bstats = static_cast<float2*>(a.workspace);
-  if (wide) {
-    lm_u32x4* packed = reinterpret_cast<lm_u32x4*>(static_cast<unsigned char*>(a.workspace) + lm_bstats_bytes(a.rows, a.V));
-    const int64_t n_items = static_cast<int64_t>((a.rows + 31) / 32) * (a.d_model / kLmKC) * 256;
-    hipLaunchKernelGGL(lm_pack_hidden_kernel, dim3(static_cast<unsigned>((n_items + 255) / 256)), dim3(256), 0, stream,
-                       P.hidden, a.rows, a.d_model, n_items, packed);
-    if (a.rows <= 256)
-      hipLaunchKernelGGL(lm_head_wide_kernel<4>, dim3(P.per_xcd * 8), dim3(kLwThreads), kLwLds, stream, P, packed);
-    else
-      hipLaunchKernelGGL(lm_head_wide_kernel<2>, dim3(P.per_xcd * 8), dim3(kLwThreads), kLwLds, stream, P, packed);
-  } else {
-    hipLaunchKernelGGL(lm_head_kernel, dim3(P.per_xcd * 8), dim3(kLmThreads), kLmLds, stream, P);
+  const bool tile = a.rows > kLmRB;
+  const int vb = tile ? kTlVB : kLmVB;
+  const int nt2 = tile ? lm_tile_rows(a.rows, a.V, current_device_cus()) : 0;
+  const int rb = tile ? 16 * nt2 : kLmRB;
+  P.nvb = (a.V + vb - 1) / vb;
+  P.nrb = (a.rows + rb - 1) / rb;
+  P.total = P.nvb * P.nrb;
+  P.per_xcd = (P.total + 7) / 8;
+  int rc = 0;
+  switch (nt2) {
+    case 0: {
+      static std::atomic<uint64_t> attr_done{0};
+      if (set_lds_once(&lm_head_kernel, kLmLds, attr_done) != 0) return -1;
+      hipLaunchKernelGGL(lm_head_kernel, dim3(P.per_xcd * 8), dim3(kLmThreads), kLmLds, stream, P);
+      break;
+    }
+    case 2: rc = launch_lm_tile<2>(P, stream); break;
+    case 4: rc = launch_lm_tile<4>(P, stream); break;
+    case 6: rc = launch_lm_tile<6>(P, stream); break;
+    case 8: rc = launch_lm_tile<8>(P, stream); break;
+    case 10: rc = launch_lm_tile<10>(P, stream); break;
+    case 11: rc = launch_lm_tile<11>(P, stream); break;
+    case 12: rc = launch_lm_tile<12>(P, stream); break;
+    case 13: rc = launch_lm_tile<13>(P, stream); break;
+    case 14: rc = launch_lm_tile<14>(P, stream); break;
+    case 15: rc = launch_lm_tile<15>(P, stream); break;
+    default: rc = launch_lm_tile<16>(P, stream); break;
   }
+  if (rc != 0) return rc;
   const int nseg = stats_segments(a.V);
-  hipLaunchKernelGGL(lm_stats_merge_kernel, dim3(nseg, a.rows), dim3(kWave), 0, stream, P.bstats, P.nvb, nseg, P.c,
+  hipLaunchKernelGGL(lm_stats_merge_kernel, dim3(nseg, a.rows), dim3(kWave), 0, stream, P.bstats, P.nvb, 8192 / vb, nseg, P.c,
                      static_cast<SegStat*>(a.stats));
   return 0;
 }
