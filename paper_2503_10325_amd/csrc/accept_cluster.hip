@@ -67,55 +67,9 @@ struct ClusterParams {
   unsigned long long* msg;        // [B][2 buffers][C][2 messages][4 words]
 };
 
-template <typename T> __device__ __forceinline__ T cl_ld(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T> __device__ __forceinline__ void cl_st(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __device__ __forceinline__ void cl_unpack(u32x4 r, float (&x)[8]) {
   x[0] = bf16_lo(r[0]); x[1] = bf16_hi(r[0]); x[2] = bf16_lo(r[1]); x[3] = bf16_hi(r[1]);
   x[4] = bf16_lo(r[2]); x[5] = bf16_hi(r[2]); x[6] = bf16_lo(r[3]); x[7] = bf16_hi(r[3]);
-}
-
-// Whole-wave reductions through the data-parallel-primitive path of the vector ALU (a few cycles per
-// step, against a trip through the LDS crossbar per step for a shuffle): an inclusive scan inside
-// each row of 16 lanes (row_shr 1, 2, 4, 8), then lane 15 of rows 0 and 2 is broadcast into rows 1 and 3
-// (row_bcast:15) and lane 31 into rows 2 and 3 (row_bcast:31); lane 63 then holds the result, which
-// is read back as a wave-uniform value.  Lanes without a source keep `old`, the identity.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_f64(double x) {
-  int lo = __double2loint(x), hi = __double2hiint(x);
-  lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, ROW_MASK, 0xf, false);
-  hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, ROW_MASK, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_sum_dpp(double x) {
-  x += dpp_f64<0x111, 0xf>(x);
-  x += dpp_f64<0x112, 0xf>(x);
-  x += dpp_f64<0x114, 0xf>(x);
-  x += dpp_f64<0x118, 0xf>(x);
-  x += dpp_f64<0x142, 0xa>(x);
-  x += dpp_f64<0x143, 0xc>(x);
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), 63);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), 63);
-  return __hiloint2double(hi, lo);
-}
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_max_step(float x) {
-  const int ninf = 0xff800000;
-  const int y = __builtin_amdgcn_update_dpp(ninf, __float_as_int(x), CTRL, ROW_MASK, 0xf, false);
-  return fmaxf(x, __int_as_float(y));
-}
-__device__ __forceinline__ float wave_max_dpp(float x) {
-  x = dpp_max_step<0x111, 0xf>(x);
-  x = dpp_max_step<0x112, 0xf>(x);
-  x = dpp_max_step<0x114, 0xf>(x);
-  x = dpp_max_step<0x118, 0xf>(x);
-  x = dpp_max_step<0x142, 0xa>(x);
-  x = dpp_max_step<0x143, 0xc>(x);
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
 // Statistics of one level of the window: row maxima and reciprocal sums of 2^((l - max) c).
@@ -280,8 +234,8 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
 #pragma unroll
       for (int j = 0; j < 8; ++j) tq = fmaxf(tq, x[j]);
     }
-    tp = wave_max_dpp(tp);
-    tq = wave_max_dpp(tq);
+    tp = wave_max(tp);
+    tq = wave_max(tq);
     __syncthreads();                              // earlier readers of sh_wm and sh_ws are done
     sh_wm[0][wave] = tp; sh_wm[1][wave] = tq;     // every lane of the wave stores the same value
     __syncthreads();
@@ -310,12 +264,12 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
         aq += static_cast<double>(sum);
       }
     }
-    ap = wave_sum_dpp(ap);
-    aq = wave_sum_dpp(aq);
+    ap = wave_sum(ap);
+    aq = wave_sum(aq);
     sh_ws[0][wave] = ap; sh_ws[1][wave] = aq;
     __syncthreads();
-    zp = wave_sum_dpp(lane < kClWaves ? sh_ws[0][lane] : 0.0);
-    zq = wave_sum_dpp(lane < kClWaves ? sh_ws[1][lane] : 0.0);
+    zp = wave_sum(lane < kClWaves ? sh_ws[0][lane] : 0.0);
+    zq = wave_sum(lane < kClWaves ? sh_ws[1][lane] : 0.0);
   };
 
   // Sum of the level-L weights of the held slice (valid in every wave).
@@ -329,11 +283,11 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
       for (int j = 0; j < 8; ++j) sum += w[j];
       acc += static_cast<double>(sum);
     }
-    acc = wave_sum_dpp(acc);
+    acc = wave_sum(acc);
     __syncthreads();                              // earlier readers of sh_ws are done
     sh_ws[0][wave] = acc;
     __syncthreads();
-    return wave_sum_dpp(lane < kClWaves ? sh_ws[0][lane] : 0.0);
+    return wave_sum(lane < kClWaves ? sh_ws[0][lane] : 0.0);
   };
 
   // Per-(unit, wave) sums of the level-L weights of the held slice, in vocabulary order, for the draw.
@@ -345,7 +299,7 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
       float sum = 0.f;
 #pragma unroll
       for (int j = 0; j < 8; ++j) sum += w[j];
-      const double d = wave_sum_dpp(static_cast<double>(sum));
+      const double d = wave_sum(static_cast<double>(sum));
       sh_part[u * kClWaves + wave] = d;
     }
     __syncthreads();
@@ -362,7 +316,7 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
       const int w = lane & 3;
       const unsigned data = w == 0 ? static_cast<unsigned>(bits) : (w == 1 ? static_cast<unsigned>(bits >> 32)
                                    : (w == 2 ? __float_as_uint(aux) : 0u));
-      cl_st(msg_ptr(r, rank, k) + w, (static_cast<unsigned long long>(data) << 32) | r);
+      st_dev(msg_ptr(r, rank, k) + w, (static_cast<unsigned long long>(data) << 32) | r);
     }
   };
   // 0: every peer's messages of round r are in sh_val / sh_aux; 1: gave up waiting; 2: the owner walks alone
@@ -376,7 +330,7 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
       int spins = 0, status = 0;
       unsigned long long w0 = 0, w1 = 0, w2 = 0;
       for (;;) {
-        w0 = cl_ld(m); w1 = cl_ld(m + 1); w2 = cl_ld(m + 2);
+        w0 = ld_dev(m); w1 = ld_dev(m + 1); w2 = ld_dev(m + 2);
         const bool ok = static_cast<unsigned>(w0) == r && static_cast<unsigned>(w1) == r && static_cast<unsigned>(w2) == r;
         const bool ab = static_cast<unsigned>(w0) == kClAbort;
         if (__any(ab)) { status = 2; break; }
@@ -446,12 +400,12 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
         const int idx = (lvw * SL + (have ? sl : 0)) * 2 + kind;
         const float m = have ? sh_aux[idx] : -INFINITY;
         const double z = have ? sh_val[idx] : 0.0;
-        const float M0 = wave_max_dpp(kind == 0 ? m : -INFINITY);
-        const float M1 = wave_max_dpp(kind == 1 ? m : -INFINITY);
+        const float M0 = wave_max(kind == 0 ? m : -INFINITY);
+        const float M1 = wave_max(kind == 1 ? m : -INFINITY);
         const float M = kind ? M1 : M0;
         const double e = (m == -INFINITY) ? 0.0 : z * exp2(static_cast<double>(m - M) * static_cast<double>(c));
-        const double Z0 = wave_sum_dpp(kind == 0 ? e : 0.0);
-        const double Z1 = wave_sum_dpp(kind == 1 ? e : 0.0);
+        const double Z0 = wave_sum(kind == 0 ? e : 0.0);
+        const double Z1 = wave_sum(kind == 1 ? e : 0.0);
         sh_M[0][lvw] = M0; sh_M[1][lvw] = M1;                   // every lane stores the same values
         sh_iZ[0][lvw] = 1.0 / Z0; sh_iZ[1][lvw] = 1.0 / Z1;
       }
@@ -486,7 +440,7 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
             __syncthreads();
           }
           // total of the slices' sums (every wave of every workgroup: the same wave-level reduction)
-          return wave_sum_dpp(lane < SL ? sh_val[j * SL + lane] : 0.0);
+          return wave_sum(lane < SL ? sh_val[j * SL + lane] : 0.0);
         };
 
         unsigned long long kids = __ballot(my_parent == cur && lane > cur);
@@ -638,7 +592,7 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
     if (st == 0 || !owner) break;
     // the owner's peers are late or gone: tell them to leave and walk the request alone
     if (wave == 0)
-      cl_st(P.msg + ((static_cast<size_t>(b) * 2 + ((lane >> 3) & 1)) * C * 2 + ((lane >> 2) & 1)) * 4 + (lane & 3),
+      st_dev(P.msg + ((static_cast<size_t>(b) * 2 + ((lane >> 3) & 1)) * C * 2 + ((lane >> 2) & 1)) * 4 + (lane & 3),
             static_cast<unsigned long long>(kClAbort));
     __syncthreads();
     solo = true;

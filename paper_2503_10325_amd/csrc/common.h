@@ -28,27 +28,33 @@ __device__ __forceinline__ float load_logit(const void* base, int dtype, int64_t
   return static_cast<const float*>(base)[idx];
 }
 
-// Eight consecutive logits of one row starting at element e0; positions >= V read as -inf.
-// VEC: the row start and e0 are 16-byte aligned (V % 8 == 0 for bf16, V % 4 == 0 for fp32).
-template <bool VEC>
-__device__ __forceinline__ void load8(const void* base, int dtype, int64_t row_off, int e0, int V,
-                                      float (&x)[8]) {
+// Eight consecutive logits of one row starting at element e0; positions >= V read as -inf.  The 16-byte loads need
+// element alignment only, which global memory allows: rows of any length and base stream alike.
+typedef uint32_t raw4 __attribute__((ext_vector_type(4)));
+typedef raw4 raw4_bf16 __attribute__((aligned(2)));
+typedef raw4 raw4_f32 __attribute__((aligned(4)));
+
+__device__ __forceinline__ void unpack_bf16(raw4 w, float (&x)[8]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { x[2 * j] = bf16_lo(w[j]); x[2 * j + 1] = bf16_hi(w[j]); }
+}
+
+__device__ __forceinline__ void load8(const void* base, int dtype, int64_t row_off, int e0, int V, float (&x)[8]) {
   if (dtype == kBF16) {
     const uint16_t* p = static_cast<const uint16_t*>(base) + row_off;
-    if (VEC && e0 + 8 <= V) {
-      const uint4 w = *reinterpret_cast<const uint4*>(p + e0);
-      x[0] = bf16_lo(w.x); x[1] = bf16_hi(w.x); x[2] = bf16_lo(w.y); x[3] = bf16_hi(w.y);
-      x[4] = bf16_lo(w.z); x[5] = bf16_hi(w.z); x[6] = bf16_lo(w.w); x[7] = bf16_hi(w.w);
+    if (e0 + 8 <= V) {
+      unpack_bf16(*reinterpret_cast<const raw4_bf16*>(p + e0), x);
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) x[j] = (e0 + j < V) ? bf16_bits_to_float(p[e0 + j]) : -INFINITY;
     }
   } else {
     const float* p = static_cast<const float*>(base) + row_off;
-    if (VEC && e0 + 8 <= V) {
-      const float4 a = *reinterpret_cast<const float4*>(p + e0);
-      const float4 b = *reinterpret_cast<const float4*>(p + e0 + 4);
-      x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+    if (e0 + 8 <= V) {
+      const raw4 a = *reinterpret_cast<const raw4_f32*>(p + e0);
+      const raw4 b = *reinterpret_cast<const raw4_f32*>(p + e0 + 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { x[j] = __uint_as_float(a[j]); x[4 + j] = __uint_as_float(b[j]); }
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) x[j] = (e0 + j < V) ? p[e0 + j] : -INFINITY;
@@ -56,20 +62,121 @@ __device__ __forceinline__ void load8(const void* base, int dtype, int64_t row_o
   }
 }
 
-__device__ __forceinline__ float wave_max(float v) {
+// N groups of eight logits with all their loads in flight together: no branch stands between one load and the next
+// (a load inside a branch is waited for at the branch's end; the row statistics took four trips to memory for their
+// four groups).  Group i holds the elements first8(e0[i], V) .. + 8 of its row: the last group of a row whose length
+// eight does not divide starts earlier, and what lies ahead of e0[i] (or, for V < 8, at or beyond V) reads as -inf.
+__device__ __forceinline__ int first8(int e0, int V) { return min(e0, max(V - 8, 0)); }
+
+template <int DT, int N>
+struct Raw8 {
+  raw4 w[N][DT == kBF16 ? 1 : 2];
+};
+// DT: the matrix's dtype as a constant (with a branch on it the compiler merges the two sides' last loads through
+// scratch memory).  row_off(i), e0(i): functions of the group number.
+template <int DT, int N, typename Off, typename E0>
+__device__ __forceinline__ void issue8(const void* base, Off row_off, E0 e0, int V, Raw8<DT, N>& r) {
+  if (V < 8) return;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+  for (int i = 0; i < N; ++i) {
+    const int64_t at = row_off(i) + first8(e0(i), V);
+    if constexpr (DT == kBF16) {
+      r.w[i][0] = *reinterpret_cast<const raw4_bf16*>(static_cast<const uint16_t*>(base) + at);
+    } else {
+      r.w[i][0] = *reinterpret_cast<const raw4_f32*>(static_cast<const float*>(base) + at);
+      r.w[i][1] = *reinterpret_cast<const raw4_f32*>(static_cast<const float*>(base) + at + 4);
+    }
+  }
 }
-__device__ __forceinline__ double wave_sum(double v) {
+// ... the values of group i (a constant after unrolling).  ROWS: the groups are of different rows; of one row only
+// group 0 can start inside it when V < 8.
+template <bool ROWS, int DT, int N>
+__device__ __forceinline__ void take8(const void* base, int64_t row_off, int e0, int V, const Raw8<DT, N>& r, int i,
+                                      float (&x)[8]) {
+  if (V < 8) {
+    if (ROWS || i == 0) {
+      load8(base, DT, row_off, e0, V, x);
+    } else {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+      for (int j = 0; j < 8; ++j) x[j] = -INFINITY;
+    }
+    return;
+  }
+  if constexpr (DT == kBF16) {
+    unpack_bf16(r.w[i][0], x);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { x[j] = __uint_as_float(r.w[i][0][j]); x[4 + j] = __uint_as_float(r.w[i][1][j]); }
+  }
+  if (__any(e0 > V - 8)) {
+    const int skip = e0 - first8(e0, V);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = j >= skip ? x[j] : -INFINITY;
+  }
 }
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+
+// Whole-wave reductions through the data-parallel-primitive path of the vector ALU (a few cycles per
+// step, against a trip through the LDS crossbar per step for a shuffle): an inclusive scan inside
+// each row of 16 lanes (row_shr 1, 2, 4, 8), then lane 15 of rows 0 and 2 is broadcast into rows 1 and 3
+// (row_bcast:15) and lane 31 into rows 2 and 3 (row_bcast:31): an inclusive scan over the wave.  Lane 63 then holds
+// the reduction, which is read back as a wave-uniform value.  Lanes without a source keep the identity.  All 64
+// lanes have to be active.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_f64(double x) {
+  int lo = __double2loint(x), hi = __double2hiint(x);
+  lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, ROW_MASK, 0xf, false);
+  hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, ROW_MASK, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_scan(double x) {
+  x += dpp_f64<0x111, 0xf>(x);
+  x += dpp_f64<0x112, 0xf>(x);
+  x += dpp_f64<0x114, 0xf>(x);
+  x += dpp_f64<0x118, 0xf>(x);
+  x += dpp_f64<0x142, 0xa>(x);
+  x += dpp_f64<0x143, 0xc>(x);
+  return x;
+}
+__device__ __forceinline__ double lane_f64(double x, int lane) {        // lane: wave-uniform
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                          __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+__device__ __forceinline__ double wave_sum(double x) { return lane_f64(wave_scan(x), 63); }
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_max_step(float x) {
+  const int ninf = 0xff800000;
+  const int y = __builtin_amdgcn_update_dpp(ninf, __float_as_int(x), CTRL, ROW_MASK, 0xf, false);
+  return fmaxf(x, __int_as_float(y));
+}
+__device__ __forceinline__ float wave_max(float x) {
+  x = dpp_max_step<0x111, 0xf>(x);
+  x = dpp_max_step<0x112, 0xf>(x);
+  x = dpp_max_step<0x114, 0xf>(x);
+  x = dpp_max_step<0x118, 0xf>(x);
+  x = dpp_max_step<0x142, 0xa>(x);
+  x = dpp_max_step<0x143, 0xc>(x);
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+// ... and over a row of 16 lanes, by rotations: the same bits in all 16.
+__device__ __forceinline__ float row16_max(float x) {
+  x = dpp_max_step<0x128, 0xf>(x);
+  x = dpp_max_step<0x124, 0xf>(x);
+  x = dpp_max_step<0x122, 0xf>(x);
+  return dpp_max_step<0x121, 0xf>(x);
+}
+__device__ __forceinline__ double row16_sum(double x) {
+  x += dpp_f64<0x128, 0xf>(x);
+  x += dpp_f64<0x124, 0xf>(x);
+  x += dpp_f64<0x122, 0xf>(x);
+  return x + dpp_f64<0x121, 0xf>(x);
+}
+
+// Relaxed device-scope accesses: words that workgroups of one kernel exchange.
+template <typename T> __device__ __forceinline__ T ld_dev(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T> __device__ __forceinline__ void st_dev(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Per-(row, segment) softmax statistics written by the row-statistics kernel:
@@ -80,5 +187,43 @@ struct __align__(16) SegStat {
   float pad;
   double z;
 };
+
+// Merged (max, sum) of one logit row from its per-segment records, by a group of 16 lanes (lane sl of the
+// group takes segments sl, sl + 16, ...); the result is in every lane of the group.  DEV: read the records
+// with device-scope loads (they were written by other workgroups of the same kernel).  The arithmetic and
+// its order are the same for every caller, so every caller gets the same bits.  All lanes of the wave take part
+// (a group without a row passes nseg = 0).
+template <bool DEV>
+__device__ __forceinline__ void merged_row_stats(const SegStat* __restrict__ rec, int nseg, float c, int sl,
+                                                 float& m_out, double& z_out) {
+  auto load = [&](int sg) -> SegStat {
+    if constexpr (DEV) {
+      const unsigned long long* w = reinterpret_cast<const unsigned long long*>(rec + sg);
+      const unsigned long long w0 = ld_dev(w), w1 = ld_dev(w + 1);
+      SegStat st;
+      st.m = __uint_as_float(static_cast<unsigned>(w0));
+      st.pad = 0.f;
+      st.z = __builtin_bit_cast(double, w1);
+      return st;
+    } else {
+      return rec[sg];
+    }
+  };
+  SegStat st;
+  st.m = -INFINITY; st.pad = 0.f; st.z = 0.0;
+  if (sl < nseg) st = load(sl);                    // up to 16 segments (131072 logits): one load per lane
+  float m = st.m;
+  for (int sg = sl + 16; sg < nseg; sg += 16) m = fmaxf(m, load(sg).m);
+  m = row16_max(m);
+  double z = 0.0;
+  for (int sg = sl;;) {
+    if (st.m != -INFINITY) z += st.z * exp2(static_cast<double>(st.m - m) * static_cast<double>(c));
+    sg += 16;
+    if (sg >= nseg) break;
+    st = load(sg);
+  }
+  m_out = m;
+  z_out = row16_sum(z);
+}
 
 }  // namespace specv

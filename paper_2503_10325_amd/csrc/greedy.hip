@@ -46,29 +46,29 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long k)
   return k;
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(kArgThreads) void row_argmax_kernel(const void* __restrict__ base, int dtype, int V,
+template <int DT>
+__global__ __launch_bounds__(kArgThreads) void row_argmax_kernel(const void* __restrict__ base, int V,
                                                                  int nseg, unsigned long long* __restrict__ keys) {
   const int seg = blockIdx.x, row = blockIdx.y;
   const int64_t row_off = static_cast<int64_t>(row) * V;
   const int e_seg = seg * kArgSeg;
-  float x[kArgPerThread];
+  constexpr int kGroups = kArgPerThread / 8;
+  float x[kGroups][8];
+  auto off = [&](int) { return row_off; };
+  auto e0 = [&](int j) { return e_seg + (j * kArgThreads + static_cast<int>(threadIdx.x)) * 8; };
+  Raw8<DT, kGroups> raw;
+  issue8(base, off, e0, V, raw);
 #pragma unroll
-  for (int j = 0; j < kArgPerThread / 8; ++j) {
-    float v8[8];
-    load8<VEC>(base, dtype, row_off, e_seg + (j * kArgThreads + threadIdx.x) * 8, V, v8);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[j * 8 + i] = v8[i];
-  }
+  for (int j = 0; j < kGroups; ++j) take8<false>(base, row_off, e0(j), V, raw, j, x[j]);
   // within the thread the indices ascend, so "strictly greater" keeps the lowest index
   float best = -INFINITY;
-  int best_i = e_seg + threadIdx.x * 8;
+  int best_i = e0(0);
 #pragma unroll
-  for (int j = 0; j < kArgPerThread / 8; ++j)
+  for (int j = 0; j < kGroups; ++j)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float v = x[j * 8 + i];              // positions >= V were loaded as -inf
-      if (v > best) { best = v; best_i = e_seg + (j * kArgThreads + threadIdx.x) * 8 + i; }
+      const float v = x[j][i];                   // positions outside the group or the row were loaded as -inf
+      if (v > best) { best = v; best_i = first8(e0(j), V) + i; }
     }
   // a thread whose elements are all -inf / NaN / beyond V proposes its first index; the key order
   // still prefers any lower index with the same value, and index < V holds for the winner because
@@ -152,11 +152,8 @@ void launch_accept_greedy(const GreedyArgs& a, hipStream_t stream) {
   const int nseg = argmax_segments(a.V);
   unsigned long long* keys = static_cast<unsigned long long*>(a.workspace);
   const dim3 grid(nseg, rows);
-  const bool vec = (a.V % 8 == 0) && aligned16(a.target);
-  if (vec)
-    hipLaunchKernelGGL(row_argmax_kernel<true>, grid, dim3(kArgThreads), 0, stream, a.target, a.t_dtype, a.V, nseg, keys);
-  else
-    hipLaunchKernelGGL(row_argmax_kernel<false>, grid, dim3(kArgThreads), 0, stream, a.target, a.t_dtype, a.V, nseg, keys);
+  hipLaunchKernelGGL((a.t_dtype == kBF16 ? row_argmax_kernel<kBF16> : row_argmax_kernel<kF32>), grid, dim3(kArgThreads), 0, stream,
+                     a.target, a.V, nseg, keys);
   hipLaunchKernelGGL(greedy_walk_kernel, dim3(a.B), dim3(kGreedyThreads), 0, stream, a.V, nseg, a.node_offsets,
                      a.parent, a.draft_tokens, keys, a.accept_len, a.out_tokens, a.out_stride, a.stop_node,
                      a.row_argmax);

@@ -19,7 +19,6 @@ constexpr int kRouteWaves = kRouteThreads / kWave;
 constexpr int kRouteMaxPos = 64;
 constexpr int kRouteDepth = 4;                 // 512-element blocks of a row in flight per wave
 
-template <bool VEC>
 __global__ __launch_bounds__(kRouteThreads) void routing_scores_kernel(
     int k_max, int N, int V, int E, const int32_t* __restrict__ k_len, const float* __restrict__ conf,
     const int32_t* __restrict__ toks, const int32_t* __restrict__ accept_len, const int32_t* __restrict__ out_tokens,
@@ -41,8 +40,8 @@ __global__ __launch_bounds__(kRouteThreads) void routing_scores_kernel(
       for (int u = 0; u < kRouteDepth; ++u) {          // all loads first; blocks past the row end re-read its start
         const int e0 = base + (u * kWave + lane) * 8;
         const int es = e0 < E ? e0 : 0;
-        load8<VEC>(emb, e_dtype, ra, es, E, a[u]);
-        load8<VEC>(emb, e_dtype, rx, es, E, x[u]);
+        load8(emb, e_dtype, ra, es, E, a[u]);
+        load8(emb, e_dtype, rx, es, E, x[u]);
       }
 #pragma unroll
       for (int u = 0; u < kRouteDepth; ++u) {
@@ -77,15 +76,9 @@ __global__ __launch_bounds__(kRouteThreads) void routing_scores_kernel(
 
 void launch_routing_scores(const RoutingArgs& a, hipStream_t stream) {
   if (a.B <= 0 || a.N <= 0) return;
-  const bool vec = (a.E % 8 == 0) && aligned16(a.embedding);
-  if (vec)
-    hipLaunchKernelGGL(routing_scores_kernel<true>, dim3(a.B, a.N), dim3(kRouteThreads), 0, stream, a.k_max, a.N, a.V, a.E,
-                       a.k_len, a.conf, a.draft_tokens, a.accept_len, a.out_tokens, a.out_stride, a.embedding,
-                       a.e_dtype, a.scores);
-  else
-    hipLaunchKernelGGL(routing_scores_kernel<false>, dim3(a.B, a.N), dim3(kRouteThreads), 0, stream, a.k_max, a.N, a.V, a.E,
-                       a.k_len, a.conf, a.draft_tokens, a.accept_len, a.out_tokens, a.out_stride, a.embedding,
-                       a.e_dtype, a.scores);
+  hipLaunchKernelGGL(routing_scores_kernel, dim3(a.B, a.N), dim3(kRouteThreads), 0, stream, a.k_max, a.N, a.V, a.E,
+                     a.k_len, a.conf, a.draft_tokens, a.accept_len, a.out_tokens, a.out_stride, a.embedding,
+                     a.e_dtype, a.scores);
 }
 
 }  // namespace specv
