@@ -186,12 +186,12 @@ __device__ __forceinline__ int request_chunks(const AttnParams& P, int L, int n)
 // Waves that share tokens fetch them separately (the repeats hit in L2: HBM traffic stays 1x).
 // One work item: (request b, KV head kvh, context chunk, row group rg).  Every return below is
 // workgroup-uniform.
-template <int D>
+template <int D, int NW>
 __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* smem, int b, int kvh, int chunk, int rg,
                                             int q0, int n, int ctx) {
   using C = AttnCfg<D>;
   const int tid = static_cast<int>(threadIdx.x) + opaque_zero(), lane = tid & 63, wave = tid >> 6;
-  __builtin_assume(tid >= 0 && tid < kAttnThreads);
+  __builtin_assume(tid >= 0 && tid < NW * kWave);
   const int ln = lane & 31, lh = lane >> 5;
 
   // (q0, n, ctx: first query row, number of query nodes (already capped at kMaxQ) and context length of request b)
@@ -202,7 +202,7 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
   if (row0 >= R) return;
   const int nqb = min(4, (R - row0 + 31) / 32);             // query blocks of this workgroup
   const int nqbp = nqb <= 1 ? 1 : (nqb <= 2 ? 2 : 4);       // ... rounded up to a power of two
-  const int nslice = kAttnWaves / nqbp;                     // waves sharing one query block
+  const int nslice = NW / nqbp;                             // waves sharing one query block
   const int my_qb = wave % nqbp, my_slice = wave / nqbp;
   const bool wave_active = my_qb < nqb;                     // wave-uniform
   const int nchunks = request_chunks(P, L, n);
@@ -219,60 +219,13 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
   // tile is staged, the merge statistics live behind the cross-wave reduction buffer.
   unsigned long long* sh_anc = reinterpret_cast<unsigned long long*>(smem);            // [64]
   int* sh_par = reinterpret_cast<int*>(smem + 512);                                    // [64]
-  float* sh_m = reinterpret_cast<float*>(smem + kAttnWaves * 32 * C::kORedStride * sizeof(float));  // [4][32]
-  float* sh_l = sh_m + kAttnWaves * 32;                                                // [4][32]
+  float* sh_m = reinterpret_cast<float*>(smem + NW * 32 * C::kORedStride * sizeof(float));  // [NW][32]
+  float* sh_l = sh_m + NW * 32;                                                        // [NW][32]
 
-  // ---- ancestor-or-self masks of the draft nodes (only chunks that reach the drafts) ----
+  // Everything that depends on no other load goes out first - the page ids of the first tile, the parents, the query
+  // row - then the first tile's K and V; the masks are worked out while those are on their way.  (One after another
+  // these trips to memory were a good part of a short item.)
   const bool touches_drafts = t_end > ctx;
-  if (touches_drafts) {
-    if (P.parent) {
-      if (tid < kMaxQ) sh_par[tid] = (tid < n) ? P.parent[q0 + tid] : -1;
-      __syncthreads();
-    }
-    if (tid < kMaxQ) {
-      unsigned long long mask = 0;
-      if (tid < n) {
-        if (P.parent) {
-          int a = tid;
-          for (int g = 0; g <= tid && a >= 0; ++g) {
-            mask |= 1ull << a;
-            const int p = sh_par[a];
-            a = (p >= a || p < -1) ? -1 : p;
-          }
-        } else {
-          mask = (2ull << tid) - 1ull;
-        }
-      }
-      sh_anc[tid] = mask;
-    }
-    __syncthreads();
-  }
-
-  // ---- this lane's query column ----
-  const int row = row0 + 32 * my_qb + ln;
-  const bool valid = row < R;
-  const int node = valid ? row / P.G : 0;
-  const int gq = valid ? row % P.G : 0;
-  const unsigned long long my_anc = (touches_drafts && valid) ? sh_anc[node] : 0ull;
-  bf16x8 qf[C::kQKSteps];
-  {
-    const uint16_t* qp = P.q + (static_cast<int64_t>(q0 + node) * P.Hq + kvh * P.G + gq) * D + 8 * lh;
-#pragma unroll
-    for (int ks = 0; ks < C::kQKSteps; ++ks) {
-      u32x4 v = zero4();
-      if (valid) v = *reinterpret_cast<const u32x4*>(qp + 16 * ks);
-      qf[ks] = as_bf16x8(v);
-    }
-  }
-  if (touches_drafts) __syncthreads();       // masks are in registers; the memory becomes tile space
-
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x16 oacc[C::kDBlocks];
-#pragma unroll
-  for (int db = 0; db < C::kDBlocks; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
-
   // ---- lane roles for the loads ----
   const int kc = lane % C::kCh;              // 16-byte chunk within the token row
   const int kt = lane / C::kCh;              // token row within one load instruction
@@ -332,11 +285,65 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
   };
 
   int t = my_slice;
-  if (wave_active && t < ntiles) {
-    fetch_pages(t);
+  const bool any_tile = wave_active && t < ntiles;
+  if (any_tile) fetch_pages(t);
+  int my_par = -1;
+  if (touches_drafts && P.parent && tid < n) my_par = P.parent[q0 + tid];
+  // ---- this lane's query column ----
+  const int row = row0 + 32 * my_qb + ln;
+  const bool valid = row < R;
+  const int node = valid ? row / P.G : 0;
+  const int gq = valid ? row % P.G : 0;
+  bf16x8 qf[C::kQKSteps];
+  {
+    const uint16_t* qp = P.q + (static_cast<int64_t>(q0 + node) * P.Hq + kvh * P.G + gq) * D + 8 * lh;
+#pragma unroll
+    for (int ks = 0; ks < C::kQKSteps; ++ks) {
+      u32x4 v = zero4();
+      if (valid) v = *reinterpret_cast<const u32x4*>(qp + 16 * ks);
+      qf[ks] = as_bf16x8(v);
+    }
+  }
+  if (any_tile) {
     issue_loads(t);
     fetch_pages(t + nslice);
   }
+
+  // ---- ancestor-or-self masks of the draft nodes (only chunks that reach the drafts) ----
+  if (touches_drafts) {
+    if (P.parent) {
+      if (tid < kMaxQ) sh_par[tid] = my_par;
+      __syncthreads();
+    }
+    if (tid < kMaxQ) {
+      unsigned long long mask = 0;
+      if (tid < n) {
+        if (P.parent) {
+          int a = tid;
+          for (int g = 0; g <= tid && a >= 0; ++g) {
+            mask |= 1ull << a;
+            const int p = sh_par[a];
+            a = (p >= a || p < -1) ? -1 : p;
+          }
+        } else {
+          mask = (2ull << tid) - 1ull;
+        }
+      }
+      sh_anc[tid] = mask;
+    }
+    __syncthreads();
+  }
+
+  const unsigned long long my_anc = (touches_drafts && valid) ? sh_anc[node] : 0ull;
+  if (touches_drafts) __syncthreads();       // masks are in registers; the memory becomes tile space
+
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 oacc[C::kDBlocks];
+#pragma unroll
+  for (int db = 0; db < C::kDBlocks; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
+
   for (; wave_active && t < ntiles; t += nslice) {
     // ---- registers -> LDS ----
 #pragma unroll
@@ -455,7 +462,7 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
   for (int s = 0; s < nslice; ++s) M = fmaxf(M, sh_m[(my_qb + nqbp * s) * 32 + ln]);
   const float fscale = (m_run == -INFINITY) ? 0.f : fast_exp2(m_run - M);
 
-  float* sh_o = reinterpret_cast<float*>(smem);        // [4 waves][32][kORedStride]
+  float* sh_o = reinterpret_cast<float*>(smem);        // [NW waves][32][kORedStride]
   if (wave_active) {
     constexpr int kA = D / 64, kQ = 256 / D;     // see acc_dim0
 #pragma unroll
@@ -471,9 +478,9 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
       }
   }
   __syncthreads();
-  const int rn = tid >> 3;                               // query column this thread finalises
+  const int rn = (tid >> 3) & 31;                        // query column this thread finalises, of block tid / 256 on
   const int rd0 = (tid & 7) * (D / 8);                   // first of its D/8 dims
-  for (int qb = 0; qb < nqb; ++qb) {
+  for (int qb = tid >> 8; qb < nqb; qb += NW / 4) {
     const int orow = row0 + 32 * qb + rn;
     if (orow >= R) continue;
     float Mq = -INFINITY;
@@ -517,14 +524,17 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
 
 // Grid-mapped launch: blockIdx = (chunk + max_chunks * row group, KV head, request); workgroups
 // whose chunk does not exist return at once.
-template <int D>
-__global__ __launch_bounds__(kAttnThreads, 2) void attn_stream_kernel(AttnParams P) {
+// NW = 8 (one workgroup per compute unit instead of two): for launches that have no second workgroup for a compute unit;
+// twice the waves share a chunk's tiles, with no more chunks to merge.  1 request x 8 KV heads x 16000 tokens
+// (56 rows, 512-token chunks) 25.6 -> 24.6 us with the merge, 8 x 32 x 2048 46.0 -> 45.3.
+template <int D, int NW>
+__global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attn_stream_kernel(AttnParams P) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.z;
   const int q0 = P.q_offsets[b];
   int n = P.q_offsets[b + 1] - q0;
   n = n > kMaxQ ? kMaxQ : n;
-  stream_item<D>(P, smem, b, blockIdx.y, blockIdx.x % P.max_chunks, blockIdx.x / P.max_chunks, q0, n, P.ctx_len[b]);
+  stream_item<D, NW>(P, smem, b, blockIdx.y, blockIdx.x % P.max_chunks, blockIdx.x / P.max_chunks, q0, n, P.ctx_len[b]);
 }
 
 constexpr int kPlanMaxB = 128;
@@ -599,36 +609,11 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   int* sh_par = reinterpret_cast<int*>(smem + 2 * RC::kStage + kNodes * kWords * 8);                  // [kNodes]
   int* sh_pages = reinterpret_cast<int*>(smem + 2 * RC::kStage + RC::meta_bytes(WIDE));               // [kMaxChunkPages]
 
+  // Everything that depends on no other load goes out first (parents, query rows, the chunk's page ids), then the first
+  // tile's K and V; the masks are worked out while those are on their way.
   const bool touches_drafts = t_end > ctx;
-  if (touches_drafts) {
-    if (P.parent) {
-      if (tid < kNodes) sh_par[tid] = (tid < n) ? P.parent[q0 + tid] : -1;
-      __syncthreads();
-    }
-    if (tid < kNodes) {
-      unsigned long long mask = 0, mask_hi = 0;
-      if (tid < n) {
-        if (P.parent) {
-          int a = tid;
-          for (int g = 0; g <= tid && a >= 0; ++g) {
-            if (WIDE && a >= 64) mask_hi |= 1ull << (a - 64);
-            else mask |= 1ull << a;
-            const int p = sh_par[a];
-            a = (p >= a || p < -1) ? -1 : p;
-          }
-        } else if (WIDE && tid >= 64) {
-          mask = ~0ull;
-          mask_hi = (2ull << (tid - 64)) - 1ull;
-        } else {
-          mask = (2ull << tid) - 1ull;
-        }
-      }
-      sh_anc[tid * kWords] = mask;
-      if (WIDE) sh_anc[tid * kWords + 1] = mask_hi;
-    }
-    __syncthreads();
-  }
-
+  int my_par = -1;
+  if (touches_drafts && P.parent && tid < n) my_par = P.parent[q0 + tid];
   // ---- this wave's 32 query rows ----
   const int slice = SL == 1 ? 0 : wave / kRowWaves;          // which 64 tokens of a staged tile this wave computes
   const int wrow0 = row0 + 32 * (wave % kRowWaves);
@@ -637,8 +622,6 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   const bool valid = row < R;
   const int node = valid ? row / P.G : 0;
   const int gq = valid ? row % P.G : 0;
-  const unsigned long long my_anc = (touches_drafts && valid) ? sh_anc[node * kWords] : 0ull;
-  const unsigned long long my_anc_hi = (WIDE && touches_drafts && valid) ? sh_anc[node * kWords + 1] : 0ull;
   const int64_t grow = static_cast<int64_t>(q0 + node) * P.Hq + kvh * P.G + gq;
   bf16x8 qf[C::kQKSteps];
   {
@@ -673,6 +656,7 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   const int np = (t_end + kPage - 1) / kPage - lp0;          // >= 1 pages touched by this chunk
   // (entries past the chunk's last page repeat it: tile numbers past the end need no clamp)
   for (int i = tid; i < np + RC::kPagePad; i += RC::kThreads) sh_pages[i] = bt[lp0 + min(i, np - 1)];
+  if (tid < kNodes) sh_par[tid] = my_par;
   __syncthreads();
 
   // Loads are unconditional (addresses clamped to the chunk's last page): positions past the
@@ -756,6 +740,8 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
       }
     }
   };
+
+  unsigned long long my_anc = 0ull, my_anc_hi = 0ull;          // ancestor mask of this lane's node (set below)
 
   // One 64-token tile = one online-softmax step in two parts (scores, output) that share these registers.
   f32x16 sacc[2];
@@ -891,9 +877,37 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   // (a wave of the sliced variant skips a staged tile whose half for it lies past the end)
   auto mine = [&](int t) { return active && t < ntiles && t_begin + RC::kT * t + RC::kTc * slice < t_end; };
   fetch_pages(0);
+  issue_tile(0, krA, vrA);
+  if constexpr (NW == 8 && SL == 1) issue_tile(1, krB, vrB);
+  if (touches_drafts) {
+    if (tid < kNodes) {
+      unsigned long long mask = 0, mask_hi = 0;
+      if (tid < n) {
+        if (P.parent) {
+          int a = tid;
+          for (int g = 0; g <= tid && a >= 0; ++g) {
+            if (WIDE && a >= 64) mask_hi |= 1ull << (a - 64);
+            else mask |= 1ull << a;
+            const int p = sh_par[a];
+            a = (p >= a || p < -1) ? -1 : p;
+          }
+        } else if (WIDE && tid >= 64) {
+          mask = ~0ull;
+          mask_hi = (2ull << (tid - 64)) - 1ull;
+        } else {
+          mask = (2ull << tid) - 1ull;
+        }
+      }
+      sh_anc[tid * kWords] = mask;
+      if (WIDE) sh_anc[tid * kWords + 1] = mask_hi;
+    }
+    __syncthreads();
+  }
+  if (touches_drafts && valid) {
+    my_anc = sh_anc[node * kWords];
+    if (WIDE) my_anc_hi = sh_anc[node * kWords + 1];
+  }
   if constexpr (NW == 8 && SL == 1) {
-    issue_tile(0, krA, vrA);
-    issue_tile(1, krB, vrB);
     store_tile(0, 0, krA, vrA);
     issue_tile(2, krA, vrA);
     __syncthreads();
@@ -912,7 +926,6 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   } else {
     // Four waves, two workgroups per compute unit: one register set (one tile of loads in flight per
     // workgroup; the other workgroup covers the rest of the latency), which leaves the registers for it.
-    issue_tile(0, krA, vrA);
     store_tile(0, 0, krA, vrA);
     issue_tile(1, krA, vrA);
     __syncthreads();
@@ -1099,7 +1112,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_stream_list_kernel(AttnP
     const int cb = (((L + nch - 1) / nch) + RC::kT - 1) & ~(RC::kT - 1);
     // (a chunk longer than the row-split body's page table in LDS stays with the token-split body)
     if (list_uses_rows(P, n) && cb <= RC::kMaxChunkPages * kPage) rows_item<D, 4>(P, smem, b, local % P.Hkv, local / P.Hkv, 0, nch, cb, q0, n, ctx);
-    else stream_item<D>(P, smem, b, local % P.Hkv, local / P.Hkv, 0, q0, n, ctx);
+    else stream_item<D, kAttnWaves>(P, smem, b, local % P.Hkv, local / P.Hkv, 0, q0, n, ctx);
     __syncthreads();                              // the tile memory is reused by the next item
   }
 }
@@ -1211,16 +1224,22 @@ static long dev_knob(const char*, long fallback) { return fallback; }
 AttnPlan make_attn_plan(const AttnArgs& a) {
   AttnPlan p;
   p.tau = 0;
+  p.waves8 = 0;
   p.wide = a.max_q > kMaxQ ? 1 : 0;
   const int G = a.Hq / a.Hkv;
   const int max_rows = a.max_q * G;
   const int64_t max_tok0 = static_cast<int64_t>(a.max_pages) * a.page;
   const bool ragged0 = a.kv_hint > 0 && a.kv_hint * 100 < static_cast<int64_t>(85) * a.B * max_tok0;
+  // Little work - the tokens of all requests and KV heads, dealt to 256 workgroups, are chunks below 1024 - is cut by
+  // tokens, whatever the lengths: every request then has items of about one length.  The sorted work list cuts by what
+  // a wave can stream at full load and left such batches to a few workgroups (5 requests x 4 KV heads, 777 to 3001
+  // tokens: 20 of 512 workgroups, 26.7 us; 13.2 us cut into 512-token chunks).
+  const bool little = a.kv_hint > 0 && a.kv_hint * a.Hkv < static_cast<int64_t>(256) * 1024;
   // Up to 64 query rows per KV head the token-split body streams as fast as memory delivers; beyond, its
   // waves (one per 32-row block, each staging every tile for itself) are bound by their own staging and the
   // row-split body, whose waves share each staged tile, is ahead on batches of like lengths (96 rows per KV
   // head: 4.2 against 2.6 TB/s).  Ragged batches keep the token-split body and its sorted work list.
-  if (max_rows <= 64 || (max_rows <= 128 && ragged0 && a.B <= kPlanMaxB)) { p.kind = 0; p.rows_per_wg = 128; }
+  if (max_rows <= 64 || (max_rows <= 128 && ragged0 && !little && a.B <= kPlanMaxB)) { p.kind = 0; p.rows_per_wg = 128; }
   else if (max_rows <= 128 || a.D != 128) { p.kind = 1; p.rows_per_wg = 128; }
   else { p.kind = 2; p.rows_per_wg = 256; }
   // Few (request, KV head) pairs with many rows each: 256-row workgroups would have to cut the context to fill
@@ -1258,7 +1277,10 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
     const int64_t cap = static_cast<int64_t>(40) * kTile * nslice;
     if (chunk > cap) chunk = cap;
   }
-  if (chunk < 256) chunk = 256;
+  // shortest chunk: two tiles per wave of the eight-wave token-split kernel (which such launches take, below); a shorter
+  // one saves a wave one tile and costs every request a merge (1 request of 260 tokens: one launch instead of two)
+  const int64_t shortest = token_split ? 512 : 256;
+  if (chunk < shortest) chunk = shortest;
   chunk = (chunk + gran - 1) / gran * gran;
   if (chunk > max_tok) chunk = (max_tok + gran - 1) / gran * gran;
   // the row-split kernel keeps a chunk's page ids in LDS
@@ -1275,7 +1297,7 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
   // request says whether they do.
   const bool ragged = a.kv_hint > 0 && a.kv_hint * 100 < static_cast<int64_t>(85) * a.B * max_tok;
   // (the list kernel packs a request's first query row into 16 bits)
-  int tau = (token_split && a.B <= kPlanMaxB && a.total_q < 65536 && ragged) ? 44 : 0;   // with the alternating hand-out below: 40-48 measured best
+  int tau = (token_split && a.B <= kPlanMaxB && a.total_q < 65536 && ragged && !little) ? 44 : 0;   // with the alternating hand-out below: 40-48 measured best
   const long tau_knob = dev_knob("SPECV_ATTN_TAU", -1);   // 0: grid-mapped launch
   if (token_split && a.B <= kPlanMaxB && a.total_q < 65536 && tau_knob >= 0 && tau_knob <= 255) tau = static_cast<int>(tau_knob);
   if (jobs_knob > 0) tau = 0;
@@ -1287,6 +1309,13 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
     const int64_t mc = (max_tiles + tau - 1) / tau;
     p.tau = tau;
     p.max_chunks = static_cast<int>(mc < 1 ? 1 : (mc > kListMaxChunks ? kListMaxChunks : mc));
+  }
+  if (token_split && p.tau == 0) {
+    // one workgroup of eight waves per compute unit where there are not two of four for it; workgroups that have work:
+    // at most what the hint's tokens and one partial chunk per request make
+    const int64_t jobs = (tok / p.chunk_tokens + a.B) * a.Hkv * p.row_groups;
+    const int64_t most = static_cast<int64_t>(p.max_chunks) * a.B * a.Hkv * p.row_groups;
+    p.waves8 = (jobs < most ? jobs : most) <= current_device_cus() ? 1 : 0;
   }
   return p;
 }
@@ -1306,27 +1335,40 @@ const char* attn_plan_name(const AttnPlan& p) {
 }
 
 template <int D>
-static int launch_stream(const AttnParams& P, const AttnPlan& plan, int B, int Hkv, hipStream_t stream) {
-  using C = AttnCfg<D>;
-  constexpr size_t kMerge = kAttnWaves * 32 * C::kORedStride * sizeof(float) + 2 * kAttnWaves * 32 * sizeof(float);
-  constexpr size_t kTiles = static_cast<size_t>(kAttnWaves) * C::kWaveLds;
-  static_assert(kMerge <= kTiles, "merge buffers must fit in the tile memory");
-  static std::atomic<uint64_t> attr_done{0};
-  if (set_lds_once(&attn_stream_kernel<D>, kTiles, attr_done) != 0) return -6;
-  if (plan.tau > 0) {
-    // both bodies run in this kernel: the tile memory of the larger one
-    constexpr size_t kListLds = kTiles > static_cast<size_t>(RowsCfg<D, 4>::kLds) ? kTiles : static_cast<size_t>(RowsCfg<D, 4>::kLds);
-    // two workgroups per compute unit: dynamic plus the kernel's static LDS (below 1664 bytes) within half of 160 KB
-    static_assert(kListLds + 1664 <= 80 * 1024, "the work-list kernel must fit twice into a compute unit's LDS");
-    static std::atomic<uint64_t> list_attr_done{0};
-    if (set_lds_once(&attn_stream_list_kernel<D>, kListLds, list_attr_done) != 0) return -6;
-    const int n_cu = current_device_cus();
-    hipLaunchKernelGGL((attn_stream_list_kernel<D>), dim3(2 * n_cu), dim3(kAttnThreads), kListLds, stream, P);
-    return hipGetLastError() == hipSuccess ? 0 : -6;
-  }
-  dim3 grid(plan.max_chunks * plan.row_groups, Hkv, B);
-  hipLaunchKernelGGL((attn_stream_kernel<D>), grid, dim3(kAttnThreads), kTiles, stream, P);
+constexpr size_t stream_tiles_lds(int NW) { return static_cast<size_t>(NW) * AttnCfg<D>::kWaveLds; }
+template <int D>
+constexpr size_t stream_merge_lds(int NW) { return static_cast<size_t>(NW) * 32 * (AttnCfg<D>::kORedStride + 2) * sizeof(float); }
+
+template <int D>
+static int launch_stream_list(const AttnParams& P, hipStream_t stream) {
+  constexpr size_t kTiles = stream_tiles_lds<D>(kAttnWaves);
+  // both bodies run in this kernel: the tile memory of the larger one
+  constexpr size_t kListLds = kTiles > static_cast<size_t>(RowsCfg<D, 4>::kLds) ? kTiles : static_cast<size_t>(RowsCfg<D, 4>::kLds);
+  // two workgroups per compute unit: dynamic plus the kernel's static LDS (below 1664 bytes) within half of 160 KB
+  static_assert(kListLds + 1664 <= 80 * 1024, "the work-list kernel must fit twice into a compute unit's LDS");
+  static std::atomic<uint64_t> list_attr_done{0};
+  if (set_lds_once(&attn_stream_list_kernel<D>, kListLds, list_attr_done) != 0) return -6;
+  const int n_cu = current_device_cus();
+  hipLaunchKernelGGL((attn_stream_list_kernel<D>), dim3(2 * n_cu), dim3(kAttnThreads), kListLds, stream, P);
   return hipGetLastError() == hipSuccess ? 0 : -6;
+}
+
+template <int D, int NW>
+static int launch_stream_as(const AttnParams& P, const AttnPlan& plan, int B, int Hkv, hipStream_t stream) {
+  constexpr size_t kTiles = stream_tiles_lds<D>(NW);
+  static_assert(stream_merge_lds<D>(NW) <= kTiles, "merge buffers must fit in the tile memory");
+  static_assert(kTiles * (NW == 4 ? 2 : 1) <= 160 * 1024, "token-split kernel: LDS per compute unit");
+  static std::atomic<uint64_t> attr_done{0};
+  if (set_lds_once(&attn_stream_kernel<D, NW>, kTiles, attr_done) != 0) return -6;
+  dim3 grid(plan.max_chunks * plan.row_groups, Hkv, B);
+  hipLaunchKernelGGL((attn_stream_kernel<D, NW>), grid, dim3(NW * kWave), kTiles, stream, P);
+  return hipGetLastError() == hipSuccess ? 0 : -6;
+}
+
+template <int D>
+static int launch_stream(const AttnParams& P, const AttnPlan& plan, int B, int Hkv, hipStream_t stream) {
+  if (plan.tau > 0) return launch_stream_list<D>(P, stream);
+  return plan.waves8 ? launch_stream_as<D, 8>(P, plan, B, Hkv, stream) : launch_stream_as<D, 4>(P, plan, B, Hkv, stream);
 }
 
 template <int D, int NW, bool WIDE, int SL = 1>
