@@ -118,18 +118,19 @@ def strerror(status: int) -> str:
     return lib().spec_strerror(int(status)).decode()
 
 
-def _ptr(t) -> ctypes.c_void_p:
+def _ptr(t) -> Optional[int]:
+    # plain integers (None: NULL): the argument types make pointers of them without an object per argument
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     assert t.is_contiguous(), "tensors handed to the library must be contiguous"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    import torch
+def _stream(stream) -> int:
     if stream is None:
+        import torch
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _dtype_code(t) -> int:
