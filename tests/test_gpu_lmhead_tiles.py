@@ -1,5 +1,5 @@
-"""Every workgroup tile of the projection's kernel for more than 128 rows (lm_head_tile_kernel: 2 to 16 row tiles of 16,
-even and odd), with row counts just past a tile or block, vocabularies that end inside a block (odd: scalar stores), two
+"""Every workgroup tile of the projection's kernel (lm_head_tile_kernel: 128 vocabulary entries with 2 to 8 row tiles of 16,
+256 with 4 to 16; even and odd), with row counts just past a tile or block, vocabularies that end inside a block (odd: scalar stores), two
 slices of the contraction (fewer than the loads run ahead) and more.
 
 Reference: the product in fp64 (plain torch).  Tolerance as in test_gpu_lmhead.py: half a bf16 step of the exact value
@@ -16,7 +16,15 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows,d_model,V", [
-    (145, 2048, 300),        # 2 row tiles per workgroup (small grids), 32 slices
+    # 128 vocabulary entries per workgroup
+    (145, 2048, 300),        # 2 row tiles, several row blocks, 32 slices
+    (16, 128, 130),          # 2, one full row tile, a second vocabulary block of two entries
+    (33, 384, 16411),        # 3 (odd vocabulary)
+    (64, 128, 16640),        # 4
+    (65, 640, 16648),        # 5
+    (81, 128, 16464),        # 6
+    (127, 1024, 16425),      # 8
+    # 256
     (129, 128, 13150),       # 4
     (129, 384, 21888),       # 6
     (193, 128, 21888),       # 8
