@@ -78,10 +78,10 @@ struct AttnParams {
   float2* ws_ml;     // [rows, max_chunks] (max in log2 units, sum)
   int B, Hq, Hkv, G, max_pages, chunk_tokens, max_chunks;
   int tau;           // > 0: a request is cut so that one wave streams at most tau tiles per work item
-  int list_rows_min; // > 0 (work list only): requests with this many query rows per KV head use the row-split body
-  int list_rows_units;
+  int list_rows_min; // > 0 (kernels with both bodies): requests with this many query rows per KV head use the row-split body
+  int list_rows_units;        // eighths of a work-list unit that 32 tokens of such a request cost
   int xcd_swizzle;            // grid-mapped row-split launch: consecutive workgroups of the logical order share an XCD
-  int n_cap;                  // query nodes per request the launched kernels handle (64, or 128 with two mask words)  // eighths of a work-list unit that 32 tokens of such a request cost
+  int n_cap;                  // query nodes per request the launched kernels handle (64, or 128 with two mask words)
   float c;           // scale * log2(e)
   int out_f32;
 };
@@ -156,8 +156,8 @@ __device__ __forceinline__ int stream_nslice(int R) {
 // Number of context chunks of a request with L tokens and n draft nodes.  The token-split,
 // sorted-work-list launch (tau > 0) cuts by the number of tiles one wave streams; the other
 // launches cut by tokens.  The attention kernels and the combine kernel all use this function.
-// Work-list launches run requests with at least P.list_rows_min query rows per KV head through the row-split
-// body (its waves share every staged tile; the token-split body stages a tile once per 32-row block).
+// Kernels that hold both bodies run requests with at least P.list_rows_min query rows per KV head through the
+// row-split body (its waves share every staged tile; the token-split body stages a tile once per 32-row block).
 __device__ __forceinline__ bool list_uses_rows(const AttnParams& P, int n) {
   return P.list_rows_min > 0 && n * P.G >= P.list_rows_min;
 }
@@ -1117,6 +1117,25 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_stream_list_kernel(AttnP
   }
 }
 
+// Grid-mapped launch of both bodies, for ragged batches with little work whose larger requests have 65 to 128 query rows
+// per KV head: the body follows each request's own row count, as in the work list, so that a request of up to 64 rows
+// keeps its two-term bf16 weights and its four waves whatever the largest request of the batch is.
+template <int D>
+__global__ __launch_bounds__(kAttnThreads, 2) void attn_mixed_kernel(AttnParams P) {
+  using RC = RowsCfg<D, 4>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int b = blockIdx.z;
+  const int q0 = P.q_offsets[b];
+  int n = P.q_offsets[b + 1] - q0;
+  n = n > kMaxQ ? kMaxQ : n;
+  const int ctx = P.ctx_len[b], L = ctx + n;
+  const int nch = request_chunks(P, L, n);
+  const int cb = (((L + nch - 1) / nch) + RC::kT - 1) & ~(RC::kT - 1);
+  // (a chunk longer than the row-split body's page table in LDS stays with the token-split body)
+  if (list_uses_rows(P, n) && cb <= RC::kMaxChunkPages * kPage) rows_item<D, 4>(P, smem, b, blockIdx.y, blockIdx.x, 0, nch, cb, q0, n, ctx);
+  else stream_item<D, kAttnWaves>(P, smem, b, blockIdx.y, blockIdx.x, 0, q0, n, ctx);
+}
+
 // Merge the per-chunk partials of every (query row, head) that spans several chunks.  A group of D/4 lanes reads
 // whole partial rows (16 bytes per lane) and S groups share one (node, head) row, group s taking chunks s, s + S, ...
 // four at a time with their loads in flight together; the groups meet in LDS.  The kernel is bound by the latency of
@@ -1225,6 +1244,7 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
   AttnPlan p;
   p.tau = 0;
   p.waves8 = 0;
+  p.mixed = 0;
   p.wide = a.max_q > kMaxQ ? 1 : 0;
   const int G = a.Hq / a.Hkv;
   const int max_rows = a.max_q * G;
@@ -1238,8 +1258,9 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
   // Up to 64 query rows per KV head the token-split body streams as fast as memory delivers; beyond, its
   // waves (one per 32-row block, each staging every tile for itself) are bound by their own staging and the
   // row-split body, whose waves share each staged tile, is ahead on batches of like lengths (96 rows per KV
-  // head: 4.2 against 2.6 TB/s).  Ragged batches keep the token-split body and its sorted work list.
-  if (max_rows <= 64 || (max_rows <= 128 && ragged0 && !little && a.B <= kPlanMaxB)) { p.kind = 0; p.rows_per_wg = 128; }
+  // head: 4.2 against 2.6 TB/s).  In ragged batches of up to 128 rows every request takes the body of its own row count
+  // (work list, or attn_mixed_kernel when there is little work): max_q is a bound, and most requests have fewer nodes.
+  if (max_rows <= 64 || (max_rows <= 128 && ragged0 && a.B <= kPlanMaxB)) { p.kind = 0; p.rows_per_wg = 128; }
   else if (max_rows <= 128 || a.D != 128) { p.kind = 1; p.rows_per_wg = 128; }
   else { p.kind = 2; p.rows_per_wg = 256; }
   // Few (request, KV head) pairs with many rows each: 256-row workgroups would have to cut the context to fill
@@ -1260,7 +1281,8 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
   // more than 64 query nodes per request (two mask words per node): the row-split kernels only
   if (p.wide && p.kind == 0) { p.kind = 1; p.rows_per_wg = 128; }
   p.row_groups = (max_rows + p.rows_per_wg - 1) / p.rows_per_wg;
-  const bool token_split = (p.kind == 0);
+  p.mixed = (p.kind == 0 && max_rows > 64 && little) ? 1 : 0;
+  const bool token_split = (p.kind == 0 && !p.mixed);                           // (a mixed launch is cut for the row-split body)
   const int gran = token_split ? kTile : (p.kind == 3 ? 128 : 64);              // chunks are whole tiles
   const int64_t max_tok = static_cast<int64_t>(a.max_pages) * a.page;
   int64_t tok = a.kv_hint > 0 ? a.kv_hint : static_cast<int64_t>(a.B) * max_tok;
@@ -1269,7 +1291,7 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
   // limits allow: (a) about one workgroup per compute unit should exist, (b) one wave should not
   // stream more than ~40 tiles in sequence, or the longest workgroup sets the kernel's duration.
   const long jobs_knob = dev_knob("SPECV_ATTN_JOBS", 0);
-  const int64_t jobs_target = jobs_knob > 0 ? jobs_knob : (p.kind == 1 ? 512 : 256);   // 4-wave bodies: two per compute unit
+  const int64_t jobs_target = jobs_knob > 0 ? jobs_knob : (p.kind == 1 || p.mixed ? 512 : 256);   // 4-wave row-split body: two per compute unit
   int64_t chunk = (tok * a.Hkv * p.row_groups + jobs_target - 1) / jobs_target;
   if (token_split && jobs_knob <= 0) {
     // waves that share one query block (pair) and therefore split its tiles
@@ -1327,6 +1349,7 @@ size_t attn_workspace_bytes(const AttnArgs& a, const AttnPlan& p) {
 }
 
 const char* attn_plan_name(const AttnPlan& p) {
+  if (p.mixed) return "attn_mixed_kernel (one workgroup per request x KV head x context chunk; token-split body, row-split body from 65 query rows per KV head)";
   if (p.kind == 0) return p.tau > 0 ? "attn_stream_list_kernel (device-built work list sorted by length; token-split body, row-split body from 65 query rows per KV head)"
                                     : "attn_stream_kernel (token-split body, one workgroup per request x KV head x context chunk)";
   if (p.kind == 1) return "attn_rows_kernel<4 waves> (row-split body)";
@@ -1339,17 +1362,32 @@ constexpr size_t stream_tiles_lds(int NW) { return static_cast<size_t>(NW) * Att
 template <int D>
 constexpr size_t stream_merge_lds(int NW) { return static_cast<size_t>(NW) * 32 * (AttnCfg<D>::kORedStride + 2) * sizeof(float); }
 
+// kernels with both four-wave bodies: the tile memory of the larger one
+template <int D>
+constexpr size_t both_bodies_lds() {
+  return stream_tiles_lds<D>(kAttnWaves) > static_cast<size_t>(RowsCfg<D, 4>::kLds) ? stream_tiles_lds<D>(kAttnWaves)
+                                                                                    : static_cast<size_t>(RowsCfg<D, 4>::kLds);
+}
+
 template <int D>
 static int launch_stream_list(const AttnParams& P, hipStream_t stream) {
-  constexpr size_t kTiles = stream_tiles_lds<D>(kAttnWaves);
-  // both bodies run in this kernel: the tile memory of the larger one
-  constexpr size_t kListLds = kTiles > static_cast<size_t>(RowsCfg<D, 4>::kLds) ? kTiles : static_cast<size_t>(RowsCfg<D, 4>::kLds);
+  constexpr size_t kListLds = both_bodies_lds<D>();
   // two workgroups per compute unit: dynamic plus the kernel's static LDS (below 1664 bytes) within half of 160 KB
   static_assert(kListLds + 1664 <= 80 * 1024, "the work-list kernel must fit twice into a compute unit's LDS");
   static std::atomic<uint64_t> list_attr_done{0};
   if (set_lds_once(&attn_stream_list_kernel<D>, kListLds, list_attr_done) != 0) return -6;
   const int n_cu = current_device_cus();
   hipLaunchKernelGGL((attn_stream_list_kernel<D>), dim3(2 * n_cu), dim3(kAttnThreads), kListLds, stream, P);
+  return hipGetLastError() == hipSuccess ? 0 : -6;
+}
+
+template <int D>
+static int launch_mixed(const AttnParams& P, const AttnPlan& plan, int B, int Hkv, hipStream_t stream) {
+  constexpr size_t kLds = both_bodies_lds<D>();
+  static_assert(kLds <= 80 * 1024, "two workgroups of the mixed kernel per compute unit");
+  static std::atomic<uint64_t> attr_done{0};
+  if (set_lds_once(&attn_mixed_kernel<D>, kLds, attr_done) != 0) return -6;
+  hipLaunchKernelGGL((attn_mixed_kernel<D>), dim3(plan.max_chunks, Hkv, B), dim3(kAttnThreads), kLds, stream, P);
   return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 
@@ -1368,6 +1406,7 @@ static int launch_stream_as(const AttnParams& P, const AttnPlan& plan, int B, in
 template <int D>
 static int launch_stream(const AttnParams& P, const AttnPlan& plan, int B, int Hkv, hipStream_t stream) {
   if (plan.tau > 0) return launch_stream_list<D>(P, stream);
+  if (plan.mixed) return launch_mixed<D>(P, plan, B, Hkv, stream);
   return plan.waves8 ? launch_stream_as<D, 8>(P, plan, B, Hkv, stream) : launch_stream_as<D, 4>(P, plan, B, Hkv, stream);
 }
 
@@ -1426,8 +1465,8 @@ int launch_attn(const AttnArgs& a, const AttnPlan& plan, hipStream_t stream) {
                                     ((rows * plan.max_chunks * sizeof(float2) + 255) / 256) * 256);
   P.B = a.B; P.Hq = a.Hq; P.Hkv = a.Hkv; P.G = a.Hq / a.Hkv; P.max_pages = a.max_pages;
   P.chunk_tokens = plan.chunk_tokens; P.max_chunks = plan.max_chunks; P.tau = plan.tau;
-  // work list: from 65 query rows per KV head (three 32-row blocks) on, a request runs the row-split body
-  P.list_rows_min = plan.tau > 0 ? static_cast<int>(dev_knob("SPECV_ATTN_LIST_ROWS", 65)) : 0;
+  // both bodies: from 65 query rows per KV head (three 32-row blocks) on, a request runs the row-split body
+  P.list_rows_min = plan.tau > 0 || plan.mixed ? static_cast<int>(dev_knob("SPECV_ATTN_LIST_ROWS", 65)) : 0;
   P.list_rows_units = static_cast<int>(dev_knob("SPECV_ATTN_ROWS_UNITS", 3));
   P.n_cap = plan.wide ? kMaxQWide : kMaxQ;
   P.xcd_swizzle = (plan.kind != 0 && plan.row_groups > 1 &&

@@ -163,6 +163,7 @@ struct AttnPlan {
   int max_chunks;
   int tau;            // > 0: sorted-work-list launch of the token-split kernel, at most tau tiles per wave and item
   int waves8;         // grid-mapped token-split kernel: workgroups of eight waves
+  int mixed;          // kind 0, grid-mapped: requests with more than 64 query rows per KV head run the row-split body
   int wide;           // more than 64 query nodes per request: kernels with two ancestor-mask words per node
 };
 AttnPlan make_attn_plan(const AttnArgs& a);

@@ -1,0 +1,74 @@
+"""Ragged batches of up to 128 query rows per KV head: every request runs the attention body of its own row count
+(token-split with two-term bf16 weights up to 64 rows, row-split beyond), whatever the largest request of the batch or
+the declared bound is."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2503_10325_amd import binding as sv
+from paper_2503_10325_amd import workloads as W
+
+from gpu_util import oracle_attn
+
+pytestmark = pytest.mark.gpu
+
+# 8, 32, 64 | 72, 112, 128 query rows per KV head; contexts that end inside a page, a tile and a chunk
+NODES, CTX = [1, 4, 8, 9, 14, 16], [40, 3001, 1000, 2500, 129, 1777]
+
+
+def structure(nodes, ctx, tree):
+    n = np.asarray(nodes, dtype=np.int32)
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    parent = np.concatenate([(np.arange(k) - 1) // 2 for k in n]).astype(np.int32) if tree else None
+    if tree:                                       # a binary heap under two roots
+        parent[np.isin(np.arange(parent.size), off[:-1])] = -1
+    return W.DraftStructure(n, off, parent, np.asarray(ctx, dtype=np.int32))
+
+
+def attention(nodes, ctx, head_dim, tree, seed=7):
+    cfg = W.scaled(W.CONFIGS["c4_llama70b_serving"], batch=len(nodes), n_q_heads=16, n_kv_heads=2, head_dim=head_dim)
+    return W.make_attn_inputs(cfg, seed=seed, st=structure(nodes, ctx, tree))
+
+
+def run_fp32(a, max_q=None):
+    """(descriptor's plan, fp32 result, natural-log sums) with the partial rows poisoned."""
+    from paper_2503_10325_amd import runner
+    dev = runner.DeviceAttn(a, out_dtype=torch.float32)
+    if max_q:
+        dev.desc.max_q_per_req = max_q
+        dev.workspace = torch.empty(max(256, sv.spec_verify_attn_workspace_size(dev.desc)), dtype=torch.uint8, device="cuda")
+    dev.workspace.fill_(0xFF)
+    dev.run()
+    torch.cuda.synchronize()
+    return sv.spec_describe_attn_plan(dev.desc), dev.out.cpu().numpy(), dev.lse.cpu().numpy()
+
+
+def check(a, got, lse):
+    ref, ref_lse = oracle_attn(a)
+    assert np.abs(lse - ref_lse).max() < 1e-4
+    for b in range(len(a.st.n)):
+        o, e = int(a.st.node_offsets[b]), int(a.st.node_offsets[b + 1])
+        rows = (e - o) * a.cfg.n_q_heads // a.cfg.n_kv_heads
+        # weights of two bf16 terms: 2^-17 of sum p |v| <= max |v| = 5.5, and fp32 sums; of one fp16 term (truncated,
+        # its mean put back): 2^-12 of the same
+        assert np.abs(got[o:e] - ref[o:e]).max() < (5e-5 if rows <= 64 else 3e-3), (b, rows)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("tree", [False, True])
+def test_little_mixed_batch_keeps_each_request_s_body(head_dim, tree):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    a = attention(NODES, CTX, head_dim, tree)
+    plan, got, lse = run_fp32(a)
+    assert "attn_mixed_kernel" in plan
+    check(a, got, lse)
+
+
+def test_loose_bound_changes_no_body():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    a = attention([1, 4, 8, 5], [40, 3001, 1000, 777], 128, False)
+    _, got, lse = run_fp32(a, max_q=16)            # no request has more than 64 rows, the bound says 128
+    check(a, got, lse)
