@@ -86,9 +86,17 @@ int32_t spec_verify_attn(const spec_attn_desc* desc, const void* q, const void* 
     return SPEC_ERR_SHAPE;
   AttnArgs a = attn_args_from(desc);
   if (a.scale == 0.f) a.scale = 1.0f / sqrtf(static_cast<float>(a.D));
-  const AttnPlan plan = make_attn_plan(a);
-  const size_t need = attn_workspace_bytes(a, plan);
-  if (need > 256 && (!workspace || workspace_bytes < need)) return SPEC_ERR_WORKSPACE;
+  AttnPlan plan = make_attn_plan(a);
+  // the token hint steers the cut only: a workspace that was sized under another hint of the same batch is taken as it is
+  // where a launch fits it
+  auto fits = [&] {
+    const size_t need = attn_workspace_bytes(a, plan);
+    return need <= 256 || (workspace && workspace_bytes >= need);
+  };
+  if (!fits()) {
+    plan = make_attn_plan(a, false);
+    if (!fits()) return SPEC_ERR_WORKSPACE;
+  }
   a.q = q; a.k_pool = k_pool; a.v_pool = v_pool; a.block_table = block_table; a.ctx_len = ctx_len;
   a.q_offsets = q_offsets; a.parent = parent; a.out = out; a.lse = lse; a.workspace = workspace;
   return launch_attn(a, plan, static_cast<hipStream_t>(stream));

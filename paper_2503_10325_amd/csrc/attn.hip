@@ -23,6 +23,8 @@
 // v_mfma_f32_32x32x16_f16 term.
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -80,6 +82,7 @@ struct AttnParams {
   int tau;           // > 0: a request is cut so that one wave streams at most tau tiles per work item
   int list_rows_min; // > 0 (kernels with both bodies): requests with this many query rows per KV head use the row-split body
   int list_rows_units;        // eighths of a work-list unit that 32 tokens of such a request cost
+  int chunks_last;            // grid-mapped token-split launch: blockIdx = (KV head, request, chunk)
   int xcd_swizzle;            // grid-mapped row-split launch: consecutive workgroups of the logical order share an XCD
   int n_cap;                  // query nodes per request the launched kernels handle (64, or 128 with two mask words)
   float c;           // scale * log2(e)
@@ -175,7 +178,7 @@ __device__ __forceinline__ int request_units(const AttnParams& P, int L, int n) 
 
 __device__ __forceinline__ int request_chunks(const AttnParams& P, int L, int n) {
   if (P.tau > 0) return min(max(1, (request_units(P, L, n) + P.tau - 1) / P.tau), P.max_chunks);
-  return max(1, (L + P.chunk_tokens - 1) / P.chunk_tokens);
+  return min(max(1, (L + P.chunk_tokens - 1) / P.chunk_tokens), P.max_chunks);   // (the bound lengthens the chunks)
 }
 
 // Token-split kernel (up to 128 query rows per KV head and workgroup).  The 4 waves of a
@@ -522,19 +525,24 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
   }
 }
 
-// Grid-mapped launch: blockIdx = (chunk + max_chunks * row group, KV head, request); workgroups
-// whose chunk does not exist return at once.
+// Grid-mapped launch: blockIdx = (chunk + max_chunks * row group, KV head, request) or, where the block table is much wider
+// than the requests (P.chunks_last), (KV head, request, chunk); workgroups whose chunk does not exist return at once.  A
+// workgroup takes its share of a compute unit's LDS whether it has work or not, so the many without then go last: 5
+// requests x 4 KV heads with at most 6 chunks of the 16 launched 16.7 -> 12.1 us with the merge (11.8 with a table as wide
+// as the longest request), 8 x 8 with 4 of 16 49.9 -> 29.4 (28.3).  Not always: the order puts the chunks of one request
+// on few compute units (4 requests x 8 KV heads, mixed kernel: 24.7 -> 31.4 us).
 // NW = 8 (one workgroup per compute unit instead of two): for launches that have no second workgroup for a compute unit;
 // twice the waves share a chunk's tiles, with no more chunks to merge.  1 request x 8 KV heads x 16000 tokens
 // (56 rows, 512-token chunks) 25.6 -> 24.6 us with the merge, 8 x 32 x 2048 46.0 -> 45.3.
 template <int D, int NW>
 __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attn_stream_kernel(AttnParams P) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int b = blockIdx.z;
+  const int b = P.chunks_last ? blockIdx.y : blockIdx.z, kvh = P.chunks_last ? blockIdx.x : blockIdx.y;
+  const int cut = P.chunks_last ? blockIdx.z : blockIdx.x;
   const int q0 = P.q_offsets[b];
   int n = P.q_offsets[b + 1] - q0;
   n = n > kMaxQ ? kMaxQ : n;
-  stream_item<D, NW>(P, smem, b, blockIdx.y, blockIdx.x % P.max_chunks, blockIdx.x / P.max_chunks, q0, n, P.ctx_len[b]);
+  stream_item<D, NW>(P, smem, b, kvh, cut % P.max_chunks, cut / P.max_chunks, q0, n, P.ctx_len[b]);
 }
 
 constexpr int kPlanMaxB = 128;
@@ -1124,7 +1132,8 @@ template <int D>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_mixed_kernel(AttnParams P) {
   using RC = RowsCfg<D, 4>;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int b = blockIdx.z;
+  const int b = P.chunks_last ? blockIdx.y : blockIdx.z, kvh = P.chunks_last ? blockIdx.x : blockIdx.y;
+  const int chunk = P.chunks_last ? blockIdx.z : blockIdx.x;
   const int q0 = P.q_offsets[b];
   int n = P.q_offsets[b + 1] - q0;
   n = n > kMaxQ ? kMaxQ : n;
@@ -1132,8 +1141,8 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_mixed_kernel(AttnParams 
   const int nch = request_chunks(P, L, n);
   const int cb = (((L + nch - 1) / nch) + RC::kT - 1) & ~(RC::kT - 1);
   // (a chunk longer than the row-split body's page table in LDS stays with the token-split body)
-  if (list_uses_rows(P, n) && cb <= RC::kMaxChunkPages * kPage) rows_item<D, 4>(P, smem, b, blockIdx.y, blockIdx.x, 0, nch, cb, q0, n, ctx);
-  else stream_item<D, kAttnWaves>(P, smem, b, blockIdx.y, blockIdx.x, 0, q0, n, ctx);
+  if (list_uses_rows(P, n) && cb <= RC::kMaxChunkPages * kPage) rows_item<D, 4>(P, smem, b, kvh, chunk, 0, nch, cb, q0, n, ctx);
+  else stream_item<D, kAttnWaves>(P, smem, b, kvh, chunk, 0, q0, n, ctx);
 }
 
 // Merge the per-chunk partials of every (query row, head) that spans several chunks.  A group of D/4 lanes reads
@@ -1240,27 +1249,48 @@ static long dev_knob(const char* name, long fallback) {
 static long dev_knob(const char*, long fallback) { return fallback; }
 #endif
 
-AttnPlan make_attn_plan(const AttnArgs& a) {
+// Most chunks the work list cuts a request into: the longest one the block table can hold, shared by as many waves as
+// the largest declared row count leaves per query block (requests with fewer rows get more waves), at tau tiles a wave.
+static int list_max_chunks(int64_t max_tok, int max_rows, int tau) {
+  const int min_slice = max_rows <= 32 ? 4 : (max_rows <= 64 ? 2 : 1);
+  const int64_t max_tiles = ((max_tok + kTile - 1) / kTile + min_slice - 1) / min_slice;
+  const int64_t mc = (max_tiles + tau - 1) / tau;
+  return static_cast<int>(mc < 1 ? 1 : (mc > kListMaxChunks ? kListMaxChunks : mc));
+}
+constexpr int kListTau = 44;         // with the alternating hand-out of the list: 40-48 measured best
+// The launch for little work has a workgroup for every chunk a request could have.  Most chunks per request such that
+// those are at most four workgroups per compute unit, or two per (request, KV head) pair.
+static int little_room(int B, int Hkv) {
+  const int64_t room = 1024 / (static_cast<int64_t>(B > 0 ? B : 1) * Hkv);
+  return room < 2 ? 2 : static_cast<int>(room);
+}
+
+AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   AttnPlan p;
   p.tau = 0;
   p.waves8 = 0;
   p.mixed = 0;
+  p.wide_table = 0;
   p.wide = a.max_q > kMaxQ ? 1 : 0;
   const int G = a.Hq / a.Hkv;
   const int max_rows = a.max_q * G;
-  const int64_t max_tok0 = static_cast<int64_t>(a.max_pages) * a.page;
-  const bool ragged0 = a.kv_hint > 0 && a.kv_hint * 100 < static_cast<int64_t>(85) * a.B * max_tok0;
+  const int64_t max_tok = static_cast<int64_t>(a.max_pages) * a.page;
+  const bool ragged = a.kv_hint > 0 && a.kv_hint * 100 < static_cast<int64_t>(85) * a.B * max_tok;
   // Little work - the tokens of all requests and KV heads, dealt to 256 workgroups, are chunks below 1024 - is cut by
   // tokens, whatever the lengths: every request then has items of about one length.  The sorted work list cuts by what
   // a wave can stream at full load and left such batches to a few workgroups (5 requests x 4 KV heads, 777 to 3001
-  // tokens: 20 of 512 workgroups, 26.7 us; 13.2 us cut into 512-token chunks).
-  const bool little = a.kv_hint > 0 && a.kv_hint * a.Hkv < static_cast<int64_t>(256) * 1024;
+  // tokens: 20 of 512 workgroups, 26.7 us; 13.2 us cut into 512-token chunks).  The list serves them all the same where
+  // a wide block table (allocated for the longest context a model allows) would ask for more chunks than there is room
+  // for, and where the caller's workspace holds the list's partial results but not these (little_ok).
+  const int list_chunks = list_max_chunks(max_tok, max_rows, kListTau);
+  const int room = little_room(a.B, a.Hkv);
+  const bool little = little_ok && a.kv_hint > 0 && a.kv_hint * a.Hkv < static_cast<int64_t>(256) * 1024 && list_chunks <= room;
   // Up to 64 query rows per KV head the token-split body streams as fast as memory delivers; beyond, its
   // waves (one per 32-row block, each staging every tile for itself) are bound by their own staging and the
   // row-split body, whose waves share each staged tile, is ahead on batches of like lengths (96 rows per KV
   // head: 4.2 against 2.6 TB/s).  In ragged batches of up to 128 rows every request takes the body of its own row count
   // (work list, or attn_mixed_kernel when there is little work): max_q is a bound, and most requests have fewer nodes.
-  if (max_rows <= 64 || (max_rows <= 128 && ragged0 && a.B <= kPlanMaxB)) { p.kind = 0; p.rows_per_wg = 128; }
+  if (max_rows <= 64 || (max_rows <= 128 && ragged && a.B <= kPlanMaxB)) { p.kind = 0; p.rows_per_wg = 128; }
   else if (max_rows <= 128 || a.D != 128) { p.kind = 1; p.rows_per_wg = 128; }
   else { p.kind = 2; p.rows_per_wg = 256; }
   // Few (request, KV head) pairs with many rows each: 256-row workgroups would have to cut the context to fill
@@ -1281,10 +1311,11 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
   // more than 64 query nodes per request (two mask words per node): the row-split kernels only
   if (p.wide && p.kind == 0) { p.kind = 1; p.rows_per_wg = 128; }
   p.row_groups = (max_rows + p.rows_per_wg - 1) / p.rows_per_wg;
-  p.mixed = (p.kind == 0 && max_rows > 64 && little) ? 1 : 0;
+  // (the list kernel packs a request's first query row into 16 bits)
+  const bool listable = p.kind == 0 && a.B <= kPlanMaxB && a.total_q < 65536;
+  p.mixed = (listable && max_rows > 64 && little) ? 1 : 0;
   const bool token_split = (p.kind == 0 && !p.mixed);                           // (a mixed launch is cut for the row-split body)
   const int gran = token_split ? kTile : (p.kind == 3 ? 128 : 64);              // chunks are whole tiles
-  const int64_t max_tok = static_cast<int64_t>(a.max_pages) * a.page;
   int64_t tok = a.kv_hint > 0 ? a.kv_hint : static_cast<int64_t>(a.B) * max_tok;
   // Chunk length.  Every workgroup pays a fixed prologue/epilogue (and, when a request is split, a
   // partial-result round trip proportional to its query rows), so chunks are as long as two
@@ -1317,20 +1348,22 @@ AttnPlan make_attn_plan(const AttnArgs& a) {
   // tokens.  The list costs every workgroup one extra round of dependent loads (~5 us per launch),
   // which only pays when lengths differ: the caller's total-token hint against batch x longest
   // request says whether they do.
-  const bool ragged = a.kv_hint > 0 && a.kv_hint * 100 < static_cast<int64_t>(85) * a.B * max_tok;
-  // (the list kernel packs a request's first query row into 16 bits)
-  int tau = (token_split && a.B <= kPlanMaxB && a.total_q < 65536 && ragged && !little) ? 44 : 0;   // with the alternating hand-out below: 40-48 measured best
+  int tau = (listable && ragged && !little) ? kListTau : 0;
   const long tau_knob = dev_knob("SPECV_ATTN_TAU", -1);   // 0: grid-mapped launch
-  if (token_split && a.B <= kPlanMaxB && a.total_q < 65536 && tau_knob >= 0 && tau_knob <= 255) tau = static_cast<int>(tau_knob);
+  if (listable && !p.mixed && tau_knob >= 0 && tau_knob <= 255) tau = static_cast<int>(tau_knob);
   if (jobs_knob > 0) tau = 0;
   if (tau > 0) {
-    // most tiles one wave can have to stream: the longest request, shared by as many waves as the
-    // largest declared row count leaves per query block (requests with fewer rows get more waves)
-    const int min_slice = max_rows <= 32 ? 4 : (max_rows <= 64 ? 2 : 1);
-    const int64_t max_tiles = ((max_tok + kTile - 1) / kTile + min_slice - 1) / min_slice;
-    const int64_t mc = (max_tiles + tau - 1) / tau;
     p.tau = tau;
-    p.max_chunks = static_cast<int>(mc < 1 ? 1 : (mc > kListMaxChunks ? kListMaxChunks : mc));
+    p.max_chunks = list_max_chunks(max_tok, max_rows, tau);
+  } else if (listable && ragged && (p.max_chunks > room || p.max_chunks > tok / p.chunk_tokens + 2)) {
+    // A table wider than there is room for, or than all tokens together are long: no more chunks than the list would make,
+    // eight, or twice those of an average request (one request: its own), and a request that is longer than so many is
+    // cut into longer ones.  Launch, partial results and the groups that merge them follow the tokens, not the table.
+    const int64_t all = (tok + p.chunk_tokens - 1) / p.chunk_tokens;
+    int64_t bound = a.B > 1 ? 2 * all / a.B : all;
+    bound = std::max<int64_t>(bound, std::max(list_chunks, 8));
+    bound = std::min<int64_t>(bound, room);
+    if (bound < p.max_chunks) { p.max_chunks = static_cast<int>(bound); p.wide_table = 1; }
   }
   if (token_split && p.tau == 0) {
     // one workgroup of eight waves per compute unit where there are not two of four for it; workgroups that have work:
@@ -1381,13 +1414,18 @@ static int launch_stream_list(const AttnParams& P, hipStream_t stream) {
   return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 
+static dim3 stream_grid(const AttnParams& P, const AttnPlan& plan, int B, int Hkv) {
+  const int cuts = plan.max_chunks * plan.row_groups;
+  return P.chunks_last ? dim3(Hkv, B, cuts) : dim3(cuts, Hkv, B);
+}
+
 template <int D>
 static int launch_mixed(const AttnParams& P, const AttnPlan& plan, int B, int Hkv, hipStream_t stream) {
   constexpr size_t kLds = both_bodies_lds<D>();
   static_assert(kLds <= 80 * 1024, "two workgroups of the mixed kernel per compute unit");
   static std::atomic<uint64_t> attr_done{0};
   if (set_lds_once(&attn_mixed_kernel<D>, kLds, attr_done) != 0) return -6;
-  hipLaunchKernelGGL((attn_mixed_kernel<D>), dim3(plan.max_chunks, Hkv, B), dim3(kAttnThreads), kLds, stream, P);
+  hipLaunchKernelGGL((attn_mixed_kernel<D>), stream_grid(P, plan, B, Hkv), dim3(kAttnThreads), kLds, stream, P);
   return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 
@@ -1398,8 +1436,7 @@ static int launch_stream_as(const AttnParams& P, const AttnPlan& plan, int B, in
   static_assert(kTiles * (NW == 4 ? 2 : 1) <= 160 * 1024, "token-split kernel: LDS per compute unit");
   static std::atomic<uint64_t> attr_done{0};
   if (set_lds_once(&attn_stream_kernel<D, NW>, kTiles, attr_done) != 0) return -6;
-  dim3 grid(plan.max_chunks * plan.row_groups, Hkv, B);
-  hipLaunchKernelGGL((attn_stream_kernel<D, NW>), grid, dim3(NW * kWave), kTiles, stream, P);
+  hipLaunchKernelGGL((attn_stream_kernel<D, NW>), stream_grid(P, plan, B, Hkv), dim3(NW * kWave), kTiles, stream, P);
   return hipGetLastError() == hipSuccess ? 0 : -6;
 }
 
@@ -1469,6 +1506,7 @@ int launch_attn(const AttnArgs& a, const AttnPlan& plan, hipStream_t stream) {
   P.list_rows_min = plan.tau > 0 || plan.mixed ? static_cast<int>(dev_knob("SPECV_ATTN_LIST_ROWS", 65)) : 0;
   P.list_rows_units = static_cast<int>(dev_knob("SPECV_ATTN_ROWS_UNITS", 3));
   P.n_cap = plan.wide ? kMaxQWide : kMaxQ;
+  P.chunks_last = plan.wide_table;
   P.xcd_swizzle = (plan.kind != 0 && plan.row_groups > 1 &&
                    (static_cast<int64_t>(plan.max_chunks) * plan.row_groups * a.Hkv * a.B) % 8 == 0) ? 1 : 0;
   P.c = a.scale * kLog2e;

@@ -1,0 +1,41 @@
+"""Launch plan of spec_verify_attn for ragged batches with little work: what it asks for follows the tokens, not the width
+of the block table (a serving engine allocates that for the longest context its model allows).  Host calls only."""
+import os
+
+import pytest
+
+from paper_2503_10325_amd import binding as sv
+
+pytestmark = pytest.mark.skipif(not os.path.exists(sv.LIB_PATH), reason="libspecverify.so not built")
+
+
+@pytest.mark.parametrize("batch,heads,total_q,max_q,hint,pages", [
+    (4, (64, 8), 40, 10, 8040, 8192),       # 80 rows per KV head
+    (8, (64, 8), 56, 7, 16056, 2048),       # 56
+    (1, (64, 8), 8, 8, 2008, 8192),         # one request
+    (16, (32, 8), 80, 5, 32080, 8192),      # many pairs of request and KV head
+    (5, (12, 4), 30, 9, 9000, 8192),
+    (2, (16, 2), 16, 8, 1, 8192),           # the hint is an estimate and may be far off
+])
+def test_wide_block_tables_do_not_scale_the_launch(batch, heads, total_q, max_q, hint, pages):
+    kw = dict(batch=batch, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=128, total_q=total_q, max_q_per_req=max_q,
+              max_pages_per_req=pages)
+    desc = sv.make_attn_desc(total_kv_tokens_hint=hint, **kw)
+    plan, need = sv.spec_describe_attn_plan(desc), sv.spec_verify_attn_workspace_size(desc)
+    chunks = int(plan.split("at most ")[1].split()[0])
+    # the work list cuts a request into at most 16 chunks, of at most 44 tiles per wave
+    rows = max_q * heads[0] // heads[1]
+    tiles = pages * 16 // 32 // (4 if rows <= 32 else 2 if rows <= 64 else 1)
+    assert chunks <= min(16, -(-tiles // 44)), plan
+    assert chunks * batch * heads[1] <= 1024 or "list" in plan, plan
+    assert need <= 256 + total_q * heads[0] * 16 * 130 * 4
+    # a workspace sized without the hint holds the partial results of every hint
+    unknown = sv.spec_verify_attn_workspace_size(sv.make_attn_desc(total_kv_tokens_hint=0, **kw))
+    assert need <= unknown
+
+
+def test_narrow_block_tables_are_cut_by_tokens():
+    desc = sv.make_attn_desc(batch=5, num_q_heads=12, num_kv_heads=4, head_dim=64, total_q=30, max_q_per_req=9,
+                             max_pages_per_req=189, total_kv_tokens_hint=9000)
+    plan = sv.spec_describe_attn_plan(desc)
+    assert "list" not in plan and "chunks of 512 tokens, at most 6 per request" in plan

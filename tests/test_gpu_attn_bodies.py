@@ -1,6 +1,9 @@
 """Ragged batches of up to 128 query rows per KV head: every request runs the attention body of its own row count
 (token-split with two-term bf16 weights up to 64 rows, row-split beyond), whatever the largest request of the batch or
-the declared bound is."""
+the declared bound is; and a block table much wider than the longest request changes neither the result nor which
+workspaces are accepted."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -72,3 +75,47 @@ def test_loose_bound_changes_no_body():
     a = attention([1, 4, 8, 5], [40, 3001, 1000, 777], 128, False)
     _, got, lse = run_fp32(a, max_q=16)            # no request has more than 64 rows, the bound says 128
     check(a, got, lse)
+
+
+def widened(a, pages):
+    table = np.full((a.block_table.shape[0], pages), -1, dtype=np.int32)
+    table[:, :a.max_pages] = a.block_table
+    return dataclasses.replace(a, block_table=table, max_pages=pages)
+
+
+# (nodes, contexts): up to 64 rows per KV head, and both bodies
+WIDE = [([1, 4, 8, 5], [40, 9000, 1000, 777]), ([1, 9, 14, 8], [300, 129, 9000, 777])]
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("nodes,ctx", WIDE)
+def test_wide_block_table(head_dim, nodes, ctx):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    a = widened(attention(nodes, ctx, head_dim, False), 8192)
+    plan, got, lse = run_fp32(a)
+    tokens, chunks = int(plan.split("chunks of ")[1].split()[0]), int(plan.split("at most ")[1].split()[0])
+    assert "list" not in plan and tokens * chunks < 9000, plan          # the longest request's chunks are lengthened
+    check(a, got, lse)
+
+
+@pytest.mark.parametrize("nodes,ctx", WIDE)
+@pytest.mark.parametrize("pages", [564, 8192])
+def test_workspace_sized_under_another_hint(nodes, ctx, pages):
+    """The hint only steers the cut: a workspace asked for without it, or with one that calls for the work list, serves
+    the same batch under its own hint."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import runner
+    a = widened(attention(nodes, ctx, 128, False), pages)
+    dev = runner.DeviceAttn(a, out_dtype=torch.float32)
+    hint = dev.desc.total_kv_tokens_hint
+    for other in (0, 130 * 1024):
+        dev.desc.total_kv_tokens_hint = other if other == 0 or other < 0.8 * 4 * pages * 16 else 0
+        need = sv.spec_verify_attn_workspace_size(dev.desc)
+        dev.desc.total_kv_tokens_hint = hint
+        dev.workspace = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda") if need > 256 else None
+        dev.out.fill_(float("nan"))
+        dev.run()
+        torch.cuda.synchronize()
+        check(a, dev.out.cpu().numpy(), dev.lse.cpu().numpy())
