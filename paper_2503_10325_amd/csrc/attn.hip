@@ -290,8 +290,6 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
   int t = my_slice;
   const bool any_tile = wave_active && t < ntiles;
   if (any_tile) fetch_pages(t);
-  int my_par = -1;
-  if (touches_drafts && P.parent && tid < n) my_par = P.parent[q0 + tid];
   // ---- this lane's query column ----
   const int row = row0 + 32 * my_qb + ln;
   const bool valid = row < R;
@@ -307,6 +305,9 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
       qf[ks] = as_bf16x8(v);
     }
   }
+  // (here, where the page ids have to be waited for anyway: a value still on its way behind the tile's loads would be
+  // waited for with all of them)
+  if (touches_drafts && P.parent && tid < kMaxQ) sh_par[tid] = tid < n ? P.parent[q0 + tid] : -1;
   if (any_tile) {
     issue_loads(t);
     fetch_pages(t + nslice);
@@ -314,10 +315,7 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
 
   // ---- ancestor-or-self masks of the draft nodes (only chunks that reach the drafts) ----
   if (touches_drafts) {
-    if (P.parent) {
-      if (tid < kMaxQ) sh_par[tid] = my_par;
-      __syncthreads();
-    }
+    if (P.parent) __syncthreads();
     if (tid < kMaxQ) {
       unsigned long long mask = 0;
       if (tid < n) {
