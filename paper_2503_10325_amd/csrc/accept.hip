@@ -849,12 +849,16 @@ static int linear_unit_classes(int B, int V, int n_cu) {
 // block sums, the block of the draw are seven dependent trips to memory at most, so the work between two trips is kept
 // short: no barrier between the node arrays and the loads they lead to, every wave takes the accept decisions itself
 // (lane j node j, one ballot), reductions and scans run on data-parallel primitives, and the block of the draw is found
-// by a scan over the lanes.  Against the version with a barrier per phase and
-// serial searches: 1 request x 1000 classes 8.8 -> 7.0 us, 8 x 32000 11.6 -> 8.8, 1 x 128256 13.0 -> 9.4, 64 x 128256
-// 21.1 -> 16.5, 5 x 50257 fp32 16.7 -> 9.8 (one element per load before).
-template <int TDT, int QDT>
+// by a scan over the lanes.  Against the version with a barrier per phase and serial searches: 1 request x 1000 classes
+// 8.8 -> 5.1 us, 8 x 32000 11.6 -> 8.2, 1 x 128256 13.0 -> 8.5, 64 x 128256 21.1 -> 15.2, 5 x 50257 fp32 16.7 -> 8.2 (one
+// element per load before).
+//
+// BPU: blocks of a unit.  A constant, so that the loads of a unit stand side by side without a branch and are those of its
+// own blocks only (with the loads of four blocks whatever their number, the neighbours' read and dropped: 8 x 32000 8.8
+// us, 1 x 128256 9.2, 5 x 50257 fp32 9.3; 16 x 128256 with its statistics 21.6 instead of 18.1).
+template <int TDT, int QDT, int BPU>
 __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptParams P, double* __restrict__ partial,
-                                                                    unsigned* __restrict__ arrived, int U, int unit_classes) {
+                                                                    unsigned* __restrict__ arrived, int U) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = blockIdx.x / U, unit = blockIdx.x % U;
   const int o = P.node_offsets[b];
@@ -874,7 +878,7 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
   __shared__ float sh_lp[kMaxNodes], sh_lq[kMaxNodes], sh_u[kMaxNodes];
   __shared__ double sh_part[kLinMaxUnits];
   __shared__ int sh_last;
-  __shared__ double sh_bw[kLinMaxBlocks][kLinWaves];
+  __shared__ double sh_bw[BPU][kLinWaves];
   const float no_scale[1] = {0.f};               // 1/R_k of lower levels: none exist at levels 0 and 1
 
   const double u_res = static_cast<double>(P.u_resample[b]);
@@ -950,70 +954,62 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
     level = 1;
   }
 
-  // Weights of this thread's eight classes in each block of unit k (at most kLinMaxBlocks blocks, their loads
-  // issued together) and the per-block fp32 sums.  Identical arithmetic wherever it is called.
-  const int bpu = unit_classes / kLinBlock;         // blocks per unit, <= kLinMaxBlocks
+  // Weights of this thread's eight classes in each block of unit k (their loads issued together) and the per-block fp32
+  // sums.  Identical arithmetic wherever it is called.
   const int nblocks = (V + kLinBlock - 1) / kLinBlock;
-  auto unit_weights = [&](int k, int L, float (&w)[kLinMaxBlocks][8], float (&lsf)[kLinMaxBlocks]) {
+  auto unit_weights = [&](int k, int L, float (&w)[BPU][8], float (&lsf)[BPU]) {
     auto t_off = [&](int) { return R.t_off; };
     auto q_off = [&](int) { return R.q_off; };
-    auto e0 = [&](int i) { return (k * bpu + i) * kLinBlock + tid * 8; };
-    Raw8<TDT, kLinMaxBlocks> rp;
-    Raw8<QDT, kLinMaxBlocks> rq;
+    auto e0 = [&](int i) { return (k * BPU + i) * kLinBlock + tid * 8; };
+    Raw8<TDT, BPU> rp;
+    Raw8<QDT, BPU> rq;
     issue8(R.t_base, t_off, e0, V, rp);
     if (L > 0) issue8(R.q_base, q_off, e0, V, rq);
 #pragma unroll
-    for (int i = 0; i < kLinMaxBlocks; ++i) {
+    for (int i = 0; i < BPU; ++i) {
       lsf[i] = 0.f;
-      if (i < bpu) {
-        float lp[8], lq[8];
-        take8<false>(R.t_base, R.t_off, e0(i), V, rp, i, lp);
-        if (L > 0) take8<false>(R.q_base, R.q_off, e0(i), V, rq, i, lq);
-        weights_from(R, lp, lq, 8, c, L, no_scale, w[i]);
-        if (__any(e0(i) > V - 8)) {
+      float lp[8], lq[8];
+      take8<false>(R.t_base, R.t_off, e0(i), V, rp, i, lp);
+      if (L > 0) take8<false>(R.q_base, R.q_off, e0(i), V, rq, i, lq);
+      weights_from(R, lp, lq, 8, c, L, no_scale, w[i]);
+      if (__any(e0(i) > V - 8)) {
 #pragma unroll
-          for (int j = 0; j < 8; ++j) w[i][j] = first8(e0(i), V) + j >= e0(i) ? w[i][j] : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) lsf[i] += w[i][j];
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[i][j] = 0.f;
+        for (int j = 0; j < 8; ++j) w[i][j] = first8(e0(i), V) + j >= e0(i) ? w[i][j] : 0.f;
       }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) lsf[i] += w[i][j];
     }
   };
   // per-block totals from the per-thread sums: fp64 across lanes and waves in a fixed order; in every thread
-  auto block_totals = [&](const float (&lsf)[kLinMaxBlocks], double (&tot)[kLinMaxBlocks]) {
+  auto block_totals = [&](const float (&lsf)[BPU], double (&tot)[BPU]) {
     __syncthreads();                  // earlier readers of sh_bw are done
 #pragma unroll
-    for (int i = 0; i < kLinMaxBlocks; ++i) {
+    for (int i = 0; i < BPU; ++i) {
       tot[i] = 0.0;
-      if (i < bpu) sh_bw[i][wave] = wave_sum(static_cast<double>(lsf[i]));      // every lane stores the same value
+      sh_bw[i][wave] = wave_sum(static_cast<double>(lsf[i]));      // every lane stores the same value
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kLinMaxBlocks; ++i)
-      if (i < bpu) {
+    for (int i = 0; i < BPU; ++i)
 #pragma unroll
-        for (int v = 0; v < kLinWaves; ++v) tot[i] += sh_bw[i][v];
-      }
+      for (int v = 0; v < kLinWaves; ++v) tot[i] += sh_bw[i][v];
   };
 
-  float w[kLinMaxBlocks][8], lsf[kLinMaxBlocks];
-  double tot[kLinMaxBlocks];
+  float w[BPU][8], lsf[BPU];
+  double tot[BPU];
   unit_weights(unit, level, w, lsf);
   block_totals(lsf, tot);
   if (U == 1) {                       // nothing to hand over
     if (wave == 0) {
 #pragma unroll
-      for (int i = 0; i < kLinMaxBlocks; ++i)
+      for (int i = 0; i < BPU; ++i)
         if (i < nblocks) sh_part[i] = tot[i];
     }
   } else {
     if (wave == 0) {                  // all lanes of wave 0 store the same words (no per-lane role around barriers)
 #pragma unroll
-      for (int i = 0; i < kLinMaxBlocks; ++i)
-        if (i < bpu && unit * bpu + i < nblocks) st_dev(&partial[static_cast<int64_t>(b) * nblocks + unit * bpu + i], tot[i]);
+      for (int i = 0; i < BPU; ++i)
+        if (unit * BPU + i < nblocks) st_dev(&partial[static_cast<int64_t>(b) * nblocks + unit * BPU + i], tot[i]);
       wait_stores();
       unsigned old = 0;
       if (lane == 0) old = __hip_atomic_fetch_add(&arrived[b * kCntStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1048,8 +1044,8 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
       __syncthreads();
       if (tid == 0) {
 #pragma unroll
-        for (int i = 0; i < kLinMaxBlocks; ++i)
-          if (i < bpu && k * bpu + i < nblocks) sh_part[k * bpu + i] = tot[i];
+        for (int i = 0; i < BPU; ++i)
+          if (k * BPU + i < nblocks) sh_part[k * BPU + i] = tot[i];
       }
     }
     __syncthreads();
@@ -1087,10 +1083,10 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
   float wh[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) wh[j] = 0.f;
-  if (!redrawn && kb_hit / bpu == unit) {
+  if (!redrawn && kb_hit / BPU == unit) {
 #pragma unroll
-    for (int i = 0; i < kLinMaxBlocks; ++i)
-      if (i == kb_hit - unit * bpu) {
+    for (int i = 0; i < BPU; ++i)
+      if (i == kb_hit - unit * BPU) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) wh[j] = w[i][j];
       }
@@ -1137,6 +1133,13 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
     found = pos ? __builtin_amdgcn_readlane(my_last, 63 - __clzll(static_cast<long long>(pos))) : min(V - 1, kb_hit * kLinBlock);
   }
   if (lane == 0 && depth < P.out_stride) P.out_tokens[static_cast<int64_t>(b) * P.out_stride + depth] = found;
+}
+
+template <int TDT, int QDT>
+static auto linear_kernel(int blocks) {
+  static_assert(kLinMaxBlocks == 4, "one instantiation per number of blocks");
+  return blocks == 1 ? accept_linear_kernel<TDT, QDT, 1> : (blocks == 2 ? accept_linear_kernel<TDT, QDT, 2>
+       : (blocks == 3 ? accept_linear_kernel<TDT, QDT, 3> : accept_linear_kernel<TDT, QDT, 4>));
 }
 
 // Workspace: [row statistics][helper protocol: pass descriptors, hand-back slots (zeroed by the
@@ -1268,10 +1271,11 @@ void launch_accept(const AcceptArgs& a, hipStream_t stream) {
     double* partial = reinterpret_cast<double*>(ws + lay.lin_off);
     unsigned* arrived = reinterpret_cast<unsigned*>(ws + lay.arrived_off);
     const dim3 grid_l(static_cast<unsigned>(a.B) * U);
+    const int blocks = unit_classes / kLinBlock;
     auto kernel = a.t_dtype == kBF16
-                      ? (a.q_dtype == kBF16 ? accept_linear_kernel<kBF16, kBF16> : accept_linear_kernel<kBF16, kF32>)
-                      : (a.q_dtype == kBF16 ? accept_linear_kernel<kF32, kBF16> : accept_linear_kernel<kF32, kF32>);
-    hipLaunchKernelGGL(kernel, grid_l, dim3(kLinThreads), 0, stream, P, partial, arrived, U, unit_classes);
+                      ? (a.q_dtype == kBF16 ? linear_kernel<kBF16, kBF16>(blocks) : linear_kernel<kBF16, kF32>(blocks))
+                      : (a.q_dtype == kBF16 ? linear_kernel<kF32, kBF16>(blocks) : linear_kernel<kF32, kF32>(blocks));
+    hipLaunchKernelGGL(kernel, grid_l, dim3(kLinThreads), 0, stream, P, partial, arrived, U);
     return;
   }
   // Helpers pay when a pass is long against a hand-off between compute units (a few microseconds):

@@ -58,6 +58,24 @@ def test_accept_and_greedy(rt, V, fp32):
             assert np.array_equal(gotg[key], rg[key]), key
 
 
+@pytest.mark.parametrize("V", [32768, 32769, 65536, 65537, 98304, 98305, 131072])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_linear_draw_blocks_per_workgroup(rt, V, fp32):
+    """64 requests leave eight workgroups each on 256 compute units: one to four 4096-class blocks per workgroup, the last
+    one full or with a single class."""
+    from paper_2503_10325_amd import binding as sv
+    cfg = W.scaled(W.CONFIGS["c4_llama70b_serving"], batch=64, vocab=V, draft=("linear", 1))
+    ai = W.make_accept_inputs(cfg, seed=V)
+    tl, dq = ai.target_logits, ai.draft_q
+    if fp32:
+        tl, dq = W.bf16_bits_to_f32(tl), W.bf16_bits_to_f32(dq)
+    ref = oracle.accept(ai.st.node_offsets, None, ai.draft_tokens, tl, dq, ai.q_row, ai.u_accept, ai.u_resample)
+    dev = rt.DeviceAccept(ai.st, tl, dq, ai.q_row, ai.draft_tokens, ai.u_accept, ai.u_resample)
+    dev.run(tuning=sv.SpecAcceptTuning(path=3))
+    bad, _, _ = compare_accept(dev.results(), ref, ai.st.n)
+    assert not bad
+
+
 @pytest.mark.parametrize("V,N", [(5, 3), (9, 1), (2047, 4), (2049, 5), (3001, 17), (140003, 2)])
 def test_mixture(rt, V, N):
     from paper_2503_10325_amd import binding as sv
