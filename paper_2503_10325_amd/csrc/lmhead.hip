@@ -68,10 +68,11 @@ struct TlCfg {
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float lm_f32x4;
 
 // 16 bytes per lane from base + off to LDS: lane i's land at byte lds_at + 16 i.  Not tracked by the compiler: the
-// loop counts these loads itself (vmcnt).
+// loop counts these loads itself (vmcnt).  The LDS address is an operand bound to M0: the compiler writes that register
+// itself and knows when it changes (a write inside the statement would have to be declared as a clobber, which it does
+// not honour for a reserved register).
 __device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned off, unsigned lds_at) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_at), "v"(off), "s"(base) : "memory", "m0");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "{m0}"(lds_at), "v"(off), "s"(base) : "memory");
 }
 
 // The product of one wave with NT row tiles of the workgroup's NT2, up to the rounded output tile and the per-row
