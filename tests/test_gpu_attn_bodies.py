@@ -29,8 +29,9 @@ def structure(nodes, ctx, tree):
     return W.DraftStructure(n, off, parent, np.asarray(ctx, dtype=np.int32))
 
 
-def attention(nodes, ctx, head_dim, tree, seed=7):
-    cfg = W.scaled(W.CONFIGS["c4_llama70b_serving"], batch=len(nodes), n_q_heads=16, n_kv_heads=2, head_dim=head_dim)
+def attention(nodes, ctx, head_dim, tree, seed=7, kv_heads=2):
+    cfg = W.scaled(W.CONFIGS["c4_llama70b_serving"], batch=len(nodes), n_q_heads=8 * kv_heads, n_kv_heads=kv_heads,
+                   head_dim=head_dim)
     return W.make_attn_inputs(cfg, seed=seed, st=structure(nodes, ctx, tree))
 
 
@@ -55,7 +56,7 @@ def check(a, got, lse):
         rows = (e - o) * a.cfg.n_q_heads // a.cfg.n_kv_heads
         # weights of two bf16 terms: 2^-17 of sum p |v| <= max |v| = 5.5, and fp32 sums; of one fp16 term (truncated,
         # its mean put back): 2^-12 of the same
-        assert np.abs(got[o:e] - ref[o:e]).max() < (5e-5 if rows <= 64 else 3e-3), (b, rows)
+        assert e == o or np.abs(got[o:e] - ref[o:e]).max() < (5e-5 if rows <= 64 else 3e-3), (b, rows)
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
@@ -119,3 +120,44 @@ def test_workspace_sized_under_another_hint(nodes, ctx, pages):
         dev.run()
         torch.cuda.synchronize()
         check(a, dev.out.cpu().numpy(), dev.lse.cpu().numpy())
+
+
+def listed(a, pages=8192):
+    """The batch with a table and a hint that call for the work list (lengths are ragged against the table, and the hint
+    says that there is much work; it only steers the cut)."""
+    from paper_2503_10325_amd import runner
+    a = widened(a, pages)
+    hint = int(0.8 * len(a.st.n) * pages * 16)
+    dev = runner.DeviceAttn(a, out_dtype=torch.float32, kv_hint=hint)
+    plan = sv.spec_describe_attn_plan(dev.desc)
+    assert "attn_stream_list_kernel" in plan
+    dev.workspace.fill_(0xFF)
+    dev.run()
+    torch.cuda.synchronize()
+    check(a, dev.out.cpu().numpy(), dev.lse.cpu().numpy())
+    return plan
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("nodes,ctx,kv_heads", [
+    (NODES, CTX, 2),
+    ([8, 3, 0, 1], [5000, 0, 200, 64], 2),                      # token-split body only; no nodes, no context
+    ([16, 12, 9], [9000, 0, 700], 2),                           # row-split body only
+    ([2, 11] * 50, [(77 * k) % 300 for k in range(100)], 8),    # 800 items on 512 workgroups: two rounds
+])
+def test_work_list(head_dim, tree, nodes, ctx, kv_heads):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    listed(attention(nodes, ctx, head_dim, tree, kv_heads=kv_heads))
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("nodes,longest", [(8, 50000), (9, 64000)])
+def test_work_list_most_chunks(head_dim, nodes, longest):
+    """Contexts that 16 chunks of 44 tiles per wave do not hold (64 rows: 45056 tokens; row-split body, whose tiles count
+    3/8: 60074): chunks get longer."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    plan = listed(attention([nodes, 2, nodes], [longest, 100, 3000], head_dim, False))
+    assert "at most 16 per request" in plan

@@ -1,6 +1,6 @@
 """GPU parity at the edges of what the library accepts: the largest vocabulary, the longest draft
-chain, contexts long enough to hit the chunk-count cap of the work-list launch and the chunk-length
-cap of the row-split kernel, and a batch just above the work-list limit."""
+chain, long ragged contexts, contexts long enough to hit the chunk-length cap of the row-split kernel, and
+a batch just above the work-list limit."""
 import numpy as np
 import pytest
 
@@ -37,8 +37,8 @@ def _attn(rt, cfg, seed, st=None, **kw):
 
 
 def test_attention_long_ragged_contexts_hit_the_chunk_cap(rt):
-    # 16 query rows per KV head (four waves per block) and 80 rows (one wave per block, every tile):
-    # the second cuts a 30000-token context into the maximum of 16 chunks
+    # 16 query rows per KV head and 80 rows: few tokens for the chip, so a 30000-token context is cut into many chunks (the
+    # work list's cap of 16 is test_gpu_attn_bodies.py's)
     for draft, heads in ((("linear", 2), (8, 1)), (("linear", 10), (8, 1))):
         cfg = W.scaled(C["c4_llama70b_serving"], batch=3, n_q_heads=heads[0], n_kv_heads=heads[1], draft=draft,
                        ctx=("fixed", 100))

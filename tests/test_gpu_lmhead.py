@@ -103,7 +103,7 @@ def check_lm_head(rt, rows, d_model, V, T, seed=0):
 @pytest.mark.parametrize("rows,d_model,V,T", [
     (70, 256, 3000, 1.0),        # ragged row tile, ragged vocabulary block
     (5, 128, 1001, 1.0),         # one slice per half, odd vocabulary (scalar stores)
-    (200, 512, 8300, 0.7),       # more than 128 rows: packed hidden states, last wave with one row tile
+    (200, 512, 8300, 0.7),       # more than 128 rows
     (300, 256, 1500, 1.0),       # two row blocks of 256, the second with 44 rows (three waves without rows)
     (128, 1024, 16384, 1.3),     # full tiles everywhere
     (1, 128, 130, 1.0),          # a single row, a second vocabulary block of two entries
@@ -254,8 +254,8 @@ def own_logits_stats_agree(dev, V, T):
 
 
 @pytest.mark.parametrize("rows,d_model,V", [
-    (72, 4096, 32000),         # c1's target rows on the Llama-2-7B head: the weight-read-bound kernel
-    (224, 4096, 32000),        # c3's target rows: the wide kernel with the weights four slices ahead
+    (72, 4096, 32000),         # c1's target rows on the Llama-2-7B head: bound by reading the weights
+    (224, 4096, 32000),        # c3's target rows: 256 vocabulary entries per workgroup
 ])
 def test_lm_head_full_size_whole_matrix(rt, rows, d_model, V):
     """Benchmark shapes of the 32000-entry heads, in the launch configuration bench.py times: every
@@ -265,7 +265,7 @@ def test_lm_head_full_size_whole_matrix(rt, rows, d_model, V):
 
 
 @pytest.mark.parametrize("rows,d_model,V", [
-    (1040, 4096, 128256),      # c2's target rows on the Llama-3-8B head: packed hidden states, 512-row blocks
+    (1040, 4096, 128256),      # c2's target rows on the Llama-3-8B head: five row blocks
     (429, 8192, 128256),       # c4's target rows on the Llama-70B head (d_model 8192)
 ])
 def test_lm_head_full_size_rows_and_columns(rt, rows, d_model, V):

@@ -32,7 +32,7 @@ ATTN_CASES = {
                                draft=("tree", (3, 2, 2), 17)),
     "ragged_gqa8": W.scaled(C["c4_llama70b_serving"], batch=7, n_q_heads=16, n_kv_heads=2,
                             ctx=("lognormal", 300, 0.8, 17, 1500)),
-    # ragged lengths with 16 to 128 query rows per KV head: the work list mixes both attention bodies, and the
+    # ragged lengths with 16 to 128 query rows per KV head: one launch mixes both attention bodies, and the
     # long requests of either kind are cut into several chunks
     "ragged_rows_mixed": W.scaled(C["c4_llama70b_serving"], batch=6, n_q_heads=16, n_kv_heads=2,
                                   ctx=("lognormal", 2500, 0.9, 30, 9000), draft=("linear_uniform", 2, 16)),
@@ -75,9 +75,9 @@ def test_attention_matches_oracle(rt, name):
                                   "chain128_multi_chunk", "tree116_gqa4"])
 @pytest.mark.parametrize("hint", ["none", "exact", "small"])
 def test_attention_launch_modes(rt, name, hint):
-    """The total-token hint only steers how the work is cut (grid-mapped chunks when it is absent or
-    says the lengths are uniform, a sorted work list when it says they are ragged): results must
-    meet the same bar whatever it says, including a hint far below the truth."""
+    """The total-token hint only steers how the work is cut (the chunk length, whether ragged batches are cut
+    by tokens or run from a sorted work list): results must meet the same bar whatever it says,
+    including a hint far below the truth."""
     cfg = ATTN_CASES[name]
     a = W.make_attn_inputs(cfg, seed=12)
     ref, ref_lse = oracle_attn(a)

@@ -81,7 +81,7 @@ def test_two_streams_do_not_interfere(rt):
         assert not bad
 
 
-@pytest.mark.parametrize("rows_extra", [0, 150])       # the weight-read-bound kernel; the packed-hidden kernel
+@pytest.mark.parametrize("rows_extra", [0, 150])       # up to and above 128 rows
 def test_graph_replay_lm_head_then_accept(rt, rows_extra):
     """spec_lm_head + spec_accept_prestats captured into one HIP graph: every replay reproduces the eager
     logits, statistics and acceptance results, with stale bytes in all scratch memory in between."""
