@@ -348,8 +348,7 @@ def measure(name, args, cpu_seconds):
         bound = "hbm" if hbm_time >= mfma_time else "mfma"
         ach = lm_bytes / lm_s / 1e9 if bound == "hbm" else lm_flops / lm_s / 1e12
         peak = HBM_PEAK_GBS if bound == "hbm" else MFMA_BF16_PEAK_TFLOPS
-        lm_kernel = ("lm_head_tile_kernel (128 vocabulary entries per workgroup)" if rows <= 128 else
-                     "lm_head_tile_kernel (256 vocabulary entries x up to 256 rows per workgroup)")
+        lm_kernel = sv.spec_describe_lm_head_plan(rows, cfg.d_model, cfg.vocab)
         lm_obj = {"kernel": f"spec_lm_head: {lm_kernel} + lm_stats_merge_kernel; duration is the whole call",
                   "rows": rows, "d_model": cfg.d_model, "vocab": cfg.vocab, "launch_us_mean": lm_s * 1e6,
                   "roofline": {"bound": bound, "achieved": ach, "peak": peak,

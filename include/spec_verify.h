@@ -363,11 +363,13 @@ int32_t spec_compact_kv(
  * target_stats receives spec_row_stats_size(rows, V) bytes in the library's internal
  * layout: pass the START of the workspace later given to spec_accept_prestats (with
  * the same temperature), or any device buffer of that size.  Any number of rows up to
- * 65535; up to 128 rows the weight matrix is read once.
+ * 65535.  The weight matrix is read from memory once; its row blocks, if there are several
+(spec_describe_lm_head_plan), run next to each other and share it in the caches.
  * All pointers are device memory owned by the caller; the call only enqueues kernels on
  * `stream` and allocates nothing.  workspace: spec_lm_head_workspace_size(rows,
- * d_model, V) bytes (per-block statistics and, above 128 rows, the hidden states
- * re-laid out in matrix-operand order); its contents need not survive the call.
+ * d_model, V) bytes (per-block statistics; above 128 rows the size also covers a copy of
+ * the hidden states, which the present kernels do not make); its contents need not survive
+ * the call.
  * Errors: SPEC_ERR_SHAPE (negative or zero sizes, temperature <= 0, misaligned
  * pointers), SPEC_ERR_UNSUPPORTED (d_model not a multiple of 128 or above 65536, V above
  * 2097152, more than 65535 rows), SPEC_ERR_NULL, SPEC_ERR_WORKSPACE, SPEC_ERR_LAUNCH;
@@ -384,6 +386,10 @@ int32_t spec_lm_head(
     void* logits,                /* [rows, V] bf16                                     */
     void* target_stats,          /* spec_row_stats_size(rows, V) bytes                 */
     void* workspace, size_t workspace_bytes, void* stream);
+
+/* One-line description of the workgroup tile spec_lm_head takes for this product on the
+ * current device (host; for logs, benchmark reports and tests). */
+int32_t spec_describe_lm_head_plan(int32_t rows, int32_t d_model, int32_t V, char* buf, size_t buf_bytes);
 
 /* ------------------------------------------------------------------------------
  * spec_accept_prestats

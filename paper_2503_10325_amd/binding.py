@@ -27,6 +27,7 @@ EXPORTS = [
     "spec_accept_greedy_workspace_size", "spec_accept_greedy",
     "spec_routing_scores", "spec_adaptive_speculation", "spec_compact_kv",
     "spec_row_stats_size", "spec_lm_head_workspace_size", "spec_lm_head", "spec_accept_prestats",
+    "spec_describe_lm_head_plan",
     "spec_strerror", "spec_abi_version",
 ]
 
@@ -108,6 +109,8 @@ def lib() -> ctypes.CDLL:
         L.spec_row_stats_size.argtypes = [i32, i32]
         L.spec_lm_head_workspace_size.restype = sz
         L.spec_lm_head_workspace_size.argtypes = [i32, i32, i32]
+        L.spec_describe_lm_head_plan.restype = i32
+        L.spec_describe_lm_head_plan.argtypes = [i32] * 3 + [ctypes.c_char_p, sz]
         L.spec_lm_head.restype = i32
         L.spec_lm_head.argtypes = [i32, i32, i32, vp, vp, f32, vp, vp, vp, sz, vp]
         _lib = L
@@ -256,6 +259,14 @@ def spec_describe_accept_plan(B, V, total_nodes, max_nodes_per_req, is_tree, tar
                                          max_nodes_per_req, int(bool(is_tree)), target_dtype, q_dtype, q_kind, buf, 512)
     if rc != SPEC_OK:
         raise SpecError("spec_describe_accept_plan", rc)
+    return buf.value.decode()
+
+
+def spec_describe_lm_head_plan(rows, d_model, V) -> str:
+    buf = ctypes.create_string_buffer(256)
+    rc = lib().spec_describe_lm_head_plan(rows, d_model, V, buf, 256)
+    if rc != SPEC_OK:
+        raise SpecError("spec_describe_lm_head_plan", rc)
     return buf.value.decode()
 
 

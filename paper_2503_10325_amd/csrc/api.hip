@@ -296,6 +296,16 @@ int32_t spec_lm_head(int32_t rows, int32_t d_model, int32_t V, const void* hidde
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_ERR_LAUNCH;
 }
 
+int32_t spec_describe_lm_head_plan(int32_t rows, int32_t d_model, int32_t V, char* buf, size_t buf_bytes) {
+  if (rows < 0 || d_model <= 0 || V <= 0) return SPEC_ERR_SHAPE;
+  if (!buf || buf_bytes == 0) return SPEC_ERR_NULL;
+  const LmHeadPlan p = make_lm_head_plan(rows, V);
+  const int tile = 16 * p.row_tiles;
+  snprintf(buf, buf_bytes, "lm_head_tile_kernel<%d, %d>: %d vocabulary entries x %d rows per workgroup, %d row block(s)",
+           p.vocab_block / 64, p.row_tiles, p.vocab_block, tile, (rows + tile - 1) / tile);
+  return SPEC_OK;
+}
+
 size_t spec_accept_greedy_workspace_size(int32_t B, int32_t total_nodes, int32_t V) {
   if (B < 0 || total_nodes < 0 || V <= 0) return 0;
   return greedy_workspace_bytes(B, total_nodes, V);

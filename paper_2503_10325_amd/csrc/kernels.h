@@ -69,6 +69,9 @@ struct LmHeadArgs {
 };
 size_t lm_head_workspace_bytes(int rows, int d_model, int V);
 size_t row_stats_bytes(int rows, int V);
+// Workgroup tile of the projection: vocabulary entries (128 or 256) and row tiles of 16.
+struct LmHeadPlan { int vocab_block, row_tiles; };
+LmHeadPlan make_lm_head_plan(int rows, int V);
 int launch_lm_head(const LmHeadArgs& a, hipStream_t stream);
 
 // ---- greedy.hip -------------------------------------------------------------------

@@ -355,6 +355,19 @@ size_t lm_head_workspace_bytes(int rows, int d_model, int V) {
 
 size_t row_stats_bytes(int rows, int V) { return static_cast<size_t>(rows) * stats_segments(V) * sizeof(SegStat); }
 
+LmHeadPlan make_lm_head_plan(int rows, int V) {
+  static constexpr int kFew[] = {8, 6, 5, 4, 3, 2}, kMany[] = {16, 15, 14, 13, 12, 11, 10, 8, 6, 4};
+  const int n_cu = current_device_cus();
+  // 128 vocabulary entries per workgroup, more slices ahead: few rows (bound by the weights: twice the workgroups fetch
+  // them), and products too small to give every compute unit a workgroup of 256 entries and two row tiles (300 x 16384 x
+  // 4096 154 -> 96 us, 600 x 4096 x 3000 33 -> 23, 150 x 2048 x 8000 19 -> 14).
+  const bool few = rows <= 128 || static_cast<int64_t>((V + 255) / 256) * ((rows + 31) / 32) <= n_cu;
+  LmHeadPlan p;
+  p.vocab_block = few ? 128 : 256;
+  p.row_tiles = few ? lm_tile_rows(kFew, p.vocab_block, rows, V, n_cu) : lm_tile_rows(kMany, p.vocab_block, rows, V, n_cu);
+  return p;
+}
+
 int launch_lm_head(const LmHeadArgs& a, hipStream_t stream) {
   if (a.rows <= 0) return 0;
   LmParams P;
@@ -364,21 +377,15 @@ int launch_lm_head(const LmHeadArgs& a, hipStream_t stream) {
   P.weight = static_cast<const uint16_t*>(a.weight);
   P.logits = static_cast<uint16_t*>(a.logits);
   P.bstats = static_cast<float2*>(a.workspace);
-  static constexpr int kFew[] = {8, 6, 5, 4, 3, 2}, kMany[] = {16, 15, 14, 13, 12, 11, 10, 8, 6, 4};
-  const int n_cu = current_device_cus();
-  // 128 vocabulary entries per workgroup, more slices ahead: few rows (bound by the weights: twice the workgroups fetch
-  // them), and products too small to give every compute unit a workgroup of 256 entries and two row tiles (300 x 16384 x
-  // 4096 154 -> 96 us, 600 x 4096 x 3000 33 -> 23, 150 x 2048 x 8000 19 -> 14).
-  const bool few = a.rows <= 128 || static_cast<int64_t>((a.V + 255) / 256) * ((a.rows + 31) / 32) <= n_cu;
-  const int vb = few ? 128 : 256;
-  const int nt2 = few ? lm_tile_rows(kFew, vb, a.rows, a.V, n_cu) : lm_tile_rows(kMany, vb, a.rows, a.V, n_cu);
+  const LmHeadPlan plan = make_lm_head_plan(a.rows, a.V);
+  const int vb = plan.vocab_block, nt2 = plan.row_tiles;
   const int rb = 16 * nt2;
   P.nvb = (a.V + vb - 1) / vb;
   P.nrb = (a.rows + rb - 1) / rb;
   P.total = P.nvb * P.nrb;
   P.per_xcd = (P.total + 7) / 8;
   int rc = -1;
-  switch (nt2 + (few ? 100 : 0)) {
+  switch (nt2 + (vb == 128 ? 100 : 0)) {
     case 102: rc = launch_lm_tile<2, 2>(P, stream); break;
     case 103: rc = launch_lm_tile<2, 3>(P, stream); break;
     case 104: rc = launch_lm_tile<2, 4>(P, stream); break;
