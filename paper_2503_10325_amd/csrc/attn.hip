@@ -5,16 +5,18 @@
 // Work decomposition.  All n*G query rows that share a KV head are processed together so every
 // K/V byte is fetched once per KV head; long requests are cut into context chunks whose
 // unnormalised partial results attn_combine_kernel merges (split-KV).  Two bodies:
-//   token-split (stream_item, up to 64 rows per KV head, up to 128 in ragged batches): a 4-wave
-//     workgroup per (request, KV head, chunk); every wave streams its own 32-token tiles (2 cache
-//     pages): coalesced 16-byte global loads -> registers -> the wave's private LDS tile -> MFMA
-//     operands; waves that share a 32-row query block merge through LDS.  Launched grid-mapped
-//     (attn_stream_kernel) or, for small ragged batches, from a work list built on the device and
-//     sorted by length (attn_stream_list_kernel).
-//   row-split (rows_item; attn_rows_kernel, more rows, and inside the work list): the 4 or 8 waves of a
-//     workgroup stage 64-token tiles together (double-buffered LDS; with 8 waves two tiles of global
-//     loads in flight) and each owns one block of 32 query rows.  Instantiated a second time for
-//     requests of 65 to 128 draft nodes (two ancestor-mask words per node).
+//   token-split (stream_item, up to 64 query rows per KV head): a workgroup of 4 waves, or 8 where a
+//     compute unit gets only one, per (request, KV head, chunk); every wave streams its own 32-token
+//     tiles (2 cache pages): coalesced 16-byte global loads -> registers -> the wave's private LDS
+//     tile -> MFMA operands; waves that share a 32-row query block merge through LDS.
+//   row-split (rows_item, more rows): the 4 or 8 waves of a workgroup stage 64-token tiles together
+//     (double-buffered LDS; with 8 waves two tiles of global loads in flight) and each owns one block of
+//     32 query rows.  Instantiated a second time for requests of 65 to 128 draft nodes (two ancestor-mask
+//     words per node).
+// Launches: attn_stream_kernel and attn_rows_kernel, grid-mapped, one body for the whole batch;
+// attn_stream_list_kernel, ragged batches of up to 128 rows from a work list built on the device and
+// sorted by length, and attn_mixed_kernel, such batches with little work: each request takes the body of
+// its own row count.
 // In both, S^T = K Q^T runs on v_mfma_f32_32x32x16_bf16 with the tokens as the M dimension, so
 // each lane owns one query column and the online-softmax statistics need a single exchange
 // between the half-waves.  V is transposed on its way into LDS (token pairs packed with v_perm).
@@ -181,8 +183,9 @@ __device__ __forceinline__ int request_chunks(const AttnParams& P, int L, int n)
   return min(max(1, (L + P.chunk_tokens - 1) / P.chunk_tokens), P.max_chunks);   // (the bound lengthens the chunks)
 }
 
-// Token-split kernel (up to 128 query rows per KV head and workgroup).  The 4 waves of a
-// workgroup take roles from the number of 32-row query blocks nqb of the request:
+// Token-split kernel (up to 128 query rows per KV head and workgroup).  The NW waves of a
+// workgroup take roles from the number of 32-row query blocks nqb of the request (NW = 4; with 8
+// twice as many waves share a block):
 //   nqb = 1: the four waves stream every 4th tile for the same query block;
 //   nqb = 2: two waves per query block, each streaming every 2nd tile;
 //   nqb = 3, 4: one wave per query block, streaming every tile.
@@ -1146,7 +1149,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_mixed_kernel(AttnParams 
 // Merge the per-chunk partials of every (query row, head) that spans several chunks.  A group of D/4 lanes reads
 // whole partial rows (16 bytes per lane) and S groups share one (node, head) row, group s taking chunks s, s + S, ...
 // four at a time with their loads in flight together; the groups meet in LDS.  The kernel is bound by the latency of
-// those loads, so S grows with the number of chunks (combine_groups): one request with 448 rows in 32 chunks took
+// those loads, so S grows with the number of chunks (launch_combine): one request with 448 rows in 32 chunks took
 // 20.7 us with one group per row walking the chunks one by one and takes 4.0 us with eight groups.
 template <int D, int S>
 __global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams P) {

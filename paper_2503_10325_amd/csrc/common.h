@@ -191,7 +191,8 @@ struct __align__(16) SegStat {
 // Merged (max, sum) of one logit row from its per-segment records, by a group of 16 lanes (lane sl of the
 // group takes segments sl, sl + 16, ...); the result is in every lane of the group.  DEV: read the records
 // with device-scope loads (they were written by other workgroups of the same kernel).  The arithmetic and
-// its order are the same for every caller, so every caller gets the same bits.  All lanes of the wave take part
+// its order are the same for every caller, so every caller gets the same bits (accept_walk_kernel merges by itself, in the
+// order of its shuffles: equal up to the last bits).  All lanes of the wave take part
 // (a group without a row passes nseg = 0).
 template <bool DEV>
 __device__ __forceinline__ void merged_row_stats(const SegStat* __restrict__ rec, int nseg, float c, int sl,

@@ -82,13 +82,13 @@ __device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned 
 // What bounds it: with many rows the matrix cores under the chip's power limit (1024 x 4096 x 128256: busy 70 % of the
 // cycles at 1.67 GHz).  A [64 vocab x 128 rows] tile per wave reads 12 KB of LDS per 32 matrix instructions (a third of the
 // LDS rate) and a workgroup fetches 64 KB per 2048 matrix cycles; 16-row granularity keeps padded rows out of the products
-// (1040 rows: 5 x 208).  Measured against the kernel this replaces (hidden operands packed by a kernel of their own and
-// read from L2 by every wave, weights through registers): 1040 x 4096 x 128256 1095 -> 856 us (1.28 PFLOP/s), 429 x
-// 8192 x 128256 909 -> 734 us, 512 x 4096 x 128256 506 -> 439 us, 224 x 4096 x 32000 89 -> 76 us, 200 x 8192 x 128256
-// 563 -> 430 us (5.0 TB/s).
+// (1040 rows: 5 x 208).  Measured in loops, against the kernel this replaces (hidden operands packed by a kernel of their
+// own and read from L2 by every wave, weights through registers): 1040 x 4096 x 128256 1091 -> 870 us (1.26 PFLOP/s),
+// 429 x 8192 x 128256 908 -> 758 us, 512 x 4096 x 128256 507 -> 437 us, 224 x 4096 x 32000 85 -> 75 us, 200 x 8192 x
+// 128256 581 -> 458 us (4.7 TB/s).
 // With up to 128 rows the weights' way from HBM, with 128 vocabulary entries per workgroup and up to five slices ahead
-// (a kernel that staged them through registers, three slices ahead, in brackets): 72 x 4096 x 32000 57 us (65), 128 x
-// 8192 x 128256 401 (450), 8 x 4096 x 128256 174 = 6.1 TB/s (204), 30 x 8192 x 2000 31 (71), 100 x 4096 x 8000 28 (48).
+// (a kernel that staged them through registers, three slices ahead, in brackets): 72 x 4096 x 32000 61 us (68), 128 x
+// 8192 x 128256 402 (449), 8 x 4096 x 128256 178 = 5.9 TB/s (202), 30 x 8192 x 2000 30 (71), 100 x 4096 x 8000 28 (48).
 template <int MI, int NT2, int NT>
 __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* lm_lds, int wave, int v0, int r0) {
   using C = TlCfg<MI, NT2>;
@@ -301,8 +301,9 @@ static int launch_lm_tile(const LmParams& P, hipStream_t stream) {
 
 // Row tiles per workgroup: the split of the rows whose rounds over the chip cost least.  A slice costs its matrix work,
 // proportional to the row tiles, plus a part that does not depend on them (weight traffic, barrier), about three tiles'
-// worth.  Measured over all choices (us): 1040 x 4096 x 128256 13 tiles 856, 14 896, 12 943, 16 988, 10 972; 429 x 8192 x
-// 128256 14 tiles 736, 15 771, 16 810, 10 831, 13 984; 224 x 4096 x 32000 8 tiles 81, 10 89, 14 92: the rule takes the fastest each time.
+// worth.  Measured over all choices, times as multiples of the fastest: 1040 x 4096 x 128256 13 tiles 1, 14 1.05, 12 1.10,
+// 10 1.14, 16 1.15; 429 x 8192 x 128256 14 tiles 1, 15 1.05, 16 1.10, 10 1.13, 13 1.34; 224 x 4096 x 32000 8 tiles 1, 10
+// 1.10, 14 1.14: the rule takes the fastest each time.
 constexpr int kTlFixed = 3;
 template <int N>
 static int lm_tile_rows(const int (&choices)[N], int vb, int rows, int V, int n_cu) {
