@@ -531,7 +531,8 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
 // workgroup takes its share of a compute unit's LDS whether it has work or not, so the many without then go last: 5
 // requests x 4 KV heads with at most 6 chunks of the 16 launched 16.7 -> 12.1 us with the merge (11.8 with a table as wide
 // as the longest request), 8 x 8 with 4 of 16 49.9 -> 29.4 (28.3).  Not always: the order puts the chunks of one request
-// on few compute units (4 requests x 8 KV heads, mixed kernel: 24.7 -> 31.4 us).
+// on few compute units (tight tables: 4 requests x 8 KV heads, mixed kernel, 24.7 -> 31.4 us; 64 x 8, six of 2500 tokens
+// among short ones, 40.9 -> 51.2).
 // NW = 8 (one workgroup per compute unit instead of two): for launches that have no second workgroup for a compute unit;
 // twice the waves share a chunk's tiles, with no more chunks to merge.  1 request x 8 KV heads x 16000 tokens
 // (56 rows, 512-token chunks) 25.6 -> 24.6 us with the merge, 8 x 32 x 2048 46.0 -> 45.3.
@@ -1260,11 +1261,8 @@ static int list_max_chunks(int64_t max_tok, int max_rows, int tau) {
 }
 constexpr int kListTau = 44;         // with the alternating hand-out of the list: 40-48 measured best
 // The launch for little work has a workgroup for every chunk a request could have.  Most chunks per request such that
-// those are at most four workgroups per compute unit, or two per (request, KV head) pair.
-static int little_room(int B, int Hkv) {
-  const int64_t room = 1024 / (static_cast<int64_t>(B > 0 ? B : 1) * Hkv);
-  return room < 2 ? 2 : static_cast<int>(room);
-}
+// those are at most sixteen workgroups per compute unit, or two per (request, KV head) pair.
+static int little_room(int64_t pairs) { return std::max<int>(2, static_cast<int>(4096 / std::max<int64_t>(pairs, 1))); }
 
 AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   AttnPlan p;
@@ -1284,7 +1282,8 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   // a wide block table (allocated for the longest context a model allows) would ask for more chunks than there is room
   // for, and where the caller's workspace holds the list's partial results but not these (little_ok).
   const int list_chunks = list_max_chunks(max_tok, max_rows, kListTau);
-  const int room = little_room(a.B, a.Hkv);
+  const int64_t pairs = static_cast<int64_t>(a.B) * a.Hkv;
+  const int room = little_room(pairs);
   const bool little = little_ok && a.kv_hint > 0 && a.kv_hint * a.Hkv < static_cast<int64_t>(256) * 1024 && list_chunks <= room;
   // Up to 64 query rows per KV head the token-split body streams as fast as memory delivers; beyond, its
   // waves (one per 32-row block, each staging every tile for itself) are bound by their own staging and the
@@ -1335,6 +1334,15 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   // one saves a wave one tile and costs every request a merge (1 request of 260 tokens: one launch instead of two)
   const int64_t shortest = token_split ? 512 : 256;
   if (chunk < shortest) chunk = shortest;
+  // Ragged batches with little work, but with a workgroup for half of the compute units before any cut, stay whole where
+  // the longest request is at most 12 units of the work list (about 30 us): a cut saves the longest workgroups less time
+  // than the partial results and a merge launch over all query rows take.  Whole against cut: 100
+  // requests x 8 KV heads of 20 to 500 tokens (up to 120 rows) 36.9 and 57.6 us (list 39.2), 20 x 32 of 20 to 500 28.8 and
+  // 49.0 (30.6), 40 x 8 of 20 to 700 (up to 32 rows) 20.8 and 28.5 (23.2), 25 x 8 of 20 to 500 18.8 and 20.5 (22.6); with 25 x
+  // 8 of 100 to 500 and three of 4000 tokens cutting stays ahead, 24.7 against 33.2.
+  if (little && ragged && p.kind == 0 && pairs >= 128 &&
+      max_tok <= 12 * kTile * (max_rows <= 32 ? 32 : (max_rows <= 64 ? 16 : 21)) / 8)
+    chunk = std::max(chunk, max_tok);
   chunk = (chunk + gran - 1) / gran * gran;
   if (chunk > max_tok) chunk = (max_tok + gran - 1) / gran * gran;
   // the row-split kernel keeps a chunk's page ids in LDS
@@ -1356,15 +1364,19 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   if (tau > 0) {
     p.tau = tau;
     p.max_chunks = list_max_chunks(max_tok, max_rows, tau);
-  } else if (listable && ragged && (p.max_chunks > room || p.max_chunks > tok / p.chunk_tokens + 2)) {
-    // A table wider than there is room for, or than all tokens together are long: no more chunks than the list would make,
-    // eight, or twice those of an average request (one request: its own), and a request that is longer than so many is
-    // cut into longer ones.  Launch, partial results and the groups that merge them follow the tokens, not the table.
-    const int64_t all = (tok + p.chunk_tokens - 1) / p.chunk_tokens;
-    int64_t bound = a.B > 1 ? 2 * all / a.B : all;
-    bound = std::max<int64_t>(bound, std::max(list_chunks, 8));
-    bound = std::min<int64_t>(bound, room);
-    if (bound < p.max_chunks) { p.max_chunks = static_cast<int>(bound); p.wide_table = 1; }
+  } else if (listable && ragged) {
+    // A table much wider than the requests - it would launch four times the workgroups that the hint's tokens and one
+    // partial chunk per request make, or it is wider than all tokens together are long: the workgroups without a chunk go
+    // last (chunks_last), and there are no more chunks than the list would make, eight, or twice those of an average
+    // request (one request: its own); a request that is longer than so many is cut into longer ones.  Launch, partial
+    // results and the groups that merge them follow the tokens, not the table.
+    const int64_t all = (tok + p.chunk_tokens - 1) / p.chunk_tokens, launched = p.max_chunks * pairs;
+    if ((launched > 1024 && launched > 4 * (all * a.Hkv + pairs)) || p.max_chunks > all + 1) {
+      int64_t bound = a.B > 1 ? 2 * all / a.B : all;
+      bound = std::min<int64_t>(std::max<int64_t>(bound, std::max(list_chunks, 8)), room);
+      p.max_chunks = static_cast<int>(std::min<int64_t>(bound, p.max_chunks));
+      p.wide_table = 1;
+    }
   }
   if (token_split && p.tau == 0) {
     // one workgroup of eight waves per compute unit where there are not two of four for it; workgroups that have work:

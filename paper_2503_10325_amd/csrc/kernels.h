@@ -167,7 +167,7 @@ struct AttnPlan {
   int tau;            // > 0: sorted-work-list launch of the token-split kernel, at most tau tiles per wave and item
   int waves8;         // grid-mapped token-split kernel: workgroups of eight waves
   int mixed;          // kind 0, grid-mapped: requests with more than 64 query rows per KV head run the row-split body
-  int wide_table;     // kind 0, grid-mapped: fewer chunks than the block table could hold, most of them without work
+  int wide_table;     // kind 0, grid-mapped: the block table holds many more chunks than there are tokens for
   int wide;           // more than 64 query nodes per request: kernels with two ancestor-mask words per node
 };
 // little_ok false: not the launch for little work, whose partial results can need more workspace than the work list's.

@@ -70,6 +70,17 @@ def test_little_mixed_batch_keeps_each_request_s_body(head_dim, tree):
     check(a, got, lse)
 
 
+@pytest.mark.parametrize("nodes,kernel", [([2, 11, 16] * 22, "attn_mixed_kernel"), ([2, 8, 5] * 22, "attn_stream_kernel")])
+def test_little_batch_with_many_requests_stays_whole(nodes, kernel):
+    """132 (request, KV head) pairs of up to 500 tokens: no request is cut, nothing is merged."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    a = attention(nodes, [(77 * k) % 500 for k in range(66)], 128, False)
+    plan, got, lse = run_fp32(a)
+    assert kernel in plan and "at most 1 per request" in plan, plan
+    check(a, got, lse)
+
+
 def test_loose_bound_changes_no_body():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
