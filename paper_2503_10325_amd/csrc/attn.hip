@@ -1163,8 +1163,10 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams P) {
   const int q0 = P.q_offsets[b];
   int n = P.q_offsets[b + 1] - q0;
   n = n > P.n_cap ? P.n_cap : n;
+  // both uniform over the workgroup; in large batches most workgroups leave here
+  if (static_cast<int>(blockIdx.x) * kRows >= n * P.Hq) return;
   const int nchunks = request_chunks(P, P.ctx_len[b] + n, n);
-  if (nchunks == 1) return;                     // (uniform over the workgroup)
+  if (nchunks == 1) return;
   const int grp = threadIdx.x / kLanes, gl = threadIdx.x % kLanes;
   const int s = grp % S, local = blockIdx.x * kRows + grp / S;
   const bool ok = local < n * P.Hq;
