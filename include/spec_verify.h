@@ -82,7 +82,9 @@ typedef struct {
   int32_t out_dtype;         /* spec_dtype of `out`: SPEC_BF16 or SPEC_F32          */
 } spec_attn_desc;
 
-/* Bytes of workspace spec_verify_attn needs for this descriptor (host call). */
+/* Bytes of workspace spec_verify_attn uses for this descriptor (host call).  The size depends on the
+ * hint; a call whose workspace was sized under another hint of the same batch is served where some
+ * launch fits it (ragged batches: the sorted work list), and refused with SPEC_ERR_WORKSPACE else. */
 size_t spec_verify_attn_workspace_size(const spec_attn_desc* desc);
 
 int32_t spec_verify_attn(
