@@ -7,8 +7,9 @@
 // unnormalised partial results attn_combine_kernel merges (split-KV).  Two bodies:
 //   token-split (stream_item, up to 64 query rows per KV head): a workgroup of 4 waves, or 8 where a
 //     compute unit gets only one, per (request, KV head, chunk); every wave streams its own 32-token
-//     tiles (2 cache pages): coalesced 16-byte global loads -> registers -> the wave's private LDS
-//     tile -> MFMA operands; waves that share a 32-row query block merge through LDS.
+//     tiles (2 cache pages) from memory straight to its private LDS tile, reads them as matrix operands
+//     (V through transposing reads) and multiplies each with one or two 32-row query blocks; the waves
+//     merge through LDS.
 //   row-split (rows_item, more rows): the 4 or 8 waves of a workgroup stage 64-token tiles together
 //     (double-buffered LDS; with 8 waves two tiles of global loads in flight) and each owns one block of
 //     32 query rows.  Instantiated a second time for requests of 65 to 128 draft nodes (two ancestor-mask
@@ -19,7 +20,7 @@
 // its own row count.
 // In both, S^T = K Q^T runs on v_mfma_f32_32x32x16_bf16 with the tokens as the M dimension, so
 // each lane owns one query column and the online-softmax statistics need a single exchange
-// between the half-waves.  V is transposed on its way into LDS (token pairs packed with v_perm).
+// between the half-waves.  The row-split body transposes V on its way into LDS (token pairs packed with v_perm).
 // O^T = V^T P^T: the token-split body keeps bf16 operands (weights as a high and a low bf16 term);
 // the row-split body converts V to fp16 while staging it and uses fp16 weights in one
 // v_mfma_f32_32x32x16_f16 term.
@@ -51,20 +52,18 @@ template <int D>
 struct AttnCfg {
   static constexpr int kCh = D / 8;                       // 16-byte chunks per token row
   static constexpr int kTokPerLoad = 64 / kCh;            // token rows one wave-wide load covers
-  static constexpr int kLoads = kTile / kTokPerLoad;      // loads per tile per tensor (8 / 4)
-  static constexpr int kKStride = D * 2 + 16;             // bytes; padded K row in LDS
-  static constexpr int kKBytes = kTile * kKStride;
-  static constexpr int kVStride = 80;                     // bytes; one V^T row = 32 tokens + pad
-  // V^T row of head dimension d: sigma(d) = (d%8)*(D/8) + d/8.  Lane ln of the output product's block db reads
-  // row 32*db + ln - consecutive rows, free of LDS bank conflicts at this stride (an odd multiple of 16 bytes) -
-  // so accumulator row m of block db belongs to head dimension acc_dim<D>(db, m): see there.
-  static constexpr int kVRows = D;
-  static constexpr int kVBytes = kVRows * kVStride;
-  static constexpr int kWaveLds = kKBytes + kVBytes;
   static constexpr int kQKSteps = D / 16;
   static constexpr int kDBlocks = D / 32;
-  static constexpr int kPagesPerLoad = 16 / kCh;          // pages one round of V loads covers: 1 (D=128) / 2 (D=64)
-  static constexpr int kVPageIters = 2 / kPagesPerLoad;
+  // token-split body: a wave's tile of K or V in LDS, natural token rows of kRowBytes without padding
+  static constexpr int kRowBytes = D * 2;
+  static constexpr int kPageBytes = kPage * kRowBytes;
+  static constexpr int kPageLoads = kPageBytes / 1024;    // loads per page
+  static constexpr int kTileBytes = kTile * kRowBytes;
+  static constexpr int kQLdsFrags = kQKSteps + kQKSteps / 2;    // two query blocks per wave: 1 KB fragments kept in LDS
+  // 16-byte chunk c of row r sits at position c ^ swizzle(r).  K operands: 16 rows at one chunk number in one go.  V: four
+  // rows of 64 contiguous bytes.  Both spread over the 256 bytes that the LDS serves at a time.
+  static __device__ constexpr int k_swizzle(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+  static __device__ constexpr int v_swizzle(int r) { return D == 128 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2); }
   static constexpr int kORedStride = D + 4;               // floats; padded row of the cross-wave reduction
 };
 
@@ -82,8 +81,9 @@ struct AttnParams {
   float2* ws_ml;     // [rows, max_chunks] (max in log2 units, sum)
   int B, Hq, Hkv, G, max_pages, chunk_tokens, max_chunks;
   int tau;           // > 0: a request is cut so that one wave streams at most tau tiles per work item
+  int tau_rows;      // ... of a request that runs the row-split body
   int list_rows_min; // > 0 (kernels with both bodies): requests with this many query rows per KV head use the row-split body
-  int list_rows_units;        // eighths of a work-list unit that 32 tokens of such a request cost
+  int list_rows_units;        // sixteenths of a work-list unit that 32 tokens of such a request cost
   int chunks_last;            // grid-mapped token-split launch: blockIdx = (KV head, request, chunk)
   int xcd_swizzle;            // grid-mapped row-split launch: consecutive workgroups of the logical order share an XCD
   int n_cap;                  // query nodes per request the launched kernels handle (64, or 128 with two mask words)
@@ -153,9 +153,40 @@ __device__ __forceinline__ int opaque_zero() {
   return z;
 }
 
+// 16 bytes per lane from base + off + 1024 j to LDS: lane i's land at byte lds_at + 1024 j + 16 i (the instruction's offset
+// counts on both sides).  Not tracked by the compiler: the loops count these loads themselves (vmcnt).  The LDS address
+// is an operand bound to M0: the compiler writes that register itself and knows when it changes.
+__device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned off, unsigned lds_at, int j) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" :: "{m0}"(lds_at), "v"(off), "s"(base), "n"(1024 * j) : "memory");
+}
+__device__ __forceinline__ unsigned lds_address(unsigned char* p) {
+  return static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)p));
+}
+__device__ __forceinline__ __attribute__((address_space(3))) u32x4* lds_u32x4(unsigned lds_at) {
+  return (__attribute__((address_space(3))) u32x4*)lds_at;
+}
+typedef __attribute__((address_space(4))) int32_t const_i32;       // read through the scalar cache
+// Which of 32 tokens a draft node sees that start at position p: bit i for token p + i, given left = ctx - p.  Context
+// tokens all, drafts by the node's ancestor mask (which has no bit at or beyond the number of nodes).
+__device__ __forceinline__ uint32_t tile_mask(unsigned long long anc, int left) {
+  if (left >= 32) return 0xffffffffu;
+  if (left > 0) return static_cast<uint32_t>(anc << left) | ((1u << left) - 1u);
+  return left > -64 ? static_cast<uint32_t>(anc >> -left) : 0u;
+}
+// Matrix operand of 8 tokens for this lane's head dimension from two transposing LDS reads of 4 tokens each.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ s16x4 tr_read(unsigned lds_at) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)lds_at);
+}
+__device__ __forceinline__ bf16x8 tr_pair(unsigned p0, unsigned p1) {
+  const s16x4 a = tr_read(p0), b = tr_read(p1);
+  const s16x8 v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8, v);
+}
+
 __device__ __forceinline__ int stream_nslice(int R) {
-  const int nqb = min(4, (R + 31) / 32);
-  return nqb <= 1 ? 4 : (nqb <= 2 ? 2 : 1);
+  return R <= 64 ? 4 : 1;
 }
 
 // Number of context chunks of a request with L tokens and n draft nodes.  The token-split,
@@ -168,153 +199,137 @@ __device__ __forceinline__ bool list_uses_rows(const AttnParams& P, int n) {
 }
 
 // Length of a request in the work list's unit, the 32-token tiles one wave of the token-split body streams.
-// For the row-split body 32 tokens count P.list_rows_units eighths of a unit: batches of equal requests
-// measure 5/8 (a 64-token tile takes 1.25 times a 32-token one), ragged batches of both kinds run best
-// with 3/8 (seven seeds of the serving mix: 1 to 8 % ahead of 4/8); the host passes 3.
+// A unit is 128 tokens of a request of up to 64 rows, whose four waves take a tile each.  For the row-split body 32 tokens
+// count P.list_rows_units sixteenths of it (the host passes 5): ragged batches of 64 requests x 8 KV heads, 512 to 12587
+// tokens, with 4/16, 5/16, 6/16 at 36 units per item: 80 rows 181 / 173 / 179 us, 128 rows 192 / 183 / 190.
 __device__ __forceinline__ int request_units(const AttnParams& P, int L, int n) {
   const int tiles = (L + kTile - 1) / kTile;
-  if (list_uses_rows(P, n)) return (tiles * P.list_rows_units + 7) / 8;
+  if (list_uses_rows(P, n)) return (tiles * P.list_rows_units + 15) / 16;
   const int nslice = stream_nslice(min(n * P.G, 128));
   return (tiles + nslice - 1) / nslice;
 }
 
 __device__ __forceinline__ int request_chunks(const AttnParams& P, int L, int n) {
-  if (P.tau > 0) return min(max(1, (request_units(P, L, n) + P.tau - 1) / P.tau), P.max_chunks);
+  const int tau = list_uses_rows(P, n) ? P.tau_rows : P.tau;
+  if (P.tau > 0) return min(max(1, (request_units(P, L, n) + tau - 1) / tau), P.max_chunks);
   return min(max(1, (L + P.chunk_tokens - 1) / P.chunk_tokens), P.max_chunks);   // (the bound lengthens the chunks)
 }
 
-// Token-split kernel (up to 128 query rows per KV head and workgroup).  The NW waves of a
-// workgroup take roles from the number of 32-row query blocks nqb of the request (NW = 4; with 8
-// twice as many waves share a block):
-//   nqb = 1: the four waves stream every 4th tile for the same query block;
-//   nqb = 2: two waves per query block, each streaming every 2nd tile;
-//   nqb = 3, 4: one wave per query block, streaming every tile.
-// Waves that share tokens fetch them separately (the repeats hit in L2: HBM traffic stays 1x).
-// One work item: (request b, KV head kvh, context chunk, row group rg).  Every return below is
-// workgroup-uniform.
-template <int D, int NW>
-__device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* smem, int b, int kvh, int chunk, int rg,
-                                            int q0, int n, int ctx) {
+// Token-split body (up to 128 query rows per KV head and workgroup).  NW waves (4, or 8 in a workgroup that has a compute
+// unit for itself) take 32-token tiles in turn; NQ: 32-row query blocks a wave multiplies every tile it streams with.
+//   up to 32 rows  (NQ = 1): all waves share the one block, each streaming every NW-th tile;
+//   up to 64 rows  (NQ = 2): the same, each wave with both blocks: no tile is fetched twice;
+//   more           (NQ = 1): one wave (NW = 8: two) per block, streaming every tile (repeats hit in L2).
+// One work item: (request b, KV head kvh, context chunk, row group rg).  Every return below is workgroup-uniform.
+//
+// A tile goes from memory to LDS directly (16 bytes per lane and load, no registers, no conversion) and natural token rows
+// serve both products: K as it lies, V through transposing LDS reads.  The 16-byte chunks of a row are placed by XOR so
+// that both reads spread over all banks.  K and V of the wave have one buffer each: the next tile's K goes out as soon as
+// the scores have read this one's and travels under the softmax and the output product, V behind the output product.
+template <int D, int NW, int NQ>
+__device__ __forceinline__ void stream_tiles(const AttnParams& P, unsigned char* smem, int b, int kvh, int chunk, int rg,
+                                             int q0, int n, int ctx, int nchunks, int cb) {
   using C = AttnCfg<D>;
-  const int tid = static_cast<int>(threadIdx.x) + opaque_zero(), lane = tid & 63, wave = tid >> 6;
+  const int tid = static_cast<int>(threadIdx.x) + opaque_zero(), lane = tid & 63;
   __builtin_assume(tid >= 0 && tid < NW * kWave);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, lh = lane >> 5;
-
-  // (q0, n, ctx: first query row, number of query nodes (already capped at kMaxQ) and context length of request b)
-  if (n <= 0) return;
   const int L = ctx + n;
   const int R = n * P.G;
   const int row0 = rg * 128;
-  if (row0 >= R) return;
   const int nqb = min(4, (R - row0 + 31) / 32);             // query blocks of this workgroup
-  const int nqbp = nqb <= 1 ? 1 : (nqb <= 2 ? 2 : 4);       // ... rounded up to a power of two
-  const int nslice = NW / nqbp;                             // waves sharing one query block
-  const int my_qb = wave % nqbp, my_slice = wave / nqbp;
-  const bool wave_active = my_qb < nqb;                     // wave-uniform
-  const int nchunks = request_chunks(P, L, n);
-  if (chunk >= nchunks) return;
-  const int cb = (((L + nchunks - 1) / nchunks) + kTile - 1) & ~(kTile - 1);
+  const int groups = NQ == 2 || nqb == 1 ? 1 : (nqb == 2 ? 2 : 4);   // waves with tiles of their own come in so many kinds
+  const int nslice = NW / groups;                           // waves sharing one query block
+  const int my_g = wave % groups, my_slice = wave / groups;
+  const bool wave_active = NQ * my_g < nqb;
   const int t_begin = chunk * cb;
   const int t_end = min(L, t_begin + cb);
   const int ntiles = (t_end - t_begin + kTile - 1) / kTile;
 
-  unsigned char* tile_lds = smem + wave * C::kWaveLds;
-  unsigned char* k_lds = tile_lds;
-  unsigned char* v_lds = tile_lds + C::kKBytes;
-  // Small arrays alias the tile memory: the ancestor masks are consumed before the first
-  // tile is staged, the merge statistics live behind the cross-wave reduction buffer.
-  unsigned long long* sh_anc = reinterpret_cast<unsigned long long*>(smem);            // [64]
-  int* sh_par = reinterpret_cast<int*>(smem + 512);                                    // [64]
+  unsigned char* k_lds = smem + wave * 2 * C::kTileBytes;
+  unsigned char* v_lds = k_lds + C::kTileBytes;
+  unsigned char* q_lds = smem + NW * 2 * C::kTileBytes;                                // query fragments (NQ = 2)
+  unsigned long long* sh_anc = reinterpret_cast<unsigned long long*>(q_lds + C::kQLdsFrags * 1024);   // [64]
+  int* sh_par = reinterpret_cast<int*>(sh_anc + kMaxQ);                                // [64]
+  // the merge of the waves' results takes the tile memory
   float* sh_m = reinterpret_cast<float*>(smem + NW * 32 * C::kORedStride * sizeof(float));  // [NW][32]
   float* sh_l = sh_m + NW * 32;                                                        // [NW][32]
 
-  // Everything that depends on no other load goes out first - the page ids of the first tile, the parents, the query
-  // row - then the first tile's K and V; the masks are worked out while those are on their way.  (One after another
-  // these trips to memory were a good part of a short item.)
-  const bool touches_drafts = t_end > ctx;
-  // ---- lane roles for the loads ----
-  const int kc = lane % C::kCh;              // 16-byte chunk within the token row
-  const int kt = lane / C::kCh;              // token row within one load instruction
-  // V: each lane loads 4 consecutive tokens (4*va + i) of a page so that the transposed
-  // LDS write packs them into 8 bytes.
-  const int vgrp = lane / C::kCh;
-  const int vg4 = vgrp & 3;
-  const int va = ((vg4 & 1) << 1) | (vg4 >> 1);     // token group within the page
-  const int vs_lane = vgrp >> 2;                     // page within one load (D=64 only)
-  const int vhh = va & 1, vpart = va >> 1;
-
-  const int32_t* bt = P.block_table + static_cast<int64_t>(b) * P.max_pages;
-  const int64_t page_elems = static_cast<int64_t>(P.Hkv) * kPage * D;
-  const int64_t head_off = static_cast<int64_t>(kvh) * kPage * D;
-
-  u32x4 kr[C::kLoads], vr[C::kLoads];
-
-  // Page ids are fetched one tile ahead of the K/V loads that need them, so the tile loads never
-  // wait on a dependent block-table read.  They are wave-uniform: the loads below take the page
-  // base from scalar registers and add a per-lane byte offset that never changes, so a tile costs
-  // no address arithmetic and no branch.  Ids past the request's last page repeat the last page and
-  // negative ids read page 0: the data is in bounds, and tokens at or beyond L are masked (K) or
-  // zeroed before they reach LDS (V).
+  // ---- tile loads: page ids come through scalar loads one tile ahead, a page of 16 token rows is contiguous ----
+  const int64_t page_bytes = static_cast<int64_t>(P.Hkv) * kPage * C::kRowBytes;
+  const unsigned char* k_head = reinterpret_cast<const unsigned char*>(P.k_pool) + static_cast<int64_t>(kvh) * kPage * C::kRowBytes;
+  const unsigned char* v_head = reinterpret_cast<const unsigned char*>(P.v_pool) + static_cast<int64_t>(kvh) * kPage * C::kRowBytes;
+  const const_i32* bt = (const const_i32*)(P.block_table + static_cast<int64_t>(b) * P.max_pages);
   const int last_page = (L - 1) / kPage;
-  int pg[2] = {0, 0};
+  const unsigned lds_k = lds_address(k_lds), lds_v = lds_address(v_lds);
+  // Ids past the request's last page repeat it, negative ids read page 0: the data is in bounds.
+  int pg0 = 0, pg1 = 0;
   auto fetch_pages = [&](int t) {
     if (t < ntiles) {
       const int lp = (t_begin + kTile * t) / kPage;
-      pg[0] = bt[lp];
-      pg[1] = bt[min(lp + 1, last_page)];
+      pg0 = max(bt[lp], 0);
+      pg1 = max(bt[min(lp + 1, last_page)], 0);
     }
   };
-  const unsigned k_lane_off = static_cast<unsigned>(kt * D + kc * 8) * 2u;            // bytes
-  const unsigned v_lane_off = static_cast<unsigned>(4 * va * D + kc * 8) * 2u;
-  const int64_t page_bytes = page_elems * 2, head_bytes = head_off * 2;
-  auto issue_loads = [&](int t) {
-    const int p0 = max(__builtin_amdgcn_readfirstlane(pg[0]), 0);
-    const int p1 = max(__builtin_amdgcn_readfirstlane(pg[1]), 0);
-    const int64_t o0 = p0 * page_bytes + head_bytes, o1 = p1 * page_bytes + head_bytes;
-    const unsigned char* kb[2] = {reinterpret_cast<const unsigned char*>(P.k_pool) + o0,
-                                  reinterpret_cast<const unsigned char*>(P.k_pool) + o1};
-    const unsigned char* vb[2] = {reinterpret_cast<const unsigned char*>(P.v_pool) + o0,
-                                  reinterpret_cast<const unsigned char*>(P.v_pool) + o1};
+  auto issue = [&](bool is_k) __attribute__((always_inline)) {        // of the tile whose page ids were fetched last
+    const unsigned char* head = is_k ? k_head : v_head;
+    int l = lane;
+    asm volatile("" : "+v"(l));              // (worked out anew, as the operand addresses below: registers are what is short)
+    const int row = l / C::kCh, ch = l % C::kCh;          // row and chunk of this lane within one load; load j: chunk ^ 4 j (K)
+    const unsigned off = row * C::kRowBytes + ((ch ^ (is_k ? C::k_swizzle(row) : C::v_swizzle(row))) << 4);
 #pragma unroll
-    for (int j = 0; j < C::kLoads; ++j) {
-      constexpr int kRowBytes = D * 2;
-      const int tk0 = j * C::kTokPerLoad;                 // first token row of this load (compile time)
-      kr[j] = *reinterpret_cast<const u32x4*>(kb[tk0 / kPage] + k_lane_off + (tk0 % kPage) * kRowBytes);
-    }
+    for (int p = 0; p < 2; ++p) {
+      const unsigned char* base = head + (p ? pg1 : pg0) * page_bytes;
 #pragma unroll
-    for (int pi = 0; pi < C::kVPageIters; ++pi) {
-      // D = 128: one page per round (scalar base); D = 64: the two half-waves read the tile's two pages
-      const unsigned char* base = (C::kPagesPerLoad == 2) ? (vs_lane ? vb[1] : vb[0]) : vb[pi];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) vr[pi * 4 + i] = *reinterpret_cast<const u32x4*>(base + v_lane_off + i * D * 2);
+      for (int j = 0; j < C::kPageLoads; ++j)
+        load_to_lds(base, is_k ? off ^ (64u * j) : off, (is_k ? lds_k : lds_v) + p * C::kPageBytes, j);
     }
   };
 
+  // Everything that depends on no other load goes out first - the page ids of the first tile, the query rows, the parents -
+  // then the first tile's K and V; the masks are worked out while those are on their way.
+  const bool touches_drafts = t_end > ctx;
   int t = my_slice;
   const bool any_tile = wave_active && t < ntiles;
-  if (any_tile) fetch_pages(t);
-  // ---- this lane's query column ----
-  const int row = row0 + 32 * my_qb + ln;
-  const bool valid = row < R;
-  const int node = valid ? row / P.G : 0;
-  const int gq = valid ? row % P.G : 0;
+  fetch_pages(t);
+  // ---- this lane's query columns ----
+  int node[NQ];
+  auto q_ptr = [&](int qi, int& nd) {
+    const int row = min(row0 + 32 * (NQ * my_g + qi) + ln, R - 1);     // (columns past the last row repeat it and are not written)
+    nd = row / P.G;
+    return P.q + (static_cast<int64_t>(q0 + nd) * P.Hq + kvh * P.G + row % P.G) * D + 8 * lh;
+  };
+  // NQ = 2: the second block, and the first steps of the first, are read from LDS by all waves (each wave brings its share
+  // of the fragments there): what registers are left would not hold both blocks' accumulators and queries.
+  constexpr int kQReg0 = NQ == 2 ? C::kQKSteps / 2 : 0;                      // first step that stays in registers
+  constexpr int kQFrags = NQ == 2 ? C::kQLdsFrags : 0, kShare = (kQFrags + NW - 1) / NW;
   bf16x8 qf[C::kQKSteps];
+  u32x4 q_share[kShare + 1];
   {
-    const uint16_t* qp = P.q + (static_cast<int64_t>(q0 + node) * P.Hq + kvh * P.G + gq) * D + 8 * lh;
+    const uint16_t* qp = q_ptr(0, node[0]);
 #pragma unroll
-    for (int ks = 0; ks < C::kQKSteps; ++ks) {
-      u32x4 v = zero4();
-      if (valid) v = *reinterpret_cast<const u32x4*>(qp + 16 * ks);
-      qf[ks] = as_bf16x8(v);
+    for (int ks = kQReg0; ks < C::kQKSteps; ++ks) qf[ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(qp + 16 * ks));
+    if constexpr (NQ == 2) {
+      const uint16_t* qp1 = q_ptr(1, node[1]);
+#pragma unroll
+      for (int i = 0; i < kShare; ++i) {
+        const int f = min(wave + NW * i, kQFrags - 1);          // fragment: first block's first steps, then the second block's
+        q_share[i] = *reinterpret_cast<const u32x4*>(f < kQReg0 ? qp + 16 * f : qp1 + 16 * (f - kQReg0));
+      }
     }
   }
   // (here, where the page ids have to be waited for anyway: a value still on its way behind the tile's loads would be
   // waited for with all of them)
   if (touches_drafts && P.parent && tid < kMaxQ) sh_par[tid] = tid < n ? P.parent[q0 + tid] : -1;
   if (any_tile) {
-    issue_loads(t);
+    issue(true);
+    issue(false);
     fetch_pages(t + nslice);
   }
+  // operand reads: K, lane ln's row, 16-byte chunk 2 ks + lh at k_at ^ 32 ks (tiles start at multiples of 256 bytes); query
+  // fragments as the lanes hold them
+  const unsigned k_at = lds_k + ln * C::kRowBytes + ((lh ^ C::k_swizzle(ln)) << 4);
+  const unsigned q_at = lds_address(q_lds) + 16 * lane;
 
   // ---- ancestor-or-self masks of the draft nodes (only chunks that reach the drafts) ----
   if (touches_drafts) {
@@ -335,195 +350,236 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
       }
       sh_anc[tid] = mask;
     }
-    __syncthreads();
   }
-
-  const unsigned long long my_anc = (touches_drafts && valid) ? sh_anc[node] : 0ull;
-  if (touches_drafts) __syncthreads();       // masks are in registers; the memory becomes tile space
-
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x16 oacc[C::kDBlocks];
+  if constexpr (NQ == 2) {
 #pragma unroll
-  for (int db = 0; db < C::kDBlocks; ++db)
+    for (int i = 0; i < kShare; ++i) *lds_u32x4(q_at + 1024 * min(wave + NW * i, kQFrags - 1)) = q_share[i];
+  }
+  if (touches_drafts || NQ == 2) __syncthreads();
+  unsigned long long my_anc[NQ];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
+  for (int qi = 0; qi < NQ; ++qi) my_anc[qi] = touches_drafts ? sh_anc[node[qi]] : 0ull;
+  // the query rows are in registers before the loop: a wait for them inside it would wait for the tiles too
+#pragma unroll
+  for (int ks = kQReg0; ks < C::kQKSteps; ++ks) asm volatile("" :: "v"(qf[ks]));
+
+  float m_run[NQ], l_run[NQ];
+  f32x16 oacc[NQ][C::kDBlocks];
+#pragma unroll
+  for (int qi = 0; qi < NQ; ++qi) {
+    m_run[qi] = -INFINITY;
+    l_run[qi] = 0.f;
+#pragma unroll
+    for (int db = 0; db < C::kDBlocks; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[qi][db][r] = 0.f;
+  }
+  // transposing reads of V: a group of 16 lanes gets a 4-token x 16-dimension piece, lane i of it dimension i.  Lane i
+  // addresses four dimensions (i % 4) of token i / 4; the two halves of the wave take the tokens of the weights they hold.
+  const int tr_tok = 4 * lh + ((lane & 15) >> 2);
+  const unsigned v_at = lds_v + tr_tok * C::kRowBytes + 8 * (lane & 1) +
+                        (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ C::v_swizzle(tr_tok)) << 4);
 
   for (; wave_active && t < ntiles; t += nslice) {
-    // ---- registers -> LDS ----
-#pragma unroll
-    for (int j = 0; j < C::kLoads; ++j) {
-      const int tk = j * C::kTokPerLoad + kt;
-      *reinterpret_cast<u32x4*>(k_lds + tk * C::kKStride + kc * 16) = kr[j];
-    }
     const int tok0 = t_begin + kTile * t;
-    if (tok0 + kTile > L) {                  // last, partial tile: stale cache slots must not reach O
-#pragma unroll
-      for (int pi = 0; pi < C::kVPageIters; ++pi)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int tok = tok0 + kPage * (pi * C::kPagesPerLoad + vs_lane) + 4 * va + i;
-          if (tok >= L) vr[pi * 4 + i] = zero4();
-        }
-    }
-#pragma unroll
-    for (int pi = 0; pi < C::kVPageIters; ++pi) {
-      const int s = pi * C::kPagesPerLoad + vs_lane;
-      const u32x4 w0 = vr[pi * 4 + 0], w1 = vr[pi * 4 + 1], w2 = vr[pi * 4 + 2], w3 = vr[pi * 4 + 3];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const uint32_t sel = half ? 0x07060302u : 0x05040100u;
-          uint2 o;
-          o.x = __builtin_amdgcn_perm(w1[k], w0[k], sel);    // tokens 4va, 4va+1 at dim 8kc+2k+half
-          o.y = __builtin_amdgcn_perm(w3[k], w2[k], sel);    // tokens 4va+2, 4va+3
-          const int vrow = (2 * k + half) * (D / 8) + kc;
-          *reinterpret_cast<uint2*>(v_lds + vrow * C::kVStride + 32 * s + 16 * vhh + 8 * vpart) = o;
-        }
-      }
-    }
-    if (t + nslice < ntiles) {
-      issue_loads(t + nslice);
-      fetch_pages(t + 2 * nslice);
-    }
-    wave_lds_fence();
+    const bool more = t + nslice < ntiles;
 
     // ---- S^T = K Q^T ----
-    f32x16 sacc;
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::kPageLoads) : "memory");          // K is here (V may still be on its way)
+    f32x16 sacc[NQ];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
+    for (int qi = 0; qi < NQ; ++qi)
 #pragma unroll
-    for (int ks = 0; ks < C::kQKSteps; ++ks) {
-      const bf16x8 a = as_bf16x8(*reinterpret_cast<const u32x4*>(k_lds + ln * C::kKStride + 32 * ks + 16 * lh));
-      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], sacc, 0, 0, 0);
+      for (int r = 0; r < 16; ++r) sacc[qi][r] = 0.f;
+    unsigned ka = k_at;
+    asm volatile("" : "+v"(ka));
+    auto k_frag = [&](int ks) __attribute__((always_inline)) { return *lds_u32x4(ka ^ (32 * ks)); };
+    auto q_frag = [&](int f) __attribute__((always_inline)) { return *lds_u32x4(q_at + 1024 * f); };
+    if constexpr (NQ == 1) {
+      u32x4 kf[C::kQKSteps];
+#pragma unroll
+      for (int ks = 0; ks < C::kQKSteps; ++ks) kf[ks] = k_frag(ks);
+#pragma unroll
+      for (int ks = 0; ks < C::kQKSteps; ++ks)
+        sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), qf[ks], sacc[0], 0, 0, 0);
+    } else {
+      // operands ahead of the products: K two steps, the queries one
+      u32x4 kf[3], qa[2], qb[2];
+      kf[0] = k_frag(0); qa[0] = q_frag(0); qb[0] = q_frag(kQReg0); kf[1] = k_frag(1);
+#pragma unroll
+      for (int ks = 0; ks < C::kQKSteps; ++ks) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (ks + 1 < C::kQKSteps) qb[(ks + 1) % 2] = q_frag(kQReg0 + ks + 1);
+        if (ks + 1 < kQReg0) qa[(ks + 1) % 2] = q_frag(ks + 1);
+        if (ks + 2 < C::kQKSteps) kf[(ks + 2) % 3] = k_frag(ks + 2);
+        const bf16x8 q0k = ks < kQReg0 ? as_bf16x8(qa[ks % 2]) : qf[ks];
+        sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks % 3]), q0k, sacc[0], 0, 0, 0);
+        sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks % 3]), as_bf16x8(qb[ks % 2]), sacc[1], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (more) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                               // K has been read
+      issue(true);
     }
 
-    // ---- mask, online softmax ----
+    // ---- mask, online softmax, P^T as two bf16 terms (value + rounding residual) ----
+    // A single bf16 rounding of P (2^-9 relative) would dominate the output error; carrying the rounding residual in a
+    // second bf16 term keeps ~16 bits of every weight.  The running maximum only has to bound the exponents: it follows
+    // the true maximum when that is first finite or has grown by more than 8, and the accumulator is rescaled then alone.
     const bool need_mask = tok0 + kTile > ctx;
-    float tmax = -INFINITY;
+    u32x4 hi[NQ][2], lo[NQ][2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float v = sacc[r];
+    for (int qi = 0; qi < NQ; ++qi) {
+      float tmax = -INFINITY;
       if (need_mask) {
-        const int pos = tok0 + 8 * (r >> 2) + 4 * lh + (r & 3);
-        // branch-free on purpose: bitwise ops, no short-circuit control flow around the accumulator
-          const bool ok = (pos < ctx) | ((pos < L) & (((my_anc >> ((pos - ctx) & 63)) & 1ull) != 0ull));
-        v = ok ? v : -INFINITY;
-        sacc[r] = v;
+        // bit 8 (r / 4) + r % 4 of the lane's word: may the query see token tok0 + 4 lh + that bit
+        uint32_t seen = tile_mask(my_anc[qi], ctx - tok0) >> (4 * lh);
+        asm volatile("" : "+v"(seen));       // (stays behind the branch: worked out ahead of it, it would cost every tile)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sacc[qi][r] = (seen & (1u << (8 * (r >> 2) + (r & 3)))) ? sacc[qi][r] : -INFINITY;
       }
-      tmax = fmaxf(tmax, v);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sacc[qi][r]);
+      tmax *= P.c;                                   // c > 0: the maximum commutes with the scaling
+      tmax = half_max(tmax);
+      float m_new = fmaxf(m_run[qi], tmax);
+      if (m_run[qi] != -INFINITY && tmax <= m_run[qi] + 8.f) m_new = m_run[qi];
+      const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+      const float alpha = fast_exp2(m_run[qi] - m_safe);
+      if (__any(alpha != 1.f)) {
+#pragma unroll
+        for (int db = 0; db < C::kDBlocks; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[qi][db][r] *= alpha;
+      }
+      float psum = 0.f;
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float p0 = fast_exp2(fmaf(sacc[qi][8 * s + 2 * j], P.c, -m_safe));
+          const float p1 = fast_exp2(fmaf(sacc[qi][8 * s + 2 * j + 1], P.c, -m_safe));
+          psum += p0 + p1;
+          const uint32_t h = pack_bf16(p0, p1);
+          hi[qi][s][j] = h;
+          lo[qi][s][j] = pack_bf16(p0 - bf16_lo(h), p1 - bf16_hi(h));
+        }
+      l_run[qi] = l_run[qi] * alpha + psum;
+      m_run[qi] = m_new;
     }
-    tmax *= P.c;                                   // c > 0: the maximum commutes with the scaling
-    tmax = half_max(tmax);
-    const float m_new = fmaxf(m_run, tmax);
-    const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-    const float alpha = fast_exp2(m_run - m_safe);
-    if (__any(alpha != 1.f)) {
+
+    // ---- O^T += V^T P^T, 16 tokens at a time ----
+    if (more) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::kPageLoads) : "memory");  // V is here (the next K may be on its way)
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (tok0 + kTile > L) {
+      // last, partial tile: stale cache slots must not reach O (their weight is zero, zero times what they hold may not be)
+      for (int i = (L - tok0) * C::kCh + lane; i < kTile * C::kCh; i += kWave) *reinterpret_cast<u32x4*>(v_lds + 16 * i) = zero4();
+    }
+    unsigned va = v_at;
+    asm volatile("" : "+v"(va));
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int db = 0; db < C::kDBlocks; ++db) {
+        const unsigned at = (va ^ (64 * db)) + 16 * s * C::kRowBytes;
+        const bf16x8 a = tr_pair(at, at + 8 * C::kRowBytes);
+#pragma unroll
+        for (int qi = 0; qi < NQ; ++qi) {
+          oacc[qi][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(hi[qi][s]), oacc[qi][db], 0, 0, 0);
+          oacc[qi][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(lo[qi][s]), oacc[qi][db], 0, 0, 0);
+        }
+      }
+    if (more) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                               // V has been read
+      issue(false);
+      fetch_pages(t + 2 * nslice);
+    }
+  }
+
+  // ---- merge the waves that share a query block, one block of each wave at a time ----
+  float* sh_o = reinterpret_cast<float*>(smem);        // [NW waves][32][kORedStride]
+#pragma unroll
+  for (int qi = 0; qi < NQ; ++qi) {
+    l_run[qi] = half_sum(l_run[qi]);
+    __syncthreads();                         // every wave is done with its tile memory (or with the block before)
+    if (lane < 32) {
+      sh_m[wave * 32 + lane] = m_run[qi];
+      sh_l[wave * 32 + lane] = l_run[qi];
+    }
+    __syncthreads();
+    float M = -INFINITY;
+    for (int s = 0; s < nslice; ++s) M = fmaxf(M, sh_m[(my_g + groups * s) * 32 + ln]);
+    const float fscale = (m_run[qi] == -INFINITY) ? 0.f : fast_exp2(m_run[qi] - M);
+    if (wave_active) {
+      // register 4a + c of block db: head dimension 32 db + 8 a + 4 lh + c
 #pragma unroll
       for (int db = 0; db < C::kDBlocks; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+        for (int a = 0; a < 4; ++a) {
+          float* dst = sh_o + (wave * 32 + ln) * C::kORedStride + 32 * db + 8 * a + 4 * lh;
+          *reinterpret_cast<float4*>(dst) = make_float4(oacc[qi][db][4 * a] * fscale, oacc[qi][db][4 * a + 1] * fscale,
+                                                        oacc[qi][db][4 * a + 2] * fscale, oacc[qi][db][4 * a + 3] * fscale);
+        }
     }
-    // ---- P^T as two bf16 terms (value + rounding residual), 16 tokens at a time; O^T += V^T P^T ----
-    // A single bf16 rounding of P (2^-9 relative) would dominate the output error; carrying the
-    // rounding residual in a second bf16 term keeps ~16 bits of every weight.
-    float psum = 0.f;
+    __syncthreads();
+    const int rn = (tid >> 3) & 31;                        // query column this thread finalises, of group tid / 256 on
+    const int rd0 = (tid & 7) * (D / 8);                   // first of its D/8 dims
+    for (int g = tid >> 8; g < groups; g += NW / 4) {
+      const int orow = row0 + 32 * (NQ * g + qi) + rn;
+      if (orow >= R) continue;
+      float Mq = -INFINITY;
+      for (int s = 0; s < nslice; ++s) Mq = fmaxf(Mq, sh_m[(g + groups * s) * 32 + rn]);
+      float Ls = 0.f;
+      float acc[D / 8];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      u32x4 hi, lo;
+      for (int i = 0; i < D / 8; ++i) acc[i] = 0.f;
+      for (int s = 0; s < nslice; ++s) {
+        const int w = g + groups * s;
+        const float mw = sh_m[w * 32 + rn];
+        if (mw != -INFINITY) Ls += sh_l[w * 32 + rn] * fast_exp2(mw - Mq);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float p0 = fast_exp2(fmaf(sacc[8 * s + 2 * j], P.c, -m_safe));
-        const float p1 = fast_exp2(fmaf(sacc[8 * s + 2 * j + 1], P.c, -m_safe));
-        psum += p0 + p1;
-        const uint32_t h = pack_bf16(p0, p1);
-        hi[j] = h;
-        lo[j] = pack_bf16(p0 - bf16_lo(h), p1 - bf16_hi(h));
+        for (int i = 0; i < D / 8; i += 4) {
+          const float4 v = *reinterpret_cast<const float4*>(sh_o + (w * 32 + rn) * C::kORedStride + rd0 + i);
+          acc[i] += v.x; acc[i + 1] += v.y; acc[i + 2] += v.z; acc[i + 3] += v.w;
+        }
       }
-      const bf16x8 phi = __builtin_bit_cast(bf16x8, hi), plo = __builtin_bit_cast(bf16x8, lo);
+      const int onode = orow / P.G, og = orow % P.G;
+      const int64_t grow = static_cast<int64_t>(q0 + onode) * P.Hq + kvh * P.G + og;
+      if (nchunks == 1) {
+        const float inv = 1.f / Ls;
+        if (P.out_f32) {
+          float* o = static_cast<float*>(P.out) + grow * D + rd0;
 #pragma unroll
-      for (int db = 0; db < C::kDBlocks; ++db) {
-        const int vrow = 32 * db + ln;           // storage order: head dimension acc_dim of this lane
-        const bf16x8 a = as_bf16x8(*reinterpret_cast<const u32x4*>(v_lds + vrow * C::kVStride + 32 * s + 16 * lh));
-        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, phi, oacc[db], 0, 0, 0);
-        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, plo, oacc[db], 0, 0, 0);
-      }
-    }
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
-    wave_lds_fence();
-  }
-
-  // ---- merge the waves that share a query block ----
-  l_run = half_sum(l_run);
-  __syncthreads();                         // every wave is done with its tile memory
-  if (lane < 32) {
-    sh_m[wave * 32 + lane] = m_run;
-    sh_l[wave * 32 + lane] = l_run;
-  }
-  __syncthreads();
-  float M = -INFINITY;
-  for (int s = 0; s < nslice; ++s) M = fmaxf(M, sh_m[(my_qb + nqbp * s) * 32 + ln]);
-  const float fscale = (m_run == -INFINITY) ? 0.f : fast_exp2(m_run - M);
-
-  float* sh_o = reinterpret_cast<float*>(smem);        // [NW waves][32][kORedStride]
-  if (wave_active) {
-    constexpr int kA = D / 64, kQ = 256 / D;     // see acc_dim0
+          for (int i = 0; i < D / 8; ++i) o[i] = acc[i] * inv;
+        } else {
+          uint32_t* o = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(P.out) + grow * D + rd0);
 #pragma unroll
-    for (int am = 0; am < kA; ++am)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        float x[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = oacc[j / kQ][4 * ((j % kQ) * kA + am) + c] * fscale;
-        float* dst = sh_o + (wave * 32 + ln) * C::kORedStride + acc_dim0<D>(am, c, lh);
-        *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
-        *reinterpret_cast<float4*>(dst + 4) = make_float4(x[4], x[5], x[6], x[7]);
-      }
-  }
-  __syncthreads();
-  const int rn = (tid >> 3) & 31;                        // query column this thread finalises, of block tid / 256 on
-  const int rd0 = (tid & 7) * (D / 8);                   // first of its D/8 dims
-  for (int qb = tid >> 8; qb < nqb; qb += NW / 4) {
-    const int orow = row0 + 32 * qb + rn;
-    if (orow >= R) continue;
-    float Mq = -INFINITY;
-    for (int s = 0; s < nslice; ++s) Mq = fmaxf(Mq, sh_m[(qb + nqbp * s) * 32 + rn]);
-    float Ls = 0.f;
-    float acc[D / 8];
-#pragma unroll
-    for (int i = 0; i < D / 8; ++i) acc[i] = 0.f;
-    for (int s = 0; s < nslice; ++s) {
-      const int w = qb + nqbp * s;
-      const float mw = sh_m[w * 32 + rn];
-      if (mw != -INFINITY) Ls += sh_l[w * 32 + rn] * fast_exp2(mw - Mq);
-#pragma unroll
-      for (int i = 0; i < D / 8; i += 4) {
-        const float4 v = *reinterpret_cast<const float4*>(sh_o + (w * 32 + rn) * C::kORedStride + rd0 + i);
-        acc[i] += v.x; acc[i + 1] += v.y; acc[i + 2] += v.z; acc[i + 3] += v.w;
-      }
-    }
-    const int onode = orow / P.G, og = orow % P.G;
-    const int64_t grow = static_cast<int64_t>(q0 + onode) * P.Hq + kvh * P.G + og;
-    if (nchunks == 1) {
-      const float inv = 1.f / Ls;
-      if (P.out_f32) {
-        float* o = static_cast<float*>(P.out) + grow * D + rd0;
-#pragma unroll
-        for (int i = 0; i < D / 8; ++i) o[i] = acc[i] * inv;
+          for (int i = 0; i < D / 16; ++i) o[i] = pack_bf16(acc[2 * i] * inv, acc[2 * i + 1] * inv);
+        }
+        if (P.lse && (tid & 7) == 0) P.lse[grow] = (Mq + log2f(Ls)) * static_cast<float>(kLn2);
       } else {
-        uint32_t* o = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(P.out) + grow * D + rd0);
+        float* o = P.ws_o + (grow * P.max_chunks + chunk) * D + rd0;
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i) o[i] = pack_bf16(acc[2 * i] * inv, acc[2 * i + 1] * inv);
+        for (int i = 0; i < D / 8; ++i) o[i] = acc[i];
+        if ((tid & 7) == 0) P.ws_ml[grow * P.max_chunks + chunk] = make_float2(Mq, Ls);
       }
-      if (P.lse && (tid & 7) == 0) P.lse[grow] = (Mq + log2f(Ls)) * static_cast<float>(kLn2);
-    } else {
-      float* o = P.ws_o + (grow * P.max_chunks + chunk) * D + rd0;
-#pragma unroll
-      for (int i = 0; i < D / 8; ++i) o[i] = acc[i];
-      if ((tid & 7) == 0) P.ws_ml[grow * P.max_chunks + chunk] = make_float2(Mq, Ls);
     }
   }
+}
+
+// (q0, n, ctx: first query row, number of query nodes (already capped at kMaxQ) and context length of request b)
+template <int D, int NW>
+__device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* smem, int b, int kvh, int chunk, int rg,
+                                            int q0, int n, int ctx) {
+  if (n <= 0) return;
+  const int L = ctx + n, left = n * P.G - rg * 128;         // query rows of this row group and behind
+  if (left <= 0) return;
+  const int nchunks = request_chunks(P, L, n);
+  if (chunk >= nchunks) return;
+  const int cb = (((L + nchunks - 1) / nchunks) + kTile - 1) & ~(kTile - 1);
+  if (left > 32 && left <= 64) stream_tiles<D, NW, 2>(P, smem, b, kvh, chunk, rg, q0, n, ctx, nchunks, cb);
+  else stream_tiles<D, NW, 1>(P, smem, b, kvh, chunk, rg, q0, n, ctx, nchunks, cb);
 }
 
 // Grid-mapped launch: blockIdx = (chunk + max_chunks * row group, KV head, request) or, where the block table is much wider
@@ -538,7 +594,7 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
 // (56 rows, 512-token chunks) 25.6 -> 24.6 us with the merge, 8 x 32 x 2048 46.0 -> 45.3.
 template <int D, int NW>
 __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attn_stream_kernel(AttnParams P) {
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   const int b = P.chunks_last ? blockIdx.y : blockIdx.z, kvh = P.chunks_last ? blockIdx.x : blockIdx.y;
   const int cut = P.chunks_last ? blockIdx.z : blockIdx.x;
   const int q0 = P.q_offsets[b];
@@ -1028,7 +1084,7 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
 
 template <int D, int NW, bool WIDE, int SL>
 __global__ __launch_bounds__(NW * 64, (NW == 4 ? 2 : 1)) void attn_rows_kernel(AttnParams P) {
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   unsigned bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
   if (P.xcd_swizzle) {
     // Workgroups go to the 8 XCDs in turn.  With several row groups per (request, KV head) pair, renumber so that
@@ -1055,14 +1111,17 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 ? 2 : 1)) void attn_rows_kernel(A
 // Sorted-work-list launch for batches of up to kPlanMaxB requests with ragged lengths.  The grid
 // is two workgroups per compute unit; every workgroup derives the same list of work items
 // (request, chunk, KV head) from the lengths on the device, ordered by decreasing number of tiles
-// a wave streams per item, and takes one item per round of gridDim.x items (in workgroup order on even
-// rounds, reversed on odd ones): long items start first, short ones fill the tail, and no workgroup is
-// launched for chunks that do not exist.
+// a wave streams per item, and no workgroup is launched for chunks that do not exist.  A compute unit takes one item of the
+// first 256 in order and one of the next 256 in reverse (its two workgroups), then two of each further 512: of a list that is
+// short or steep at its head the shortest for the units that had the longest, else so that the sums of both workgroups stay even.
+// Against rounds over the 512 workgroups, which gave a unit items i and 256 + i: 12 requests x 16 KV heads of 1000 to 7000
+// tokens 110 -> 97 us, 32 x 8 122 -> 109, 128 x 8 of 512 to 6000 (steep) 179 -> 162; 32 x 32 of 1123 to 3922 is level (266 if
+// taken for steep, 261).
 // An item runs the token-split body or, for requests with many query rows, the row-split body.
 template <int D>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_stream_list_kernel(AttnParams P) {
   using RC = RowsCfg<D, 4>;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   __shared__ int sh_first[kPlanMaxB + 1];        // first item of the request at sorted position s
   // the request at sorted position s: first query row (below 2^16) | nodes << 16 | request << 24, and its context
   // length: an item starts without a round trip to global memory for them
@@ -1103,17 +1162,32 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_stream_list_kernel(AttnP
   }
   __syncthreads();
   const int total = sh_first[P.B];
-  // Round r hands out items r*G .. r*G+G-1 (G workgroups), in workgroup order on even rounds and in reverse
-  // on odd ones: the workgroup that got the longest item of one round gets the shortest of the next.
-  for (int round = 0;; ++round) {
-    const int slot = (round & 1) ? static_cast<int>(gridDim.x - 1 - blockIdx.x) : static_cast<int>(blockIdx.x);
-    const int item = round * static_cast<int>(gridDim.x) + slot;
-    if (item >= total) break;
-    int lo = 0, hi = P.B;                         // largest s with sh_first[s] <= item
+  auto at_item = [&](int item) __attribute__((always_inline)) {     // sorted position of its request: largest s with sh_first[s] <= item
+    int lo = 0, hi = P.B;
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
       if (sh_first[mid] <= item) lo = mid; else hi = mid;
     }
+    return lo;
+  };
+  const int grid = static_cast<int>(gridDim.x), half = grid / 2, wg = static_cast<int>(blockIdx.x);
+  const int unit = wg < half ? wg : wg - half;               // compute unit, with its two workgroups
+  const int place = wg < half ? unit : grid - 1 - unit;
+  bool skewed = true;             // the longest and the shortest of the first two turns together are well ahead of the two in the middle
+  if (total > grid + half) {
+    const int lane = tid & 63, at = lane == 0 ? 0 : (lane == 1 ? half - 1 : (lane == 2 ? half : grid - 1));
+    const int s = at_item(at), n = (sh_meta[s] >> 16) & 0xff, L = sh_ctx[s] + n, nch = request_chunks(P, L, n);
+    const int len = (request_units(P, L, n) + nch - 1) / nch;
+    auto of = [&](int l) { return __builtin_amdgcn_readlane(len, l); };
+    skewed = 10 * (of(0) + of(3)) > 11 * (of(1) + of(2));
+  }
+  for (int round = 0;; ++round) {
+    int item = place;
+    if (round > 0) item = skewed ? (wg < half ? half : grid) - 1 - unit : ((round & 1) ? grid - 1 - place : place);
+    item += round * grid;
+    if (round * grid >= total) break;
+    if (item >= total) continue;
+    const int lo = at_item(item);
     const int meta = sh_meta[lo];
     const int b = meta >> 24, q0 = meta & 0xffff, n = (meta >> 16) & 0xff, ctx = sh_ctx[lo];
     const int local = item - sh_first[lo];
@@ -1133,7 +1207,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_stream_list_kernel(AttnP
 template <int D>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_mixed_kernel(AttnParams P) {
   using RC = RowsCfg<D, 4>;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   const int b = P.chunks_last ? blockIdx.y : blockIdx.z, kvh = P.chunks_last ? blockIdx.x : blockIdx.y;
   const int chunk = P.chunks_last ? blockIdx.z : blockIdx.x;
   const int q0 = P.q_offsets[b];
@@ -1253,15 +1327,23 @@ static long dev_knob(const char* name, long fallback) {
 static long dev_knob(const char*, long fallback) { return fallback; }
 #endif
 
-// Most chunks the work list cuts a request into: the longest one the block table can hold, shared by as many waves as
-// the largest declared row count leaves per query block (requests with fewer rows get more waves), at tau tiles a wave.
-static int list_max_chunks(int64_t max_tok, int max_rows, int tau) {
-  const int min_slice = max_rows <= 32 ? 4 : (max_rows <= 64 ? 2 : 1);
-  const int64_t max_tiles = ((max_tok + kTile - 1) / kTile + min_slice - 1) / min_slice;
-  const int64_t mc = (max_tiles + tau - 1) / tau;
+// Longest item of the list in units.  An item longer than an average workgroup's share sets the end of the launch, a cut costs
+// partial results and a merge.  At 36, 32, 30, 28 units: the serving mix (64 requests x 8 KV heads, 16 to 80 rows) 167, 168, 168,
+// 168 us, 128 x 8 of 512 to 6000 tokens 167, 161, 162, 161, 16 x 8 of 4400 to 16000 117, 114, 114, 113, 12 x 16 of 4300 to 13600
+// 190, 200, 201, 196, 32 x 32 of 512 to 16384 248, 251, 250, 261, of 1123 to 3922 (up to 31 units) 265, 265,
+// 273, 276.
+constexpr int kListTau = 32;
+// ... of an item that runs the row-split body (3686, 4506, 4915 tokens at 36, 44, 48): 64 requests of 80 rows 184, 176, 175 us, of
+// 128 rows 193, 184, 186, the mix of both bodies on the worst of three seeds 144, 144, 167.
+constexpr int kListTauRows = 44;
+// Most chunks the work list cuts a request into: the longest one the block table can hold, in items of kListTau units for up
+// to 32 rows.  More rows count twice and four times the waves they take, at 44: an upper bound, which sizes the workspace.
+static int list_max_chunks(int64_t max_tok, int max_rows) {
+  const int64_t tiles = (max_tok + kTile - 1) / kTile;
+  const int64_t per_chunk = max_rows <= 32 ? 4 * kListTau : (max_rows <= 64 ? 88 : 44);
+  const int64_t mc = (tiles + per_chunk - 1) / per_chunk;
   return static_cast<int>(mc < 1 ? 1 : (mc > kListMaxChunks ? kListMaxChunks : mc));
 }
-constexpr int kListTau = 44;         // with the alternating hand-out of the list: 40-48 measured best
 // The launch for little work has a workgroup for every chunk a request could have.  Most chunks per request such that
 // those are at most sixteen workgroups per compute unit, or two per (request, KV head) pair.
 static int little_room(int64_t pairs) { return std::max<int>(2, static_cast<int>(4096 / std::max<int64_t>(pairs, 1))); }
@@ -1283,10 +1365,14 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   // tokens: 20 of 512 workgroups, 26.7 us; 13.2 us cut into 512-token chunks).  The list serves them all the same where
   // a wide block table (allocated for the longest context a model allows) would ask for more chunks than there is room
   // for, and where the caller's workspace holds the list's partial results but not these (little_ok).
-  const int list_chunks = list_max_chunks(max_tok, max_rows, kListTau);
+  const int list_chunks = list_max_chunks(max_tok, max_rows);
   const int64_t pairs = static_cast<int64_t>(a.B) * a.Hkv;
   const int room = little_room(pairs);
-  const bool little = little_ok && a.kv_hint > 0 && a.kv_hint * a.Hkv < static_cast<int64_t>(256) * 1024 && list_chunks <= room;
+  // Batches of up to 128 pairs of request and KV head go further (chunks below 1792), where the list has too few items for its
+  // 512 workgroups: 4 requests x 16 KV heads of 1174 to 3487 tokens 43 -> 22 us, 8 x 4 of 6000 to 14600 65 -> 48, 6 x 16 of 1200 to
+  // 5700 54 -> 40, 32 x 4 of 1000 to 7800 70 -> 66; at chunks above 2000 the list is even (8 x 8 of 6000 to 14600 78 and 81) or ahead.
+  const int64_t little_tokens = static_cast<int64_t>(256) * (pairs <= 128 ? 1792 : 1024);
+  const bool little = little_ok && a.kv_hint > 0 && a.kv_hint * a.Hkv < little_tokens && list_chunks <= room;
   // Up to 64 query rows per KV head the token-split body streams as fast as memory delivers; beyond, its
   // waves (one per 32-row block, each staging every tile for itself) are bound by their own staging and the
   // row-split body, whose waves share each staged tile, is ahead on batches of like lengths (96 rows per KV
@@ -1365,7 +1451,7 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   if (jobs_knob > 0) tau = 0;
   if (tau > 0) {
     p.tau = tau;
-    p.max_chunks = list_max_chunks(max_tok, max_rows, tau);
+    p.max_chunks = list_max_chunks(max_tok, max_rows);
   } else if (listable && ragged) {
     // A table much wider than the requests - it would launch four times the workgroups that the hint's tokens and one
     // partial chunk per request make, or it is wider than all tokens together are long: the workgroups without a chunk go
@@ -1405,23 +1491,24 @@ const char* attn_plan_name(const AttnPlan& p) {
   return "attn_rows_kernel<8 waves> (row-split body, 256 query rows per workgroup)";
 }
 
+// token-split body: a tile of K and one of V per wave, a query block, masks and parents; the merge takes the same memory
 template <int D>
-constexpr size_t stream_tiles_lds(int NW) { return static_cast<size_t>(NW) * AttnCfg<D>::kWaveLds; }
-template <int D>
-constexpr size_t stream_merge_lds(int NW) { return static_cast<size_t>(NW) * 32 * (AttnCfg<D>::kORedStride + 2) * sizeof(float); }
+constexpr size_t stream_lds(int NW) {
+  return std::max(2 * static_cast<size_t>(NW) * AttnCfg<D>::kTileBytes + AttnCfg<D>::kQLdsFrags * 1024 + kMaxQ * 12,
+                  static_cast<size_t>(NW) * 32 * (AttnCfg<D>::kORedStride + 2) * sizeof(float));
+}
 
 // kernels with both four-wave bodies: the tile memory of the larger one
 template <int D>
 constexpr size_t both_bodies_lds() {
-  return stream_tiles_lds<D>(kAttnWaves) > static_cast<size_t>(RowsCfg<D, 4>::kLds) ? stream_tiles_lds<D>(kAttnWaves)
-                                                                                    : static_cast<size_t>(RowsCfg<D, 4>::kLds);
+  return std::max(stream_lds<D>(kAttnWaves), static_cast<size_t>(RowsCfg<D, 4>::kLds));
 }
 
 template <int D>
 static int launch_stream_list(const AttnParams& P, hipStream_t stream) {
   constexpr size_t kListLds = both_bodies_lds<D>();
-  // two workgroups per compute unit: dynamic plus the kernel's static LDS (below 1664 bytes) within half of 160 KB
-  static_assert(kListLds + 1664 <= 80 * 1024, "the work-list kernel must fit twice into a compute unit's LDS");
+  // two workgroups per compute unit: dynamic plus the kernel's static LDS (1792 bytes with its alignment) within half of 160 KB
+  static_assert(kListLds + 1792 <= 80 * 1024, "the work-list kernel must fit twice into a compute unit's LDS");
   static std::atomic<uint64_t> list_attr_done{0};
   if (set_lds_once(&attn_stream_list_kernel<D>, kListLds, list_attr_done) != 0) return -6;
   const int n_cu = current_device_cus();
@@ -1446,8 +1533,7 @@ static int launch_mixed(const AttnParams& P, const AttnPlan& plan, int B, int Hk
 
 template <int D, int NW>
 static int launch_stream_as(const AttnParams& P, const AttnPlan& plan, int B, int Hkv, hipStream_t stream) {
-  constexpr size_t kTiles = stream_tiles_lds<D>(NW);
-  static_assert(stream_merge_lds<D>(NW) <= kTiles, "merge buffers must fit in the tile memory");
+  constexpr size_t kTiles = stream_lds<D>(NW);
   static_assert(kTiles * (NW == 4 ? 2 : 1) <= 160 * 1024, "token-split kernel: LDS per compute unit");
   static std::atomic<uint64_t> attr_done{0};
   if (set_lds_once(&attn_stream_kernel<D, NW>, kTiles, attr_done) != 0) return -6;
@@ -1519,7 +1605,8 @@ int launch_attn(const AttnArgs& a, const AttnPlan& plan, hipStream_t stream) {
   P.chunk_tokens = plan.chunk_tokens; P.max_chunks = plan.max_chunks; P.tau = plan.tau;
   // both bodies: from 65 query rows per KV head (three 32-row blocks) on, a request runs the row-split body
   P.list_rows_min = plan.tau > 0 || plan.mixed ? static_cast<int>(dev_knob("SPECV_ATTN_LIST_ROWS", 65)) : 0;
-  P.list_rows_units = static_cast<int>(dev_knob("SPECV_ATTN_ROWS_UNITS", 3));
+  P.tau_rows = static_cast<int>(dev_knob("SPECV_ATTN_TAU_ROWS", kListTauRows));
+  P.list_rows_units = static_cast<int>(dev_knob("SPECV_ATTN_ROWS_UNITS", 5));
   P.n_cap = plan.wide ? kMaxQWide : kMaxQ;
   P.chunks_last = plan.wide_table;
   P.xcd_swizzle = (plan.kind != 0 && plan.row_groups > 1 &&
