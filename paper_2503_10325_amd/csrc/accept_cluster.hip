@@ -10,10 +10,10 @@
 // reduces its part of the softmax statistics, and all workgroups exchange their parts through small
 // tagged messages in device memory.  Every workgroup then takes the same accept decisions from the
 // same numbers (a replicated state machine: nothing has to be broadcast).  A rejection needs the
-// mass of max(0, r - q): the workgroups of that level sum their slices FROM LDS and exchange
+// mass of max(0, r - q): the workgroups of that level sum their slices (from registers or LDS) and exchange
 // again; the final inverse-CDF draw locates the slice from the exchanged sums and the workgroup that
-// holds it finds the token in its LDS.  Rows behind the first rejection are never read, and no
-// row is read twice.
+// holds it finds the token there.  The rows of the child under test are fetched before it is accepted; else rows
+// behind the first rejection are never read.
 //
 // Messages.  One message = four 64-bit words {data : tag}, written with relaxed device-scope stores
 // and read with relaxed device-scope loads; a word is valid when its tag equals the round number, so
@@ -38,6 +38,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kClThreads = 256;             // four waves, one per SIMD: the per-wave reductions and the replicated
                                             // scalar steps cost a quarter of what sixteen waves would pay
 constexpr int kClWaves = kClThreads / kWave;
+// One more wave waits for the messages: loads return in order, and a wave with rows on their way would not see a message
+// before them.  It takes part in the barriers and in the replicated state, and holds no logits.
+constexpr int kClBlock = kClThreads + kWave;
 constexpr int kClUnit = kClThreads * 8;        // logits one workgroup-wide 16-byte load covers (2048)
 constexpr int kClNodes = 128;
 constexpr int kClMaxUpt = 16;                  // units per slice: 16 x 4 KiB per row, two rows = 128 KiB of LDS
@@ -66,6 +69,12 @@ struct ClusterParams {
   int patience;                   // polls the owner spends on one round before it walks alone
   unsigned long long* msg;        // [B][2 buffers][C][2 messages][4 words]
 };
+
+// 16 bytes per lane from base + off to LDS: lane i's land at byte lds_at + 16 i.  Not tracked by the compiler (the reader
+// waits); the LDS address is an operand bound to M0.
+__device__ __forceinline__ void cl_load_to_lds(const uint16_t* base, unsigned off, unsigned lds_at) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "{m0}"(lds_at), "v"(off), "s"(base) : "memory");
+}
 
 __device__ __forceinline__ void cl_unpack(u32x4 r, float (&x)[8]) {
   x[0] = bf16_lo(r[0]); x[1] = bf16_hi(r[0]); x[2] = bf16_lo(r[1]); x[3] = bf16_hi(r[1]);
@@ -101,26 +110,81 @@ __device__ __forceinline__ void cl_weights(u32x4 rp, u32x4 rq, const LevelStats&
   }
 }
 
-__global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParams P) {
-  // the slice this workgroup holds: [target row, draft row][UPT units][thread] x 16 bytes; a thread
+// Barrier for what the waves of a workgroup exchange through LDS: rows on their way to LDS and stores to memory stay in flight.
+__device__ __forceinline__ void cl_sync() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// 2^x to 1e-14 relative: 2^n by ldexp, 2^f for |f| <= 1/2 by the exponential series (terms (f ln 2)^k / k! up to k = 11, even and
+// odd powers side by side: the walk is a chain of such values, and the library's function took twice as long).
+__device__ __forceinline__ double cl_exp2(double x) {
+  const double y = x < -2000.0 ? -2000.0 : x;             // (-inf: 0; NaN stays)
+  const double n = __builtin_rint(y), f = y - n, g = f * f;
+  auto k = [](double c) __attribute__((always_inline)) {  // (a scalar where it is used: kept in vector registers they fill 22 of them)
+    asm volatile("" : "+s"(c));
+    return c;
+  };
+  double even = fma(k(7.0549116208011233e-9), g, k(1.3215486790144309e-6)), odd = fma(k(4.4455382718708115e-10), g, k(1.0178086009239699e-7));
+  even = fma(even, g, k(1.5403530393381609e-4)); odd = fma(odd, g, k(1.5252733804059840e-5));
+  even = fma(even, g, k(9.6181291076284772e-3)); odd = fma(odd, g, k(1.3333558146428443e-3));
+  even = fma(even, g, k(2.4022650695910072e-1)); odd = fma(odd, g, k(5.5504108664821580e-2));
+  even = fma(even, g, 1.0); odd = fma(odd, g, k(6.9314718055994531e-1));
+  return __builtin_ldexp(fma(f, odd, even), static_cast<int>(n));
+}
+
+// Two wave reductions side by side (each step of one fills the waits of the other).
+__device__ __forceinline__ void cl_max2(float& a, float& b) {
+  a = dpp_max_step<0x111, 0xf>(a); b = dpp_max_step<0x111, 0xf>(b);
+  a = dpp_max_step<0x112, 0xf>(a); b = dpp_max_step<0x112, 0xf>(b);
+  a = dpp_max_step<0x114, 0xf>(a); b = dpp_max_step<0x114, 0xf>(b);
+  a = dpp_max_step<0x118, 0xf>(a); b = dpp_max_step<0x118, 0xf>(b);
+  a = dpp_max_step<0x142, 0xa>(a); b = dpp_max_step<0x142, 0xa>(b);
+  a = dpp_max_step<0x143, 0xc>(a); b = dpp_max_step<0x143, 0xc>(b);
+  a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 63));
+  b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b), 63));
+}
+__device__ __forceinline__ void cl_sum2(double& a, double& b) {
+  a += dpp_f64<0x111, 0xf>(a); b += dpp_f64<0x111, 0xf>(b);
+  a += dpp_f64<0x112, 0xf>(a); b += dpp_f64<0x112, 0xf>(b);
+  a += dpp_f64<0x114, 0xf>(a); b += dpp_f64<0x114, 0xf>(b);
+  a += dpp_f64<0x118, 0xf>(a); b += dpp_f64<0x118, 0xf>(b);
+  a += dpp_f64<0x142, 0xa>(a); b += dpp_f64<0x142, 0xa>(b);
+  a += dpp_f64<0x143, 0xc>(a); b += dpp_f64<0x143, 0xc>(b);
+  a = lane_f64(a, 63);
+  b = lane_f64(b, 63);
+}
+
+// U: units per slice of a cluster whose slice is worked out once and kept in registers (4, the library's choice wherever
+// every 8192-logit slice has a compute unit of its own): the exponentials that the statistics need are the weights up to a
+// factor per row, so a rejection costs a subtraction per class instead of two exponentials, and the rows of the node under
+// test are fetched into the LDS space that the raw slice has left.  U = 0: any number of units, read from LDS each time.
+// What bounds it is a chain: per accepted node one exchange (1.2 us), the exponentials of the slice (0.7 us on its compute unit),
+// reductions and fp64 scalars, per rejection one exchange.  16 trees of 64 nodes, 128256 classes: 52.6 -> 46.0 us (kernel) with
+// weights kept, rows fetched ahead, the messages in a wave of their own (no barrier waits for a store or a row) and the scalar
+// steps shortened; the same without that wave was 57.
+template <int U>
+__global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams P) {
+  // the slice this workgroup holds (or the one on its way): [target row, draft row][UPT units][thread] x 16 bytes; a thread
   // only ever touches its own 16-byte slots, so no barrier orders these accesses
   extern __shared__ __align__(16) unsigned char cl_rows[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int SL = P.SL, LV = P.LV, C = SL * LV, UPT = P.UPT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int SL = P.SL, LV = P.LV, C = SL * LV, UPT = U ? U : P.UPT;
   const int CP = P.solo ? 1 : C;                  // workgroups that really exist per request
   const int b = blockIdx.x / CP, rank = blockIdx.x - b * CP;
   const int my_lv = rank / SL, my_sl = rank - my_lv * SL;
   const bool owner = rank == 0;
+  const bool data = wave < kClWaves;              // this wave holds a part of the slice
   const int V = P.V;
   const float c = P.c;
 
   __shared__ int sh_par[kClNodes], sh_tok[kClNodes], sh_qrow[kClNodes];
   __shared__ float sh_u[kClNodes], sh_lp[kClNodes], sh_lq[kClNodes];   // uniforms; raw logits of the drafted tokens
   __shared__ int sh_fc[kClNodes + 1];          // first child of node cur at [cur + 1], -2 = none
-  __shared__ int sh_chain[16];                 // nodes of the window, -2 = the chain has ended
+  __shared__ int sh_out[kClNodes + 1];         // accepted tokens
   __shared__ double sh_val[64];                // gathered messages
   __shared__ float sh_aux[64];
-  __shared__ double sh_e[64];
   __shared__ float sh_M[2][16];                // per level: maximum of the target row / the draft row
   __shared__ double sh_iZ[2][16];              //            reciprocal sums
   __shared__ __align__(16) float sh_wm[2][kClWaves];
@@ -137,108 +201,165 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
   const int64_t trow0 = static_cast<int64_t>(o) + b;
   const double u_res = static_cast<double>(P.u_resample[b]);
 
-  // ---- the target row of this workgroup's level, when it is known before the node arrays arrive (the
-  // root's row; any level of a linear draft): its loads go out first and overlap the dependent reads below
-  const bool early_t = !P.solo && (my_lv == 0 || P.parent == nullptr) && my_lv - 1 < n;
-  u32x4 early_r[kClMaxUpt];
-  {
-    const uint16_t* tp = P.target + (trow0 + my_lv) * static_cast<int64_t>(V);
-    const u32x4 ninf = {kNegInf2, kNegInf2, kNegInf2, kNegInf2};
+  // ---- slices: thread t holds chunk t of every unit.  They go from memory straight to LDS. ----
+  auto row_p = [&](int u) -> u32x4* { return reinterpret_cast<u32x4*>(cl_rows) + (u * kClThreads + tid); };
+  auto row_q = [&](int u) -> u32x4* { return reinterpret_cast<u32x4*>(cl_rows) + ((UPT + u) * kClThreads + tid); };
+  const unsigned rows_at = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)cl_rows)) +
+                           wave * kWave * 16;
+  auto issue_rows = [&](const uint16_t* tp, const uint16_t* qp, int sl) {       // (qp may be null: no child)
+    if (!data) return;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the slots have been read
 #pragma unroll
-    for (int u = 0; u < kClMaxUpt; ++u) {
-      const int e = (my_sl * UPT + u) * kClUnit + tid * 8;
-      early_r[u] = ninf;
-      if (early_t && u < UPT && e < V) early_r[u] = *reinterpret_cast<const u32x4*>(tp + e);
+    for (int u = 0; u < UPT; ++u) {
+      const int e = (sl * UPT + u) * kClUnit + tid * 8;
+      const unsigned off = e < V ? 2u * e : 0u;   // (V is a multiple of 8; chunks past the end are overwritten in settle)
+      cl_load_to_lds(tp, off, rows_at + u * kClThreads * 16);
+      if (qp) cl_load_to_lds(qp, off, rows_at + (UPT + u) * kClThreads * 16);
     }
+  };
+  auto settle = [&](bool child, int sl) {         // the rows are here
+    if (!data) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const u32x4 ninf = {kNegInf2, kNegInf2, kNegInf2, kNegInf2};
+    for (int u = 0; u < UPT; ++u) {
+      const bool out = (sl * UPT + u) * kClUnit + tid * 8 >= V;
+      if (out) *row_p(u) = ninf;
+      if (out || !child) *row_q(u) = ninf;
+    }
+  };
+  // the rows of this workgroup's level, when they are known before the node arrays arrive (the root's, whose first child is
+  // node 0; any level of a linear draft): their loads go out first and overlap the dependent reads below
+  const bool early = !P.solo && (my_lv == 0 || P.parent == nullptr) && my_lv - 1 < n;
+  if (early) {
+    const int qr = my_lv < n ? min(max(P.q_row[o + my_lv], 0), P.n_q_rows - 1) : 0;
+    issue_rows(P.target + (trow0 + my_lv) * static_cast<int64_t>(V),
+               my_lv < n ? P.draft_q + static_cast<int64_t>(__builtin_amdgcn_readfirstlane(qr)) * V : nullptr, my_sl);
   }
 
-  // ---- node arrays (indices come from device memory the host cannot check: clamp them) ----
-  if (tid < kClNodes) {
-    int par = -2, tok = 0, qr = 0;
-    float u = 0.f;
-    if (tid < n) {
-      par = P.parent ? P.parent[o + tid] : tid - 1;
-      if (par < -1 || par >= tid) par = -1;
-      tok = min(max(P.draft_tokens[o + tid], 0), V - 1);
-      qr = min(max(P.q_row[o + tid], 0), P.n_q_rows - 1);
-      u = P.u_accept[o + tid];
-      if (owner && P.dbg_ratio) P.dbg_ratio[o + tid] = __builtin_nanf("");
+  // ---- node arrays, by the wave that holds no logits: its loads do not queue behind the rows.  (Indices come from device
+  // memory the host cannot check: clamp them.)  Lane l takes nodes l and l + 64; the steps are ordered within the wave. ----
+  int my_tok[2] = {0, 0}, my_prt[2] = {-1, -1};
+  if (!data) {
+    int qr[2] = {0, 0};
+    float u[2] = {0.f, 0.f};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int nd = lane + 64 * h;
+      my_prt[h] = -2;
+      if (nd < n) {
+        my_prt[h] = P.parent ? P.parent[o + nd] : nd - 1;
+        my_tok[h] = P.draft_tokens[o + nd];
+        qr[h] = P.q_row[o + nd];
+        u[h] = P.u_accept[o + nd];
+        if (owner && P.dbg_ratio) P.dbg_ratio[o + nd] = __builtin_nanf("");
+      }
     }
-    sh_par[tid] = par; sh_tok[tid] = tok; sh_qrow[tid] = qr; sh_u[tid] = u;
-    sh_invRf[tid] = 0.f;
-    sh_invR[tid] = 0.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int nd = lane + 64 * h;
+      if (nd < n && (my_prt[h] < -1 || my_prt[h] >= nd)) my_prt[h] = -1;
+      my_tok[h] = min(max(my_tok[h], 0), V - 1);
+      sh_par[nd] = my_prt[h]; sh_tok[nd] = my_tok[h]; sh_qrow[nd] = min(max(qr[h], 0), P.n_q_rows - 1); sh_u[nd] = u[h];
+      sh_fc[nd] = kClNodes;
+      sh_invRf[nd] = 0.f;
+      sh_invR[nd] = 0.0;
+    }
+    if (lane == 0) sh_fc[kClNodes] = kClNodes;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (lane + 64 * h < n) atomicMin(&sh_fc[my_prt[h] + 1], lane + 64 * h);    // first child = lowest index among the children
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    for (int i = lane; i <= kClNodes; i += kWave)
+      if (sh_fc[i] >= kClNodes) sh_fc[i] = -2;    // no child
   }
-  if (tid <= kClNodes) sh_fc[tid] = kClNodes;
-  __syncthreads();
-  if (tid < n) atomicMin(&sh_fc[sh_par[tid] + 1], tid);      // first child = lowest index among the children
-  // the two logits of every drafted token, kept in registers until the first round's loads are out
-  float g_lp = 0.f, g_lq = 0.f;
-  if (tid < n) g_lp = bf16_bits_to_float(P.target[(trow0 + 1 + sh_par[tid]) * static_cast<int64_t>(V) + sh_tok[tid]]);
-  __syncthreads();
-  // the draft row of a sibling group is the one its first child names (the row the slices hold for that group)
-  if (tid < n) {
-    const int fc = min(sh_fc[sh_par[tid] + 1], kClNodes - 1);
-    g_lq = bf16_bits_to_float(P.draft_q[static_cast<int64_t>(sh_qrow[fc]) * V + sh_tok[tid]]);
+  cl_sync();
+  // The two logits of every drafted token; the draft row of a sibling group is the one its first child names (the row the
+  // slices hold for that group).  Read after the first exchange, whose barriers order it.
+  if (!data) {
+    float lp[2] = {0.f, 0.f}, lq[2] = {0.f, 0.f};
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (lane + 64 * h < n) {
+        const int fc = min(max(sh_fc[my_prt[h] + 1], 0), kClNodes - 1);
+        lp[h] = bf16_bits_to_float(P.target[(trow0 + 1 + my_prt[h]) * static_cast<int64_t>(V) + my_tok[h]]);
+        lq[h] = bf16_bits_to_float(P.draft_q[static_cast<int64_t>(sh_qrow[fc]) * V + my_tok[h]]);
+      }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) { sh_lp[lane + 64 * h] = lp[h]; sh_lq[lane + 64 * h] = lq[h]; }
   }
-  if (tid <= kClNodes && sh_fc[tid] >= kClNodes) sh_fc[tid] = -2;   // no child
-  __syncthreads();
   // lane l looks after nodes l and l + 64; nodes that do not exist hold an impossible parent
   const int my_parent = (lane < n) ? sh_par[lane] : -3;
   const int my_parent_hi = (lane + 64 < n) ? sh_par[lane + 64] : -3;
 
-  // ---- the slice held in LDS ----
-  auto row_p = [&](int u) -> u32x4* { return reinterpret_cast<u32x4*>(cl_rows) + (u * kClThreads + tid); };
-  auto row_q = [&](int u) -> u32x4* { return reinterpret_cast<u32x4*>(cl_rows) + ((UPT + u) * kClThreads + tid); };
-  if (early_t) {
-#pragma unroll
-    for (int u = 0; u < kClMaxUpt; ++u)
-      if (u < UPT) *row_p(u) = early_r[u];
-  }
-  // (a node < -1 stands for "the chain has ended"; skip_t: the target part is in LDS already)
-  auto load_slice = [&](int node, int sl, bool skip_t = false) {
-    const bool exists = node >= -1;
-    node = max(node, -1);
-    const int fcn = exists ? sh_fc[node + 1] : -2;
-    const uint16_t* tp = P.target + (trow0 + 1 + node) * static_cast<int64_t>(V);
-    const uint16_t* qp = P.draft_q + static_cast<int64_t>(sh_qrow[max(fcn, 0)]) * V;
-    const u32x4 ninf = {kNegInf2, kNegInf2, kNegInf2, kNegInf2};
-    u32x4 tp_r[kClMaxUpt], tq_r[kClMaxUpt];
-#pragma unroll
-    for (int u = 0; u < kClMaxUpt; ++u) {         // all loads first: up to 8 x 16 bytes in flight per thread
-      const int e = (sl * UPT + u) * kClUnit + tid * 8;
-      tp_r[u] = ninf;
-      tq_r[u] = ninf;
-      if (u < UPT && exists && e < V) {           // V is a multiple of 8: a chunk is inside or outside
-        if (!skip_t) tp_r[u] = *reinterpret_cast<const u32x4*>(tp + e);
-        if (fcn >= 0) tq_r[u] = *reinterpret_cast<const u32x4*>(qp + e);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kClMaxUpt; ++u)
-      if (u < UPT) {
-        if (!skip_t) *row_p(u) = tp_r[u];
-        *row_q(u) = tq_r[u];
-      }
+  auto issue_node = [&](int node, int sl) {         // node >= -1
+    node = __builtin_amdgcn_readfirstlane(node);
+    const int fcn = __builtin_amdgcn_readfirstlane(sh_fc[node + 1]);
+    const int qr = __builtin_amdgcn_readfirstlane(sh_qrow[max(fcn, 0)]);
+    issue_rows(P.target + (trow0 + 1 + node) * static_cast<int64_t>(V),
+               fcn >= 0 ? P.draft_q + static_cast<int64_t>(qr) * V : nullptr, sl);
+  };
+  // The window that begins at a child that is about to be tested: this workgroup's slice of it is fetched while the present
+  // round is worked out and its messages travel.  A wrong guess costs its bytes.
+  int next_start = -1;                            // first node of the window the rows on their way belong to
+  auto chain_node = [&](int start, int steps) {   // the node `steps` first children below, -2 = the chain has ended
+    int node = start;
+    for (int j = 0; j < steps; ++j) node = node >= -1 ? sh_fc[node + 1] : -2;
+    return node;
+  };
+  auto fetch_ahead = [&](int start) {
+    if (U == 0 || start < 0 || start == next_start) return;
+    if (next_start >= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // an earlier guess has landed
+    next_start = start;
+    const int node = chain_node(start, my_lv);
+    if (node >= 0) issue_node(node, my_sl);
+  };
+  auto load_slice = [&](int node, int sl) {
+    next_start = -1;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (a guess may still be on its way to the same slots)
+    issue_node(node, sl);
+    settle(sh_fc[node + 1] >= 0, sl);
   };
 
-  // Local statistics of the held slice: (max, sum 2^((l - max) c)) of the target part and the draft part.
-  // The results are valid in wave 0 (the wave that posts them).
+  auto waves_total = [&](int k) {                 // sum of the waves' sums, the same order everywhere
+    double t = sh_ws[k][0];
+#pragma unroll
+    for (int w = 1; w < kClWaves; ++w) t += sh_ws[k][w];
+    return t;
+  };
+
+  // Local statistics of the slice in LDS: (max, sum 2^((l - max) c)) of the target part and the draft part.
+  // Between two calls (of this or of slice_weight_sum) every wave passes another barrier: what is exchanged here has been read.
+  constexpr int N = U ? U : 1;
+  float ep[N][8], eq[N][8];                       // U: 2^((l - max of the slice) c), then weights (see weights_to)
+  float sl_mp = -INFINITY, sl_mq = -INFINITY;     // ... those maxima
+  int held = -1;                                  // ... level of the weights in ep; -1: exponentials
   auto slice_stats = [&](bool have_q, float& mp, double& zp, float& mq, double& zq) {
     float tp = -INFINITY, tq = -INFINITY;
-    for (int u = 0; u < UPT; ++u) {
-      float x[8];
-      cl_unpack(*row_p(u), x);
+    const int units = data ? UPT : 0;
+    if constexpr (U != 0) {
+      if (data) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) tp = fmaxf(tp, x[j]);
-      cl_unpack(*row_q(u), x);
+        for (int u = 0; u < N; ++u) { cl_unpack(*row_p(u), ep[u]); cl_unpack(*row_q(u), eq[u]); }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) tq = fmaxf(tq, x[j]);
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) { tp = fmaxf(tp, ep[u][j]); tq = fmaxf(tq, eq[u][j]); }
+      }
+    } else {
+      for (int u = 0; u < units; ++u) {
+        float x[8];
+        cl_unpack(*row_p(u), x);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) tp = fmaxf(tp, x[j]);
+        cl_unpack(*row_q(u), x);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) tq = fmaxf(tq, x[j]);
+      }
     }
-    tp = wave_max(tp);
-    tq = wave_max(tq);
-    __syncthreads();                              // earlier readers of sh_wm and sh_ws are done
-    sh_wm[0][wave] = tp; sh_wm[1][wave] = tq;     // every lane of the wave stores the same value
-    __syncthreads();
+    cl_max2(tp, tq);
+    if (data) { sh_wm[0][wave] = tp; sh_wm[1][wave] = tq; }     // every lane of the wave stores the same value
+    cl_sync();
     mp = -INFINITY; mq = -INFINITY;
 #pragma unroll
     for (int w = 0; w < kClWaves; w += 4) {
@@ -249,138 +370,236 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
     }
     const float sp = (mp == -INFINITY) ? 0.f : mp, sq = (mq == -INFINITY) ? 0.f : mq;
     double ap = 0.0, aq = 0.0;
-    for (int u = 0; u < UPT; ++u) {
-      float x[8];
-      cl_unpack(*row_p(u), x);
-      float sum = 0.f;
+    if constexpr (U != 0) {
+      sl_mp = mp; sl_mq = mq;
+      held = -1;
+      if (data) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sum += fast_exp2((x[j] - sp) * c);
-      ap += static_cast<double>(sum);
-      if (have_q) {
-        cl_unpack(*row_q(u), x);
-        sum = 0.f;
+        for (int u = 0; u < N; ++u) {
+          float sum = 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sum += fast_exp2((x[j] - sq) * c);
-        aq += static_cast<double>(sum);
+          for (int j = 0; j < 8; ++j) { ep[u][j] = fast_exp2((ep[u][j] - sp) * c); sum += ep[u][j]; }
+          ap += static_cast<double>(sum);
+        }
+        if (have_q) {
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+            float sum = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { eq[u][j] = fast_exp2((eq[u][j] - sq) * c); sum += eq[u][j]; }
+            aq += static_cast<double>(sum);
+          }
+        }
+      }
+    } else {
+      for (int u = 0; u < units; ++u) {
+        float x[8];
+        cl_unpack(*row_p(u), x);
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum += fast_exp2((x[j] - sp) * c);
+        ap += static_cast<double>(sum);
+        if (have_q) {
+          cl_unpack(*row_q(u), x);
+          sum = 0.f;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) sum += fast_exp2((x[j] - sq) * c);
+          aq += static_cast<double>(sum);
+        }
       }
     }
-    ap = wave_sum(ap);
-    aq = wave_sum(aq);
-    sh_ws[0][wave] = ap; sh_ws[1][wave] = aq;
-    __syncthreads();
-    zp = wave_sum(lane < kClWaves ? sh_ws[0][lane] : 0.0);
-    zq = wave_sum(lane < kClWaves ? sh_ws[1][lane] : 0.0);
+    cl_sum2(ap, aq);
+    if (data) { sh_ws[0][wave] = ap; sh_ws[1][wave] = aq; }
+    cl_sync();
+    zp = waves_total(0);
+    zq = waves_total(1);
+  };
+
+  // U: brings ep from the exponentials to the weights of level L (cl_weights says what they are), eq to the draft row's
+  // probabilities.  Levels only go up; a level is entered when its mass is known to be positive.
+  auto weights_to = [&](const LevelStats& S, int L) {
+    if (held < 0) {
+      const float m = lane == 0 ? sl_mp : sl_mq, M = lane == 0 ? S.mp : S.mq;
+      const double iz = lane == 0 ? S.izp : S.izq;
+      const float f = m == -INFINITY ? 0.f : static_cast<float>(cl_exp2(static_cast<double>(m - M) * static_cast<double>(c)) * iz);
+      const float fp = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), 0));
+      const float fq = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), 1));
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { ep[u][j] *= fp; eq[u][j] *= fq; }
+      held = 0;
+    }
+    for (; held < L; ++held) {
+      const float scale = held > 0 ? sh_invRf[held - 1] : 1.f;
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ep[u][j] = fmaxf(ep[u][j] * scale - eq[u][j], 0.f);
+    }
   };
 
   // Sum of the level-L weights of the held slice (valid in every wave).
   auto slice_weight_sum = [&](const LevelStats& S, int L) -> double {
     double acc = 0.0;
-    for (int u = 0; u < UPT; ++u) {
-      float w[8];
-      cl_weights(*row_p(u), *row_q(u), S, c, L, sh_invRf, w);
-      float sum = 0.f;
+    if constexpr (U != 0) {
+      if (data) {
+        weights_to(S, L > 0 ? L - 1 : 0);         // (the level itself is not entered: its mass may turn out to be zero)
+        const float scale = L > 1 ? sh_invRf[L - 2] : 1.f;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sum += w[j];
-      acc += static_cast<double>(sum);
+        for (int u = 0; u < N; ++u) {
+          float sum = 0.f;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) sum += (L > 0 && held < L) ? fmaxf(ep[u][j] * scale - eq[u][j], 0.f) : ep[u][j];
+          acc += static_cast<double>(sum);
+        }
+      }
+    } else {
+      for (int u = 0; u < (data ? UPT : 0); ++u) {
+        float w[8];
+        cl_weights(*row_p(u), *row_q(u), S, c, L, sh_invRf, w);
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum += w[j];
+        acc += static_cast<double>(sum);
+      }
     }
     acc = wave_sum(acc);
-    __syncthreads();                              // earlier readers of sh_ws are done
-    sh_ws[0][wave] = acc;
-    __syncthreads();
-    return wave_sum(lane < kClWaves ? sh_ws[0][lane] : 0.0);
+    if (data) sh_ws[0][wave] = acc;
+    cl_sync();
+    return waves_total(0);
+  };
+
+  // Level-L weights of unit u's classes of this thread.
+  auto unit_weights = [&](const LevelStats& S, int L, int u, float (&w)[8]) {
+    if constexpr (U != 0) {                       // (slice_parts has brought them to level L)
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        if (k == u) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) w[j] = ep[k][j];
+        }
+    } else {
+      cl_weights(*row_p(u), *row_q(u), S, c, L, sh_invRf, w);
+    }
   };
 
   // Per-(unit, wave) sums of the level-L weights of the held slice, in vocabulary order, for the draw.
   auto slice_parts = [&](const LevelStats& S, int L) {
-    __syncthreads();
+    cl_sync();
+    if (U != 0 && data) weights_to(S, L);
+#pragma unroll
     for (int u = 0; u < UPT; ++u) {
+      if (!data) break;
       float w[8];
-      cl_weights(*row_p(u), *row_q(u), S, c, L, sh_invRf, w);
+      unit_weights(S, L, u, w);
       float sum = 0.f;
 #pragma unroll
       for (int j = 0; j < 8; ++j) sum += w[j];
       const double d = wave_sum(static_cast<double>(sum));
       sh_part[u * kClWaves + wave] = d;
     }
-    __syncthreads();
+    cl_sync();
   };
 
-  // ---- messages ----
-  auto msg_ptr = [&](unsigned r, int wg, int k) {
-    return P.msg + ((((static_cast<size_t>(b) * 2 + (r & 1u)) * C + wg) * 2 + k) * 4);
-  };
-  // every lane of wave 0 stores one of the four words (same values from the lanes that share a word)
+  // ---- messages ---- (byte offsets from P.msg, worked out where they are used: kept in registers they end up in scratch
+  // memory, and a reload waits behind the message that has just been stored)
+  auto msg_at = [&](unsigned r, int wg, int k) { return (((static_cast<unsigned>(b) * 2u + (r & 1u)) * C + wg) * 2u + k) * 32u; };
+  auto msg_word = [&](unsigned at) { return reinterpret_cast<unsigned long long*>(reinterpret_cast<unsigned char*>(P.msg) + at); };
+  // every lane stores one of the four words (same values from the lanes that share a word)
   auto post = [&](unsigned r, int k, double val, float aux) {
-    if (wave == 0) {
-      const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(val));
-      const int w = lane & 3;
-      const unsigned data = w == 0 ? static_cast<unsigned>(bits) : (w == 1 ? static_cast<unsigned>(bits >> 32)
-                                   : (w == 2 ? __float_as_uint(aux) : 0u));
-      st_dev(msg_ptr(r, rank, k) + w, (static_cast<unsigned long long>(data) << 32) | r);
-    }
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    const int w = l & 3;
+    unsigned word = w == 2 ? __float_as_uint(aux) : 0u;
+    word = w == 0 ? static_cast<unsigned>(__double2loint(val)) : word;
+    word = w == 1 ? static_cast<unsigned>(__double2hiint(val)) : word;
+    st_dev(msg_word(msg_at(r, rank, k) + 8u * w), (static_cast<unsigned long long>(word) << 32) | r);
   };
+  // Round r: the wave without logits posts this workgroup's one or two messages and waits for everybody's (the other waves
+  // go on to the barrier).  Every wave has passed a barrier since it read what the round before left here.
   // 0: every peer's messages of round r are in sh_val / sh_aux; 1: gave up waiting; 2: the owner walks alone
-  auto gather = [&](unsigned r, int nmsg) -> int {
-    __syncthreads();                              // earlier readers of sh_val / sh_status are done
-    if (wave == 0) {
-      const int nslots = C * nmsg;
-      const int my = min(lane, nslots - 1);       // lanes beyond repeat the last slot
-      const unsigned long long* m = msg_ptr(r, my / nmsg, my % nmsg);
+  auto exchange = [&](unsigned r, int nmsg, double v0, float a0, double v1, float a1) -> int {
+    if (!data) {
+      post(r, 0, v0, a0);
+      if (nmsg == 2) post(r, 1, v1, a1);
+      int l = lane;
+      asm volatile("" : "+v"(l));
+      const int my = min(l, C * nmsg - 1);        // lanes beyond repeat the last message
+      const unsigned at = nmsg == 2 ? msg_at(r, my >> 1, my & 1) : msg_at(r, my, 0);
       const int limit = owner ? P.patience : 4 * P.patience + 16;
-      int spins = 0, status = 0;
-      unsigned long long w0 = 0, w1 = 0, w2 = 0;
-      for (;;) {
-        w0 = ld_dev(m); w1 = ld_dev(m + 1); w2 = ld_dev(m + 2);
-        const bool ok = static_cast<unsigned>(w0) == r && static_cast<unsigned>(w1) == r && static_cast<unsigned>(w2) == r;
-        const bool ab = static_cast<unsigned>(w0) == kClAbort;
-        if (__any(ab)) { status = 2; break; }
-        if (__all(ok)) break;
-        if (++spins > limit) { status = 1; break; }
-        __builtin_amdgcn_s_sleep(2);
-      }
-      if (status == 0) {
-        sh_val[my] = __longlong_as_double(static_cast<long long>((w1 & 0xffffffff00000000ull) | (w0 >> 32)));
-        sh_aux[my] = __uint_as_float(static_cast<unsigned>(w2 >> 32));
+      int spins = 0, status = -1;
+      unsigned long long w[2][3];
+      auto look = [&](unsigned long long (&x)[3]) __attribute__((always_inline)) {
+        x[0] = ld_dev(msg_word(at)); x[1] = ld_dev(msg_word(at + 8u)); x[2] = ld_dev(msg_word(at + 16u));
+      };
+      auto judge = [&](const unsigned long long (&x)[3]) __attribute__((always_inline)) {     // -1: look again
+        const bool ok = static_cast<unsigned>(x[0]) == r && static_cast<unsigned>(x[1]) == r && static_cast<unsigned>(x[2]) == r;
+        if (__any(static_cast<unsigned>(x[0]) == kClAbort)) { status = 2; return; }
+        if (__all(ok)) {
+          status = 0;
+          sh_val[my] = __hiloint2double(static_cast<int>(x[1] >> 32), static_cast<int>(x[0] >> 32));
+          sh_aux[my] = __uint_as_float(static_cast<unsigned>(x[2] >> 32));
+          return;
+        }
+        if (++spins > 2 * limit) status = 1;      // (two looks take the time of one trip)
+      };
+      look(w[0]);
+      for (;;) {                                  // the next look is on its way while this one is judged
+        look(w[1]);
+        judge(w[0]);
+        if (status >= 0) break;
+        look(w[0]);
+        judge(w[1]);
+        if (status >= 0) break;
       }
       sh_status = status;
     }
-    __syncthreads();
+    cl_sync();
     return sh_status;
   };
 
   // ---- the walk; solo: this workgroup computes every slice's part itself ----
   auto walk = [&](const bool solo) -> int {
-    int cur = -1, depth = 0;
+    int cur = -1, win = -1, depth = 0;            // node the walk is at, first node of the window, tokens accepted
     unsigned r = 0;
     int held_lv = -1, held_sl = -1;               // slice in registers (solo mode)
+    auto bring = [&](int lv, int sl) {            // solo: slice sl of level lv of the window, as the workgroup that holds it has it
+      const int node = chain_node(win, lv);
+      load_slice(node, sl);
+      held_lv = lv; held_sl = sl;
+      if (U != 0) {
+        float mp, mq;
+        double zp, zq;
+        cl_sync();
+        slice_stats(sh_fc[node + 1] >= 0, mp, zp, mq, zq);
+        cl_sync();
+      }
+    };
     for (int guard = 0; guard <= kClNodes + 1; ++guard) {
       // ---- window: the current node and its chain of first children ----
-      __syncthreads();
-      if (wave == 0) {                            // all lanes store the same words
-        int cn = cur;
-        for (int j = 0; j < LV; ++j) {
-          sh_chain[j] = cn;
-          cn = (cn >= -1) ? sh_fc[cn + 1] : -2;
-        }
-      }
-      __syncthreads();
+      win = cur;
       ++r;
       if (!solo) {
-        const int node = sh_chain[my_lv];
+        const int node = chain_node(win, my_lv);
         float mp = -INFINITY, mq = -INFINITY;
         double zp = 0.0, zq = 0.0;
-        load_slice(node, my_sl, guard == 0 && early_t);
-        if (guard == 0 && tid < n) { sh_lp[tid] = g_lp; sh_lq[tid] = g_lq; }
+        const bool there = guard == 0 ? early : next_start == cur;     // (on its way or here)
+        if (node >= -1) {
+          if (there) settle(sh_fc[node + 1] >= 0, my_sl);
+          else load_slice(node, my_sl);
+        }
+        next_start = -1;
         if (node >= -1) slice_stats(sh_fc[node + 1] >= 0, mp, zp, mq, zq);
-        post(r, 0, zp, mp);
-        post(r, 1, zq, mq);
-        const int st = gather(r, 2);
+        else cl_sync();
+        const int last = chain_node(win, LV - 1);
+        fetch_ahead(last >= -1 ? sh_fc[last + 1] : -1);
+        const int st = exchange(r, 2, zp, mp, zq, mq);
         if (st) return st;
       } else {
-        if (guard == 0 && tid < n) { sh_lp[tid] = g_lp; sh_lq[tid] = g_lq; }
         for (int v = 0; v < C; ++v) {
           const int lv = v / SL, sl = v - lv * SL;
-          const int node = sh_chain[lv];
+          const int node = chain_node(win, lv);
           float mp = -INFINITY, mq = -INFINITY;
           double zp = 0.0, zq = 0.0;
           if (node >= -1) {
@@ -388,28 +607,24 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
             held_lv = lv; held_sl = sl;
             slice_stats(sh_fc[node + 1] >= 0, mp, zp, mq, zq);
           }
-          __syncthreads();
+          cl_sync();
           if (wave == 0) { sh_val[2 * v] = zp; sh_aux[2 * v] = mp; sh_val[2 * v + 1] = zq; sh_aux[2 * v + 1] = mq; }
         }
-        __syncthreads();
+        cl_sync();
       }
-      // ---- merge the slices' parts per level: a wave per level, lane = (slice, row kind) ----
-      for (int lvw = wave; lvw < LV; lvw += kClWaves) {
-        const int sl = lane >> 1, kind = lane & 1;
-        const bool have = sl < SL;
-        const int idx = (lvw * SL + (have ? sl : 0)) * 2 + kind;
+      // ---- merge the slices' parts: a wave per (level, row kind), a lane per slice ----
+      for (int k = wave; k < 2 * LV; k += kClBlock / kWave) {
+        const int lvw = k >> 1, kind = k & 1;
+        const bool have = lane < SL;
+        const int idx = (lvw * SL + (have ? lane : 0)) * 2 + kind;
         const float m = have ? sh_aux[idx] : -INFINITY;
         const double z = have ? sh_val[idx] : 0.0;
-        const float M0 = wave_max(kind == 0 ? m : -INFINITY);
-        const float M1 = wave_max(kind == 1 ? m : -INFINITY);
-        const float M = kind ? M1 : M0;
-        const double e = (m == -INFINITY) ? 0.0 : z * exp2(static_cast<double>(m - M) * static_cast<double>(c));
-        const double Z0 = wave_sum(kind == 0 ? e : 0.0);
-        const double Z1 = wave_sum(kind == 1 ? e : 0.0);
-        sh_M[0][lvw] = M0; sh_M[1][lvw] = M1;                   // every lane stores the same values
-        sh_iZ[0][lvw] = 1.0 / Z0; sh_iZ[1][lvw] = 1.0 / Z1;
+        const float M = wave_max(m);
+        const double Z = wave_sum((m == -INFINITY) ? 0.0 : z * cl_exp2(static_cast<double>(m - M) * static_cast<double>(c)));
+        sh_M[kind][lvw] = M;                                     // every lane stores the same value
+        sh_iZ[kind][lvw] = 1.0 / Z;
       }
-      __syncthreads();
+      cl_sync();
 
       // ---- decisions, level by level while the walk follows the chain ----
       int j = 0;
@@ -422,22 +637,23 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
 
         // one exchange of level-L weight sums of pair j; the slices' sums land in sh_val[j*SL + sl]
         int fail = 0;
-        auto sum_round = [&](int L) -> double {
+        auto sum_round = [&](int L, int candidate) -> double {          // candidate: the child that is tested next, -1 = none
           ++r;
           if (!solo) {
             double mine = 0.0;
             if (my_lv == j) mine = slice_weight_sum(S, L);
-            post(r, 0, mine, 0.f);
-            const int st = gather(r, 1);
+            else cl_sync();
+            fetch_ahead(candidate);
+            const int st = exchange(r, 1, mine, 0.f, 0.0, 0.f);
             if (st) { fail = st; return 0.0; }
           } else {
             for (int sl = 0; sl < SL; ++sl) {
-              if (held_lv != j || held_sl != sl) { load_slice(sh_chain[j], sl); held_lv = j; held_sl = sl; }
+              if (held_lv != j || held_sl != sl) bring(j, sl);
               const double t = slice_weight_sum(S, L);
-              __syncthreads();
+              cl_sync();
               if (wave == 0) sh_val[j * SL + sl] = t;
             }
-            __syncthreads();
+            cl_sync();
           }
           // total of the slices' sums (every wave of every workgroup: the same wave-level reduction)
           return wave_sum(lane < SL ? sh_val[j * SL + lane] : 0.0);
@@ -445,30 +661,35 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
 
         unsigned long long kids = __ballot(my_parent == cur && lane > cur);
         unsigned long long kids_hi = __ballot(my_parent_hi == cur && lane + 64 > cur);
+        // p and q of every child's token, each lane its own nodes
+        const auto prob = [&](float l, float m, double iz) {
+          return cl_exp2((static_cast<double>(l) - static_cast<double>(m)) * static_cast<double>(c)) * iz;
+        };
+        double lane_p = 0.0, lane_q = 0.0, lane_p_hi = 0.0, lane_q_hi = 0.0;
+        if (kids) { lane_p = prob(sh_lp[lane], S.mp, S.izp); lane_q = prob(sh_lq[lane], S.mq, S.izq); }
+        if (kids_hi) { lane_p_hi = prob(sh_lp[lane + 64], S.mp, S.izp); lane_q_hi = prob(sh_lq[lane + 64], S.mq, S.izq); }
         int accepted = -1;
         while (kids | kids_hi) {
           int ch;
           if (kids) { ch = __ffsll(static_cast<long long>(kids)) - 1; kids &= kids - 1; }
           else { ch = 64 + __ffsll(static_cast<long long>(kids_hi)) - 1; kids_hi &= kids_hi - 1; }
-          const double qx = exp2((static_cast<double>(sh_lq[ch]) - static_cast<double>(S.mq)) * static_cast<double>(c)) * S.izq;
-          double rx = exp2((static_cast<double>(sh_lp[ch]) - static_cast<double>(S.mp)) * static_cast<double>(c)) * S.izp;
+          const double qx = lane_f64(ch < 64 ? lane_q : lane_q_hi, ch & 63);
+          double rx = lane_f64(ch < 64 ? lane_p : lane_p_hi, ch & 63);
           for (int k = 0; k < level; ++k) {
             double w = rx - qx;
             w = w > 0.0 ? w : 0.0;
             rx = w * sh_invR[k];
           }
-          double ratio;
-          if (qx > 0.0) ratio = rx / qx;
-          else ratio = (rx > 0.0) ? INFINITY : 0.0;
-          if (owner && P.dbg_ratio && wave == 0) P.dbg_ratio[o + ch] = static_cast<float>(ratio);
-          if (static_cast<double>(sh_u[ch]) < ratio) { accepted = ch; break; }
+          if (owner && P.dbg_ratio && wave == 0)
+            P.dbg_ratio[o + ch] = static_cast<float>(qx > 0.0 ? rx / qx : (rx > 0.0 ? INFINITY : 0.0));
+          if (static_cast<double>(sh_u[ch]) * qx < rx) { accepted = ch; break; }      // u < r(x) / q(x)
           // rejected: mass of max(0, r - q)
-          const double mass = sum_round(level + 1);
+          const int sibling = kids ? __ffsll(static_cast<long long>(kids)) - 1 : (kids_hi ? 63 + __ffsll(static_cast<long long>(kids_hi)) : -1);
+          const double mass = sum_round(level + 1, sibling);
           if (fail) return fail;
           if (mass > 0.0) {
-            __syncthreads();
-            if (wave == 0) { sh_invR[level] = 1.0 / mass; sh_invRf[level] = static_cast<float>(1.0 / mass); }
-            __syncthreads();
+            const double inv = 1.0 / mass;         // every wave stores the same value and reads its own
+            sh_invR[level] = inv; sh_invRf[level] = static_cast<float>(inv);
             ++level;
             sums_level = level;
             total = mass;
@@ -477,18 +698,17 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
           }
         }
         if (accepted >= 0) {
-          if (owner && wave == 0 && depth < P.out_stride)
-            P.out_tokens[static_cast<int64_t>(b) * P.out_stride + depth] = sh_tok[accepted];
+          sh_out[depth] = sh_tok[accepted];        // (all waves: the same value)
           ++depth;
           cur = accepted;
-          if (j + 1 < LV && sh_chain[j + 1] == accepted) { ++j; continue; }   // its statistics are in this window
+          if (j + 1 < LV && chain_node(win, j + 1) == accepted) { ++j; continue; }   // its statistics are in this window
           new_window = true;
           continue;
         }
 
         // ---- no child, or every child rejected: draw from the level's weights by inverse CDF ----
         if (sums_level != level) {
-          total = sum_round(level);
+          total = sum_round(level, -1);
           if (fail) return fail;
         }
         const double target = u_res * total;
@@ -508,10 +728,7 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
           s_hit = __ffsll(static_cast<long long>(hit)) - 1;       // no crossing (rounding): the last slice with positive mass
           before = __shfl(inc - mine, s_hit, kWave);
         }
-        if (solo && (held_lv != j || held_sl != s_hit)) {       // bring that slice back
-          load_slice(sh_chain[j], s_hit);
-          held_lv = j; held_sl = s_hit;
-        }
+        if (solo && (held_lv != j || held_sl != s_hit)) bring(j, s_hit);
         if (solo || (my_lv == j && my_sl == s_hit)) {
           slice_parts(S, level);
           // (unit, wave) part the crossing falls in: scan of the parts in vocabulary order (every wave alike)
@@ -535,7 +752,7 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
           const int u_hit = p_hit / kClWaves, w_hit = p_hit % kClWaves;
           if (wave == w_hit) {
             float w[8];
-            cl_weights(*row_p(u_hit), *row_q(u_hit), S, c, level, sh_invRf, w);
+            unit_weights(S, level, u_hit, w);
             const int e0 = (s_hit * UPT + u_hit) * kClUnit + tid * 8;
             float lsf = 0.f;                       // summed exactly as the parts were
             int my_last = -1;
@@ -577,8 +794,9 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
             P.accept_len[b] = depth;
             if (P.stop_node) P.stop_node[b] = cur;
           }
-          for (int i = depth + 1 + tid; i < P.out_stride; i += kClThreads)
-            P.out_tokens[static_cast<int64_t>(b) * P.out_stride + i] = -1;
+          // (wave 0 alone: it reads what it has stored itself; the token at `depth` is the drawn one)
+          for (int i = tid; wave == 0 && i < P.out_stride; i += kWave)
+            if (i != depth) P.out_tokens[static_cast<int64_t>(b) * P.out_stride + i] = i < depth ? sh_out[i] : -1;
         }
         return 0;
       }
@@ -594,9 +812,10 @@ __global__ __launch_bounds__(kClThreads) void accept_cluster_kernel(ClusterParam
     if (wave == 0)
       st_dev(P.msg + ((static_cast<size_t>(b) * 2 + ((lane >> 3) & 1)) * C * 2 + ((lane >> 2) & 1)) * 4 + (lane & 3),
             static_cast<unsigned long long>(kClAbort));
-    __syncthreads();
+    cl_sync();
     solo = true;
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no slice is on its way to memory that the workgroup gives back
 }
 
 __global__ __launch_bounds__(256) void cluster_zero_kernel(unsigned long long* __restrict__ words, int n) {
@@ -674,8 +893,12 @@ void launch_accept_cluster(const AcceptArgs& a, const ClusterPlan& plan, int pat
   }
   const size_t lds = static_cast<size_t>(plan.upt) * 2 * kClThreads * 16;
   static std::atomic<uint64_t> attr_done{0};
-  if (set_lds_once(&accept_cluster_kernel, static_cast<size_t>(kClMaxUpt) * 2 * kClThreads * 16, attr_done) != 0) return;
-  hipLaunchKernelGGL(accept_cluster_kernel, grid, dim3(kClThreads), lds, stream, P);
+  if (plan.upt == 4) {                            // (32 KB of rows: no attribute needed)
+    hipLaunchKernelGGL(accept_cluster_kernel<4>, grid, dim3(kClBlock), lds, stream, P);
+    return;
+  }
+  if (set_lds_once(&accept_cluster_kernel<0>, static_cast<size_t>(kClMaxUpt) * 2 * kClThreads * 16, attr_done) != 0) return;
+  hipLaunchKernelGGL(accept_cluster_kernel<0>, grid, dim3(kClBlock), lds, stream, P);
 }
 
 }  // namespace specv
