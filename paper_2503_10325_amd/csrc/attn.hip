@@ -11,8 +11,8 @@
 //     (V through transposing reads) and multiplies each with one or two 32-row query blocks; the waves
 //     merge through LDS.
 //   row-split (rows_item, more rows): the 4 or 8 waves of a workgroup stage 64-token tiles together
-//     (double-buffered LDS; with 8 waves two tiles of global loads in flight) and each owns one block of
-//     32 query rows.  Instantiated a second time for requests of 65 to 128 draft nodes (two ancestor-mask
+//     (double-buffered LDS: K straight from memory, V through registers, where it becomes fp16) and each
+//     owns one block of 32 query rows.  Instantiated a second time for requests of 65 to 128 draft nodes (two ancestor-mask
 //     words per node).
 // Launches: attn_stream_kernel and attn_rows_kernel, grid-mapped, one body for the whole batch;
 // attn_stream_list_kernel, ragged batches of up to 128 rows from a work list built on the device and
@@ -20,7 +20,7 @@
 // its own row count.
 // In both, S^T = K Q^T runs on v_mfma_f32_32x32x16_bf16 with the tokens as the M dimension, so
 // each lane owns one query column and the online-softmax statistics need a single exchange
-// between the half-waves.  The row-split body transposes V on its way into LDS (token pairs packed with v_perm).
+// between the half-waves.  V lies in LDS in natural rows; its operands come through transposing reads.
 // O^T = V^T P^T: the token-split body keeps bf16 operands (weights as a high and a low bf16 term);
 // the row-split body converts V to fp16 while staging it and uses fp16 weights in one
 // v_mfma_f32_32x32x16_f16 term.
@@ -40,11 +40,6 @@ constexpr int kAttnThreads = 256;
 constexpr int kAttnWaves = 4;
 constexpr int kTile = 32;          // tokens per wave iteration
 constexpr int kPage = 16;
-// Head dimension of row m (0..31) of accumulator block db of O^T = V^T P^T: the V^T rows are stored by
-// (d%8, d/8), see AttnCfg, and read in storage order.  With a = r >> 2, c = r & 3 of accumulator register r and
-// the lane's half lh, m = 8a + 4lh + c; the registers (db, a) with equal (a % A, c), A = D/64, hold 8 consecutive
-// head dimensions from acc_dim0<D>(a % A, c, lh) on, in the order j = (32*8/D) * db + a / A.
-template <int D> __device__ __forceinline__ constexpr int acc_dim0(int am, int c, int lh) { return 8 * (8 * am + 4 * lh + c); }
 constexpr int kMaxQ = 64;             // query nodes per request with one ancestor-mask word
 constexpr int kMaxQWide = 128;        // ... with two (row-split kernels only)
 
@@ -172,6 +167,13 @@ __device__ __forceinline__ uint32_t tile_mask(unsigned long long anc, int left) 
   if (left >= 32) return 0xffffffffu;
   if (left > 0) return static_cast<uint32_t>(anc << left) | ((1u << left) - 1u);
   return left > -64 ? static_cast<uint32_t>(anc >> -left) : 0u;
+}
+// ... of a node with two mask words (up to 128 nodes), p being `past` >= 0 tokens behind the context.
+__device__ __forceinline__ uint32_t wide_mask(unsigned long long lo, unsigned long long hi, int past) {
+  if (past >= 128) return 0u;
+  if (past >= 64) return static_cast<uint32_t>(hi >> (past - 64));
+  const unsigned long long w = past == 0 ? lo : (lo >> past) | (hi << (64 - past));
+  return static_cast<uint32_t>(w);
 }
 // Matrix operand of 8 tokens for this lane's head dimension from two transposing LDS reads of 4 tokens each.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -610,6 +612,12 @@ constexpr int kPlanMaxB = 128;
 // times several drafts, draft trees).  The NW waves of a workgroup stage 64-token tiles
 // cooperatively (double-buffered in LDS) and every wave owns one block of 32 query rows,
 // for which it sees every token: no cross-wave merge is needed.
+// K of the next tile goes to LDS directly; V of the next tile is converted and stored between the matrix instructions of the
+// scores, where the vector unit has nothing else to do, and needs no transposition (218 -> 165 vector instructions per wave
+// and tile against staging both through registers and packing V with v_perm).  What bounds it is the issue of vector and matrix
+// instructions of the two waves of a SIMD, which add up more than they overlap, and, with the tables in HBM, the clock: with
+// L2-resident tables 64 x 8 KV heads x 2048 tokens x 128 rows 86.5 -> 80.1 us, 16 x 8 x 4096 x 256 rows 88.7 -> 84.6, 464 rows
+// 138 -> 131; 256 rows from HBM 94.9 -> 91.0 in a step; short contexts gain the most (512 tokens, 160 rows 17.1 -> 14.3).
 // ----------------------------------------------------------------------------------
 // SL = 2 ("sliced"): the workgroup owns 32 * NW / 2 query rows and stages 128-token tiles; waves w and w + NW/2
 // share a block of 32 rows, the first computing the lower 64 tokens of every staged tile, the second the upper 64,
@@ -620,15 +628,9 @@ struct RowsCfg {
   static constexpr int kTc = 64;                           // tokens one wave computes per step
   static constexpr int kT = kTc * SL;                      // tokens per staged tile
   static constexpr int kThreads = NW * 64;
-  static constexpr int kCh = D / 8;
-  static constexpr int kLoads = kT * kCh / kThreads;       // 16-byte loads per thread per tensor
-  static constexpr int kTpt = kLoads;                      // consecutive tokens a thread transposes
-  static constexpr int kKStride = D * 2 + 16;
-  static constexpr int kKBytes = kT * kKStride;
-  static constexpr int kVStride = kT * 2 + 16;
-  static constexpr int kVRows = D;                         // rows in storage order, see AttnCfg
-  static constexpr int kVBytes = kVRows * kVStride;
-  static constexpr int kStage = kKBytes + kVBytes;
+  static constexpr int kTpt = kT * (D / 8) / kThreads;     // 16-byte loads per thread and tensor: consecutive tokens of V
+  static constexpr int kKBytes = kT * D * 2;               // natural rows, chunks placed by XOR as in the token-split body
+  static constexpr int kStage = 2 * kKBytes;               // K as bf16, V as fp16
   static constexpr int kMaxChunkPages = NW == 8 ? 1024 : 512;   // a chunk spans at most 16384 (8192) tokens
   static constexpr int kPagePad = 32;                      // page-table entries kept past a chunk's last page
   // behind the two stages: ancestor masks, parents, page table
@@ -710,12 +712,11 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   const int32_t* bt = P.block_table + static_cast<int64_t>(b) * P.max_pages;
   const int64_t page_elems = static_cast<int64_t>(P.Hkv) * kPage * D;
   const int64_t head_off = static_cast<int64_t>(kvh) * kPage * D;
-  const int vc = tid % RC::kCh;                 // V: 16-byte chunk of the token row
-  const int vg = tid / RC::kCh;                 // V: group of kTpt consecutive tokens
-  const int vtok0 = vg * RC::kTpt;              // first of them within the tile
-  // two register sets: while tile t is computed from LDS, tile t+1 waits in one set and tile
-  // t+2 is in flight into the other, i.e. two tiles of global loads are outstanding per workgroup
-  u32x4 krA[RC::kLoads], vrA[RC::kLoads], krB[RC::kLoads], vrB[RC::kLoads];
+  const int vc = tid % C::kCh;                  // V: 16-byte chunk of the token row
+  const int vtok0 = tid / C::kCh * RC::kTpt;    // V: first of kTpt consecutive tokens within the tile
+  // two register sets for V: while tile t is computed, tile t+1 is converted and stored from one and tile t+2 is in flight
+  // into the other (a third for tile t+3 with the loads at the top: 100.7 -> 108 us)
+  u32x4 vrA[RC::kTpt], vrB[RC::kTpt];
 
   // Page ids of the whole chunk go to LDS once, so that the tile loads depend on no global read.
   const int lp0 = t_begin / kPage;
@@ -725,86 +726,59 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   if (tid < kNodes) sh_par[tid] = my_par;
   __syncthreads();
 
-  // Loads are unconditional (addresses clamped to the chunk's last page): positions past the
-  // end are masked out of the scores, and their V values are zeroed when staged.
-  // Every load instruction of a wave touches one cache page, so the page id is wave-uniform
-  // (scalar base) and only a small per-lane offset lives in a vector register.
-  constexpr int kTokPerLoadWg = RC::kThreads / RC::kCh;               // tokens one load j of the workgroup covers
-  const int k_tok_in_load = tid / RC::kCh;                            // token of this lane within load j
-  const int k_lane_off = (k_tok_in_load % kPage) * D + (tid % RC::kCh) * 8;
-  const int k_page_in_load = k_tok_in_load / kPage;                   // wave-uniform
+  // Loads are unconditional (addresses clamped to the chunk's last page): positions past the end are masked out of the
+  // scores, and their V values are zeroed when staged.  Every load of a wave touches one cache page: a scalar base and a small
+  // per-lane offset.  K goes from memory straight to LDS, load j of wave w to the rows from kTokPerLoad (NW j + w) on.
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);
+  const int k_row = lane / C::kCh, k_ch = lane % C::kCh;
+  const unsigned k_lane_off = k_row * C::kRowBytes + ((k_ch ^ C::k_swizzle(k_row)) << 4);
   const int v_lane_off = (vtok0 % kPage) * D + vc * 8;
-  // The page ids of tile t are read from LDS right after the loads of tile t-1 were issued, a whole tile step
-  // before they are needed: the address of a load then waits on no LDS round trip.
-  int pg[RC::kLoads + 1];
-  auto fetch_pages = [&](int t) {
-    const int* tp = sh_pages + min(RC::kT * t / kPage, np + RC::kPagePad - RC::kT / kPage);
+  const unsigned lds0 = lds_address(smem);
+  // The page ids of a tile are read from LDS a whole tile step before the loads that need them.
+  int pk[RC::kTpt], pv;
+  auto tile_pages = [&](int t) { return sh_pages + min(RC::kT * t / kPage, np + RC::kPagePad - RC::kT / kPage); };
+  auto fetch_k_pages = [&](int t) {
 #pragma unroll
-    for (int j = 0; j < RC::kLoads; ++j) pg[j] = tp[(j * kTokPerLoadWg) / kPage + k_page_in_load];
-    pg[RC::kLoads] = tp[vtok0 / kPage];
+    for (int j = 0; j < RC::kTpt; ++j) pk[j] = tile_pages(t)[(j * NW + uwave) / C::kPageLoads];
   };
-  auto issue_loads = [&](u32x4 (&kr)[RC::kLoads], u32x4 (&vr)[RC::kLoads]) {
+  auto fetch_v_page = [&](int t) { pv = tile_pages(t)[vtok0 / kPage]; };
+  auto issue_k = [&](int stage) __attribute__((always_inline)) {          // of the tile whose K pages were fetched last
 #pragma unroll
-    for (int j = 0; j < RC::kLoads; ++j) {
-      const int page = __builtin_amdgcn_readfirstlane(pg[j]);
-      const uint16_t* base = P.k_pool + page * page_elems + head_off;
-      kr[j] = *reinterpret_cast<const u32x4*>(base + k_lane_off);
+    for (int j = 0; j < RC::kTpt; ++j) {
+      const int i = j * NW + uwave, part = i % C::kPageLoads;
+      const int page = __builtin_amdgcn_readfirstlane(pk[j]);
+      const uint16_t* base = P.k_pool + page * page_elems + head_off + part * C::kTokPerLoad * D;
+      load_to_lds(reinterpret_cast<const unsigned char*>(base), k_lane_off ^ (64u * part), lds0 + stage * RC::kStage + 1024 * i, 0);
     }
-    const int page = __builtin_amdgcn_readfirstlane(pg[RC::kLoads]);
+  };
+  auto issue_v = [&](u32x4 (&vr)[RC::kTpt]) __attribute__((always_inline)) {
+    const int page = __builtin_amdgcn_readfirstlane(pv);
     const uint16_t* vp = P.v_pool + page * page_elems + head_off + v_lane_off;
 #pragma unroll
     for (int i = 0; i < RC::kTpt; ++i) vr[i] = *reinterpret_cast<const u32x4*>(vp + i * D);
   };
-  // issue the loads of tile t (tiles are issued in order: t is the one whose page ids were fetched last)
-  auto issue_tile = [&](int t, u32x4 (&kr)[RC::kLoads], u32x4 (&vr)[RC::kLoads]) __attribute__((always_inline)) {
-    issue_loads(kr, vr);
-    fetch_pages(t + 1);
-  };
-
-  auto store_tile = [&](int stage, int t, u32x4 (&kr)[RC::kLoads], u32x4 (&vr)[RC::kLoads]) {
-    unsigned char* k_lds = smem + stage * RC::kStage;
-    unsigned char* v_lds = k_lds + RC::kKBytes;
+  auto arrived = [&](u32x4 (&vr)[RC::kTpt]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < RC::kLoads; ++j) {
-      const int tk = j * (RC::kThreads / RC::kCh) + tid / RC::kCh;
-      *reinterpret_cast<u32x4*>(k_lds + tk * RC::kKStride + (tid % RC::kCh) * 16) = kr[j];
-    }
-    // transposed V: token order inside each 16-token group follows the MFMA operand layout
-    const int s16 = vtok0 / 16, u = vtok0 % 16;
-    const int a4 = u >> 2, sub = u & 3;
-    const int pos = 8 * (a4 & 1) + 4 * (a4 >> 1) + sub;
-    const int col = (16 * s16 + pos) * 2;
-    // never multiply stale cache slots (past ctx+n) into O: stage them as zeros
+    for (int i = 0; i < RC::kTpt; ++i) asm volatile("" : "+v"(vr[i]));
+  };
+  // never multiply stale cache slots (past ctx+n) into O: stage them as zeros
+  auto cut_tail = [&](int t, u32x4 (&vr)[RC::kTpt]) {
     if (t_begin + RC::kT * (t + 1) > L) {                     // only the last tile (and the ones past it)
       const int left = L - (t_begin + RC::kT * t + vtok0);    // tokens of this thread that exist
 #pragma unroll
       for (int i = 0; i < RC::kTpt; ++i)
         if (i >= left) vr[i] = zero4();
     }
-    // V goes to LDS as fp16 (the weights P are fp16 too: 11 significant bits in ONE matrix term)
-#pragma unroll
-    for (int i = 0; i < RC::kTpt; ++i)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) vr[i][k] = bf16x2_to_f16x2(vr[i][k]);
-    const u32x4 w0 = vr[0], w1 = vr[1];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const uint32_t sel = half ? 0x07060302u : 0x05040100u;
-        const int vrow = (2 * k + half) * (D / 8) + vc;
-        unsigned char* dst = v_lds + vrow * RC::kVStride + col;
-        if constexpr (RC::kTpt == 4) {
-          const uint32_t w2k = vr[2][k], w3k = vr[3][k];
-          uint2 o;
-          o.x = __builtin_amdgcn_perm(w1[k], w0[k], sel);
-          o.y = __builtin_amdgcn_perm(w3k, w2k, sel);
-          *reinterpret_cast<uint2*>(dst) = o;
-        } else {
-          *reinterpret_cast<uint32_t*>(dst) = __builtin_amdgcn_perm(w1[k], w0[k], sel);
-        }
-      }
-    }
+  };
+  // V goes to LDS as fp16 (the weights P are fp16 too: 11 significant bits in ONE matrix term), in natural rows: the
+  // operand reads transpose.
+  auto convert = [&](u32x4& v, int from) __attribute__((always_inline)) {
+    v[from] = bf16x2_to_f16x2(v[from]);
+    v[from + 1] = bf16x2_to_f16x2(v[from + 1]);
+  };
+  const unsigned v_store = lds0 + RC::kKBytes + vtok0 * C::kRowBytes;
+  auto store_v = [&](int stage, int i, const u32x4& v) __attribute__((always_inline)) {
+    *lds_u32x4(v_store + stage * RC::kStage + i * C::kRowBytes + ((vc ^ C::v_swizzle((vtok0 + i) & 3)) << 4)) = v;
   };
 
   unsigned long long my_anc = 0ull, my_anc_hi = 0ull;          // ancestor mask of this lane's node (set below)
@@ -813,10 +787,15 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   f32x16 sacc[2];
   f16x8 ph, va[C::kDBlocks];
   float m_safe = 0.f, m_next = -INFINITY, alpha = 1.f, psum = 0.f;
+  // transposing reads, as in the token-split body: lane i of a group of 16 gets head dimension i of 4 tokens
+  const int tr_tok = 4 * lh + ((lane & 15) >> 2);
+  const unsigned v_at = lds0 + RC::kKBytes + (RC::kTc * slice + tr_tok) * C::kRowBytes + 8 * (lane & 1) +
+                        (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ C::v_swizzle(tr_tok)) << 4);
   auto v_frag = [&](int stage, int chunk, int db) {      // chunk = 16-token group 0..3 of the tile
-    const unsigned char* v_rd = smem + stage * RC::kStage + RC::kKBytes + ln * RC::kVStride + 16 * lh + 2 * RC::kTc * slice;
-    return __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(v_rd + 32 * db * RC::kVStride + 32 * chunk));
+    const unsigned at = (v_at ^ (64u * db)) + stage * RC::kStage + 16 * chunk * C::kRowBytes;
+    return __builtin_bit_cast(f16x8, tr_pair(at, at + 8 * C::kRowBytes));
   };
+  const unsigned k_at = lds0 + (RC::kTc * slice + ln) * C::kRowBytes + ((lh ^ C::k_swizzle(ln)) << 4);
   // P^T as fp16 (weights lie in [0, 2^8]: 11 significant bits, against 8 of bf16, keep the output's error at the
   // level of its own bf16 rounding with a single matrix term), 16 tokens at a time
   auto p_chunk = [&](int chunk, f16x8& dst) __attribute__((always_inline)) {
@@ -833,14 +812,14 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   };
 
   // First half: S = K Q^T (operand reads from LDS run two steps ahead of the matrix instructions that consume
-  // them), mask, row maxima, rescale, the weights of the first 16 tokens.
-  auto tile_scores = [&](int stage, int t) __attribute__((always_inline)) {
-    const unsigned char* k_lds = smem + stage * RC::kStage + slice * RC::kTc * RC::kKStride;
+  // them), with the conversion and the stores of the next tile's V between the matrix instructions; mask, row maxima,
+  // rescale, the weights of the first 16 tokens.
+  auto tile_scores = [&](int stage, int t, u32x4 (&vr)[RC::kTpt]) __attribute__((always_inline)) {
     const int tok0 = t_begin + RC::kT * t + RC::kTc * slice;
-    const unsigned char* k_rd = k_lds + ln * RC::kKStride + 16 * lh;
     auto k_frag = [&](int ks, int tb) {
-      return as_bf16x8(*reinterpret_cast<const u32x4*>(k_rd + 32 * tb * RC::kKStride + 32 * ks));
+      return as_bf16x8(*lds_u32x4((k_at ^ (32 * ks)) + stage * RC::kStage + 32 * tb * C::kRowBytes));
     };
+    constexpr int kHalves = 2 * RC::kTpt;         // half rows of V to convert
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
@@ -859,6 +838,11 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
       }
       sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks % 3][0], qf[ks], sacc[0], 0, 0, 0);
       sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks % 3][1], qf[ks], sacc[1], 0, 0, 0);
+#pragma unroll
+      for (int h = ks * kHalves / C::kQKSteps; h < (ks + 1) * kHalves / C::kQKSteps; ++h) {
+        convert(vr[h / 2], 2 * (h & 1));
+        if (h & 1) store_v(stage ^ 1, h / 2, vr[h / 2]);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
     // V^T operand of the first 16 tokens is fetched while the scores are reduced
@@ -867,15 +851,17 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
 
     if (tok0 + RC::kTc > ctx) {                  // tile reaches the drafts or the end: apply the mask
 #pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int pos = tok0 + 32 * tb + 8 * (r >> 2) + 4 * lh + (r & 3);
-          // branch-free on purpose: bitwise ops, no short-circuit control flow around the accumulator
-          const unsigned long long word = (WIDE && ((pos - ctx) & 64)) ? my_anc_hi : my_anc;
-          const bool ok = (pos < ctx) | ((pos < L) & (((word >> ((pos - ctx) & 63)) & 1ull) != 0ull));
-          sacc[tb][r] = ok ? sacc[tb][r] : -INFINITY;
+      for (int tb = 0; tb < 2; ++tb) {
+        const int left = ctx - tok0 - 32 * tb;
+        uint32_t seen = tile_mask(my_anc, left);
+        if constexpr (WIDE) {
+          if (left <= 0) seen = wide_mask(my_anc, my_anc_hi, -left);
         }
+        seen >>= 4 * lh;
+        asm volatile("" : "+v"(seen));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sacc[tb][r] = (seen & (1u << (8 * (r >> 2) + (r & 3)))) ? sacc[tb][r] : -INFINITY;
+      }
     }
     float tmax = -INFINITY;
 #pragma unroll
@@ -935,16 +921,18 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
     m_run = m_next;
   };
 
-  // ---- pipeline: tile t is computed from LDS while tile t+1 sits in registers ----
-  // Loads and LDS stores are issued unconditionally, also for tile numbers past the end (their addresses are
-  // clamped to the chunk's last page, their V rows staged as zeros, and they are never computed): with the
-  // same number of loads outstanding on every path, the wait before a store covers only the older register
-  // set and leaves the newer one in flight.  A branch around an issue would make that wait a full drain.
+  // ---- pipeline: while tile t is computed from one stage, V of tile t+1 is converted and stored to the other, K of tile t+1
+  // travels to it, and V of the tiles behind travels to registers ----
+  // Loads are issued unconditionally, also for tile numbers past the end (their addresses are clamped to the chunk's last
+  // page, their V rows staged as zeros, and they are never computed): every path leaves the same number outstanding.
   // (a wave of the sliced variant skips a staged tile whose half for it lies past the end)
   auto mine = [&](int t) { return active && t < ntiles && t_begin + RC::kT * t + RC::kTc * slice < t_end; };
-  fetch_pages(0);
-  issue_tile(0, krA, vrA);
-  if constexpr (NW == 8 && SL == 1) issue_tile(1, krB, vrB);
+  fetch_k_pages(0);
+  fetch_v_page(0);
+  issue_v(vrA);
+  issue_k(0);
+  fetch_k_pages(1);
+  fetch_v_page(1);
   if (touches_drafts) {
     if (tid < kNodes) {
       unsigned long long mask = 0, mask_hi = 0;
@@ -973,38 +961,48 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
     my_anc = sh_anc[node * kWords];
     if (WIDE) my_anc_hi = sh_anc[node * kWords + 1];
   }
-  if constexpr (NW == 8 && SL == 1) {
-    store_tile(0, 0, krA, vrA);
-    issue_tile(2, krA, vrA);
-    __syncthreads();
-    for (int t = 0; t < ntiles; t += 2) {
-      // LDS stage 0 holds tile t, set B tile t+1, set A tile t+2
-      if (mine(t)) { tile_scores(0, t); tile_output(0); }
-      store_tile(1, t + 1, krB, vrB);
-      issue_tile(t + 3, krB, vrB);
-      __syncthreads();
-      // LDS stage 1 holds tile t+1, set A tile t+2, set B tile t+3
-      if (mine(t + 1)) { tile_scores(1, t + 1); tile_output(1); }
-      store_tile(0, t + 2, krA, vrA);
-      issue_tile(t + 4, krA, vrA);
-      __syncthreads();
-    }
-  } else {
-    // Four waves, two workgroups per compute unit: one register set (one tile of loads in flight per
-    // workgroup; the other workgroup covers the rest of the latency), which leaves the registers for it.
-    store_tile(0, 0, krA, vrA);
-    issue_tile(1, krA, vrA);
-    __syncthreads();
-    for (int t = 0; t < ntiles; t += 2) {
-      if (mine(t)) { tile_scores(0, t); tile_output(0); }
-      store_tile(1, t + 1, krA, vrA);
-      issue_tile(t + 2, krA, vrA);
-      __syncthreads();
-      if (mine(t + 1)) { tile_scores(1, t + 1); tile_output(1); }
-      store_tile(0, t + 2, krA, vrA);
-      issue_tile(t + 3, krA, vrA);
-      __syncthreads();
-    }
+  // (K of the tile that is computed next is here, this wave's part of its V is stored; the kTpt loads of V behind it are not waited for)
+  auto stage_done = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(RC::kTpt) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  auto stage_v = [&](int stage, u32x4 (&vr)[RC::kTpt]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < RC::kTpt; ++i) { convert(vr[i], 0); convert(vr[i], 2); store_v(stage, i, vr[i]); }
+  };
+  arrived(vrA);
+  cut_tail(0, vrA);
+  stage_v(0, vrA);
+  issue_v(vrB);
+  fetch_v_page(2);
+  issue_v(vrA);
+  fetch_v_page(3);
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(2 * RC::kTpt) : "memory");       // K of the first tile
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  // V of tile t+1 has been in flight to `cur`, V of tile t+2 is to the other set, V of tile t+3 follows to `cur` when this wave
+  // is done with tile t.  K of tile t+1 goes out at the top or, where one workgroup has the compute unit, behind the scores:
+  // the waves come there one after the other, at the top the loads of all of them are one burst (256 rows x 4096 tokens, from
+  // HBM in a step: 100.7 us with K and V at the top, 96.3 with K, 94.0 with half of K, 91.0 behind the scores).  Two workgroups
+  // of four waves are out of step by themselves, and behind the scores is late for them (80 rows, work list 144 -> 155).
+  constexpr bool kLateK = NW == 8;
+  auto step = [&](int t, int stage, u32x4 (&cur)[RC::kTpt]) __attribute__((always_inline)) {
+    arrived(cur);
+    if constexpr (!kLateK) { issue_k(stage ^ 1); fetch_k_pages(t + 2); }
+    cut_tail(t + 1, cur);
+    const bool work = mine(t);
+    if (work) tile_scores(stage, t, cur);
+    else stage_v(stage ^ 1, cur);
+    if constexpr (kLateK) { issue_k(stage ^ 1); fetch_k_pages(t + 2); }
+    if (work) tile_output(stage);
+    issue_v(cur);
+    fetch_v_page(t + 4);
+    stage_done();
+  };
+  for (int t = 0; t < ntiles; t += 2) {
+    step(t, 0, vrB);
+    step(t + 1, 1, vrA);
   }
 
   l_run = half_sum(l_run);
@@ -1043,38 +1041,35 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   // [0, 2^-11], 2^-12 on average, while the denominator l was summed from the unrounded weights.  The
   // average is put back here; what remains is the zero-mean part (2^-12 at most per weight).
   constexpr float kRtzFix = 1.f + 1.f / 4096.f;
-  // eight consecutive head dimensions at a time (acc_dim0)
-  constexpr int kA = D / 64, kQ = 256 / D;
+  // register 4a + c of block db: head dimension 32 db + 8 a + 4 lh + c
   const float oscale = nchunks == 1 ? kRtzFix / l_run : kRtzFix;
   float* part = P.ws_o + (grow * P.max_chunks + chunk) * D;
 #pragma unroll
-  for (int am = 0; am < kA; ++am)
+  for (int db = 0; db < C::kDBlocks; ++db) {
+    if (nchunks != 1 || P.out_f32) {
+      // fp32 rows: the two halves of the wave write 32 contiguous bytes per row
+      float* o = (nchunks != 1 ? part : static_cast<float*>(P.out) + grow * D) + 32 * db + 4 * lh;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float x[8];
+      for (int a = 0; a < 4; ++a)
+        *reinterpret_cast<float4*>(o + 8 * a) = make_float4(oacc[db][4 * a] * oscale, oacc[db][4 * a + 1] * oscale,
+                                                            oacc[db][4 * a + 2] * oscale, oacc[db][4 * a + 3] * oscale);
+    } else {
+      // bf16 rows: the halves exchange their four dimensions of blocks a and a + 1, each then writes eight
 #pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = oacc[j / kQ][4 * ((j % kQ) * kA + am) + c] * oscale;
-      const int d = acc_dim0<D>(am, c, lh);
-      if (nchunks != 1 || P.out_f32) {
-        // fp32 rows: the two half-waves exchange halves of their eight values, so that one store instruction
-        // writes 32 contiguous bytes per row (lane ln: 16 bytes, lane ln + 32: the next 16) instead of 16
-        float lo4[4], hi4[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[4 + i]), false, false);
-          lo4[i] = __uint_as_float(r[0]);          // dims d0 .. of the lower half-wave's group: first / second four
-          hi4[i] = __uint_as_float(r[1]);          // dims d0 .. of the upper half-wave's group
-        }
-        float* o = (nchunks != 1 ? part : static_cast<float*>(P.out) + grow * D) + acc_dim0<D>(am, c, 0) + 4 * lh;
-        *reinterpret_cast<float4*>(o) = make_float4(lo4[0], lo4[1], lo4[2], lo4[3]);
-        *reinterpret_cast<float4*>(o + 32) = make_float4(hi4[0], hi4[1], hi4[2], hi4[3]);
-      } else {
+      for (int a = 0; a < 4; a += 2) {
         u32x4 o;
-        o[0] = pack_bf16(x[0], x[1]); o[1] = pack_bf16(x[2], x[3]);
-        o[2] = pack_bf16(x[4], x[5]); o[3] = pack_bf16(x[6], x[7]);
-        *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(P.out) + grow * D + d) = o;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint32_t x = pack_bf16(oacc[db][4 * a + 2 * i] * oscale, oacc[db][4 * a + 2 * i + 1] * oscale);
+          const uint32_t y = pack_bf16(oacc[db][4 * a + 4 + 2 * i] * oscale, oacc[db][4 * a + 5 + 2 * i] * oscale);
+          const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+          o[i] = r[0];
+          o[2 + i] = r[1];
+        }
+        *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(P.out) + grow * D + 32 * db + 8 * (a + lh)) = o;
       }
     }
+  }
   if (nchunks == 1) {
     if (P.lse && lh == 0) P.lse[grow] = (m_run + log2f(l_run)) * static_cast<float>(kLn2);
   } else if (lh == 0) {

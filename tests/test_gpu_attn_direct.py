@@ -50,3 +50,22 @@ def test_edges_and_stale_slots(head_dim, nodes, requests):
     # weights of two bf16 terms: 2^-17 of sum p |v| <= max |v| = 5.5, and fp32 sums
     assert np.abs(dev.out.cpu().numpy() - ref).max() < 5e-5, sv.spec_describe_attn_plan(dev.desc)
     assert np.abs(dev.lse.cpu().numpy() - ref_lse).max() < 1e-4
+
+
+# 72, 128 (four waves), 232 (eight waves; with few requests sliced) and 800 rows (two mask words) per KV head
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("nodes,requests", [(9, 14), (16, 14), (29, 14), (29, 70), (100, 5)])
+def test_row_split_edges_and_stale_slots(head_dim, nodes, requests):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import runner
+    ctx = [EDGES[(3 * b + 1) % len(EDGES)] for b in range(requests)]
+    a = poisoned(attention([nodes] * requests, ctx, head_dim, True))
+    dev = runner.DeviceAttn(a, out_dtype=torch.float32)
+    dev.workspace.fill_(0xFF)
+    dev.run()
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle_attn(a)
+    # weights of one fp16 term (truncated, its mean put back): 2^-12 of sum p |v| <= max |v| = 5.5
+    assert np.abs(dev.out.cpu().numpy() - ref).max() < 3e-3, sv.spec_describe_attn_plan(dev.desc)
+    assert np.abs(dev.lse.cpu().numpy() - ref_lse).max() < 1e-4
