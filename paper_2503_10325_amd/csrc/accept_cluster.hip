@@ -682,7 +682,8 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
           }
           if (owner && P.dbg_ratio && wave == 0)
             P.dbg_ratio[o + ch] = static_cast<float>(qx > 0.0 ? rx / qx : (rx > 0.0 ? INFINITY : 0.0));
-          if (static_cast<double>(sh_u[ch]) * qx < rx) { accepted = ch; break; }      // u < r(x) / q(x)
+          // u < r(x) / q(x); q is 0, or NaN where the draft row is no distribution: accepted if r(x) > 0, as on the other paths
+          if (qx > 0.0 ? static_cast<double>(sh_u[ch]) * qx < rx : rx > 0.0) { accepted = ch; break; }
           // rejected: mass of max(0, r - q)
           const int sibling = kids ? __ffsll(static_cast<long long>(kids)) - 1 : (kids_hi ? 63 + __ffsll(static_cast<long long>(kids_hi)) : -1);
           const double mass = sum_round(level + 1, sibling);
