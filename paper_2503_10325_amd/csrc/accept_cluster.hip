@@ -421,7 +421,8 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
     if (held < 0) {
       const float m = lane == 0 ? sl_mp : sl_mq, M = lane == 0 ? S.mp : S.mq;
       const double iz = lane == 0 ? S.izp : S.izq;
-      const float f = m == -INFINITY ? 0.f : static_cast<float>(cl_exp2(static_cast<double>(m - M) * static_cast<double>(c)) * iz);
+      // (a row that is -inf throughout is no distribution: its probabilities are NaN, which leaves no residual mass, not 0)
+      const float f = m == -INFINITY && M != m ? 0.f : static_cast<float>(cl_exp2(static_cast<double>(m - M) * static_cast<double>(c)) * iz);
       const float fp = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), 0));
       const float fq = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), 1));
 #pragma unroll

@@ -69,3 +69,22 @@ def test_chain_accepts(vocab, path):
     assert (ref["accept_len"] >= 1).all()
     bad, ties, _ = compare_accept(got, ref, ai.st.n)
     assert not bad and ties <= 1
+
+
+@pytest.mark.parametrize("vocab,tuning", CLUSTERS + WALKS)
+def test_rejected_sibling_leaves_the_target_distribution(vocab, tuning):
+    """The root's first child holds a token without target mass; its siblings are tested against the same distribution."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cfg = W.scaled(W.CONFIGS["c2_tree_llama3_8b"], batch=6, vocab=vocab, draft=("tree", (3, 2), 9))
+    ai, target, draft, tokens = spoiled(cfg, seed=5)
+    off = ai.st.node_offsets
+    for b in range(cfg.batch):
+        row = int(off[b]) + b
+        tokens[off[b]] = np.argmin(W.bf16_bits_to_f32(target[row]))       # (no sibling holds it)
+        target[row, tokens[off[b]]] = NEG_INF
+    got, ref = run(cfg, ai, target, draft, tokens, tuning)
+    assert (ref["accept_len"] >= 1).all() and np.isinf(ref["ratio"][off[:-1] + 1]).all()
+    bad, ties, _ = compare_accept(got, ref, ai.st.n)
+    assert not bad and ties <= 1
+    assert visited_pattern_agrees(got, ref, off)
