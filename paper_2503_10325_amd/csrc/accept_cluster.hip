@@ -212,9 +212,11 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
   auto issue_rows = [&](const uint16_t* tp, const uint16_t* qp, int sl) {       // (qp may be null: no child)
     if (!data) return;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the slots have been read
+    int t = tid;
+    asm volatile("" : "+v"(t));                            // (offsets are worked out here, see msg_at)
 #pragma unroll
     for (int u = 0; u < UPT; ++u) {
-      const int e = (sl * UPT + u) * kClUnit + tid * 8;
+      const int e = (sl * UPT + u) * kClUnit + t * 8;
       const unsigned off = e < V ? 2u * e : 0u;   // (V is a multiple of 8; chunks past the end are overwritten in settle)
       cl_load_to_lds(tp, off, rows_at + u * kClThreads * 16);
       if (qp) cl_load_to_lds(qp, off, rows_at + (UPT + u) * kClThreads * 16);
