@@ -590,6 +590,8 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
         const int node = chain_node(win, my_lv);
         float mp = -INFINITY, mq = -INFINITY;
         double zp = 0.0, zq = 0.0;
+        // (A later window begins at the child that was fetched ahead last, which waited for the guess before it: what is on its
+        // way is this window's, and where this workgroup's level does not exist below that child nothing is.)
         const bool there = guard == 0 ? early : next_start == cur;     // (on its way or here)
         if (node >= -1) {
           if (there) settle(sh_fc[node + 1] >= 0, my_sl);

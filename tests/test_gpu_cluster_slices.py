@@ -68,3 +68,35 @@ def test_slices_in_registers(vocab, levels):
     for key in ("accept_len", "out_tokens", "stop_node"):
         assert np.array_equal(got[-1][key], got[0][key]), key
     assert np.array_equal(got[-1]["ratio"], got[0]["ratio"], equal_nan=True)
+
+
+# first-child chains that end inside a window, next to siblings whose chains go on: leaf, leaf, chain of three; chain of two, leaf,
+# chain of four; three leaves below a node below a leaf's sibling; no node
+SHORT = [[-1, -1, -1, 2, 3], [-1, 0, -1, -1, 3, 4, 5], [-1, -1, 1, 1, 1, 4, 5, 6, 6, 8], [], [-1, -1, 0, 0, 1, 3, 5, 5, 7, 4]]
+
+
+@pytest.mark.parametrize("levels", [2, 3, 4])
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_chains_shorter_than_the_window(levels, seed):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import runner
+    n = np.array([len(p) for p in SHORT], dtype=np.int32)
+    st = W.DraftStructure(n, np.concatenate([[0], np.cumsum(n)]).astype(np.int32), np.concatenate(SHORT).astype(np.int32),
+                          np.zeros(len(SHORT), dtype=np.int32))
+    cfg = W.scaled(W.CONFIGS["c2_tree_llama3_8b"], batch=len(SHORT), vocab=65536)
+    ai = W.make_accept_inputs(cfg, seed=seed, st=st)
+    draft = ai.draft_q.copy()
+    rng = np.random.default_rng(seed)
+    for q in range(0, len(draft), 2):             # every other draft row has nothing to do with the target
+        draft[q] = rng.permutation(draft[q])
+    ref = oracle.accept(st.node_offsets, st.parent, ai.draft_tokens, ai.target_logits, draft, ai.q_row, ai.u_accept, ai.u_resample,
+                        temperature=cfg.temperature)
+    dev = runner.DeviceAccept(st, ai.target_logits, draft, ai.q_row, ai.draft_tokens, ai.u_accept, ai.u_resample,
+                              temperature=cfg.temperature)
+    dev.workspace.fill_(0xFF)
+    dev.run(tuning=sv.SpecAcceptTuning(path=2, levels=levels, slices=8))
+    got = dev.results()
+    bad, ties, _ = compare_accept(got, ref, n)
+    assert not bad and ties <= 1
+    assert ratio_err(got["ratio"], ref["ratio"]) < 5e-6 or ties
