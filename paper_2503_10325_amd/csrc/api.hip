@@ -94,7 +94,7 @@ int32_t spec_verify_attn(const spec_attn_desc* desc, const void* q, const void* 
     return need <= 256 || (workspace && workspace_bytes >= need);
   };
   if (!fits()) {
-    plan = make_attn_plan(a, false);
+    plan = make_attn_plan(a, true);
     if (!fits()) return SPEC_ERR_WORKSPACE;
   }
   a.q = q; a.k_pool = k_pool; a.v_pool = v_pool; a.block_table = block_table; a.ctx_len = ctx_len;

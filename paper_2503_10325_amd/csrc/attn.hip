@@ -1334,9 +1334,11 @@ constexpr int kListTau = 32;
 constexpr int kListTauRows = 42;
 // Most chunks the work list cuts a request into: the longest one the block table can hold, in items of kListTau units for up
 // to 32 rows.  More rows count twice and four times the waves they take, at 44: an upper bound, which sizes the workspace.
-static int list_max_chunks(int64_t max_tok, int max_rows) {
+// least: ... for a workspace that does not hold that many, as one that was sized without a hint (chunks of up to 5120 tokens)
+// may not: items of up to 44 units (5632 tokens).  The kernels lengthen the items of a request that is cut into more.
+static int list_max_chunks(int64_t max_tok, int max_rows, bool least) {
   const int64_t tiles = (max_tok + kTile - 1) / kTile;
-  const int64_t per_chunk = max_rows <= 32 ? 4 * kListTau : (max_rows <= 64 ? 88 : 44);
+  const int64_t per_chunk = max_rows <= 32 ? (least ? 4 * 44 : 4 * kListTau) : (max_rows <= 64 ? 88 : 44);
   const int64_t mc = (tiles + per_chunk - 1) / per_chunk;
   return static_cast<int>(mc < 1 ? 1 : (mc > kListMaxChunks ? kListMaxChunks : mc));
 }
@@ -1344,7 +1346,7 @@ static int list_max_chunks(int64_t max_tok, int max_rows) {
 // those are at most sixteen workgroups per compute unit, or two per (request, KV head) pair.
 static int little_room(int64_t pairs) { return std::max<int>(2, static_cast<int>(4096 / std::max<int64_t>(pairs, 1))); }
 
-AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
+AttnPlan make_attn_plan(const AttnArgs& a, bool small_workspace) {
   AttnPlan p;
   p.tau = 0;
   p.waves8 = 0;
@@ -1360,15 +1362,15 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   // a wave can stream at full load and left such batches to a few workgroups (5 requests x 4 KV heads, 777 to 3001
   // tokens: 20 of 512 workgroups, 26.7 us; 13.2 us cut into 512-token chunks).  The list serves them all the same where
   // a wide block table (allocated for the longest context a model allows) would ask for more chunks than there is room
-  // for, and where the caller's workspace holds the list's partial results but not these (little_ok).
-  const int list_chunks = list_max_chunks(max_tok, max_rows);
+  // for, and where the caller's workspace holds the list's partial results but not these (small_workspace).
+  const int list_chunks = list_max_chunks(max_tok, max_rows, small_workspace);
   const int64_t pairs = static_cast<int64_t>(a.B) * a.Hkv;
   const int room = little_room(pairs);
   // Batches of up to 128 pairs of request and KV head go further (chunks below 1792), where the list has too few items for its
   // 512 workgroups: 4 requests x 16 KV heads of 1174 to 3487 tokens 43 -> 22 us, 8 x 4 of 6000 to 14600 65 -> 48, 6 x 16 of 1200 to
   // 5700 54 -> 40, 32 x 4 of 1000 to 7800 70 -> 66; at chunks above 2000 the list is even (8 x 8 of 6000 to 14600 78 and 81) or ahead.
   const int64_t little_tokens = static_cast<int64_t>(256) * (pairs <= 128 ? 1792 : 1024);
-  const bool little = little_ok && a.kv_hint > 0 && a.kv_hint * a.Hkv < little_tokens && list_chunks <= room;
+  const bool little = !small_workspace && a.kv_hint > 0 && a.kv_hint * a.Hkv < little_tokens && list_chunks <= room;
   // Up to 64 query rows per KV head the token-split body streams as fast as memory delivers; beyond, its
   // waves (one per 32-row block, each staging every tile for itself) are bound by their own staging and the
   // row-split body, whose waves share each staged tile, is ahead on batches of like lengths (96 rows per KV
@@ -1447,7 +1449,7 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok) {
   if (jobs_knob > 0) tau = 0;
   if (tau > 0) {
     p.tau = tau;
-    p.max_chunks = list_max_chunks(max_tok, max_rows);
+    p.max_chunks = list_chunks;
   } else if (listable && ragged) {
     // A table much wider than the requests - it would launch four times the workgroups that the hint's tokens and one
     // partial chunk per request make, or it is wider than all tokens together are long: the workgroups without a chunk go

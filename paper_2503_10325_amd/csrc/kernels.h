@@ -170,8 +170,9 @@ struct AttnPlan {
   int wide_table;     // kind 0, grid-mapped: the block table holds many more chunks than there are tokens for
   int wide;           // more than 64 query nodes per request: kernels with two ancestor-mask words per node
 };
-// little_ok false: not the launch for little work, whose partial results can need more workspace than the work list's.
-AttnPlan make_attn_plan(const AttnArgs& a, bool little_ok = true);
+// small_workspace: for a workspace that does not hold this plan's partial results: not the launch for little work, which can need
+// more than the work list, and the work list with the fewest chunks that it has always been served with.
+AttnPlan make_attn_plan(const AttnArgs& a, bool small_workspace = false);
 size_t attn_workspace_bytes(const AttnArgs& a, const AttnPlan& plan);
 const char* attn_plan_name(const AttnPlan& plan);
 int launch_attn(const AttnArgs& a, const AttnPlan& plan, hipStream_t stream);   // 0 or a negative spec_status

@@ -1,10 +1,13 @@
 """Launch plan of spec_verify_attn for ragged batches with little work: what it asks for follows the tokens, not the width
 of the block table (a serving engine allocates that for the longest context its model allows).  Host calls only."""
+import ctypes
 import os
 
 import pytest
 
 from paper_2503_10325_amd import binding as sv
+
+SPEC_ERR_WORKSPACE, SPEC_ERR_LAUNCH = -4, -6
 
 pytestmark = pytest.mark.skipif(not os.path.exists(sv.LIB_PATH), reason="libspecverify.so not built")
 
@@ -54,3 +57,31 @@ def test_short_requests_of_batches_with_many_pairs_stay_whole(batch, heads, max_
     desc = sv.make_attn_desc(batch=batch, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=128, total_q=batch * max_q,
                              max_q_per_req=max_q, max_pages_per_req=pages, total_kv_tokens_hint=hint)
     assert f"at most {chunks} per request" in sv.spec_describe_attn_plan(desc), sv.spec_describe_attn_plan(desc)
+
+
+def status_of_a_call(desc, workspace_bytes):
+    """Status of spec_verify_attn with pointers to nothing: without a GPU a call that is not refused ends with the launch."""
+    p = ctypes.c_void_p(4096)
+    return sv.lib().spec_verify_attn(ctypes.byref(desc), p, p, p, p, p, p, None, p, None, p, workspace_bytes, None)
+
+
+@pytest.mark.parametrize("batch,heads,total_q,max_q,pages,hints", [
+    (109, (7, 1), 33, 2, 1568, (2176346,)),             # 14 rows, chunks of 5120 tokens without a hint, 4096 in the list
+    (64, (64, 8), 200, 4, 1000, (300000, 500000, 850000)),
+    (64, (32, 8), 400, 8, 1024, (300000, 850000)),
+    (16, (8, 8), 100, 16, 4000, (600000, 850000)),
+    (128, (32, 32), 500, 6, 2048, (100000, 3500000)),
+    (64, (64, 8), 400, 8, 1000, (300000, 850000)),      # 64 rows
+])
+def test_a_workspace_sized_without_a_hint_serves_the_work_list(batch, heads, total_q, max_q, pages, hints):
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the pointers of these calls are not to be launched with")
+    kw = dict(batch=batch, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=128, total_q=total_q, max_q_per_req=max_q,
+              max_pages_per_req=pages)
+    unknown = sv.spec_verify_attn_workspace_size(sv.make_attn_desc(total_kv_tokens_hint=0, **kw))
+    for hint in hints:
+        desc = sv.make_attn_desc(total_kv_tokens_hint=hint, **kw)
+        assert "list" in sv.spec_describe_attn_plan(desc)
+        assert status_of_a_call(desc, unknown) == SPEC_ERR_LAUNCH, (hint, unknown, sv.spec_verify_attn_workspace_size(desc))
+        assert status_of_a_call(desc, 256) == SPEC_ERR_WORKSPACE

@@ -172,3 +172,22 @@ def test_work_list_most_chunks(head_dim, nodes, longest):
         pytest.skip("no GPU")
     plan = listed(attention([nodes, 2, nodes], [longest, 100, 3000], head_dim, False))
     assert "at most 16 per request" in plan
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_work_list_in_a_workspace_sized_without_a_hint(head_dim):
+    """32 rows per KV head, a table for 65536 tokens: the list has up to 16 chunks of 4096, the workspace holds the results of 13."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import runner
+    a = widened(attention([4, 2, 4], [60000, 100, 5600], head_dim, False, kv_heads=8), 4096)
+    need = runner.DeviceAttn(a, out_dtype=torch.float32, kv_hint=0).workspace.numel()
+    dev = runner.DeviceAttn(a, out_dtype=torch.float32, kv_hint=3 * 52000)
+    assert "list" in sv.spec_describe_attn_plan(dev.desc) and dev.workspace.numel() > need
+    # (held in a larger block whose other bytes have to stay as they are)
+    block = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+    dev.workspace = block[:need]
+    dev.run()
+    torch.cuda.synchronize()
+    assert (block[need:] == 0xFF).all()
+    check(a, dev.out.cpu().numpy(), dev.lse.cpu().numpy())
