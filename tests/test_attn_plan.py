@@ -26,10 +26,10 @@ def test_wide_block_tables_do_not_scale_the_launch(batch, heads, total_q, max_q,
     desc = sv.make_attn_desc(total_kv_tokens_hint=hint, **kw)
     plan, need = sv.spec_describe_attn_plan(desc), sv.spec_verify_attn_workspace_size(desc)
     chunks = int(plan.split("at most ")[1].split()[0])
-    # the work list cuts a request into at most 16 chunks, of at most 44 tiles per wave
+    # the work list cuts a request into at most 16 chunks, of 44 tiles per wave (32 for up to 32 rows) and more
     rows = max_q * heads[0] // heads[1]
     tiles = pages * 16 // 32 // (4 if rows <= 32 else 2 if rows <= 64 else 1)
-    assert chunks <= min(16, -(-tiles // 44)), plan
+    assert chunks <= min(16, -(-tiles // (32 if rows <= 32 else 44))), plan
     assert chunks * batch * heads[1] <= 4096 or "list" in plan, plan
     assert need <= 256 + total_q * heads[0] * 16 * 130 * 4
     # a workspace sized without the hint holds the partial results of every hint

@@ -164,14 +164,36 @@ def test_work_list(head_dim, tree, nodes, ctx, kv_heads):
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
-@pytest.mark.parametrize("nodes,longest", [(8, 50000), (9, 64000)])
-def test_work_list_most_chunks(head_dim, nodes, longest):
-    """Contexts that 16 chunks of 44 tiles per wave do not hold (64 rows: 45056 tokens; row-split body, whose tiles count
-    3/8: 60074): chunks get longer."""
+@pytest.mark.parametrize("nodes,longest,item", [(8, 70000, 32 * 128), (9, 75000, 42 * 16 * 32 // 5)])
+def test_work_list_most_chunks(head_dim, nodes, longest, item):
+    """Contexts that 16 items do not hold (64 rows: of 32 units of 128 tokens, 65536 in all; 72 rows, row-split body, whose 32
+    tokens count 5/16 of a unit: of 42 units, 68800): the chunks get longer."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    assert longest > 16 * item
     plan = listed(attention([nodes, 2, nodes], [longest, 100, 3000], head_dim, False))
     assert "at most 16 per request" in plan
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("nodes", [9, 16])        # 72 and 128 rows: three and four 32-row blocks
+def test_work_list_chunks_beyond_the_page_table_of_the_row_split_body(head_dim, nodes):
+    """A 16th of 140000 tokens is more than the 8192 whose page ids the row-split body holds: the token-split body takes the
+    request, a wave per 32-row block, with its two-term bf16 weights."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import runner
+    a = widened(attention([nodes, 2, 8], [140000, 100, 3000], head_dim, False), 9000)
+    dev = runner.DeviceAttn(a, out_dtype=torch.float32, kv_hint=int(0.8 * 3 * 9000 * 16))
+    plan = sv.spec_describe_attn_plan(dev.desc)
+    assert "attn_stream_list_kernel" in plan and "at most 16 per request" in plan and 140000 > 16 * 8192
+    dev.workspace.fill_(0xFF)
+    dev.run()
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle_attn(a)
+    # 2^-17 of sum p |v| <= max |v| = 5.5, and fp32 sums; the row-split body's weights of one fp16 term would be off by more
+    assert np.abs(dev.out.cpu().numpy() - ref).max() < 5e-5
+    assert np.abs(dev.lse.cpu().numpy() - ref_lse).max() < 1e-4
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
