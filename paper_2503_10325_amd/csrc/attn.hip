@@ -1328,10 +1328,10 @@ static long dev_knob(const char*, long fallback) { return fallback; }
 // 190, 200, 201, 196, 32 x 32 of 512 to 16384 248, 251, 250, 261, of 1123 to 3922 (up to 31 units) 265, 265,
 // 273, 276.
 constexpr int kListTau = 32;
-// ... of an item that runs the row-split body: 36, 40, 42, 44 units are 3686, 4096, 4301, 4506 tokens.  64 requests of 80 rows take
-// 180, 178, 174, 172 us, of 128 rows 189, 188, 184, 183; seven seeds of the serving mix 148.3, 147.5, 148.0, 149.7 on average, one
-// of them 137.0, 137.1, 137.4, 147.5.
-constexpr int kListTauRows = 42;
+// ... of an item that runs the row-split body: 40, 42, 44, 46 units are 4096, 4301, 4506, 4710 tokens.  Averages over twelve seeds of
+// the serving mix 159.8, 159.8, 159.4, 160.1 us, over twelve batches of 64 requests of 80 or 128 rows (512 to 12587 tokens) 363.6,
+// 362.8, 360.9, 359.7; 48 units left one compute unit two long items on one seed of the mix (144 -> 167).
+constexpr int kListTauRows = 44;
 // Most chunks the work list cuts a request into: the longest one the block table can hold, in items of kListTau units for up
 // to 32 rows.  More rows count twice and four times the waves they take, at 44: an upper bound, which sizes the workspace.
 // least: ... for a workspace that does not hold that many, as one that was sized without a hint (chunks of up to 5120 tokens)
