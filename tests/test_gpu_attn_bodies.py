@@ -213,3 +213,21 @@ def test_work_list_in_a_workspace_sized_without_a_hint(head_dim):
     torch.cuda.synchronize()
     assert (block[need:] == 0xFF).all()
     check(a, dev.out.cpu().numpy(), dev.lse.cpu().numpy())
+
+
+@pytest.mark.parametrize("hint_units,cut", [(68, True), (77, False), (90, True)])      # 96 pairs: 252, 279, 318 items of 32 units; 211, 233, 264 of 40
+def test_work_list_items_follow_the_compute_units(hint_units, cut):
+    """Requests of up to 39 units: cut into items of 32, whole in items of 40 (no partial result is written)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the numbers are those of 256 compute units")
+    from paper_2503_10325_amd import runner
+    a = widened(attention([4] * 12, [4900 - 37 * k for k in range(12)], 64, False, kv_heads=8), 2048)
+    dev = runner.DeviceAttn(a, out_dtype=torch.float32, kv_hint=12 * 128 * hint_units)
+    assert "attn_stream_list_kernel" in sv.spec_describe_attn_plan(dev.desc)
+    dev.workspace.fill_(0xFF)
+    dev.run()
+    torch.cuda.synchronize()
+    assert bool((dev.workspace != 0xFF).any()) == cut
+    check(a, dev.out.cpu().numpy(), dev.lse.cpu().numpy())
