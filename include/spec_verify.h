@@ -196,7 +196,8 @@ int32_t spec_accept(
  * draw a chain needs over the chip (path 3); large batches use a statistics pass that stops reading a
  * request's rows at its first rejection (path 4).  Trees with bf16 logit rows (16-byte aligned, V a multiple
  * of 8) and a batch of at most one request per compute unit are walked by a cluster of workgroups per
- * request that keep slices of the walked rows in LDS and read no other row (path 2); other inputs take the
+ * request that keep slices of the walked rows in registers or LDS and read, besides those, only the rows of a
+ * node whose test is under way (path 2); other inputs take the
  * statistics pass followed by one walking workgroup per request (path 1).  No wait between workgroups is
  * unbounded: `patience` is the number of polls one spends waiting for its peers before it does their share
  * itself (0 = never wait); path 3 has no waits at all.  tuning == NULL is spec_accept. */

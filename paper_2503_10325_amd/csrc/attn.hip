@@ -86,12 +86,6 @@ struct AttnParams {
   int out_f32;
 };
 
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // The value held by the same lane of the other half-wave (lane ^ 32), through the gfx950 half-wave
@@ -138,7 +132,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, x);
 }
 
-// Waves of a token-split workgroup that share one query block, for R <= 128 query rows.
 // A zero the compiler cannot see through.  Added to the thread id at the top of a work item's body, it ties the
 // per-lane constants of that body (lane offsets, LDS addresses) to the item: in a kernel that loops over items
 // of two different bodies they would otherwise be hoisted out of the loop and held in registers across both.
@@ -187,13 +180,12 @@ __device__ __forceinline__ bf16x8 tr_pair(unsigned p0, unsigned p1) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
+// Waves of a four-wave token-split workgroup that share the tiles of a request of R <= 128 query rows: all of them where a
+// wave multiplies a tile with every query row (up to 64), none where each has a 32-row block of its own.
 __device__ __forceinline__ int stream_nslice(int R) {
   return R <= 64 ? 4 : 1;
 }
 
-// Number of context chunks of a request with L tokens and n draft nodes.  The token-split,
-// sorted-work-list launch (tau > 0) cuts by the number of tiles one wave streams; the other
-// launches cut by tokens.  The attention kernels and the combine kernel all use this function.
 // Kernels that hold both bodies run requests with at least P.list_rows_min query rows per KV head through the
 // row-split body (its waves share every staged tile; the token-split body stages a tile once per 32-row block).
 __device__ __forceinline__ bool list_uses_rows(const AttnParams& P, int n) {
@@ -211,6 +203,8 @@ __device__ __forceinline__ int request_units(const AttnParams& P, int L, int n) 
   return (tiles + nslice - 1) / nslice;
 }
 
+// Number of context chunks of a request with L tokens and n draft nodes.  The sorted work list (tau > 0) cuts by units, the
+// other launches by tokens.  The attention kernels and the combine kernel all use this function.
 __device__ __forceinline__ int request_chunks(const AttnParams& P, int L, int n) {
   const int tau = list_uses_rows(P, n) ? P.tau_rows : P.tau;
   if (P.tau > 0) return min(max(1, (request_units(P, L, n) + tau - 1) / tau), P.max_chunks);
@@ -240,7 +234,7 @@ __device__ __forceinline__ void stream_tiles(const AttnParams& P, unsigned char*
   const int R = n * P.G;
   const int row0 = rg * 128;
   const int nqb = min(4, (R - row0 + 31) / 32);             // query blocks of this workgroup
-  const int groups = NQ == 2 || nqb == 1 ? 1 : (nqb == 2 ? 2 : 4);   // waves with tiles of their own come in so many kinds
+  const int groups = NQ == 2 || nqb == 1 ? 1 : 4;           // a wave per query block (two blocks share the wave: NQ = 2), or all for one
   const int nslice = NW / groups;                           // waves sharing one query block
   const int my_g = wave % groups, my_slice = wave / groups;
   const bool wave_active = NQ * my_g < nqb;
@@ -608,7 +602,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attn_stream_kerne
 constexpr int kPlanMaxB = 128;
 
 // ----------------------------------------------------------------------------------
-// Row-split variant for requests with more than 32 query rows per KV head (GQA groups
+// Row-split variant for requests with more than 64 query rows per KV head (GQA groups
 // times several drafts, draft trees).  The NW waves of a workgroup stage 64-token tiles
 // cooperatively (double-buffered in LDS) and every wave owns one block of 32 query rows,
 // for which it sees every token: no cross-wave merge is needed.
@@ -1422,15 +1416,14 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool small_workspace) {
   int64_t tok = a.kv_hint > 0 ? a.kv_hint : static_cast<int64_t>(a.B) * max_tok;
   // Chunk length.  Every workgroup pays a fixed prologue/epilogue (and, when a request is split, a
   // partial-result round trip proportional to its query rows), so chunks are as long as two
-  // limits allow: (a) about one workgroup per compute unit should exist, (b) one wave should not
-  // stream more than ~40 tiles in sequence, or the longest workgroup sets the kernel's duration.
+  // limits allow: (a) about one workgroup per compute unit should exist, (b) a chunk of the token-split body should not
+  // exceed 5120 tokens (40 tiles for each of four waves) for up to 32 rows, 2560 for up to 64, 1280 for more, or the longest
+  // workgroup sets the kernel's duration.
   const long jobs_knob = dev_knob("SPECV_ATTN_JOBS", 0);
   const int64_t jobs_target = jobs_knob > 0 ? jobs_knob : (p.kind == 1 || p.mixed ? 512 : 256);   // 4-wave row-split body: two per compute unit
   int64_t chunk = (tok * a.Hkv * p.row_groups + jobs_target - 1) / jobs_target;
   if (token_split && jobs_knob <= 0) {
-    // waves that share one query block (pair) and therefore split its tiles
-    const int nslice = max_rows <= 32 ? 4 : (max_rows <= 64 ? 2 : 1);
-    const int64_t cap = static_cast<int64_t>(40) * kTile * nslice;
+    const int64_t cap = max_rows <= 32 ? 5120 : (max_rows <= 64 ? 2560 : 1280);
     if (chunk > cap) chunk = cap;
   }
   // shortest chunk: two tiles per wave of the eight-wave token-split kernel (which such launches take, below); a shorter
@@ -1438,13 +1431,13 @@ AttnPlan make_attn_plan(const AttnArgs& a, bool small_workspace) {
   const int64_t shortest = token_split ? 512 : 256;
   if (chunk < shortest) chunk = shortest;
   // Ragged batches with little work, but with a workgroup for half of the compute units before any cut, stay whole where
-  // the longest request is at most 12 units of the work list (about 30 us): a cut saves the longest workgroups less time
-  // than the partial results and a merge launch over all query rows take.  Whole against cut: 100
+  // the longest request is at most 1536 tokens (up to 32 rows), 768 (up to 64) or 1008 long: a cut saves the longest workgroups less
+  // time than the partial results and a merge launch over all query rows take.  Whole against cut: 100
   // requests x 8 KV heads of 20 to 500 tokens (up to 120 rows) 36.9 and 57.6 us (list 39.2), 20 x 32 of 20 to 500 28.8 and
   // 49.0 (30.6), 40 x 8 of 20 to 700 (up to 32 rows) 20.8 and 28.5 (23.2), 25 x 8 of 20 to 500 18.8 and 20.5 (22.6); with 25 x
   // 8 of 100 to 500 and three of 4000 tokens cutting stays ahead, 24.7 against 33.2.
   if (little && ragged && p.kind == 0 && pairs >= 128 &&
-      max_tok <= 12 * kTile * (max_rows <= 32 ? 32 : (max_rows <= 64 ? 16 : 21)) / 8)
+      max_tok <= (max_rows <= 32 ? 1536 : (max_rows <= 64 ? 768 : 1008)))
     chunk = std::max(chunk, max_tok);
   chunk = (chunk + gran - 1) / gran * gran;
   if (chunk > max_tok) chunk = (max_tok + gran - 1) / gran * gran;

@@ -45,9 +45,9 @@ def test_narrow_block_tables_are_cut_by_tokens():
 
 
 @pytest.mark.parametrize("batch,heads,max_q,hint,pages,chunks", [
-    (100, (32, 8), 29, 26000, 33, 1),       # 800 pairs, up to 116 rows, 528 tokens: 12 units are 1008
+    (100, (32, 8), 29, 26000, 33, 1),       # 800 pairs, up to 116 rows: whole up to 1008 tokens, 528
     (100, (32, 8), 29, 30000, 64, 2),       # 1024
-    (40, (32, 8), 8, 16000, 96, 1),         # up to 32 rows: 12 units are 1536 tokens
+    (40, (32, 8), 8, 16000, 96, 1),         # up to 32 rows: 1536
     (40, (32, 8), 8, 16000, 97, 4),
     (40, (32, 8), 16, 16000, 48, 1),        # up to 64: 768
     (40, (32, 8), 16, 16000, 49, 2),
