@@ -181,7 +181,7 @@ __device__ __forceinline__ bf16x8 tr_pair(unsigned p0, unsigned p1) {
 }
 
 // Waves of a four-wave token-split workgroup that share the tiles of a request of R <= 128 query rows: all of them where a
-// wave multiplies a tile with every query row (up to 64), none where each has a 32-row block of its own.
+// wave multiplies a tile with every query row (up to 64; short chunks aside, see stream_item), none where each has a 32-row block of its own.
 __device__ __forceinline__ int stream_nslice(int R) {
   return R <= 64 ? 4 : 1;
 }
@@ -215,7 +215,8 @@ __device__ __forceinline__ int request_chunks(const AttnParams& P, int L, int n)
 // unit for itself) take 32-token tiles in turn; NQ: 32-row query blocks a wave multiplies every tile it streams with.
 //   up to 32 rows  (NQ = 1): all waves share the one block, each streaming every NW-th tile;
 //   up to 64 rows  (NQ = 2): the same, each wave with both blocks: no tile is fetched twice;
-//   more           (NQ = 1): one wave (NW = 8: two) per block, streaming every tile (repeats hit in L2).
+//                  (NQ = 1): half of the waves per block, each streaming every NW/2-th tile (repeats hit in L2); see stream_item;
+//   more           (NQ = 1): one wave (NW = 8: two) per block, streaming every tile.
 // One work item: (request b, KV head kvh, context chunk, row group rg).  Every return below is workgroup-uniform.
 //
 // A tile goes from memory to LDS directly (16 bytes per lane and load, no registers, no conversion) and natural token rows
@@ -234,7 +235,7 @@ __device__ __forceinline__ void stream_tiles(const AttnParams& P, unsigned char*
   const int R = n * P.G;
   const int row0 = rg * 128;
   const int nqb = min(4, (R - row0 + 31) / 32);             // query blocks of this workgroup
-  const int groups = NQ == 2 || nqb == 1 ? 1 : 4;           // a wave per query block (two blocks share the wave: NQ = 2), or all for one
+  const int groups = NQ == 2 || nqb == 1 ? 1 : (nqb == 2 ? 2 : 4);   // waves with tiles of their own come in so many kinds
   const int nslice = NW / groups;                           // waves sharing one query block
   const int my_g = wave % groups, my_slice = wave / groups;
   const bool wave_active = NQ * my_g < nqb;
@@ -574,8 +575,16 @@ __device__ __forceinline__ void stream_item(const AttnParams& P, unsigned char* 
   const int nchunks = request_chunks(P, L, n);
   if (chunk >= nchunks) return;
   const int cb = (((L + nchunks - 1) / nchunks) + kTile - 1) & ~(kTile - 1);
-  if (left > 32 && left <= 64) stream_tiles<D, NW, 2>(P, smem, b, kvh, chunk, rg, q0, n, ctx, nchunks, cb);
-  else stream_tiles<D, NW, 1>(P, smem, b, kvh, chunk, rg, q0, n, ctx, nchunks, cb);
+  // Two blocks per wave save a fetch of every tile and cost a longer start (queries through LDS) and a second merge.  They pay
+  // where the launch's tiles are many: more than three per wave and two workgroups per compute unit.  One block against two,
+  // 40 or 64 rows, us, of 16, 120, 250, 375, 500, 900, 2000 tokens: 40 requests x 8 KV heads (four waves) 9.8 11.9 15.3 22.3 27.5 43.7
+  // 86 against 9.8 12.9 16.4 22.3 26.9 41.1 76; 4 x 8 (eight waves) 8.2 8.4 9.6 12.0 13.5 16.3 18.3 against 9.5 10.1 11.3
+  // 13.3 15.3 18.2 19.5.
+  if constexpr (NW == 4) {
+    if (left > 32 && left <= 64 && min(cb, L - chunk * cb) > 3 * NW * kTile)
+      return stream_tiles<D, NW, 2>(P, smem, b, kvh, chunk, rg, q0, n, ctx, nchunks, cb);
+  }
+  stream_tiles<D, NW, 1>(P, smem, b, kvh, chunk, rg, q0, n, ctx, nchunks, cb);
 }
 
 // Grid-mapped launch: blockIdx = (chunk + max_chunks * row group, KV head, request) or, where the block table is much wider

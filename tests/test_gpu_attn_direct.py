@@ -69,3 +69,24 @@ def test_row_split_edges_and_stale_slots(head_dim, nodes, requests):
     # weights of one fp16 term (truncated, its mean put back): 2^-12 of sum p |v| <= max |v| = 5.5
     assert np.abs(dev.out.cpu().numpy() - ref).max() < 3e-3, sv.spec_describe_attn_plan(dev.desc)
     assert np.abs(dev.lse.cpu().numpy() - ref_lse).max() < 1e-4
+
+
+# 384 tokens of a chunk: up to there a wave has one 32-row query block, then two (four-wave workgroups)
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("nodes", [5, 8])         # 40 and 64 rows
+def test_one_and_two_query_blocks_per_wave(head_dim, tree, nodes):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import runner
+    ctx = [384 - nodes + k for k in (-33, -32, -31, -1, 0, 1, 15, 16, 17, 31, 32, 33)] * 12
+    a = poisoned(attention([nodes] * len(ctx), ctx, head_dim, tree))
+    dev = runner.DeviceAttn(a, out_dtype=torch.float32)
+    assert "attn_stream_kernel" in sv.spec_describe_attn_plan(dev.desc)
+    dev.workspace.fill_(0xFF)
+    dev.run()
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle_attn(a)
+    # as above: 2^-17 of max |v| = 5.5, and fp32 sums
+    assert np.abs(dev.out.cpu().numpy() - ref).max() < 5e-5
+    assert np.abs(dev.lse.cpu().numpy() - ref_lse).max() < 1e-4
