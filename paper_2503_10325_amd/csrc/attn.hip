@@ -1351,8 +1351,9 @@ static int list_max_chunks(int64_t max_tok, int max_rows, bool least) {
 // one or two per compute unit, some get one more than the others and the launch waits for them.  Of 164 batches of 48 to 256
 // pairs (3000 to 16000 tokens, even and lognormal, 4 to 64 rows) the rule takes the longer items in 46: 9 % faster
 // on average (6 x 16 of 4278 to 13606 tokens 115 -> 101 us, 24 x 8 of 4278 to 13606 190 -> 175), at worst 2 % slower (5 x 16 of 9000 to
-// 16000: 97 -> 99).  Items of 36 units fit seldomer, 44 gain 7 %; for a third item per compute unit the estimate is too rough
-// (32 x 8 of 9000 to 16000: 319 -> 339).
+// 16000: 97 -> 99).  At the line itself (18 batches of 256 to 262 items estimated) both are even on average, 15 % faster to 7 % slower;
+// below it (225 to 255) the shorter items are 2 % ahead.  Items of 36 units fit seldomer, 44 gain 7 %; for a third item per
+// compute unit the estimate is too rough (32 x 8 of 9000 to 16000: 319 -> 339).
 static int list_tau(const AttnArgs& a, int64_t pairs, int max_rows) {
   if (max_rows > 64 || a.kv_hint <= 0) return kListTau;               // (a unit is 128 tokens for up to 64 rows)
   const double units = static_cast<double>(a.kv_hint) / a.B / (4 * kTile);
