@@ -1332,7 +1332,7 @@ static long dev_knob(const char*, long fallback) { return fallback; }
 // 273, 276.
 constexpr int kListTau = 32;
 // ... where the items of kListTau units would be just more than one or two per compute unit and these are not (list_tau).
-constexpr int kListTauFew = 40;
+constexpr int kListTauFew[] = {40, 44};
 // ... of an item that runs the row-split body: 40, 42, 44, 46 units are 4096, 4301, 4506, 4710 tokens.  Averages over twelve seeds of
 // the serving mix 159.8, 159.8, 159.4, 160.1 us, over twelve batches of 64 requests of 80 or 128 rows (512 to 12587 tokens) 363.6,
 // 362.8, 360.9, 359.7; 48 units left one compute unit two long items on one seed of the mix (144 -> 167).
@@ -1349,18 +1349,20 @@ static int list_max_chunks(int64_t max_tok, int max_rows, bool least) {
 }
 // Units per item.  Batches of like lengths make pairs * (units of a request / units of an item + 1/2) items; when those spill over
 // one or two per compute unit, some get one more than the others and the launch waits for them.  Of 164 batches of 48 to 256
-// pairs (3000 to 16000 tokens, even and lognormal, 4 to 64 rows) the rule takes the longer items in 46: 9 % faster
+// pairs (3000 to 16000 tokens, even and lognormal, 4 to 64 rows) the rule takes 40 units in 46: 9 % faster
 // on average (6 x 16 of 4278 to 13606 tokens 115 -> 101 us, 24 x 8 of 4278 to 13606 190 -> 175), at worst 2 % slower (5 x 16 of 9000 to
-// 16000: 97 -> 99).  At the line itself (18 batches of 256 to 262 items estimated) both are even on average, 15 % faster to 7 % slower;
-// below it (225 to 255) the shorter items are 2 % ahead.  Items of 36 units fit seldomer, 44 gain 7 %; for a third item per
-// compute unit the estimate is too rough (32 x 8 of 9000 to 16000: 319 -> 339).
+// 16000: 97 -> 99); and 44 in 13: 4 % (3 x 32 of 9000 to 16000 128 -> 113), at worst 2 %.  At the line itself (18 batches of 256 to 262
+// items estimated) both are even on average, 15 % faster to 7 % slower; below it (225 to 255) the shorter items are 2 % ahead.
+// Items of 36 units ahead of these gain nothing; for a third item per compute unit the estimate is too rough (32 x 8 of 9000 to
+// 16000: 319 -> 339).
 static int list_tau(const AttnArgs& a, int64_t pairs, int max_rows) {
   if (max_rows > 64 || a.kv_hint <= 0) return kListTau;               // (a unit is 128 tokens for up to 64 rows)
   const double units = static_cast<double>(a.kv_hint) / a.B / (4 * kTile);
   auto items = [&](int tau) { return static_cast<double>(pairs) * (units / tau + 0.5); };
   const int n_cu = current_device_cus();
-  for (int k = 1; k <= 2; ++k)
-    if (items(kListTau) > k * n_cu && items(kListTauFew) <= k * n_cu) return kListTauFew;
+  for (int most = n_cu; most <= 2 * n_cu; most += n_cu)
+    for (int tau : kListTauFew)
+      if (items(kListTau) > most && items(tau) <= most) return tau;
   return kListTau;
 }
 // The launch for little work has a workgroup for every chunk a request could have.  Most chunks per request such that

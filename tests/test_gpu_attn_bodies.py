@@ -215,9 +215,10 @@ def test_work_list_in_a_workspace_sized_without_a_hint(head_dim):
     check(a, dev.out.cpu().numpy(), dev.lse.cpu().numpy())
 
 
-@pytest.mark.parametrize("hint_units,cut", [(68, True), (77, False), (90, True)])      # 96 pairs: 252, 279, 318 items of 32 units; 211, 233, 264 of 40
+# 96 pairs: 252, 279, 318, 348 items of 32 units; 211, 233, 264, 288 of 40; 196, 216, 244, 266 of 44
+@pytest.mark.parametrize("hint_units,cut", [(68, True), (77, False), (90, False), (100, True)])
 def test_work_list_items_follow_the_compute_units(hint_units, cut):
-    """Requests of up to 39 units: cut into items of 32, whole in items of 40 (no partial result is written)."""
+    """Requests of up to 39 units: cut into items of 32, whole in items of 40 or 44 (no partial result is written)."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
