@@ -1333,10 +1333,10 @@ static long dev_knob(const char*, long fallback) { return fallback; }
 constexpr int kListTau = 32;
 // ... where the items of kListTau units would be just more than one or two per compute unit and these are not (list_tau).
 constexpr int kListTauFew[] = {40, 44};
-// ... of an item that runs the row-split body: 40, 42, 44, 46 units are 4096, 4301, 4506, 4710 tokens.  Averages over twelve seeds of
-// the serving mix 159.8, 159.8, 159.4, 160.1 us, over twelve batches of 64 requests of 80 or 128 rows (512 to 12587 tokens) 363.6,
-// 362.8, 360.9, 359.7; 48 units left one compute unit two long items on one seed of the mix (144 -> 167).
-constexpr int kListTauRows = 44;
+// ... of an item that runs the row-split body: 38, 40, 42, 44, 46 units are 3891, 4096, 4301, 4506, 4710 tokens.  Averages over forty seeds
+// of the serving mix 157.8, 157.5, 157.4, 158.2, 159.3 us, at worst 2, 2, 3, 11, 12 % behind the best of a seed; over 55 batches with
+// more such requests (5 to 16 drafts each, or ten, twelve, sixteen; 32 or 64 requests) 44 is 0.8 % behind 42.
+constexpr int kListTauRows = 42;
 // Most chunks the work list cuts a request into: the longest one the block table can hold, in items of kListTau units for up
 // to 32 rows.  More rows count twice and four times the waves they take, at 44: an upper bound, which sizes the workspace.
 // least: ... for a workspace that does not hold that many, as one that was sized without a hint (chunks of up to 5120 tokens)
