@@ -615,12 +615,17 @@ constexpr int kPlanMaxB = 128;
 // times several drafts, draft trees).  The NW waves of a workgroup stage 64-token tiles
 // cooperatively (double-buffered in LDS) and every wave owns one block of 32 query rows,
 // for which it sees every token: no cross-wave merge is needed.
-// K of the next tile goes to LDS directly; V of the next tile is converted and stored between the matrix instructions of the
-// scores, where the vector unit has nothing else to do, and needs no transposition (218 -> 165 vector instructions per wave
+// K of the next tile goes to LDS directly; V of the next tile is converted ahead of the matrix instructions of the
+// scores, stored between them, and needs no transposition (218 -> 165 vector instructions per wave
 // and tile against staging both through registers and packing V with v_perm).  What bounds it is the issue of vector and matrix
 // instructions of the two waves of a SIMD, which add up more than they overlap, and, with the tables in HBM, the clock: with
 // L2-resident tables 64 x 8 KV heads x 2048 tokens x 128 rows 86.5 -> 80.1 us, 16 x 8 x 4096 x 256 rows 88.7 -> 84.6, 464 rows
 // 138 -> 131; 256 rows from HBM 94.9 -> 91.0 in a step; short contexts gain the most (512 tokens, 160 rows 17.1 -> 14.3).
+// One page id and one scalar base per wave and tile, and operand reads that need no address arithmetic (RowsCfg): about 500
+// -> 410 instructions per wave and step of the sliced kernel.  In loops of the attention call, tables from HBM: 16 x 8 KV heads x
+// 4096 tokens x 256 rows 95.7 -> 90.3 us, 464 rows 150.8 -> 148.3, 32 x 8 x 2048 x 224 85.4 -> 83.2, 64 x 8 x 2048 x 240
+// 177.6 -> 175.1, ragged 64 x 8, 16 to 80 rows 173.7 -> 170.8.  (The conversion of V stands ahead of the scores' matrix
+// instructions, where the compiler puts it: pinned between them the first of these takes 95.)
 // ----------------------------------------------------------------------------------
 // SL = 2 ("sliced"): the workgroup owns 32 * NW / 2 query rows and stages 128-token tiles; waves w and w + NW/2
 // share a block of 32 rows, the first computing the lower 64 tokens of every staged tile, the second the upper 64,
@@ -632,15 +637,22 @@ struct RowsCfg {
   static constexpr int kT = kTc * SL;                      // tokens per staged tile
   static constexpr int kThreads = NW * 64;
   static constexpr int kTpt = kT * (D / 8) / kThreads;     // 16-byte loads per thread and tensor: consecutive tokens of V
-  static constexpr int kKBytes = kT * D * 2;               // natural rows, chunks placed by XOR as in the token-split body
-  static constexpr int kStage = 2 * kKBytes;               // K as bf16, V as fp16
+  static constexpr int kTileBytes = kT * D * 2;            // bytes of a tile: natural rows, chunks placed by XOR as in the token-split body
+  static constexpr int kStage = 2 * kTileBytes;            // K as bf16, V as fp16
+  // The two tiles of K lie side by side, the two of V behind them: what an operand read adds to its lane's address, the stage
+  // among it, then fits the 16 bits an LDS instruction has for it (with K and V of a stage side by side the tiles of 128
+  // tokens took an addition per read in every second step).
+  static constexpr int kV0 = 2 * kTileBytes;
+  static_assert(kTileBytes + 64 * D * 2 <= 65536, "stage and row offsets of an operand read within an instruction's offset");
   static constexpr int kMaxChunkPages = NW == 8 ? 1024 : 512;   // a chunk spans at most 16384 (8192) tokens
   static constexpr int kPagePad = 32;                      // page-table entries kept past a chunk's last page
   // behind the two stages: ancestor masks, parents, page table
   static constexpr int meta_bytes(bool wide) { return wide ? kMaxQWide * 16 + kMaxQWide * 4 : kMaxQ * 8 + kMaxQ * 4; }
   static constexpr int lds_bytes(bool wide) { return 2 * kStage + meta_bytes(wide) + (kMaxChunkPages + kPagePad) * 4; }
   static constexpr int kLds = lds_bytes(false);
+  static constexpr int kPageLoads = AttnCfg<D>::kPageLoads;
   static_assert(kTpt == 4 || kTpt == 2, "unsupported tile/thread combination");
+  static_assert(kPageLoads % kTpt == 0, "a wave's loads of a tile are of one page");
 };
 
 // One work item of the row-split body: (request b, KV head kvh, context chunk `chunk` of `nchunks`, row group
@@ -713,8 +725,6 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
 
   // ---- cooperative tile loads ----
   const int32_t* bt = P.block_table + static_cast<int64_t>(b) * P.max_pages;
-  const int64_t page_elems = static_cast<int64_t>(P.Hkv) * kPage * D;
-  const int64_t head_off = static_cast<int64_t>(kvh) * kPage * D;
   const int vc = tid % C::kCh;                  // V: 16-byte chunk of the token row
   const int vtok0 = tid / C::kCh * RC::kTpt;    // V: first of kTpt consecutive tokens within the tile
   // two register sets for V: while tile t is computed, tile t+1 is converted and stored from one and tile t+2 is in flight
@@ -725,38 +735,40 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   const int lp0 = t_begin / kPage;
   const int np = (t_end + kPage - 1) / kPage - lp0;          // >= 1 pages touched by this chunk
   // (entries past the chunk's last page repeat it: tile numbers past the end need no clamp)
-  for (int i = tid; i < np + RC::kPagePad; i += RC::kThreads) sh_pages[i] = bt[lp0 + min(i, np - 1)];
+  for (int i = tid; i < np + RC::kPagePad; i += RC::kThreads) sh_pages[i] = max(bt[lp0 + min(i, np - 1)], 0);
   if (tid < kNodes) sh_par[tid] = my_par;
   __syncthreads();
 
   // Loads are unconditional (addresses clamped to the chunk's last page): positions past the end are masked out of the
-  // scores, and their V values are zeroed when staged.  Every load of a wave touches one cache page: a scalar base and a small
-  // per-lane offset.  K goes from memory straight to LDS, load j of wave w to the rows from kTokPerLoad (NW j + w) on.
+  // scores, and their V values are zeroed when staged.  A wave's share of a tile, K and V alike, is kTpt loads within one cache
+  // page: one page id, one scalar base (32 x 32 bits: pages and page sizes are not negative), a small per-lane offset; the
+  // loads differ by the instruction's offset.  K goes from memory straight to LDS, the tokens from 16 wave_page + kTokPerLoad part0 on.
   const int uwave = __builtin_amdgcn_readfirstlane(wave);
+  const int wave_page = uwave * RC::kTpt / RC::kPageLoads, part0 = uwave * RC::kTpt % RC::kPageLoads;
   const int k_row = lane / C::kCh, k_ch = lane % C::kCh;
-  const unsigned k_lane_off = k_row * C::kRowBytes + ((k_ch ^ C::k_swizzle(k_row)) << 4);
-  const int v_lane_off = (vtok0 % kPage) * D + vc * 8;
+  const unsigned k_lane_off = (k_row * C::kRowBytes + ((k_ch ^ C::k_swizzle(k_row)) << 4)) ^ (64u * part0);
+  const unsigned v_lane_off = (vtok0 % kPage) * C::kRowBytes + vc * 16;
   const unsigned lds0 = lds_address(smem);
+  const unsigned k_dst = lds0 + 1024 * RC::kTpt * uwave;
+  const unsigned page_bytes = static_cast<unsigned>(P.Hkv) * (kPage * C::kRowBytes);
+  const int64_t head_off = static_cast<int64_t>(kvh) * (kPage * C::kRowBytes);
+  const unsigned char* k_base = reinterpret_cast<const unsigned char*>(P.k_pool) + head_off + part0 * 1024;
+  const unsigned char* v_base = reinterpret_cast<const unsigned char*>(P.v_pool) + head_off;
   // The page ids of a tile are read from LDS a whole tile step before the loads that need them.
-  int pk[RC::kTpt], pv;
-  auto tile_pages = [&](int t) { return sh_pages + min(RC::kT * t / kPage, np + RC::kPagePad - RC::kT / kPage); };
-  auto fetch_k_pages = [&](int t) {
-#pragma unroll
-    for (int j = 0; j < RC::kTpt; ++j) pk[j] = tile_pages(t)[(j * NW + uwave) / C::kPageLoads];
+  int pk, pv;
+  auto tile_page = [&](int t) { return sh_pages[min(RC::kT * t / kPage, np + RC::kPagePad - RC::kT / kPage) + wave_page]; };
+  auto fetch_k_page = [&](int t) { pk = tile_page(t); };
+  auto fetch_v_page = [&](int t) { pv = tile_page(t); };
+  auto page_at = [&](const unsigned char* base, int page) __attribute__((always_inline)) {
+    return base + static_cast<uint64_t>(static_cast<unsigned>(__builtin_amdgcn_readfirstlane(page))) * page_bytes;
   };
-  auto fetch_v_page = [&](int t) { pv = tile_pages(t)[vtok0 / kPage]; };
-  auto issue_k = [&](int stage) __attribute__((always_inline)) {          // of the tile whose K pages were fetched last
+  auto issue_k = [&](int stage) __attribute__((always_inline)) {          // of the tile whose K page was fetched last
+    const unsigned char* base = page_at(k_base, pk);
 #pragma unroll
-    for (int j = 0; j < RC::kTpt; ++j) {
-      const int i = j * NW + uwave, part = i % C::kPageLoads;
-      const int page = __builtin_amdgcn_readfirstlane(pk[j]);
-      const uint16_t* base = P.k_pool + page * page_elems + head_off + part * C::kTokPerLoad * D;
-      load_to_lds(reinterpret_cast<const unsigned char*>(base), k_lane_off ^ (64u * part), lds0 + stage * RC::kStage + 1024 * i, 0);
-    }
+    for (int j = 0; j < RC::kTpt; ++j) load_to_lds(base, k_lane_off ^ (64u * j), k_dst + stage * RC::kTileBytes, j);
   };
   auto issue_v = [&](u32x4 (&vr)[RC::kTpt]) __attribute__((always_inline)) {
-    const int page = __builtin_amdgcn_readfirstlane(pv);
-    const uint16_t* vp = P.v_pool + page * page_elems + head_off + v_lane_off;
+    const uint16_t* vp = reinterpret_cast<const uint16_t*>(page_at(v_base, pv) + v_lane_off);
 #pragma unroll
     for (int i = 0; i < RC::kTpt; ++i) vr[i] = *reinterpret_cast<const u32x4*>(vp + i * D);
   };
@@ -779,9 +791,9 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
     v[from] = bf16x2_to_f16x2(v[from]);
     v[from + 1] = bf16x2_to_f16x2(v[from + 1]);
   };
-  const unsigned v_store = lds0 + RC::kKBytes + vtok0 * C::kRowBytes;
+  const unsigned v_store = lds0 + RC::kV0 + vtok0 * C::kRowBytes;
   auto store_v = [&](int stage, int i, const u32x4& v) __attribute__((always_inline)) {
-    *lds_u32x4(v_store + stage * RC::kStage + i * C::kRowBytes + ((vc ^ C::v_swizzle((vtok0 + i) & 3)) << 4)) = v;
+    *lds_u32x4(v_store + stage * RC::kTileBytes + i * C::kRowBytes + ((vc ^ C::v_swizzle((vtok0 + i) & 3)) << 4)) = v;
   };
 
   unsigned long long my_anc = 0ull, my_anc_hi = 0ull;          // ancestor mask of this lane's node (set below)
@@ -792,10 +804,10 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   float m_safe = 0.f, m_next = -INFINITY, alpha = 1.f, psum = 0.f;
   // transposing reads, as in the token-split body: lane i of a group of 16 gets head dimension i of 4 tokens
   const int tr_tok = 4 * lh + ((lane & 15) >> 2);
-  const unsigned v_at = lds0 + RC::kKBytes + (RC::kTc * slice + tr_tok) * C::kRowBytes + 8 * (lane & 1) +
+  const unsigned v_at = lds0 + RC::kV0 + (RC::kTc * slice + tr_tok) * C::kRowBytes + 8 * (lane & 1) +
                         (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ C::v_swizzle(tr_tok)) << 4);
   auto v_frag = [&](int stage, int chunk, int db) {      // chunk = 16-token group 0..3 of the tile
-    const unsigned at = (v_at ^ (64u * db)) + stage * RC::kStage + 16 * chunk * C::kRowBytes;
+    const unsigned at = (v_at ^ (64u * db)) + stage * RC::kTileBytes + 16 * chunk * C::kRowBytes;
     return __builtin_bit_cast(f16x8, tr_pair(at, at + 8 * C::kRowBytes));
   };
   const unsigned k_at = lds0 + (RC::kTc * slice + ln) * C::kRowBytes + ((lh ^ C::k_swizzle(ln)) << 4);
@@ -815,12 +827,12 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   };
 
   // First half: S = K Q^T (operand reads from LDS run two steps ahead of the matrix instructions that consume
-  // them), with the conversion and the stores of the next tile's V between the matrix instructions; mask, row maxima,
-  // rescale, the weights of the first 16 tokens.
+  // them), with the stores of the next tile's V between the matrix instructions; mask, row maxima, rescale, the weights of the
+  // first 16 tokens.
   auto tile_scores = [&](int stage, int t, u32x4 (&vr)[RC::kTpt]) __attribute__((always_inline)) {
     const int tok0 = t_begin + RC::kT * t + RC::kTc * slice;
     auto k_frag = [&](int ks, int tb) {
-      return as_bf16x8(*lds_u32x4((k_at ^ (32 * ks)) + stage * RC::kStage + 32 * tb * C::kRowBytes));
+      return as_bf16x8(*lds_u32x4((k_at ^ (32 * ks)) + stage * RC::kTileBytes + 32 * tb * C::kRowBytes));
     };
     constexpr int kHalves = 2 * RC::kTpt;         // half rows of V to convert
 #pragma unroll
@@ -930,11 +942,11 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   // page, their V rows staged as zeros, and they are never computed): every path leaves the same number outstanding.
   // (a wave of the sliced variant skips a staged tile whose half for it lies past the end)
   auto mine = [&](int t) { return active && t < ntiles && t_begin + RC::kT * t + RC::kTc * slice < t_end; };
-  fetch_k_pages(0);
+  fetch_k_page(0);
   fetch_v_page(0);
   issue_v(vrA);
   issue_k(0);
-  fetch_k_pages(1);
+  fetch_k_page(1);
   fetch_v_page(1);
   if (touches_drafts) {
     if (tid < kNodes) {
@@ -992,12 +1004,12 @@ __device__ __forceinline__ void rows_item(const AttnParams& P, unsigned char* sm
   constexpr bool kLateK = NW == 8;
   auto step = [&](int t, int stage, u32x4 (&cur)[RC::kTpt]) __attribute__((always_inline)) {
     arrived(cur);
-    if constexpr (!kLateK) { issue_k(stage ^ 1); fetch_k_pages(t + 2); }
+    if constexpr (!kLateK) { issue_k(stage ^ 1); fetch_k_page(t + 2); }
     cut_tail(t + 1, cur);
     const bool work = mine(t);
     if (work) tile_scores(stage, t, cur);
     else stage_v(stage ^ 1, cur);
-    if constexpr (kLateK) { issue_k(stage ^ 1); fetch_k_pages(t + 2); }
+    if constexpr (kLateK) { issue_k(stage ^ 1); fetch_k_page(t + 2); }
     if (work) tile_output(stage);
     issue_v(cur);
     fetch_v_page(t + 4);
