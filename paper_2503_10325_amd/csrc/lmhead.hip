@@ -21,6 +21,7 @@ typedef uint32_t lm_u32x2 __attribute__((ext_vector_type(2)));
 struct LmParams {
   int rows, K, V;
   int nvb, nrb, total, per_xcd;
+  int slots;               // workgroups of an XCD
   float c;
   const uint16_t* hidden;
   const uint16_t* weight;
@@ -28,10 +29,11 @@ struct LmParams {
   float2* bstats;          // [rows][nvb]
 };
 
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
+// Two fp32 values to bf16, round to nearest even: the first in the lower half.
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+  typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
 // ----------------------------------------------------------------------------------
@@ -58,14 +60,32 @@ struct TlCfg {
   static constexpr int kFit = kTlLds / (kABuf + kBBuf) < 6 ? kTlLds / (kABuf + kBBuf) : 6;
   static constexpr int kABufs = MI == 2 ? kFit : 3;
   static constexpr int kBBufs = MI == 2 ? kFit : (NT2 <= 10 ? 3 : 2);
-  static constexpr int kOutPitch = kVB * 2 + 16;              // bytes per row of the output tile in LDS
   static constexpr int kLoop = kABufs * kABuf + kBBufs * kBBuf;
-  static constexpr int kEpi = kRows * (kOutPitch + 4 * 8);    // output tile, then (max, sum) per row and vocabulary quarter
-  static constexpr int kLds = kLoop > kEpi ? kLoop : kEpi;
+  static constexpr int kStat = kRows * 4 * 8;                 // (max, sum) per row and vocabulary quarter
+  // A workgroup takes several tiles one after the other, and its loads run on into the next, where the statistics have
+  // room beside the slices.  Not with few rows: reading the weights alone evens out better over workgroups that start as
+  // others end (8 x 4096 x 128256 174 us, 180 with fixed shares).
+  static constexpr bool kStream = MI > 2 && kLoop + kStat <= kTlLds;
+  static constexpr int kLds = kStream ? kLoop + kStat : (kLoop > kStat ? kLoop : kStat);
   static_assert(kLds <= kTlLds && kABufs >= 3 && kBBufs >= 2 && kABufs >= kBBufs, "one workgroup per compute unit");
 };
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float lm_f32x4;
+
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// op over the four lanes that are 16 and 32 apart: the same bits in all of them.
+template <typename Op>
+__device__ __forceinline__ float across16_32(float x, Op op) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned y = __float_as_uint(op(__uint_as_float(r[0]), __uint_as_float(r[1])));
+  const auto q = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
 
 // 16 bytes per lane from base + off to LDS: lane i's land at byte lds_at + 16 i.  Not tracked by the compiler: the
 // loop counts these loads itself (vmcnt).  The LDS address is an operand bound to M0: the compiler writes that register
@@ -75,56 +95,82 @@ __device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned 
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "{m0}"(lds_at), "v"(off), "s"(base) : "memory");
 }
 
-// The product of one wave with NT row tiles of the workgroup's NT2, up to the rounded output tile and the per-row
-// statistics of its 64 vocabulary entries in LDS.  Waves of a workgroup may run it with different NT: every copy
-// passes the same barriers and issues the same loads.
+// The products of one wave with NT row tiles of the workgroup's NT2, for the workgroup's tiles first, first + slots, ...
+// below end.  Waves of a workgroup may run it with different NT: every copy passes the same barriers and issues the same
+// loads.
 //
-// What bounds it: with many rows the matrix cores under the chip's power limit (1024 x 4096 x 128256: busy 70 % of the
-// cycles at 1.67 GHz).  A [64 vocab x 128 rows] tile per wave reads 12 KB of LDS per 32 matrix instructions (a third of the
-// LDS rate) and a workgroup fetches 64 KB per 2048 matrix cycles; 16-row granularity keeps padded rows out of the products
-// (1040 rows: 5 x 208).  Measured in loops, against the kernel this replaces (hidden operands packed by a kernel of their
-// own and read from L2 by every wave, weights through registers): 1040 x 4096 x 128256 1091 -> 870 us (1.26 PFLOP/s),
-// 429 x 8192 x 128256 908 -> 758 us, 512 x 4096 x 128256 507 -> 437 us, 224 x 4096 x 32000 85 -> 75 us, 200 x 8192 x
-// 128256 581 -> 458 us (4.7 TB/s).
-// With up to 128 rows the weights' way from HBM, with 128 vocabulary entries per workgroup and up to five slices ahead
-// (a kernel that staged them through registers, three slices ahead, in brackets): 72 x 4096 x 32000 61 us (68), 128 x
-// 8192 x 128256 402 (449), 8 x 4096 x 128256 178 = 5.9 TB/s (202), 30 x 8192 x 2000 30 (71), 100 x 4096 x 8000 28 (48).
+// What bounds it: with many rows the matrix cores under the chip's power limit (busy 70 % of the cycles at 1.8 GHz).  Of
+// the 862 us of 1040 x 4096 x 128256 a fifth went into what does not depend on the contraction (20 thousand cycles per tile:
+// first slices, output tile through LDS), so a workgroup now keeps its compute unit, the loads of its next tile go out
+// under the last slices of the present one, and the logits go from the accumulators to memory (64 contiguous bytes per row
+// and instruction after a swap between lanes) with no barrier but that of the statistics: 829 us (1.32 PFLOP/s), 429 x 8192
+// x 128256 753 -> 733, 1040 x 1024 x 32000 73 -> 63, 512 x 4096 x 128256 437 -> 430.  With loads from memory left out the
+// same loop takes 700, with the LDS reads left out too 630: what is left is mostly moving data.
+// A [64 vocab x 128 rows] tile per wave reads 12 KB of LDS per 32 matrix instructions (a third of the LDS rate) and a
+// workgroup fetches 64 KB per 2048 matrix cycles; 16-row granularity keeps padded rows out of the products (1040 rows: 5 x
+// 208).
+// With up to 128 rows the weights' way from HBM, with 128 vocabulary entries per workgroup and up to five slices ahead: 72
+// x 4096 x 32000 45 us, 128 x 8192 x 128256 399, 8 x 4096 x 128256 173 = 6.1 TB/s, 30 x 8192 x 2000 30.
 template <int MI, int NT2, int NT>
-__device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* lm_lds, int wave, int v0, int r0) {
+__device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* lm_lds, int wave, int first, int end) {
   using C = TlCfg<MI, NT2>;
-  constexpr int kRows = C::kRows;
+  constexpr int kRows = C::kRows, kVB = C::kVB;
   constexpr int kABufs = C::kABufs, kBBufs = C::kBBufs;
   constexpr int kABuf = C::kABuf, kBBuf = C::kBBuf;
+  constexpr bool kStream = C::kStream;
   constexpr int kBLoads = kRows / 8;                // load instructions per hidden slice (8 rows each), dealt to 8 waves
   constexpr int kBPer = (kBLoads + 7) / 8;          // ... at most per wave
+  constexpr int kBMin = kBLoads / 8;                // ... at least
+  constexpr int kStores = MI / 2 * NT;              // store instructions of a wave's logits
   const int lane = static_cast<int>(threadIdx.x) & 63;
   const int wm = wave & 3, row0 = (wave >> 2) * 16 * ((NT2 + 1) / 2);      // this wave's first row in the tile
-  const int nch = P.K / 64, last = nch - 1;
+  const int nch = P.K / 64;
 
-  // ---- loads: instruction j of a wave covers 8 rows, 8 lanes per row ----
-  const int lr = lane >> 3, lp = lane & 7;
+  // ---- loads: instruction j of a wave covers 8 rows, 8 lanes per row.  Each operand has a cursor: the tile and slice
+  // its next loads are of.  Behind the last tile it stays at the last slice (into a buffer nobody reads any more): every
+  // slice issues the same loads ----
+  // (opaque(lane): what is worked out from it once per tile is not kept in registers over the products)
   unsigned aoff[MI], boff[kBPer];
+  const unsigned char *acur, *bcur;
+  int atile, btile, aleft, bleft;
+  auto seek_a = [&](int t) __attribute__((always_inline)) {
+    const int v0 = __builtin_amdgcn_readfirstlane(t / P.nrb * kVB);
+    acur = reinterpret_cast<const unsigned char*>(P.weight + static_cast<int64_t>(v0) * P.K);
+    atile = t; aleft = nch;
+    const int l = opaque(lane), lr = l >> 3, lp = l & 7;
 #pragma unroll
-  for (int j = 0; j < MI; ++j) {
-    const int ra = (wave * MI + j) * 8 + lr;
-    aoff[j] = static_cast<unsigned>(min(ra, P.V - 1 - v0)) * static_cast<unsigned>(P.K) * 2u + ((lp ^ ((ra >> 1) & 7)) << 4);
-  }
+    for (int j = 0; j < MI; ++j) {
+      const int ra = (wave * MI + j) * 8 + lr;
+      aoff[j] = static_cast<unsigned>(min(ra, P.V - 1 - v0)) * static_cast<unsigned>(P.K) * 2u + ((lp ^ ((ra >> 1) & 7)) << 4);
+    }
+  };
+  auto seek_b = [&](int t) __attribute__((always_inline)) {
+    const int r0 = __builtin_amdgcn_readfirstlane(t % P.nrb * kRows);
+    bcur = reinterpret_cast<const unsigned char*>(P.hidden + static_cast<int64_t>(r0) * P.K);
+    btile = t; bleft = nch;
+    const int l = opaque(lane), lr = l >> 3, lp = l & 7;
 #pragma unroll
-  for (int j = 0; j < kBPer; ++j) {
-    const int rb = (wave + 8 * j) * 8 + lr;
-    boff[j] = static_cast<unsigned>(min(rb, P.rows - 1 - r0)) * static_cast<unsigned>(P.K) * 2u + ((lp ^ ((rb >> 1) & 7)) << 4);
-  }
-  const unsigned char* abase = reinterpret_cast<const unsigned char*>(P.weight + static_cast<int64_t>(v0) * P.K);
-  const unsigned char* bbase = reinterpret_cast<const unsigned char*>(P.hidden + static_cast<int64_t>(r0) * P.K);
+    for (int j = 0; j < kBPer; ++j) {
+      const int rb = (wave + 8 * j) * 8 + lr;
+      boff[j] = static_cast<unsigned>(min(rb, P.rows - 1 - r0)) * static_cast<unsigned>(P.K) * 2u + ((lp ^ ((rb >> 1) & 7)) << 4);
+    }
+  };
+  auto wrap_a = [&]() __attribute__((always_inline)) {
+    if (atile + P.slots < end) seek_a(atile + P.slots);
+    else { acur -= kTlSlice; aleft = 1; }
+  };
+  auto wrap_b = [&]() __attribute__((always_inline)) {
+    if (btile + P.slots < end) seek_b(btile + P.slots);
+    else { bcur -= kTlSlice; bleft = 1; }
+  };
   const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>(
       (__attribute__((address_space(3))) unsigned char*)lm_lds));
-  // slices past the end repeat the last one into a buffer nobody reads any more: every slice issues the same loads
-  auto load_a = [&](int s, int buf, int j) __attribute__((always_inline)) {
-    load_to_lds(abase + min(s, last) * kTlSlice, aoff[j], lds0 + buf * kABuf + (wave * MI + j) * 8 * kTlSlice);
+  auto load_a = [&](int buf, int j) __attribute__((always_inline)) {
+    load_to_lds(acur, aoff[j], lds0 + buf * kABuf + (wave * MI + j) * 8 * kTlSlice);
   };
-  auto load_b = [&](int s, int buf, int j) __attribute__((always_inline)) {
+  auto load_b = [&](int buf, int j) __attribute__((always_inline)) {
     if (8 * j + 7 < kBLoads || wave + 8 * j < kBLoads)
-      load_to_lds(bbase + min(s, last) * kTlSlice, boff[j], lds0 + kABufs * kABuf + buf * kBBuf + (wave + 8 * j) * 8 * kTlSlice);
+      load_to_lds(bcur, boff[j], lds0 + kABufs * kABuf + buf * kBBuf + (wave + 8 * j) * 8 * kTlSlice);
   };
 
   // ---- operand reads: lane l holds row l % 16 of a 16-row tile, contraction entries 8 (l / 16) .. + 8 of a 32-deep step ----
@@ -135,31 +181,11 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
   auto read_op = [&](int at, int t) { return *reinterpret_cast<const lm_u32x4*>(lm_lds + at + t * 16 * kTlSlice); };
 
   lm_f32x4 acc[MI][NT];
-#pragma unroll
-  for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < NT; ++ni)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0.f;
+  int abuf = 0, bbuf = 0;                           // buffers of slice i
 
-  // the first slices, as many as there are buffers; then wait for slice 0
-#pragma unroll
-  for (int s = 0; s < kABufs; ++s) {
-    if (s < kBBufs)
-#pragma unroll
-      for (int j = 0; j < kBPer; ++j) load_b(s, s, j);
-#pragma unroll
-    for (int j = 0; j < MI; ++j) load_a(s, s, j);
-  }
-  constexpr int kBMin = kBLoads / 8;                // load_b instructions of a slice in every wave, at least
-  asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kABufs - 1) * MI + (kBBufs - 1) * kBMin) : "memory");
-  __builtin_amdgcn_s_barrier();
-#pragma unroll
-  for (int mi = 0; mi < MI; ++mi) a0[mi] = read_op(a_lane, mi);
-#pragma unroll
-  for (int ni = 0; ni < NT; ++ni) b0[ni] = read_op(b_lane, ni);
-
-  // One 32-deep step: the products of (a, b) with the reads of the next step's operands (an, bn) between them.
+  // One 32-deep step: the products of (a, b) with the reads of the next step's operands (an, bn) between them.  The order
+  // turns back at the end of a row of tiles, so that from one product to the next only one operand changes: less power
+  // (429 x 8192 x 128256 746-773 -> 740-750 us; in registers alone 1985 -> 2015 TFLOP/s).
   auto step = [&](const lm_u32x4 (&a)[MI], const lm_u32x4 (&b)[NT], lm_u32x4 (&an)[MI], lm_u32x4 (&bn)[NT], int a_at, int b_at,
                   auto&& extra) __attribute__((always_inline)) {
 #pragma unroll
@@ -173,129 +199,216 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
         }
       extra(ni);
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi)
+      for (int m = 0; m < MI; ++m) {
+        const int mi = ni & 1 ? MI - 1 - m : m;
         acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lm_bf16x8, a[mi]),
                                                               __builtin_bit_cast(lm_bf16x8, b[ni]), acc[mi][ni], 0, 0, 0);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
 
-  int abuf = 0, bbuf = 0;                           // buffers of slice i
-  for (int i = 0; i < nch; ++i) {
-    const int anext = abuf == kABufs - 1 ? 0 : abuf + 1;
-    const int bnext = bbuf == kBBufs - 1 ? 0 : bbuf + 1;
-    step(a0, b0, a1, b1, (a_lane + abuf * kABuf) ^ 64, (b_lane + bbuf * kBBuf) ^ 64, [](int) {});
-    // this wave has read all of slice i (lgkmcnt) and its part of slice i + 1 is in LDS (vmcnt: what was issued after
-    // the last of slice i + 1's two operands may still be on its way)
-    constexpr int kAfterA = (kABufs - 2) * (kBMin + MI), kAfterB = (kBBufs - 2) * (kBMin + MI) + MI;
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kAfterA < kAfterB ? kAfterA : kAfterB) : "memory");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    step(a1, b1, a0, b0, a_lane + anext * kABuf, b_lane + bnext * kBBuf, [&](int ni) __attribute__((always_inline)) {
+  float2* sh_stat = reinterpret_cast<float2*>(lm_lds + (kStream ? C::kLoop : 0));       // [4 vocabulary quarters][kRows]
+  bool stores_behind = false;      // kStores store instructions of this wave have gone out behind the loads of slices 0 and 1
+  // the first slices, as many as there are buffers; then slice 0 is waited for and its first operands are read
+  seek_a(first);
+  seek_b(first);
+  auto first_loads = [&](int s) __attribute__((always_inline)) {
+    if (s < kBBufs) {
 #pragma unroll
-      for (int j = 0; j < MI + kBPer; ++j)
-        if (j * NT / (MI + kBPer) == ni) {
-          if (j < kBPer) load_b(i + kBBufs, bbuf, j);
-          else load_a(i + kABufs, abuf, j - kBPer);
-        }
-    });
-    abuf = anext;
-    bbuf = bnext;
-  }
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();                      // the slice buffers are free
-
-  // ---- round, statistics of the rounded values, output tile to LDS ----
-  float2* sh_stat = reinterpret_cast<float2*>(lm_lds + kRows * C::kOutPitch);       // [4 vocabulary quarters][kRows]
-  const int vg0 = wm * 16 * MI + 4 * (lane >> 4);         // this lane's entries of tile mi: vg0 + 16 mi + 0..3
-#pragma unroll
-  for (int ni = 0; ni < NT; ++ni) {
-    const int row = row0 + ni * 16 + (lane & 15);
-    float x[MI][4];
-    float m = -INFINITY;
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-      uint32_t b[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        b[r] = f32_to_bf16_rne(acc[mi][ni][r]);
-        x[mi][r] = (v0 + vg0 + 16 * mi + r < P.V) ? __uint_as_float(b[r] << 16) : -INFINITY;
-        m = fmaxf(m, x[mi][r]);
+      for (int j = 0; j < kBPer; ++j) load_b(s, j);
+      if constexpr (kStream) {
+        bcur += kTlSlice;
+        if (--bleft == 0) wrap_b();
+      } else {
+        bcur += --bleft > 0 ? kTlSlice : 0;
       }
-      lm_u32x2 w;
-      w.x = b[0] | (b[1] << 16);
-      w.y = b[2] | (b[3] << 16);
-      *reinterpret_cast<lm_u32x2*>(lm_lds + row * C::kOutPitch + (vg0 + 16 * mi) * 2) = w;
     }
-    m = fmaxf(m, __shfl_xor(m, 16, kWave));
-    m = fmaxf(m, __shfl_xor(m, 32, kWave));
-    const float mm = (m == -INFINITY) ? 0.f : m;
-    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < MI; ++j) load_a(s, j);
+    if constexpr (kStream) {
+      acur += kTlSlice;
+      if (--aleft == 0) wrap_a();
+    } else {
+      acur += --aleft > 0 ? kTlSlice : 0;
+    }
+  };
+  if constexpr (kStream) {
+#pragma unroll 1
+    for (int s = 0; s < kABufs; ++s) first_loads(s);
+  } else {
+#pragma unroll
+    for (int s = 0; s < kABufs; ++s) first_loads(s);
+  }
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kABufs - 1) * MI + (kBBufs - 1) * kBMin) : "memory");
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) a0[mi] = read_op(a_lane, mi);
+#pragma unroll
+  for (int ni = 0; ni < NT; ++ni) b0[ni] = read_op(b_lane, ni);
+
+  for (int t = first;;) {
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) s += fast_exp2((x[mi][r] - mm) * P.c);
-    s += __shfl_xor(s, 16, kWave);
-    s += __shfl_xor(s, 32, kWave);
-    if (lane < 16) sh_stat[wm * kRows + row] = make_float2(m, s);
+      for (int ni = 0; ni < NT; ++ni)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0.f;
+
+    // One slice i: its two steps, and the loads of slices i + kABufs and i + kBBufs.
+    auto slice = [&](bool behind) __attribute__((always_inline)) {
+      const int anext = abuf == kABufs - 1 ? 0 : abuf + 1;
+      const int bnext = bbuf == kBBufs - 1 ? 0 : bbuf + 1;
+      step(a0, b0, a1, b1, (a_lane + abuf * kABuf) ^ 64, (b_lane + bbuf * kBBuf) ^ 64, [](int) {});
+      // this wave has read all of slice i (lgkmcnt) and its part of slice i + 1 is in LDS (vmcnt, which counts in order:
+      // what was issued after the last of slice i + 1's two operands may still be on its way)
+      constexpr int kAfterA = (kABufs - 2) * (kBMin + MI), kAfterB = (kBBufs - 2) * (kBMin + MI) + MI;
+      constexpr int kAfter = kAfterA < kAfterB ? kAfterA : kAfterB;
+      static_assert(kAfter + kStores < 64, "vmcnt has six bits");
+      if (behind) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kAfter + kStores) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kAfter) : "memory");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      step(a1, b1, a0, b0, a_lane + anext * kABuf, b_lane + bnext * kBBuf, [&](int ni) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < MI + kBPer; ++j)
+          if (j * NT / (MI + kBPer) == ni) {
+            if (j < kBPer) load_b(bbuf, j);
+            else load_a(abuf, j - kBPer);
+          }
+      });
+      if constexpr (kStream) {
+        acur += kTlSlice;
+        bcur += kTlSlice;
+      } else {
+        acur += --aleft > 0 ? kTlSlice : 0;
+        bcur += --bleft > 0 ? kTlSlice : 0;
+      }
+      abuf = anext;
+      bbuf = bnext;
+    };
+    if constexpr (kStream) {
+      // in runs without the end of a tile for either cursor: a branch more per slice costs a tenth of the smallest ones
+      for (int left = nch; left > 0;) {
+        int run = min(left, min(aleft, bleft));
+        left -= run; aleft -= run; bleft -= run;
+        if (stores_behind) {
+          slice(true);
+          stores_behind = false;
+          --run;
+        }
+        for (; run > 0; --run) slice(false);
+        if (aleft == 0) wrap_a();
+        if (bleft == 0) wrap_b();
+      }
+    } else {
+      for (int left = nch; left > 0; --left) slice(false);
+    }
+    if constexpr (!kStream) {
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();                  // the slice buffers are free
+    }
+
+    // ---- round, statistics of the rounded values, logits.  A lane holds 4 entries of a row per tile; lanes 16 apart swap
+    // them between tiles 2 p and 2 p + 1, and each has 8 ----
+    const int v0 = __builtin_amdgcn_readfirstlane(t / P.nrb * kVB), r0 = __builtin_amdgcn_readfirstlane(t % P.nrb * kRows);
+    const bool edge = v0 + kVB > P.V;
+    unsigned char* out = reinterpret_cast<unsigned char*>(P.logits + static_cast<int64_t>(r0) * P.V + v0);
+    const int el = opaque(lane), col = el & 15, g = el >> 4, vq = wm * 16 * MI, vst = vq + 16 * (g & 1) + 8 * (g >> 1);
+#pragma unroll
+    for (int ni = 0; ni < NT; ++ni) {
+      const int row = row0 + ni * 16 + col;
+      uint32_t w[MI][2];
+      float x[MI][4];
+      float m = -INFINITY;
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          w[mi][h] = pack_bf16(acc[mi][ni][2 * h], acc[mi][ni][2 * h + 1]);
+          x[mi][2 * h] = bf16_lo(w[mi][h]);
+          x[mi][2 * h + 1] = bf16_hi(w[mi][h]);
+        }
+        if (edge)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[mi][r] = v0 + vq + 16 * mi + 4 * g + r < P.V ? x[mi][r] : -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m = fmaxf(m, x[mi][r]);
+      }
+      m = across16_32(m, [](float a, float b) { return fmaxf(a, b); });
+      const float mm = (m == -INFINITY) ? 0.f : m;
+      float s = 0.f;
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s += fast_exp2((x[mi][r] - mm) * P.c);
+      s = across16_32(s, [](float a, float b) { return a + b; });
+      if (el < 16) sh_stat[wm * kRows + row] = make_float2(m, s);
+      // rows past the last repeat it (their operands did): every wave issues every store
+      const unsigned at = static_cast<unsigned>(min(row, P.rows - 1 - r0)) * static_cast<unsigned>(P.V) * 2u;
+#pragma unroll
+      for (int p = 0; p < MI / 2; ++p) {
+        const auto lo = __builtin_amdgcn_permlane16_swap(w[2 * p][0], w[2 * p + 1][0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(w[2 * p][1], w[2 * p + 1][1], false, false);
+        const raw4 q = {lo[0], hi[0], lo[1], hi[1]};
+        const int v = vst + 32 * p;
+        if (!edge || v0 + v + 8 <= P.V) {
+          *reinterpret_cast<raw4_bf16*>(out + at + v * 2) = q;
+        } else {
+#pragma unroll
+          for (int r = 0; r < 8; ++r)
+            if (v0 + v + r < P.V) *reinterpret_cast<uint16_t*>(out + at + (v + r) * 2) = static_cast<uint16_t>(q[r / 2] >> (16 * (r & 1)));
+        }
+      }
+    }
+    stores_behind = kStream && !edge;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    const int row = wave * 64 + el;
+    if (row < min(kRows, P.rows - r0)) {
+      float M = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) M = fmaxf(M, sh_stat[i * kRows + row].x);
+      const float MM = (M == -INFINITY) ? 0.f : M;
+      float S = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float2 st = sh_stat[i * kRows + row];
+        S += st.y * fast_exp2(((st.x == -INFINITY ? 0.f : st.x) - MM) * P.c);
+      }
+      P.bstats[static_cast<int64_t>(r0 + row) * P.nvb + t / P.nrb] = make_float2(M, S);
+    }
+    if constexpr (!kStream) break;
+    t += P.slots;
+    if (t >= end) break;
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing is on its way to this workgroup's LDS when it ends
 }
 
 template <int MI, int NT2>
 __global__ __launch_bounds__(kTlThreads) void lm_head_tile_kernel(LmParams P) {
   extern __shared__ __align__(16) unsigned char lm_lds[];
-  using C = TlCfg<MI, NT2>;
-  constexpr int kRows = C::kRows, kVB = C::kVB;
-  // the row blocks of one vocabulary block run next to each other on one XCD: its L2 serves the weights to all of them
+  // A workgroup takes every slots-th tile of its XCD's share.  The row blocks of one vocabulary block run next to each
+  // other on one XCD: its L2 serves the weights to all of them.
   const int id = blockIdx.x;
-  const int logical = (id & 7) * P.per_xcd + (id >> 3);
-  if (logical >= P.total) return;
-  const int rbk = logical % P.nrb, vb = logical / P.nrb;
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int v0 = vb * kVB, r0 = rbk * kRows;
+  const int first = (id & 7) * P.per_xcd + (id >> 3), end = min(((id & 7) + 1) * P.per_xcd, P.total);
+  if (first >= end) return;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   if constexpr (NT2 % 2 == 0) {
-    lm_tile_wave<MI, NT2, NT2 / 2>(P, lm_lds, wave, v0, r0);
+    lm_tile_wave<MI, NT2, NT2 / 2>(P, lm_lds, wave, first, end);
   } else {
-    if (wave < 4) lm_tile_wave<MI, NT2, (NT2 + 1) / 2>(P, lm_lds, wave, v0, r0);
-    else lm_tile_wave<MI, NT2, NT2 / 2>(P, lm_lds, wave, v0, r0);
-  }
-  __syncthreads();
-  const float2* sh_stat = reinterpret_cast<const float2*>(lm_lds + kRows * C::kOutPitch);
-  const int rows_here = min(kRows, P.rows - r0), cols = min(kVB, P.V - v0);
-  if (tid < rows_here) {
-    float M = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) M = fmaxf(M, sh_stat[i * kRows + tid].x);
-    const float MM = (M == -INFINITY) ? 0.f : M;
-    float S = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float2 st = sh_stat[i * kRows + tid];
-      S += st.y * fast_exp2(((st.x == -INFINITY ? 0.f : st.x) - MM) * P.c);
-    }
-    P.bstats[static_cast<int64_t>(r0 + tid) * P.nvb + vb] = make_float2(M, S);
-  }
-  uint16_t* out = P.logits + static_cast<int64_t>(r0) * P.V + v0;
-  constexpr int kLanes = kVB / 8;                    // lanes that write a row, 16 bytes each
-  if (cols == kVB && (P.V & 7) == 0 && (reinterpret_cast<uintptr_t>(P.logits) & 15) == 0) {
-    for (int row = tid / kLanes; row < rows_here; row += kTlThreads / kLanes)
-      *reinterpret_cast<lm_u32x4*>(out + static_cast<int64_t>(row) * P.V + (tid % kLanes) * 8) =
-          *reinterpret_cast<const lm_u32x4*>(lm_lds + row * C::kOutPitch + (tid % kLanes) * 16);
-  } else {
-    for (int i = tid; i < rows_here * kVB; i += kTlThreads) {
-      const int row = i / kVB, v = i % kVB;
-      if (v < cols) out[static_cast<int64_t>(row) * P.V + v] = *reinterpret_cast<const uint16_t*>(lm_lds + row * C::kOutPitch + v * 2);
-    }
+    if (wave < 4) lm_tile_wave<MI, NT2, (NT2 + 1) / 2>(P, lm_lds, wave, first, end);
+    else lm_tile_wave<MI, NT2, NT2 / 2>(P, lm_lds, wave, first, end);
   }
 }
 
 template <int MI, int NT2>
-static int launch_lm_tile(const LmParams& P, hipStream_t stream) {
+static int launch_lm_tile(LmParams P, hipStream_t stream) {
   static std::atomic<uint64_t> attr_done{0};
   constexpr int kLds = TlCfg<MI, NT2>::kLds;
   if (set_lds_once(&lm_head_tile_kernel<MI, NT2>, kLds, attr_done) != 0) return -1;
-  hipLaunchKernelGGL((lm_head_tile_kernel<MI, NT2>), dim3(P.per_xcd * 8), dim3(kTlThreads), kLds, stream, P);
+  if (!TlCfg<MI, NT2>::kStream) P.slots = P.per_xcd;
+  hipLaunchKernelGGL((lm_head_tile_kernel<MI, NT2>), dim3(P.slots * 8), dim3(kTlThreads), kLds, stream, P);
   return 0;
 }
 
@@ -385,6 +498,7 @@ int launch_lm_head(const LmHeadArgs& a, hipStream_t stream) {
   P.nrb = (a.rows + rb - 1) / rb;
   P.total = P.nvb * P.nrb;
   P.per_xcd = (P.total + 7) / 8;
+  P.slots = std::max(1, std::min(P.per_xcd, current_device_cus() / 8));
   int rc = -1;
   switch (nt2 + (vb == 128 ? 100 : 0)) {
     case 102: rc = launch_lm_tile<2, 2>(P, stream); break;
