@@ -193,7 +193,8 @@ int32_t spec_accept(
 /* spec_accept with explicit launch choices, for tests and sweeps (same arguments, same results).
  * The library's choice: linear drafts (parent == NULL) take a statistics pass over all rows and then one
  * kernel that repeats the scalar accept tests in every workgroup and spreads the single vocabulary-wide
- * draw a chain needs over the chip (path 3); large batches use a statistics pass that stops reading a
+ * draw a chain needs over the chip (path 3); small batches do both in one launch, a workgroup per vocabulary
+ * segment of a row pair (library's choice only); large batches use a statistics pass that stops reading a
  * request's rows at its first rejection (path 4).  Trees with bf16 logit rows (16-byte aligned, V a multiple
  * of 8) and a batch of at most one request per compute unit are walked by a cluster of workgroups per
  * request that keep slices of the walked rows in registers or LDS and read, besides those, only the rows of a

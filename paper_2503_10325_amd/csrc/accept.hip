@@ -22,7 +22,35 @@
 #include "common.h"
 #include "kernels.h"
 
+#include <algorithm>
+#include <chrono>
+
 namespace specv {
+
+// ----------------------------------------------------------------------------------
+// messages between the workgroups of one launch
+// ----------------------------------------------------------------------------------
+unsigned next_message_tag() {
+  static std::atomic<unsigned> calls{static_cast<unsigned>(std::chrono::steady_clock::now().time_since_epoch().count() * 2654435761u >> 9)};
+  return calls.fetch_add(1, std::memory_order_relaxed) * kTagsPerCall;
+}
+
+bool stream_captures(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+__global__ __launch_bounds__(256) void clear_messages_kernel(unsigned long long* __restrict__ words, int64_t n) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * 256) words[i] = 0ull;
+}
+
+void clear_messages(unsigned long long* words, int64_t n, hipStream_t stream) {
+  hipLaunchKernelGGL(clear_messages_kernel, dim3(static_cast<unsigned>(std::min<int64_t>((n + 255) / 256, 512))), dim3(256), 0, stream, words, n);
+}
 
 // ----------------------------------------------------------------------------------
 // row statistics
@@ -845,6 +873,147 @@ static int linear_unit_classes(int B, int V, int n_cu) {
   return (per + kLinBlock - 1) / kLinBlock * kLinBlock;
 }
 
+// Weights of a thread's eight classes in each block of unit k (their loads issued together) and the per-block fp32 sums.
+// Identical arithmetic wherever it is called.
+template <int TDT, int QDT, int BPU>
+__device__ __forceinline__ void unit_weights_from(const WalkRows& R, const Raw8<TDT, BPU>& rp, const Raw8<QDT, BPU>& rq, int k, int L,
+                                                  int V, float c, float (&w)[BPU][8], float (&lsf)[BPU]) {
+  const float no_scale[1] = {0.f};               // 1/R_k of lower levels: none exist at levels 0 and 1
+  const int tid = threadIdx.x;
+  auto e0 = [&](int i) { return (k * BPU + i) * kLinBlock + tid * 8; };
+#pragma unroll
+  for (int i = 0; i < BPU; ++i) {
+    lsf[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) w[i][j] = 0.f;
+    if ((k * BPU + i) * kLinBlock + __builtin_amdgcn_readfirstlane(tid) * 8 < V) {       // (else none of this wave's classes exist)
+      float lp[8], lq[8], x[8];
+      take8<false>(R.t_base, R.t_off, e0(i), V, rp, i, lp);
+      if (L > 0) take8<false>(R.q_base, R.q_off, e0(i), V, rq, i, lq);
+      weights_from(R, lp, lq, 8, c, L, no_scale, x);
+      const int first = __any(e0(i) > V - 8) ? e0(i) - first8(e0(i), V) : 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        w[i][j] = j >= first ? x[j] : 0.f;
+        lsf[i] += w[i][j];
+      }
+    }
+  }
+}
+
+template <int TDT, int QDT, int BPU>
+__device__ __forceinline__ void unit_weights(const WalkRows& R, int k, int L, int V, float c, float (&w)[BPU][8], float (&lsf)[BPU]) {
+  const int tid = threadIdx.x;
+  auto t_off = [&](int) { return R.t_off; };
+  auto q_off = [&](int) { return R.q_off; };
+  auto e0 = [&](int i) { return (k * BPU + i) * kLinBlock + tid * 8; };
+  Raw8<TDT, BPU> rp;
+  Raw8<QDT, BPU> rq;
+  issue8(R.t_base, t_off, e0, V, rp);
+  if (L > 0) issue8(R.q_base, q_off, e0, V, rq);
+  unit_weights_from<TDT, QDT, BPU>(R, rp, rq, k, L, V, c, w, lsf);
+}
+
+// Per-block totals from the per-thread sums: fp64 across lanes and waves in a fixed order; in every thread.
+template <int BPU>
+__device__ __forceinline__ void block_totals(const float (&lsf)[BPU], double (&sh_bw)[BPU][kLinWaves], double (&tot)[BPU]) {
+  const int wave = threadIdx.x >> 6;
+  __syncthreads();                  // earlier readers of sh_bw are done
+#pragma unroll
+  for (int i = 0; i < BPU; ++i) {
+    tot[i] = 0.0;
+    sh_bw[i][wave] = wave_sum(static_cast<double>(lsf[i]));      // every lane stores the same value
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < BPU; ++i)
+#pragma unroll
+    for (int v = 0; v < kLinWaves; ++v) tot[i] += sh_bw[i][v];
+}
+
+// Every wave alike: lane l holds the sum of `per` blocks from l * per on (one block up to 262144 classes), scanned;
+// returns the total.
+__device__ __forceinline__ double scan_blocks(const double* sh_part, int nblocks, double& mine, double& inc_b) {
+  const int lane = threadIdx.x & 63, per = (nblocks + kWave - 1) / kWave;
+  mine = 0.0;
+  for (int k = lane * per; k < min(nblocks, (lane + 1) * per); ++k) mine += sh_part[k];
+  inc_b = wave_scan(mine);
+  return lane_f64(inc_b, kWave - 1);
+}
+
+// Block of the draw: the first whose running sum passes the target (rounding left no crossing: the last with mass), and
+// the mass ahead of it.
+__device__ __forceinline__ int block_of_draw(const double* sh_part, int nblocks, double mine, double inc_b, double target,
+                                             double& before) {
+  const int per = (nblocks + kWave - 1) / kWave;
+  const unsigned long long hit = __ballot(inc_b > target && mine > 0.0);
+  const unsigned long long pos = __ballot(mine > 0.0);
+  const int l = hit ? __ffsll(static_cast<long long>(hit)) - 1 : (pos ? 63 - __clzll(static_cast<long long>(pos)) : 0);
+  before = 0.0;
+  if (l > 0) before = lane_f64(inc_b, l - 1);
+  int kb_hit = l * per;
+  if (per > 1) {
+    int k_pos = kb_hit;
+    double run = before, run_pos = before;
+    bool found = false;
+    for (int k = l * per; k < min(nblocks, (l + 1) * per) && !found; ++k) {
+      const double sk = sh_part[k];
+      if (sk > 0.0) { k_pos = k; run_pos = run; }
+      found = sk > 0.0 && run + sk > target;
+      run += sk;
+    }
+    kb_hit = k_pos;
+    before = run_pos;
+  }
+  return kb_hit;
+}
+
+// The class of the draw inside block kb_hit, from this thread's eight weights wh (classes e0 on); the wave it falls in
+// writes it.
+__device__ __forceinline__ void draw_class(const float (&wh)[8], int e0, int kb_hit, double before, double target, int V,
+                                           double* sh_wave, int32_t* out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float lsh = 0.f;                    // summed exactly as the block sums were
+  int my_last = -1;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) { lsh += wh[j]; if (wh[j] > 0.f) my_last = e0 + j; }
+  const double ls = static_cast<double>(lsh);
+  const double inc = wave_scan(ls);   // inclusive scan of the lane sums inside the wave
+  __syncthreads();                    // earlier readers of sh_wave are done
+  sh_wave[wave] = lane_f64(inc, 63);
+  __syncthreads();
+  // the wave the crossing falls in (or, when rounding left none, the last one with a positive class) names the class
+  int v_hit = -1, v_pos = 0;
+  double run = before, acc_w = before;     // mass ahead of this wave; of the wave looked at
+#pragma unroll
+  for (int v = 0; v < kLinWaves; ++v) {
+    const double sv = sh_wave[v];
+    if (v == wave) run = acc_w;
+    acc_w += sv;
+    if (v_hit < 0 && sv > 0.0 && acc_w > target) v_hit = v;
+    if (sv > 0.0) v_pos = v;
+  }
+  if (wave != (v_hit >= 0 ? v_hit : v_pos)) return;
+  int found;
+  const unsigned long long cross = __ballot(run + inc > target && lsh > 0.f);
+  if (cross) {
+    // every lane works out its own candidate: no lane-dependent branch ahead of the broadcast
+    int tok = -1;
+    double acc = run + (inc - ls);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      acc += static_cast<double>(wh[j]);
+      if (tok < 0 && acc > target && wh[j] > 0.f) tok = e0 + j;
+    }
+    if (tok < 0) tok = my_last;       // rounding inside the lane: its last positive class
+    found = __builtin_amdgcn_readlane(tok, __ffsll(static_cast<long long>(cross)) - 1);
+  } else {                            // rounding: the last positive class of the wave
+    const unsigned long long pos = __ballot(my_last >= 0);
+    found = pos ? __builtin_amdgcn_readlane(my_last, 63 - __clzll(static_cast<long long>(pos))) : min(V - 1, kb_hit * kLinBlock);
+  }
+  if (lane == 0 && out) *out = found;
+}
+
 // What bounds it: latency - offsets, node arrays, statistics and logits of the drafted tokens, weights, hand-over,
 // block sums, the block of the draw are seven dependent trips to memory at most, so the work between two trips is kept
 // short: no barrier between the node arrays and the loads they lead to, every wave takes the accept decisions itself
@@ -879,8 +1048,6 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
   __shared__ double sh_part[kLinMaxUnits];
   __shared__ int sh_last;
   __shared__ double sh_bw[BPU][kLinWaves];
-  const float no_scale[1] = {0.f};               // 1/R_k of lower levels: none exist at levels 0 and 1
-
   const double u_res = static_cast<double>(P.u_resample[b]);
   // (1) the last wave: node arrays (indices clamped: a bad entry gives a wrong answer for that request, never a wild
   // read) and the two logits of every drafted token; the others: the merged statistics of the n+1 target rows and the
@@ -954,51 +1121,11 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
     level = 1;
   }
 
-  // Weights of this thread's eight classes in each block of unit k (their loads issued together) and the per-block fp32
-  // sums.  Identical arithmetic wherever it is called.
   const int nblocks = (V + kLinBlock - 1) / kLinBlock;
-  auto unit_weights = [&](int k, int L, float (&w)[BPU][8], float (&lsf)[BPU]) {
-    auto t_off = [&](int) { return R.t_off; };
-    auto q_off = [&](int) { return R.q_off; };
-    auto e0 = [&](int i) { return (k * BPU + i) * kLinBlock + tid * 8; };
-    Raw8<TDT, BPU> rp;
-    Raw8<QDT, BPU> rq;
-    issue8(R.t_base, t_off, e0, V, rp);
-    if (L > 0) issue8(R.q_base, q_off, e0, V, rq);
-#pragma unroll
-    for (int i = 0; i < BPU; ++i) {
-      lsf[i] = 0.f;
-      float lp[8], lq[8];
-      take8<false>(R.t_base, R.t_off, e0(i), V, rp, i, lp);
-      if (L > 0) take8<false>(R.q_base, R.q_off, e0(i), V, rq, i, lq);
-      weights_from(R, lp, lq, 8, c, L, no_scale, w[i]);
-      if (__any(e0(i) > V - 8)) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[i][j] = first8(e0(i), V) + j >= e0(i) ? w[i][j] : 0.f;
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) lsf[i] += w[i][j];
-    }
-  };
-  // per-block totals from the per-thread sums: fp64 across lanes and waves in a fixed order; in every thread
-  auto block_totals = [&](const float (&lsf)[BPU], double (&tot)[BPU]) {
-    __syncthreads();                  // earlier readers of sh_bw are done
-#pragma unroll
-    for (int i = 0; i < BPU; ++i) {
-      tot[i] = 0.0;
-      sh_bw[i][wave] = wave_sum(static_cast<double>(lsf[i]));      // every lane stores the same value
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < BPU; ++i)
-#pragma unroll
-      for (int v = 0; v < kLinWaves; ++v) tot[i] += sh_bw[i][v];
-  };
-
   float w[BPU][8], lsf[BPU];
   double tot[BPU];
-  unit_weights(unit, level, w, lsf);
-  block_totals(lsf, tot);
+  unit_weights<TDT, QDT, BPU>(R, unit, level, V, c, w, lsf);
+  block_totals(lsf, sh_bw, tot);
   if (U == 1) {                       // nothing to hand over
     if (wave == 0) {
 #pragma unroll
@@ -1022,16 +1149,8 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
     for (int k = tid; k < nblocks; k += kLinThreads) sh_part[k] = ld_dev(&partial[static_cast<int64_t>(b) * nblocks + k]);
   }
   __syncthreads();
-  // Every wave alike: lane l holds the sum of `per` blocks from l * per on (one block up to 262144 classes), scanned.
-  const int per = (nblocks + kWave - 1) / kWave;
   double mine, inc_b;
-  auto scan_blocks = [&]() {
-    mine = 0.0;
-    for (int k = lane * per; k < min(nblocks, (lane + 1) * per); ++k) mine += sh_part[k];
-    inc_b = wave_scan(mine);
-  };
-  scan_blocks();
-  double total = lane_f64(inc_b, kWave - 1);
+  double total = scan_blocks(sh_part, nblocks, mine, inc_b);
   bool redrawn = false;
   if (level == 1 && !(total > 0.0)) {
     // a residual without mass leaves the distribution as it was: draw from p (sums redone here; rare)
@@ -1039,8 +1158,8 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
     R.have_q = 0;
     redrawn = true;
     for (int k = 0; k < U; ++k) {
-      unit_weights(k, 0, w, lsf);
-      block_totals(lsf, tot);
+      unit_weights<TDT, QDT, BPU>(R, k, 0, V, c, w, lsf);
+      block_totals(lsf, sh_bw, tot);
       __syncthreads();
       if (tid == 0) {
 #pragma unroll
@@ -1049,33 +1168,11 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
       }
     }
     __syncthreads();
-    scan_blocks();
-    total = lane_f64(inc_b, kWave - 1);
+    total = scan_blocks(sh_part, nblocks, mine, inc_b);
   }
   const double target = u_res * total;
-  // block of the draw: the first whose running sum passes the target (rounding left no crossing: the last with mass)
-  int kb_hit = 0;
-  double before = 0.0;
-  {
-    const unsigned long long hit = __ballot(inc_b > target && mine > 0.0);
-    const unsigned long long pos = __ballot(mine > 0.0);
-    const int l = hit ? __ffsll(static_cast<long long>(hit)) - 1 : (pos ? 63 - __clzll(static_cast<long long>(pos)) : 0);
-    if (l > 0) before = lane_f64(inc_b, l - 1);
-    kb_hit = l * per;
-    if (per > 1) {
-      int k_pos = kb_hit;
-      double run = before, run_pos = before;
-      bool found = false;
-      for (int k = l * per; k < min(nblocks, (l + 1) * per) && !found; ++k) {
-        const double sk = sh_part[k];
-        if (sk > 0.0) { k_pos = k; run_pos = run; }
-        found = sk > 0.0 && run + sk > target;
-        run += sk;
-      }
-      kb_hit = k_pos;
-      before = run_pos;
-    }
-  }
+  double before;
+  const int kb_hit = block_of_draw(sh_part, nblocks, mine, inc_b, target, before);
   // that block alone: this thread's eight weights (kept, when the block is of this workgroup's own unit), the wave
   // sums in LDS
   const int e_hit = kb_hit * kLinBlock + tid * 8;
@@ -1092,47 +1189,10 @@ __global__ __launch_bounds__(kLinThreads, 2) void accept_linear_kernel(AcceptPar
       }
   } else {
     e0 = e_hit;
+    const float no_scale[1] = {0.f};
     if (e0 < V) weights8(R, e0, V, c, level, no_scale, wh);
   }
-  float lsh = 0.f;                    // summed exactly as the block sums were
-  int my_last = -1;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) { lsh += wh[j]; if (wh[j] > 0.f) my_last = e0 + j; }
-  const double ls = static_cast<double>(lsh);
-  const double inc = wave_scan(ls);   // inclusive scan of the lane sums inside the wave
-  __syncthreads();                    // earlier readers of sh_bw are done
-  sh_bw[0][wave] = lane_f64(inc, 63);
-  __syncthreads();
-  // the wave the crossing falls in (or, when rounding left none, the last one with a positive class) names the class
-  int v_hit = -1, v_pos = 0;
-  double run = before, acc_w = before;     // mass ahead of this wave; of the wave looked at
-#pragma unroll
-  for (int v = 0; v < kLinWaves; ++v) {
-    const double sv = sh_bw[0][v];
-    if (v == wave) run = acc_w;
-    acc_w += sv;
-    if (v_hit < 0 && sv > 0.0 && acc_w > target) v_hit = v;
-    if (sv > 0.0) v_pos = v;
-  }
-  if (wave != (v_hit >= 0 ? v_hit : v_pos)) return;
-  int found;
-  const unsigned long long cross = __ballot(run + inc > target && lsh > 0.f);
-  if (cross) {
-    // every lane works out its own candidate: no lane-dependent branch ahead of the broadcast
-    int tok = -1;
-    double acc = run + (inc - ls);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      acc += static_cast<double>(wh[j]);
-      if (tok < 0 && acc > target && wh[j] > 0.f) tok = e0 + j;
-    }
-    if (tok < 0) tok = my_last;       // rounding inside the lane: its last positive class
-    found = __builtin_amdgcn_readlane(tok, __ffsll(static_cast<long long>(cross)) - 1);
-  } else {                            // rounding: the last positive class of the wave
-    const unsigned long long pos = __ballot(my_last >= 0);
-    found = pos ? __builtin_amdgcn_readlane(my_last, 63 - __clzll(static_cast<long long>(pos))) : min(V - 1, kb_hit * kLinBlock);
-  }
-  if (lane == 0 && depth < P.out_stride) P.out_tokens[static_cast<int64_t>(b) * P.out_stride + depth] = found;
+  draw_class(wh, e0, kb_hit, before, target, V, sh_bw[0], depth < P.out_stride ? P.out_tokens + static_cast<int64_t>(b) * P.out_stride + depth : nullptr);
 }
 
 template <int TDT, int QDT>
@@ -1140,6 +1200,369 @@ static auto linear_kernel(int blocks) {
   static_assert(kLinMaxBlocks == 4, "one instantiation per number of blocks");
   return blocks == 1 ? accept_linear_kernel<TDT, QDT, 1> : (blocks == 2 ? accept_linear_kernel<TDT, QDT, 2>
        : (blocks == 3 ? accept_linear_kernel<TDT, QDT, 3> : accept_linear_kernel<TDT, QDT, 4>));
+}
+
+// ----------------------------------------------------------------------------------
+// Linear drafts in one launch: accept_chain_kernel.  A workgroup takes one 8192-class segment of the pair (target row j,
+// draft row of node j) of a request, works out the two rows' statistics there and posts them; it gathers those of rows
+// 0 .. j, takes the accept decisions itself, and leaves unless the chain ends at node j.  The workgroups of that pair
+// still hold its logits: they sum the weights of their segments, post the sums, gather the others', and the one whose
+// segment the draw falls into names the class.  Two exchanges instead of a second launch that starts from nothing.
+//
+// Messages are 64-bit words {data : tag}, relaxed device-scope accesses; the tag is the call's own number, so that the
+// workspace needs no clearing (a launch that is being captured is preceded by a kernel that clears them: replays repeat the
+// tag).  Waits are bounded: a workgroup that misses a record after `patience` polls works it out itself, with the same
+// arithmetic in the same order, and goes on; nobody's result depends on who came first.
+//
+// What bounds it: latency.  Offsets, draft row numbers, logits, the two exchanges (a trip each way), the class.
+// ----------------------------------------------------------------------------------
+constexpr int kChainMaxRecords = 512;      // (nodes + 1) x segments of a request: a thread gathers one
+constexpr int kChainWords = 6;             // words of a record: (sum, 2; maximum) of the target and of the draft row
+constexpr int kChainSumWords = 4;          // ... of a segment's weights: two blocks, 2 each
+constexpr int kChainBlocks = 2;            // blocks of 4096 classes in a segment
+
+__device__ __forceinline__ unsigned long long chain_word(unsigned data, unsigned tag) {
+  return (static_cast<unsigned long long>(data) << 32) | tag;
+}
+__device__ __forceinline__ double chain_double(unsigned long long hi, unsigned long long lo) {
+  return __hiloint2double(static_cast<int>(hi >> 32), static_cast<int>(lo >> 32));
+}
+
+struct ChainScratch {
+  float m[2][kLinWaves];
+  double z[2][kLinWaves];
+};
+
+// (maximum, sum of 2^((l - max) c)) of one segment of two rows, from their loads; in every thread.
+template <bool T, bool Q, int TDT, int QDT>
+__device__ __forceinline__ void chain_stats(const WalkRows& R, const Raw8<TDT, kChainBlocks>& rt, const Raw8<QDT, kChainBlocks>& rq, int e_seg,
+                                            int V, float c, ChainScratch& sh, float (&M)[2], double (&Z)[2]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float m[2], sum[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    m[k] = -INFINITY;
+    sum[k] = 0.f;
+    if (k == 0 ? !T : !Q) continue;
+    float x[kChainBlocks][8];
+    auto any = [&](int i) { return e_seg + i * kLinBlock + wave * kWave * 8 < V; };      // this wave has classes of block i
+#pragma unroll
+    for (int i = 0; i < kChainBlocks; ++i) {
+      const int e0 = e_seg + i * kLinBlock + tid * 8;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[i][j] = -INFINITY;
+      if (!any(i)) continue;
+      if (k == 0) take8<false>(R.t_base, R.t_off, e0, V, rt, i, x[i]);
+      else take8<false>(R.q_base, R.q_off, e0, V, rq, i, x[i]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) m[k] = fmaxf(m[k], x[i][j]);
+    }
+    const float mm = (m[k] == -INFINITY) ? 0.f : m[k];
+#pragma unroll
+    for (int i = 0; i < kChainBlocks; ++i)
+      if (any(i))
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum[k] += fast_exp2((x[i][j] - mm) * c);
+  }
+  __syncthreads();                    // earlier readers of sh are done
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (k == 0 ? T : Q) sh.m[k][wave] = wave_max(m[k]);        // every lane stores the same value
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (k == 0 ? !T : !Q) continue;
+    M[k] = sh.m[k][0];
+#pragma unroll
+    for (int w = 1; w < kLinWaves; ++w) M[k] = fmaxf(M[k], sh.m[k][w]);
+    const float MM = (M[k] == -INFINITY) ? 0.f : M[k], mm = (m[k] == -INFINITY) ? 0.f : m[k];
+    double z = static_cast<double>(sum[k]) * static_cast<double>(fast_exp2((mm - MM) * c));
+    if (m[k] == -INFINITY) z = 0.0;
+    sh.z[k][wave] = wave_sum(z);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (k == 0 ? !T : !Q) continue;
+    Z[k] = 0.0;
+#pragma unroll
+    for (int w = 0; w < kLinWaves; ++w) Z[k] += sh.z[k][w];
+  }
+}
+
+// T_STATS: the statistics of the target rows are taken here (else they lie in P.stats); Q_STATS: draft rows are logits.
+template <int TDT, int QDT, bool T_STATS, bool Q_STATS>
+__global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptParams P, unsigned long long* __restrict__ msg,
+                                                                      unsigned long long* __restrict__ sums, unsigned tag, int levels) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int S = P.nseg, V = P.V;
+  const int seg = blockIdx.x % S, bj = blockIdx.x / S, j = bj % levels, b = bj / levels;
+  const int o = P.node_offsets[b];
+  int n = P.node_offsets[b + 1] - o;
+  n = n < 0 ? 0 : min(n, levels - 1);
+  if (j > n) return;
+  const int64_t trow0 = static_cast<int64_t>(o) + b;
+  __builtin_assume(V >= 8);
+  const float c = P.c;
+  constexpr bool q_is_probs = !Q_STATS;
+
+  __shared__ float sh_m[2][kChainMaxRecords];
+  __shared__ double sh_z[2][kChainMaxRecords];
+  __shared__ unsigned char sh_have[kChainMaxRecords];
+  __shared__ float sh_tm[kMaxNodes + 1], sh_qm[kMaxNodes];
+  __shared__ double sh_tinvz[kMaxNodes + 1], sh_qinvz[kMaxNodes];
+  __shared__ int sh_tok[kMaxNodes], sh_qrow[kMaxNodes];
+  __shared__ float sh_lp[kMaxNodes], sh_lq[kMaxNodes], sh_u[kMaxNodes];
+  __shared__ double sh_part[kChainMaxRecords];
+  __shared__ double sh_bw[kChainBlocks][kLinWaves];
+  __shared__ ChainScratch sh_stat;
+
+  // ---- this workgroup's logits, and (last wave) the node arrays with the two logits of every drafted token ----
+  WalkRows R;
+  R.t_base = P.target; R.t_dtype = TDT;
+  R.q_base = P.draft_q; R.q_dtype = QDT; R.q_is_probs = q_is_probs;
+  R.t_off = (trow0 + j) * static_cast<int64_t>(V);
+  R.q_off = 0; R.q_m = 0.f; R.q_invz = 0.0;
+  R.have_q = 0;
+  auto q_off_of = [&](int i) { return static_cast<int64_t>(min(max(P.q_row[o + i], 0), P.n_q_rows - 1)) * V; };
+  auto e_of = [&](int sg) { return [=](int i) { return sg * kChainBlocks * kLinBlock + i * kLinBlock + tid * 8; }; };
+  Raw8<TDT, kChainBlocks> rt;
+  Raw8<QDT, kChainBlocks> rq;
+  if constexpr (T_STATS) issue8(R.t_base, [&](int) { return R.t_off; }, e_of(seg), V, rt);
+  const bool tested = j < n;          // row j has a draft row
+  const double u_res = static_cast<double>(P.u_resample[b]);
+  if (tested) R.q_off = q_off_of(j);
+  if constexpr (Q_STATS) issue8(R.q_base, [&](int) { return R.q_off; }, e_of(seg), V, rq);      // (row n: draft row 0, unused)
+  const int n_seen = min(j + 1, n);   // nodes whose decisions this workgroup takes
+  if (wave == kLinWaves - 1) {
+    for (int i = lane; i < n_seen; i += kWave) {
+      const int x = min(max(P.draft_tokens[o + i], 0), V - 1);
+      const int qr = min(max(P.q_row[o + i], 0), P.n_q_rows - 1);
+      sh_u[i] = P.u_accept[o + i];
+      sh_lp[i] = load_logit(P.target, TDT, (trow0 + i) * static_cast<int64_t>(V) + x);
+      sh_lq[i] = load_logit(P.draft_q, QDT, static_cast<int64_t>(qr) * V + x);
+      sh_tok[i] = x;
+      sh_qrow[i] = qr;
+    }
+  }
+  const int n_rec = (j + 1) * S, own = j * S + seg;
+  if constexpr (!T_STATS) {
+    if (tid < n_rec) {
+      const SegStat st = P.stats[trow0 * S + tid];
+      sh_m[0][tid] = st.m; sh_z[0][tid] = st.z;
+    }
+    if constexpr (!Q_STATS) __syncthreads();
+  }
+  if constexpr (T_STATS || Q_STATS) {
+    float M[2];
+    double Z[2];
+    chain_stats<T_STATS, Q_STATS>(R, rt, rq, seg * kChainBlocks * kLinBlock, V, c, sh_stat, M, Z);
+    if (wave == 0 && lane < kChainWords && (lane < 3 ? T_STATS : (Q_STATS && tested))) {
+      const int k = lane >= 3, part = lane - 3 * k;
+      const double z = k ? Z[1] : Z[0];
+      const unsigned data = part == 2 ? __float_as_uint(k ? M[1] : M[0]) : static_cast<unsigned>(part == 0 ? __double2hiint(z) : __double2loint(z));
+      st_dev(msg + ((trow0 + j) * S + seg) * kChainWords + lane, chain_word(data, tag));
+    }
+    // ---- gather: thread r the record of segment r % S of rows r / S ----
+    bool have = true;
+    if (tid < (n_rec + kWave - 1) / kWave * kWave) {            // (wave-uniform)
+      const bool mine = tid < n_rec && tid != own;
+      const int i = tid / S, sg = tid - i * S;
+      const unsigned long long* from = msg + ((trow0 + min(i, j)) * S + sg) * kChainWords;
+      const bool want_q = Q_STATS && i < n;
+      unsigned long long w[kChainWords];
+#pragma unroll
+      for (int k = 0; k < kChainWords; ++k) w[k] = 0ull;
+      for (int poll = 0;; ++poll) {
+        have = true;
+        if (mine) {
+#pragma unroll
+          for (int k = 0; k < kChainWords; ++k)
+            if (k < 3 ? T_STATS : Q_STATS) w[k] = ld_dev(from + k);
+#pragma unroll
+          for (int k = 0; k < kChainWords; ++k)
+            if (k < 3 ? T_STATS : want_q) have &= static_cast<unsigned>(w[k]) == tag;
+        }
+        if (__all(have) || poll >= P.patience) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      if (tid < n_rec) {
+        sh_have[tid] = have;
+        if (tid == own) {
+          if constexpr (T_STATS) { sh_m[0][tid] = M[0]; sh_z[0][tid] = Z[0]; }
+          if constexpr (Q_STATS) { sh_m[1][tid] = M[1]; sh_z[1][tid] = Z[1]; }
+        } else {
+          if constexpr (T_STATS) { sh_m[0][tid] = __uint_as_float(static_cast<unsigned>(w[2] >> 32)); sh_z[0][tid] = chain_double(w[0], w[1]); }
+          if constexpr (Q_STATS) { sh_m[1][tid] = __uint_as_float(static_cast<unsigned>(w[5] >> 32)); sh_z[1][tid] = chain_double(w[3], w[4]); }
+        }
+      }
+    }
+    if (__syncthreads_or(!have)) {    // records that did not come: worked out here
+      for (int r = 0; r < n_rec; ++r) {
+        if (sh_have[r]) continue;
+        const int i = r / S, sg = r % S;
+        WalkRows X = R;
+        X.t_off = (trow0 + i) * static_cast<int64_t>(V);
+        X.q_off = i < n ? q_off_of(i) : 0;
+        Raw8<TDT, kChainBlocks> xt;
+        Raw8<QDT, kChainBlocks> xq;
+        if constexpr (T_STATS) issue8(X.t_base, [&](int) { return X.t_off; }, e_of(sg), V, xt);
+        if constexpr (Q_STATS) issue8(X.q_base, [&](int) { return X.q_off; }, e_of(sg), V, xq);
+        chain_stats<T_STATS, Q_STATS>(X, xt, xq, sg * kChainBlocks * kLinBlock, V, c, sh_stat, M, Z);
+        if (tid == 0) {
+          if constexpr (T_STATS) { sh_m[0][r] = M[0]; sh_z[0][r] = Z[0]; }
+          if constexpr (Q_STATS) { sh_m[1][r] = M[1]; sh_z[1][r] = Z[1]; }
+        }
+      }
+      __syncthreads();
+    }
+  }
+  // ---- merged statistics of target rows 0 .. j and of the draft rows tested against them ----
+  {
+    const int n_rows = (j + 1) + (Q_STATS ? n_seen : 0);
+    const int sl = tid & 15;
+    for (int r0 = wave * 4; r0 < n_rows; r0 += kLinThreads / 16) {                 // (wave-uniform: whole waves reduce)
+      const int ri = r0 + (lane >> 4);
+      const bool is_q = ri > j, any = ri < n_rows;
+      const int i = is_q ? ri - (j + 1) : ri;
+      float m;
+      double z;
+      merged_stats([&](int sg) -> SegStat {
+        SegStat st;
+        st.m = sh_m[is_q][i * S + sg]; st.pad = 0.f; st.z = sh_z[is_q][i * S + sg];
+        return st;
+      }, any ? S : 0, c, sl, m, z);
+      if (sl == 0 && any) {
+        if (is_q) { sh_qm[i] = m; sh_qinvz[i] = 1.0 / z; }
+        else { sh_tm[i] = m; sh_tinvz[i] = 1.0 / z; }
+      }
+    }
+  }
+  __syncthreads();
+  // ---- the accept decisions on nodes 0 .. j, by every wave (lane i nodes i, i + 64): the chain ends here or not ----
+  auto ratio_of = [&](int i) {
+    return accept_ratio(static_cast<double>(sh_lp[i]), sh_tm[i], sh_tinvz[i], static_cast<double>(sh_lq[i]),
+                        q_is_probs ? 0.f : sh_qm[i], q_is_probs ? 0.0 : sh_qinvz[i], c, q_is_probs);
+  };
+  int rejected = -1;
+  for (int h = 0; h < n_seen && rejected < 0; h += kWave) {
+    const int i = h + lane;
+    bool rej = false;
+    if (i < n_seen) rej = !(static_cast<double>(sh_u[i]) < ratio_of(i));
+    const unsigned long long rm = __ballot(rej);
+    if (rm) rejected = h + __ffsll(static_cast<long long>(rm)) - 1;
+  }
+  if (rejected >= 0 ? rejected < j : j < n) return;
+  const int depth = j;
+  if (seg == 0) {           // everything but the drawn token is known here
+    if (P.dbg_ratio) {
+      for (int i = tid; i < n; i += kLinThreads) P.dbg_ratio[o + i] = i <= depth ? static_cast<float>(ratio_of(i)) : __builtin_nanf("");
+    }
+    for (int i = tid; i < P.out_stride; i += kLinThreads)
+      if (i != depth) P.out_tokens[static_cast<int64_t>(b) * P.out_stride + i] = (i < depth) ? sh_tok[i] : -1;
+    if (tid == 0) {
+      P.accept_len[b] = depth;
+      if (P.stop_node) P.stop_node[b] = depth - 1;
+    }
+  }
+  int level = rejected >= 0;
+  R.t_m = sh_tm[depth]; R.t_invz = sh_tinvz[depth];
+  R.have_q = level;
+  if (Q_STATS && level) { R.q_m = sh_qm[depth]; R.q_invz = sh_qinvz[depth]; }
+  if constexpr (!T_STATS) issue8(R.t_base, [&](int) { return R.t_off; }, e_of(seg), V, rt);
+  if constexpr (!Q_STATS)
+    if (level) issue8(R.q_base, [&](int) { return R.q_off; }, e_of(seg), V, rq);
+
+  // ---- weights of this segment, the sums of all segments ----
+  const int nblocks = (V + kLinBlock - 1) / kLinBlock;
+  float w[kChainBlocks][8], lsf[kChainBlocks];
+  double tot[kChainBlocks];
+  unit_weights_from<TDT, QDT, kChainBlocks>(R, rt, rq, seg, level, V, c, w, lsf);
+  block_totals(lsf, sh_bw, tot);
+  if (S > 1) {
+    unsigned long long* mine = sums + static_cast<int64_t>(b) * S * kChainSumWords;
+    if (wave == 0 && lane < kChainSumWords) {
+      const double z = lane >= 2 ? tot[1] : tot[0];
+      st_dev(mine + seg * kChainSumWords + lane, chain_word(static_cast<unsigned>(lane & 1 ? __double2loint(z) : __double2hiint(z)), tag));
+    }
+    bool have = true;
+    if (tid < (nblocks + kWave - 1) / kWave * kWave) {          // (wave-uniform) thread k gathers block k
+      const bool want = tid < nblocks && tid / kChainBlocks != seg;
+      unsigned long long hi = 0ull, lo = 0ull;
+      for (int poll = 0;; ++poll) {
+        have = true;
+        if (want) {
+          hi = ld_dev(mine + tid * 2);
+          lo = ld_dev(mine + tid * 2 + 1);
+          have = static_cast<unsigned>(hi) == tag && static_cast<unsigned>(lo) == tag;
+        }
+        if (__all(have) || poll >= P.patience) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      if (tid < nblocks) {
+        sh_have[tid] = have;
+        sh_part[tid] = want ? chain_double(hi, lo) : (tid & 1 ? tot[1] : tot[0]);
+      }
+    }
+    if (__syncthreads_or(!have)) {
+      float wx[kChainBlocks][8], lx[kChainBlocks];
+      double tx[kChainBlocks];
+      for (int k = 0; k < S; ++k) {
+        if (sh_have[k * kChainBlocks] && (k * kChainBlocks + 1 >= nblocks || sh_have[k * kChainBlocks + 1])) continue;
+        unit_weights<TDT, QDT, kChainBlocks>(R, k, level, V, c, wx, lx);
+        block_totals(lx, sh_bw, tx);
+        if (tid == 0) {
+#pragma unroll
+          for (int i = 0; i < kChainBlocks; ++i)
+            if (k * kChainBlocks + i < nblocks) sh_part[k * kChainBlocks + i] = tx[i];
+        }
+      }
+    }
+  } else if (tid == 0) {
+#pragma unroll
+    for (int i = 0; i < kChainBlocks; ++i)
+      if (i < nblocks) sh_part[i] = tot[i];
+  }
+  __syncthreads();
+  double mine, inc_b;
+  double total = scan_blocks(sh_part, nblocks, mine, inc_b);
+  bool redrawn = false;
+  if (level == 1 && !(total > 0.0)) {
+    // a residual without mass leaves the distribution as it was: draw from p (one workgroup alone; rare)
+    if (seg != 0) return;
+    level = 0;
+    redrawn = true;
+    __syncthreads();                  // earlier readers of sh_part are done
+    for (int k = 0; k < S; ++k) {
+      unit_weights<TDT, QDT, kChainBlocks>(R, k, 0, V, c, w, lsf);
+      block_totals(lsf, sh_bw, tot);
+      if (tid == 0) {
+#pragma unroll
+        for (int i = 0; i < kChainBlocks; ++i)
+          if (k * kChainBlocks + i < nblocks) sh_part[k * kChainBlocks + i] = tot[i];
+      }
+    }
+    __syncthreads();
+    total = scan_blocks(sh_part, nblocks, mine, inc_b);
+  }
+  const double target = u_res * total;
+  double before;
+  const int kb_hit = block_of_draw(sh_part, nblocks, mine, inc_b, target, before);
+  const int e_hit = kb_hit * kLinBlock + tid * 8;
+  int e0 = first8(e_hit, V);          // class of wh[0]
+  float wh[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) wh[i] = 0.f;
+  if (redrawn) {
+    const float no_scale[1] = {0.f};
+    e0 = e_hit;
+    if (e0 < V) weights8(R, e0, V, c, level, no_scale, wh);
+  } else {
+    if (kb_hit / kChainBlocks != seg) return;       // (the same for all workgroups of the pair: one stays)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) wh[i] = kb_hit & 1 ? w[1][i] : w[0][i];
+  }
+  draw_class(wh, e0, kb_hit, before, target, V, sh_bw[0], depth < P.out_stride ? P.out_tokens + static_cast<int64_t>(b) * P.out_stride + depth : nullptr);
 }
 
 // Workspace: [row statistics][helper protocol: pass descriptors, hand-back slots (zeroed by the
@@ -1183,6 +1606,29 @@ static bool linear_path(const AcceptArgs& a) {
   return a.parent == nullptr && a.V >= 8 && (a.path == 0 || a.path == 3 || a.path == 4) && linear_units(a.V) <= kLinMaxUnits;
 }
 
+// Where the one-launch kernel takes a linear draft: one thread gathers one record, the messages lie behind the target
+// statistics a caller supplies, and the launch is small.
+static size_t chain_offset(const AcceptArgs& a) {
+  return a.target_stats_ready ? (static_cast<size_t>(a.total_nodes + a.B) * stats_segments(a.V) * sizeof(SegStat) + 255) / 256 * 256 : 0;
+}
+static size_t chain_words(const AcceptArgs& a) {
+  return static_cast<size_t>(stats_segments(a.V)) * (static_cast<size_t>(a.total_nodes + a.B) * kChainWords + static_cast<size_t>(a.B) * kChainSumWords);
+}
+// The line: up to five workgroups per four compute units and 64 KB of logits per compute unit.  Beyond, workgroups that wait
+// share their units with others that work and the two launches are the faster.  Kernel times (the two launches have the
+// gap between them, 1 to 1.5 us, on top), chain / statistics + draw: 1 x 2 drafts x 1000 classes 7.8 / 8.6, 48 x 4 x
+// 2000 9.0 / 11.0, 16 x 16 x 8000 11.1 / 13.2, 4 x 8 x 32000 fp32 11.1 / 12.4, 8 x 8 x 32000 11.7 / 13.4, 32 x 4 x 16000 (320
+// workgroups) 13.2 / 13.5; 12 x 8 x 32000 (432) 13.2 / 13.7 but slower in a step, 3 x 8 x 128256 (432) 13.5 / 13.2, 16 x 8 x
+// 32000 (576) 17.4 / 14.5, 8 x 8 x 32000 fp32 (18 MB) 13.7 / 13.6.
+static bool chain_path(const AcceptArgs& a) {
+  if (!linear_path(a) || a.path != 0 || a.max_nodes > kMaxNodes) return false;
+  const int64_t S = stats_segments(a.V), levels = a.max_nodes + 1, n_cu = current_device_cus();
+  if (levels * S > kChainMaxRecords || S * kChainBlocks > kChainMaxRecords) return false;
+  if (levels * S * a.B * 4 > n_cu * 5) return false;
+  if (levels * a.B * a.V * ((a.t_dtype == kBF16 ? 2 : 4) + (a.q_dtype == kBF16 ? 2 : 4)) > n_cu * 65536) return false;
+  return chain_offset(a) + chain_words(a) * sizeof(unsigned long long) <= accept_layout(a.B, a.total_nodes, a.n_q_rows, a.V).total;
+}
+
 // The statistics pass that stops at each request's first rejection pays when the launch is several times what
 // the chip holds at once (about 2048 workgroups): later levels then start after the decisions of earlier ones.
 // It needs draft logits (their statistics are part of the decision) and computes the target rows itself.
@@ -1198,12 +1644,33 @@ const char* accept_plan_name(const AcceptArgs& a, int n_cu) {
   const bool cluster_ok = vec && a.V >= 8 && a.V <= kClusterMaxV && a.t_dtype == kBF16 && a.q_dtype == kBF16 &&
                           a.q_kind == 0;
   const bool cluster = cluster_ok && (a.path == 2 || (a.path == 0 && a.parent != nullptr && cluster_pays(a.B, a.V, n_cu)));
+  if (!cluster && chain_path(a)) return "accept_chain_kernel (one launch in place of row_stats_kernel + accept_linear_kernel: a vocabulary segment of one row pair per workgroup)";
   if (!cluster && progressive_stats(a)) return "row_stats_prog_kernel (rows up to each request's first rejection) + accept_linear_kernel (linear drafts: one vocabulary unit per workgroup, the last to arrive draws)";
   if (!cluster && linear_path(a)) return "row_stats_kernel (all rows) + accept_linear_kernel (linear drafts: one vocabulary unit per workgroup, the last to arrive draws)";
   if (!cluster) return "row_stats_kernel (all rows) + accept_walk_kernel (one workgroup per request, helper workgroups)";
   const ClusterPlan p = make_cluster_plan(a.B, a.V, a.max_nodes, a.parent != nullptr, n_cu, a.levels, a.slices);
   return p.solo ? "accept_cluster_kernel (one workgroup per request, rows of the walked path only)"
                 : "accept_cluster_kernel (cluster of workgroups per request, row slices held in registers or LDS)";
+}
+
+static AcceptParams accept_params(const AcceptArgs& a, int n_t_rows, float c, const SegStat* stats) {
+  AcceptParams P;
+  P.B = a.B; P.V = a.V; P.n_t_rows = n_t_rows; P.n_q_rows = a.n_q_rows > 0 ? a.n_q_rows : 1; P.nseg = stats_segments(a.V);
+  P.node_offsets = a.node_offsets; P.parent = a.parent; P.draft_tokens = a.draft_tokens;
+  P.target = a.target; P.t_dtype = a.t_dtype;
+  P.draft_q = a.draft_q; P.q_dtype = a.q_dtype; P.q_kind = a.q_kind;
+  P.q_row = a.q_row; P.c = c; P.u_accept = a.u_accept; P.u_resample = a.u_resample;
+  P.accept_len = a.accept_len; P.out_tokens = a.out_tokens; P.out_stride = a.out_stride;
+  P.stop_node = a.stop_node; P.dbg_ratio = a.dbg_ratio; P.stats = stats;
+  P.helpers = 0; P.patience = 0; P.desc = nullptr; P.part = nullptr;
+  return P;
+}
+
+template <int TDT, int QDT>
+static auto chain_kernel(const AcceptArgs& a) {
+  const bool q_stats = a.q_kind == 0 && a.n_q_rows > 0;       // (no draft rows: every request draws from its one target row)
+  return a.target_stats_ready ? (q_stats ? accept_chain_kernel<TDT, QDT, false, true> : accept_chain_kernel<TDT, QDT, false, false>)
+                              : (q_stats ? accept_chain_kernel<TDT, QDT, true, true> : accept_chain_kernel<TDT, QDT, true, false>);
 }
 
 void launch_accept(const AcceptArgs& a, hipStream_t stream) {
@@ -1227,6 +1694,19 @@ void launch_accept(const AcceptArgs& a, hipStream_t stream) {
     }
   }
   SegStat* stats = reinterpret_cast<SegStat*>(ws);
+  if (chain_path(a)) {
+    AcceptParams P = accept_params(a, n_t_rows, c, stats);
+    P.patience = (a.patience >= 0 && a.patience <= 1000000) ? a.patience : 1000;
+    auto* msg = reinterpret_cast<unsigned long long*>(ws + chain_offset(a));
+    unsigned long long* sums = msg + static_cast<size_t>(n_t_rows) * P.nseg * kChainWords;
+    if (stream_captures(stream)) clear_messages(msg, static_cast<int64_t>(chain_words(a)), stream);
+    const int levels = a.max_nodes + 1;
+    const dim3 grid(static_cast<unsigned>(static_cast<int64_t>(a.B) * levels * P.nseg));
+    auto kernel = a.t_dtype == kBF16 ? (a.q_dtype == kBF16 ? chain_kernel<kBF16, kBF16>(a) : chain_kernel<kBF16, kF32>(a))
+                                     : (a.q_dtype == kBF16 ? chain_kernel<kF32, kBF16>(a) : chain_kernel<kF32, kF32>(a));
+    hipLaunchKernelGGL(kernel, grid, dim3(kLinThreads), 0, stream, P, msg, sums, next_message_tag() + (kTagsPerCall - 1), levels);
+    return;
+  }
   unsigned* words = reinterpret_cast<unsigned*>(ws + lay.words_off);      // start of the zeroed region
   if (progressive_stats(a)) {
     unsigned* node_cnt = reinterpret_cast<unsigned*>(ws + lay.prog_cnt_off);
@@ -1254,20 +1734,13 @@ void launch_accept(const AcceptArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(kStatThreads), 0, stream, words,
                        static_cast<int>(lay.n_zero_words));
   }
-  AcceptParams P;
-  P.B = a.B; P.V = a.V; P.n_t_rows = n_t_rows; P.n_q_rows = a.n_q_rows > 0 ? a.n_q_rows : 1; P.nseg = stats_segments(a.V);
-  P.node_offsets = a.node_offsets; P.parent = a.parent; P.draft_tokens = a.draft_tokens;
-  P.target = a.target; P.t_dtype = a.t_dtype;
-  P.draft_q = a.draft_q; P.q_dtype = a.q_dtype; P.q_kind = a.q_kind;
-  P.q_row = a.q_row; P.c = c; P.u_accept = a.u_accept; P.u_resample = a.u_resample;
-  P.accept_len = a.accept_len; P.out_tokens = a.out_tokens; P.out_stride = a.out_stride;
-  P.stop_node = a.stop_node; P.dbg_ratio = a.dbg_ratio; P.stats = stats;
+  AcceptParams P = accept_params(a, n_t_rows, c, stats);
   P.desc = reinterpret_cast<PassDesc*>(ws + lay.desc_off);
   P.part = reinterpret_cast<PartSlot*>(ws + lay.part_off);
   if (linear_path(a)) {
     const int unit_classes = linear_unit_classes(a.B, a.V, n_cu);
     const int U = (a.V + unit_classes - 1) / unit_classes;
-    P.helpers = 0; P.patience = 0; P.parent = nullptr;
+    P.parent = nullptr;
     double* partial = reinterpret_cast<double*>(ws + lay.lin_off);
     unsigned* arrived = reinterpret_cast<unsigned*>(ws + lay.arrived_off);
     const dim3 grid_l(static_cast<unsigned>(a.B) * U);

@@ -16,11 +16,13 @@
 // behind the first rejection are never read.
 //
 // Messages.  One message = four 64-bit words {data : tag}, written with relaxed device-scope stores
-// and read with relaxed device-scope loads; a word is valid when its tag equals the round number, so
+// and read with relaxed device-scope loads; a word is valid when its tag is the call's plus the round number, so
 // no ordering between words is needed.  Every workgroup posts in every round (a dummy when it has
 // nothing to add) into one of two buffers chosen by the round's parity: a workgroup can post round
 // r+2 only after it has seen every peer's round r+1, i.e. after every peer has finished reading
-// round r, so two buffers suffice.  The buffers are zeroed by a small kernel launched ahead.
+// round r, so two buffers suffice.  Whatever the buffers hold carries other tags (see next_message_tag), so nothing clears
+// them (a kernel ahead that did cost 5 of 128 us of a step of 16 x 64 tree nodes), but for launches that are being
+// captured: replays repeat their tag.
 //
 // No wait is unbounded and the result never depends on a peer making progress: a workgroup that does
 // not see a round complete within its patience leaves; if it is the cluster's first workgroup (the
@@ -45,7 +47,7 @@ constexpr int kClUnit = kClThreads * 8;        // logits one workgroup-wide 16-b
 constexpr int kClNodes = 128;
 constexpr int kClMaxUpt = 16;                  // units per slice: 16 x 4 KiB per row, two rows = 128 KiB of LDS
 constexpr int kClMaxParts = kClMaxUpt * kClWaves;
-constexpr unsigned kClAbort = 0xffffffffu;
+constexpr unsigned kClAbort = kTagsPerCall - 2;       // added to the call's tag in place of a round number (258 rounds at most)
 constexpr uint32_t kNegInf2 = 0xff80ff80u;     // two bf16 -inf
 
 struct ClusterParams {
@@ -66,6 +68,7 @@ struct ClusterParams {
   int LV, SL;                     // window levels x vocabulary slices = workgroups per request
   int UPT;                        // units (2048 logits) per slice
   int solo;                       // one workgroup per request, which computes all LV x SL parts itself
+  unsigned tag;                   // of the call's messages, plus the round number
   int patience;                   // polls the owner spends on one round before it walks alone
   unsigned long long* msg;        // [B][2 buffers][C][2 messages][4 words]
 };
@@ -520,7 +523,7 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
     unsigned word = w == 2 ? __float_as_uint(aux) : 0u;
     word = w == 0 ? static_cast<unsigned>(__double2loint(val)) : word;
     word = w == 1 ? static_cast<unsigned>(__double2hiint(val)) : word;
-    st_dev(msg_word(msg_at(r, rank, k) + 8u * w), (static_cast<unsigned long long>(word) << 32) | r);
+    st_dev(msg_word(msg_at(r, rank, k) + 8u * w), (static_cast<unsigned long long>(word) << 32) | (P.tag + r));
   };
   // Round r: the wave without logits posts this workgroup's one or two messages and waits for everybody's (the other waves
   // go on to the barrier).  Every wave has passed a barrier since it read what the round before left here.
@@ -540,8 +543,9 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
         x[0] = ld_dev(msg_word(at)); x[1] = ld_dev(msg_word(at + 8u)); x[2] = ld_dev(msg_word(at + 16u));
       };
       auto judge = [&](const unsigned long long (&x)[3]) __attribute__((always_inline)) {     // -1: look again
-        const bool ok = static_cast<unsigned>(x[0]) == r && static_cast<unsigned>(x[1]) == r && static_cast<unsigned>(x[2]) == r;
-        if (__any(static_cast<unsigned>(x[0]) == kClAbort)) { status = 2; return; }
+        const unsigned tag = P.tag + r;
+        const bool ok = static_cast<unsigned>(x[0]) == tag && static_cast<unsigned>(x[1]) == tag && static_cast<unsigned>(x[2]) == tag;
+        if (__any(static_cast<unsigned>(x[0]) == P.tag + kClAbort)) { status = 2; return; }
         if (__all(ok)) {
           status = 0;
           sh_val[my] = __hiloint2double(static_cast<int>(x[1] >> 32), static_cast<int>(x[0] >> 32));
@@ -820,15 +824,11 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
     // the owner's peers are late or gone: tell them to leave and walk the request alone
     if (wave == 0)
       st_dev(P.msg + ((static_cast<size_t>(b) * 2 + ((lane >> 3) & 1)) * C * 2 + ((lane >> 2) & 1)) * 4 + (lane & 3),
-            static_cast<unsigned long long>(kClAbort));
+            static_cast<unsigned long long>(P.tag + kClAbort));
     cl_sync();
     solo = true;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no slice is on its way to memory that the workgroup gives back
-}
-
-__global__ __launch_bounds__(256) void cluster_zero_kernel(unsigned long long* __restrict__ words, int n) {
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) words[i] = 0ull;
 }
 
 ClusterPlan make_cluster_plan(int B, int V, int max_nodes, bool tree, int n_cu, int want_levels, int want_slices) {
@@ -895,11 +895,8 @@ void launch_accept_cluster(const AcceptArgs& a, const ClusterPlan& plan, int pat
   const int C = plan.solo ? 1 : plan.levels * plan.slices;
   // a cluster of one workgroup exchanges nothing: SL stays the number of slices it computes in turn
   const dim3 grid(a.B * C);
-  if (!plan.solo) {
-    const int words = a.B * C * 16;
-    hipLaunchKernelGGL(cluster_zero_kernel, dim3((words + 255) / 256 > 64 ? 64 : (words + 255) / 256), dim3(256), 0,
-                       stream, P.msg, words);
-  }
+  P.tag = plan.solo ? 0 : next_message_tag();
+  if (!plan.solo && stream_captures(stream)) clear_messages(P.msg, static_cast<int64_t>(a.B) * C * 16, stream);
   const size_t lds = static_cast<size_t>(plan.upt) * 2 * kClThreads * 16;
   static std::atomic<uint64_t> attr_done{0};
   if (plan.upt == 4) {                            // (32 KB of rows: no attribute needed)

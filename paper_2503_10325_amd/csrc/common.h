@@ -188,28 +188,13 @@ struct __align__(16) SegStat {
   double z;
 };
 
-// Merged (max, sum) of one logit row from its per-segment records, by a group of 16 lanes (lane sl of the
-// group takes segments sl, sl + 16, ...); the result is in every lane of the group.  DEV: read the records
-// with device-scope loads (they were written by other workgroups of the same kernel).  The arithmetic and
-// its order are the same for every caller, so every caller gets the same bits (accept_walk_kernel merges by itself, in the
+// Merged (max, sum) of one logit row from its per-segment records load(0) .. load(nseg - 1), by a group of 16 lanes (lane sl
+// of the group takes segments sl, sl + 16, ...); the result is in every lane of the group.  The arithmetic and its order
+// are the same for every caller, so every caller gets the same bits (accept_walk_kernel merges by itself, in the
 // order of its shuffles: equal up to the last bits).  All lanes of the wave take part
 // (a group without a row passes nseg = 0).
-template <bool DEV>
-__device__ __forceinline__ void merged_row_stats(const SegStat* __restrict__ rec, int nseg, float c, int sl,
-                                                 float& m_out, double& z_out) {
-  auto load = [&](int sg) -> SegStat {
-    if constexpr (DEV) {
-      const unsigned long long* w = reinterpret_cast<const unsigned long long*>(rec + sg);
-      const unsigned long long w0 = ld_dev(w), w1 = ld_dev(w + 1);
-      SegStat st;
-      st.m = __uint_as_float(static_cast<unsigned>(w0));
-      st.pad = 0.f;
-      st.z = __builtin_bit_cast(double, w1);
-      return st;
-    } else {
-      return rec[sg];
-    }
-  };
+template <typename Load>
+__device__ __forceinline__ void merged_stats(Load load, int nseg, float c, int sl, float& m_out, double& z_out) {
   SegStat st;
   st.m = -INFINITY; st.pad = 0.f; st.z = 0.0;
   if (sl < nseg) st = load(sl);                    // up to 16 segments (131072 logits): one load per lane
@@ -225,6 +210,26 @@ __device__ __forceinline__ void merged_row_stats(const SegStat* __restrict__ rec
   }
   m_out = m;
   z_out = row16_sum(z);
+}
+
+// ... from records in memory.  DEV: read them with device-scope loads (they were written by other workgroups of the same
+// kernel).
+template <bool DEV>
+__device__ __forceinline__ void merged_row_stats(const SegStat* __restrict__ rec, int nseg, float c, int sl,
+                                                 float& m_out, double& z_out) {
+  merged_stats([&](int sg) -> SegStat {
+    if constexpr (DEV) {
+      const unsigned long long* w = reinterpret_cast<const unsigned long long*>(rec + sg);
+      const unsigned long long w0 = ld_dev(w), w1 = ld_dev(w + 1);
+      SegStat st;
+      st.m = __uint_as_float(static_cast<unsigned>(w0));
+      st.pad = 0.f;
+      st.z = __builtin_bit_cast(double, w1);
+      return st;
+    } else {
+      return rec[sg];
+    }
+  }, nseg, c, sl, m_out, z_out);
 }
 
 }  // namespace specv

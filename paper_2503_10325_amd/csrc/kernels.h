@@ -18,6 +18,17 @@ void launch_row_stats(const void* t_base, int t_dtype, int n_t_rows, const void*
                       unsigned* zero_words = nullptr, int n_zero = 0, const int32_t* q_row = nullptr,
                       int n_nodes = 0);
 
+// Messages between the workgroups of one launch are words {data : tag} in a workspace that nothing clears: a word counts when
+// it carries a tag of the launch.  next_message_tag() is the first of kTagsPerCall tags that belong to the call alone (a
+// process-wide count: they come round again after 2^23 calls, when a word would have to have stayed in place, unwritten
+// by all calls between); the last of them is the one-launch kernel's for linear drafts, the others are the cluster walk's.
+constexpr unsigned kTagsPerCall = 512;
+unsigned next_message_tag();
+// Whether launches on the stream are being recorded, to be replayed with the same arguments, tags among them (unknown counts
+// as yes): such a launch is preceded by clear_messages (tag 0 with round 0 is never sent).
+bool stream_captures(hipStream_t stream);
+void clear_messages(unsigned long long* words, int64_t n, hipStream_t stream);
+
 struct AcceptArgs {
   int B, V, total_nodes, n_q_rows, max_nodes;
   const int32_t* node_offsets;

@@ -1,0 +1,132 @@
+"""accept_chain_kernel (linear drafts in one launch) against the statistics pass + accept_linear_kernel (path 3, which the oracle
+tests cover): same lengths, tokens and stop nodes, ratios to the last bits of the fp64 sums.  Vocabularies at the edges
+of 8-class groups, waves, 4096-class blocks and 8192-class segments; requests without nodes; every dtype; probability drafts;
+target statistics from the caller; and patience 0, where every record that is not there yet is worked out by the
+workgroup that misses it.  The workspace starts as garbage and is not cleared between the calls."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def inputs(V, n, tdt, qdt, probs, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    n = np.asarray(n)
+    off = np.concatenate([[0], np.cumsum(n)])
+    B, total = len(n), int(n.sum())
+    target = torch.randn((total + B, V), generator=g, device="cuda") * 2
+    rows = torch.from_numpy(np.concatenate([off[b] + b + np.arange(k) for b, k in enumerate(n)] + [[]]).astype(np.int64)).cuda()
+    draft = target[rows] + 0.7 * torch.randn((total, V), generator=g, device="cuda")
+    e = torch.empty_like(draft).exponential_(generator=g)
+    tokens = (torch.softmax(draft, 1) / e).argmax(1).int()
+    draft = (torch.softmax(draft, 1) if probs else draft).to(qdt).contiguous()
+    u = torch.randint(0, 1 << 24, (total + B,), generator=g, device="cuda").float() * 2.0 ** -24
+    return dict(B=B, total=total, most=int(n.max()), off=torch.from_numpy(off.astype(np.int32)).cuda(), tokens=tokens,
+                target=target.to(tdt).contiguous(), draft=draft, q_row=torch.arange(total, dtype=torch.int32, device="cuda"),
+                ua=u[:total].contiguous(), ur=u[total:].contiguous(), probs=probs)
+
+
+def run(sv, d, tuning, workspace, T=0.9, prestats=False):
+    out = dict(len=torch.full((d["B"],), -7, dtype=torch.int32, device="cuda"),
+               tok=torch.full((d["B"], d["most"] + 1), -7, dtype=torch.int32, device="cuda"),
+               stop=torch.full((d["B"],), -7, dtype=torch.int32, device="cuda"),
+               ratio=torch.full((max(1, d["total"]),), -7.0, device="cuda"))
+    a = (d["B"], d["total"], d["most"], d["off"], None, d["tokens"], d["target"], d["draft"],
+         sv.SPEC_Q_PROBS if d["probs"] else sv.SPEC_Q_LOGITS, d["q_row"], T, d["ua"], d["ur"], out["len"], out["tok"], out["stop"],
+         out["ratio"], workspace)
+    if prestats:
+        sv.spec_accept_prestats(*a)
+    else:
+        sv.spec_accept_tuned(tuning, *a)
+    return out
+
+
+def same(a, b):
+    for k in ("len", "tok", "stop"):
+        assert torch.equal(a[k], b[k]), k
+    assert torch.equal(a["ratio"].isnan(), b["ratio"].isnan())
+    assert torch.allclose(a["ratio"].nan_to_num(1.0), b["ratio"].nan_to_num(1.0), rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("V,n,tdt,qdt,probs", [
+    (8, [2, 0, 3], torch.bfloat16, torch.bfloat16, False),
+    (9, [1], torch.float32, torch.float32, False),
+    (519, [4, 4], torch.bfloat16, torch.float32, False),
+    (4095, [3, 1, 0, 2], torch.bfloat16, torch.bfloat16, False),
+    (4097, [5], torch.float32, torch.bfloat16, False),
+    (8191, [16, 2], torch.bfloat16, torch.bfloat16, False),
+    (8193, [3, 3], torch.bfloat16, torch.bfloat16, False),
+    (12289, [2, 6], torch.bfloat16, torch.float32, True),
+    (32000, [8, 1, 8], torch.bfloat16, torch.float32, True),
+    (8200, [70, 5], torch.float32, torch.float32, False),        # more nodes than lanes
+    (50257, [8, 3], torch.float32, torch.float32, False),
+    (131072, [5, 2, 0], torch.bfloat16, torch.bfloat16, False),   # 16 segments
+    (140000, [4], torch.bfloat16, torch.bfloat16, False),         # 18: more than a group of 16 lanes merges at once
+    (600000, [1], torch.bfloat16, torch.bfloat16, False),         # 74 segments, 147 blocks: more than one block per lane
+    (20000, [0, 0], torch.bfloat16, torch.bfloat16, False),       # no drafts at all
+])
+def test_chain_matches_two_launches(V, n, tdt, qdt, probs):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import binding as sv
+    plan = None
+    for seed in range(3):
+        d = inputs(V, n, tdt, qdt, probs, seed)
+        code = {torch.bfloat16: sv.SPEC_BF16, torch.float32: sv.SPEC_F32}
+        plan = sv.spec_describe_accept_plan(d["B"], V, d["total"], d["most"], False, target_dtype=code[tdt], q_dtype=code[qdt],
+                                            q_kind=sv.SPEC_Q_PROBS if probs else sv.SPEC_Q_LOGITS)
+        assert plan.startswith("accept_chain_kernel"), plan
+        size = sv.spec_accept_workspace_size(d["B"], d["total"], d["draft"].shape[0], V)
+        ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device="cuda")
+        ref = run(sv, d, sv.SpecAcceptTuning(path=3), ws.clone())
+        for _ in range(2):
+            same(run(sv, d, None, ws), ref)
+        same(run(sv, d, sv.SpecAcceptTuning(patience=0), ws), ref)
+
+
+@pytest.mark.parametrize("probs", [False, True])
+def test_chain_from_given_target_statistics(probs):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import binding as sv
+    from paper_2503_10325_amd import runner, workloads as W
+    V, n = 16424, [3, 0, 6, 2]
+    d = inputs(V, n, torch.bfloat16, torch.float32 if probs else torch.bfloat16, probs, 5)
+    li = W.make_lm_head_inputs(d["total"] + d["B"], 256, V, seed=3)
+    dev = runner.DeviceLmHead(li, temperature=0.9)
+    dev.run()
+    d["target"] = dev.logits
+    size = sv.spec_accept_workspace_size(d["B"], d["total"], d["draft"].shape[0], V)
+    ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device="cuda")
+    head = torch.empty(max(256, sv.spec_lm_head_workspace_size(*dev.hidden.shape, V)), dtype=torch.uint8, device="cuda")
+    ref = run(sv, d, sv.SpecAcceptTuning(path=3), ws.clone())
+    for _ in range(2):
+        sv.spec_lm_head(dev.hidden, dev.weight, 0.9, dev.logits, ws, head)
+        same(run(sv, d, None, ws, prestats=True), ref)
+
+
+def test_chain_replays():
+    """A captured call repeats its message tag: replays on new inputs in the same buffers must not see old messages."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import binding as sv
+    sets = [inputs(32000, [6, 3, 8], torch.bfloat16, torch.bfloat16, False, s) for s in range(4)]
+    d = {k: (v.clone() if torch.is_tensor(v) else v) for k, v in sets[0].items()}
+    ws = torch.empty(sv.spec_accept_workspace_size(d["B"], d["total"], d["total"], 32000), dtype=torch.uint8, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        run(sv, d, None, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        out = run(sv, d, None, ws)
+    for s in sets + sets:
+        for k, v in s.items():
+            if torch.is_tensor(v):
+                d[k].copy_(v)
+        graph.replay()
+        torch.cuda.synchronize()
+        same(out, run(sv, s, sv.SpecAcceptTuning(path=3), torch.empty_like(ws)))
