@@ -132,14 +132,14 @@ int32_t spec_fuse_drafts(int32_t B, int32_t k_max, int32_t N, int32_t V, const i
     if (V <= 0 || !(temperature > 0.f)) return SPEC_ERR_SHAPE;
     if (logits_dtype != SPEC_BF16 && logits_dtype != SPEC_F32) return SPEC_ERR_UNSUPPORTED;
     if (!draft_logits || !fused_probs) return SPEC_ERR_NULL;
-    const size_t need = fuse_workspace_bytes(B, k_max, N, V, mode);
+    const size_t need = fuse_workspace_min_bytes(B, k_max, N, V, mode);
     if (!workspace || workspace_bytes < need) return SPEC_ERR_WORKSPACE;
   }
   FuseArgs a{};
   a.B = B; a.k_max = k_max; a.N = N; a.V = V; a.k_len = k_len; a.conf = conf; a.draft_tokens = draft_tokens;
   a.draft_logits = draft_logits; a.l_dtype = logits_dtype; a.temperature = temperature; a.mode = mode;
   a.fused_token = fused_token; a.winner = winner; a.q_row = q_row; a.fused_probs = fused_probs;
-  a.workspace = workspace;
+  a.workspace = workspace; a.workspace_bytes = workspace_bytes;
   launch_fuse(a, static_cast<hipStream_t>(stream));
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_ERR_LAUNCH;
 }

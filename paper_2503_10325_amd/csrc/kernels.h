@@ -145,9 +145,10 @@ struct FuseArgs {
   int32_t* winner;
   int32_t* q_row;
   float* fused_probs;
-  void* workspace;
+  void* workspace; size_t workspace_bytes;
 };
-size_t fuse_workspace_bytes(int B, int k_max, int N, int V, int mode);
+size_t fuse_workspace_bytes(int B, int k_max, int N, int V, int mode);       // what the size query answers
+size_t fuse_workspace_min_bytes(int B, int k_max, int N, int V, int mode);   // the least that is taken
 void launch_fuse(const FuseArgs& a, hipStream_t stream);
 
 // ---- attn.hip ---------------------------------------------------------------------
