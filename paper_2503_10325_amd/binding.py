@@ -129,11 +129,20 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+_raw_stream = None
+
+
 def _stream(stream) -> int:
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # The handle itself: the object that torch.cuda.current_stream() builds around it costs 2.7 us, a third of a whole call
+    # (1 request x 4 drafts x 1000 classes, two calls a step, bound by the host: 18.6 -> 13.6 us).
+    global _raw_stream
+    import torch
+    if _raw_stream is None:
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _raw_stream = raw if raw is not None else lambda device: torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dtype_code(t) -> int:
