@@ -1233,15 +1233,20 @@ struct ChainScratch {
   double z[2][kLinWaves];
 };
 
-// (maximum, sum of 2^((l - max) c)) of one segment of two rows, from their loads; in every thread.
+// A thread's share of one segment of the target row [0] and the draft row [1]: exponentials relative to its own maximum m (rows
+// whose statistics are taken), or the values as they are.  Classes that do not exist: 0, or -inf.
+struct ChainValues {
+  float e[2][kChainBlocks][8];
+  float m[2];
+};
+
 template <bool T, bool Q, int TDT, int QDT>
-__device__ __forceinline__ void chain_stats(const WalkRows& R, const Raw8<TDT, kChainBlocks>& rt, const Raw8<QDT, kChainBlocks>& rq, int e_seg,
-                                            int V, float c, ChainScratch& sh, float (&M)[2], double (&Z)[2]) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float m[2], sum[2];
+__device__ __forceinline__ void chain_exponentials(const WalkRows& R, const Raw8<TDT, kChainBlocks>& rt, const Raw8<QDT, kChainBlocks>& rq, int e_seg,
+                                                   int V, float c, ChainValues& v, float (&sum)[2]) {
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    m[k] = -INFINITY;
+    v.m[k] = -INFINITY;
     sum[k] = 0.f;
     if (k == 0 ? !T : !Q) continue;
     float x[kChainBlocks][8];
@@ -1251,42 +1256,80 @@ __device__ __forceinline__ void chain_stats(const WalkRows& R, const Raw8<TDT, k
       const int e0 = e_seg + i * kLinBlock + tid * 8;
 #pragma unroll
       for (int j = 0; j < 8; ++j) x[i][j] = -INFINITY;
-      if (!any(i)) continue;
-      if (k == 0) take8<false>(R.t_base, R.t_off, e0, V, rt, i, x[i]);
-      else take8<false>(R.q_base, R.q_off, e0, V, rq, i, x[i]);
+      if (any(i)) {
+        if (k == 0) take8<false>(R.t_base, R.t_off, e0, V, rt, i, x[i]);
+        else take8<false>(R.q_base, R.q_off, e0, V, rq, i, x[i]);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) m[k] = fmaxf(m[k], x[i][j]);
+        for (int j = 0; j < 8; ++j) v.m[k] = fmaxf(v.m[k], x[i][j]);
+      }
     }
-    const float mm = (m[k] == -INFINITY) ? 0.f : m[k];
+    const float mm = (v.m[k] == -INFINITY) ? 0.f : v.m[k];
 #pragma unroll
-    for (int i = 0; i < kChainBlocks; ++i)
+    for (int i = 0; i < kChainBlocks; ++i) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v.e[k][i][j] = 0.f;
       if (any(i))
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sum[k] += fast_exp2((x[i][j] - mm) * c);
+        for (int j = 0; j < 8; ++j) {
+          v.e[k][i][j] = fast_exp2((x[i][j] - mm) * c);
+          sum[k] += v.e[k][i][j];
+        }
+    }
   }
-  __syncthreads();                    // earlier readers of sh are done
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-    if (k == 0 ? T : Q) sh.m[k][wave] = wave_max(m[k]);        // every lane stores the same value
-  __syncthreads();
+}
+
+// (maximum, sum) of every wave's classes of both rows, to LDS.
+template <bool T, bool Q>
+__device__ __forceinline__ void chain_wave_stats(const ChainValues& v, const float (&sum)[2], float c, ChainScratch& sh) {
+  const int wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     if (k == 0 ? !T : !Q) continue;
-    M[k] = sh.m[k][0];
-#pragma unroll
-    for (int w = 1; w < kLinWaves; ++w) M[k] = fmaxf(M[k], sh.m[k][w]);
-    const float MM = (M[k] == -INFINITY) ? 0.f : M[k], mm = (m[k] == -INFINITY) ? 0.f : m[k];
-    double z = static_cast<double>(sum[k]) * static_cast<double>(fast_exp2((mm - MM) * c));
-    if (m[k] == -INFINITY) z = 0.0;
+    const float wm = wave_max(v.m[k]), wmm = (wm == -INFINITY) ? 0.f : wm, mm = (v.m[k] == -INFINITY) ? 0.f : v.m[k];
+    double z = static_cast<double>(sum[k]) * static_cast<double>(fast_exp2((mm - wmm) * c));
+    if (v.m[k] == -INFINITY) z = 0.0;
+    sh.m[k][wave] = wm;               // every lane stores the same value
     sh.z[k][wave] = wave_sum(z);
   }
-  __syncthreads();
+}
+
+// The thread's weights of a segment at level L and their sums per block.  Exponentials become probabilities by one factor per
+// thread and row (fp64 up to its rounding); values as they are by an exponential each (target) or as probabilities (draft).
+template <bool T, bool Q, int TDT, int QDT>
+__device__ __forceinline__ void chain_weights(const WalkRows& R, const ChainValues& v, const Raw8<TDT, kChainBlocks>& rt,
+                                              const Raw8<QDT, kChainBlocks>& rq, int seg, int L, int V, float c, float (&w)[kChainBlocks][8],
+                                              float (&lsf)[kChainBlocks]) {
+  const int tid = threadIdx.x;
+  float f[2] = {0.f, 0.f};
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    if (k == 0 ? !T : !Q) continue;
-    Z[k] = 0.0;
+    if (k == 0 ? !T : (!Q || L == 0)) continue;
+    const float mm = (v.m[k] == -INFINITY) ? 0.f : v.m[k];
+    f[k] = static_cast<float>(exp2(static_cast<double>(mm - (k ? R.q_m : R.t_m)) * static_cast<double>(c)) * (k ? R.q_invz : R.t_invz));
+  }
+  const float t_invz = static_cast<float>(R.t_invz);
 #pragma unroll
-    for (int w = 0; w < kLinWaves; ++w) Z[k] += sh.z[k][w];
+  for (int i = 0; i < kChainBlocks; ++i) {
+    const int e0 = seg * kChainBlocks * kLinBlock + i * kLinBlock + tid * 8;
+    lsf[i] = 0.f;
+    float lp[8], lq[8];
+    if constexpr (!T) take8<false>(R.t_base, R.t_off, e0, V, rt, i, lp);
+    if constexpr (!Q) {
+      if (L > 0) take8<false>(R.q_base, R.q_off, e0, V, rq, i, lq);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      float p, q = 0.f;
+      if constexpr (T) p = v.e[0][i][j] * f[0];
+      else p = fast_exp2((lp[j] - R.t_m) * c) * t_invz;
+      if (L > 0) {
+        if constexpr (Q) q = v.e[1][i][j] * f[1];
+        else q = lq[j] == -INFINITY ? 0.f : lq[j];
+        p = fmaxf(p - q, 0.f);
+      }
+      w[i][j] = p;
+      lsf[i] += p;
+    }
   }
 }
 
@@ -1353,15 +1396,28 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
     }
     if constexpr (!Q_STATS) __syncthreads();
   }
+  ChainValues val;
+  // ... of another segment or pair, from memory (records and sums that did not come)
+  auto values_of = [&](const WalkRows& X, int sg, int L, Raw8<TDT, kChainBlocks>& xt, Raw8<QDT, kChainBlocks>& xq, ChainValues& v,
+                       float (&sum)[2]) __attribute__((always_inline)) {
+    issue8(X.t_base, [&](int) { return X.t_off; }, e_of(sg), V, xt);
+    if (L > 0) issue8(X.q_base, [&](int) { return X.q_off; }, e_of(sg), V, xq);
+    chain_exponentials<T_STATS, Q_STATS>(X, xt, xq, sg * kChainBlocks * kLinBlock, V, c, v, sum);
+  };
   if constexpr (T_STATS || Q_STATS) {
-    float M[2];
-    double Z[2];
-    chain_stats<T_STATS, Q_STATS>(R, rt, rq, seg * kChainBlocks * kLinBlock, V, c, sh_stat, M, Z);
-    if (wave == 0 && lane < kChainWords && (lane < 3 ? T_STATS : (Q_STATS && tested))) {
-      const int k = lane >= 3, part = lane - 3 * k;
-      const double z = k ? Z[1] : Z[0];
-      const unsigned data = part == 2 ? __float_as_uint(k ? M[1] : M[0]) : static_cast<unsigned>(part == 0 ? __double2hiint(z) : __double2loint(z));
-      st_dev(msg + ((trow0 + j) * S + seg) * kChainWords + lane, chain_word(data, tag));
+    float sum[2];
+    chain_exponentials<T_STATS, Q_STATS>(R, rt, rq, seg * kChainBlocks * kLinBlock, V, c, val, sum);
+    chain_wave_stats<T_STATS, Q_STATS>(val, sum, c, sh_stat);
+    __syncthreads();
+    if (tid < 2 && (tid == 0 ? T_STATS : Q_STATS)) {            // thread 0: the target row's record, 1: the draft row's
+      float M;
+      double Z;
+      merge_waves<kLinWaves>(sh_stat.m[tid], sh_stat.z[tid], c, M, Z);
+      sh_m[tid][own] = M; sh_z[tid][own] = Z;
+      unsigned long long* to = msg + ((trow0 + j) * S + seg) * kChainWords + 3 * tid;
+      st_dev(to, chain_word(static_cast<unsigned>(__double2hiint(Z)), tag));
+      st_dev(to + 1, chain_word(static_cast<unsigned>(__double2loint(Z)), tag));
+      st_dev(to + 2, chain_word(__float_as_uint(M), tag));
     }
     // ---- gather: thread r the record of segment r % S of rows r / S ----
     bool have = true;
@@ -1388,10 +1444,7 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
       }
       if (tid < n_rec) {
         sh_have[tid] = have;
-        if (tid == own) {
-          if constexpr (T_STATS) { sh_m[0][tid] = M[0]; sh_z[0][tid] = Z[0]; }
-          if constexpr (Q_STATS) { sh_m[1][tid] = M[1]; sh_z[1][tid] = Z[1]; }
-        } else {
+        if (tid != own) {
           if constexpr (T_STATS) { sh_m[0][tid] = __uint_as_float(static_cast<unsigned>(w[2] >> 32)); sh_z[0][tid] = chain_double(w[0], w[1]); }
           if constexpr (Q_STATS) { sh_m[1][tid] = __uint_as_float(static_cast<unsigned>(w[5] >> 32)); sh_z[1][tid] = chain_double(w[3], w[4]); }
         }
@@ -1406,13 +1459,12 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
         X.q_off = i < n ? q_off_of(i) : 0;
         Raw8<TDT, kChainBlocks> xt;
         Raw8<QDT, kChainBlocks> xq;
-        if constexpr (T_STATS) issue8(X.t_base, [&](int) { return X.t_off; }, e_of(sg), V, xt);
-        if constexpr (Q_STATS) issue8(X.q_base, [&](int) { return X.q_off; }, e_of(sg), V, xq);
-        chain_stats<T_STATS, Q_STATS>(X, xt, xq, sg * kChainBlocks * kLinBlock, V, c, sh_stat, M, Z);
-        if (tid == 0) {
-          if constexpr (T_STATS) { sh_m[0][r] = M[0]; sh_z[0][r] = Z[0]; }
-          if constexpr (Q_STATS) { sh_m[1][r] = M[1]; sh_z[1][r] = Z[1]; }
-        }
+        ChainValues v;
+        values_of(X, sg, Q_STATS, xt, xq, v, sum);
+        __syncthreads();              // earlier readers of sh_stat are done
+        chain_wave_stats<T_STATS, Q_STATS>(v, sum, c, sh_stat);
+        __syncthreads();
+        if (tid < 2 && (tid == 0 ? T_STATS : Q_STATS)) merge_waves<kLinWaves>(sh_stat.m[tid], sh_stat.z[tid], c, sh_m[tid][r], sh_z[tid][r]);
       }
       __syncthreads();
     }
@@ -1477,8 +1529,18 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
   const int nblocks = (V + kLinBlock - 1) / kLinBlock;
   float w[kChainBlocks][8], lsf[kChainBlocks];
   double tot[kChainBlocks];
-  unit_weights_from<TDT, QDT, kChainBlocks>(R, rt, rq, seg, level, V, c, w, lsf);
+  chain_weights<T_STATS, Q_STATS>(R, val, rt, rq, seg, level, V, c, w, lsf);
   block_totals(lsf, sh_bw, tot);
+  // ... of another segment of this pair, from memory
+  auto weights_of = [&](int k, int L, float (&wx)[kChainBlocks][8], float (&lx)[kChainBlocks], double (&tx)[kChainBlocks]) {
+    Raw8<TDT, kChainBlocks> xt;
+    Raw8<QDT, kChainBlocks> xq;
+    ChainValues v;
+    float sum[2];
+    values_of(R, k, L, xt, xq, v, sum);
+    chain_weights<T_STATS, Q_STATS>(R, v, xt, xq, k, L, V, c, wx, lx);
+    block_totals(lx, sh_bw, tx);
+  };
   if (S > 1) {
     unsigned long long* mine = sums + static_cast<int64_t>(b) * S * kChainSumWords;
     if (wave == 0 && lane < kChainSumWords) {
@@ -1509,8 +1571,7 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
       double tx[kChainBlocks];
       for (int k = 0; k < S; ++k) {
         if (sh_have[k * kChainBlocks] && (k * kChainBlocks + 1 >= nblocks || sh_have[k * kChainBlocks + 1])) continue;
-        unit_weights<TDT, QDT, kChainBlocks>(R, k, level, V, c, wx, lx);
-        block_totals(lx, sh_bw, tx);
+        weights_of(k, level, wx, lx, tx);
         if (tid == 0) {
 #pragma unroll
           for (int i = 0; i < kChainBlocks; ++i)
@@ -1534,8 +1595,7 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
     redrawn = true;
     __syncthreads();                  // earlier readers of sh_part are done
     for (int k = 0; k < S; ++k) {
-      unit_weights<TDT, QDT, kChainBlocks>(R, k, 0, V, c, w, lsf);
-      block_totals(lsf, sh_bw, tot);
+      weights_of(k, 0, w, lsf, tot);
       if (tid == 0) {
 #pragma unroll
         for (int i = 0; i < kChainBlocks; ++i)
@@ -1548,21 +1608,13 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
   const double target = u_res * total;
   double before;
   const int kb_hit = block_of_draw(sh_part, nblocks, mine, inc_b, target, before);
-  const int e_hit = kb_hit * kLinBlock + tid * 8;
-  int e0 = first8(e_hit, V);          // class of wh[0]
+  if (redrawn) weights_of(kb_hit / kChainBlocks, 0, w, lsf, tot);
+  else if (kb_hit / kChainBlocks != seg) return;    // (the same for all workgroups of the pair: one stays)
   float wh[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) wh[i] = 0.f;
-  if (redrawn) {
-    const float no_scale[1] = {0.f};
-    e0 = e_hit;
-    if (e0 < V) weights8(R, e0, V, c, level, no_scale, wh);
-  } else {
-    if (kb_hit / kChainBlocks != seg) return;       // (the same for all workgroups of the pair: one stays)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) wh[i] = kb_hit & 1 ? w[1][i] : w[0][i];
-  }
-  draw_class(wh, e0, kb_hit, before, target, V, sh_bw[0], depth < P.out_stride ? P.out_tokens + static_cast<int64_t>(b) * P.out_stride + depth : nullptr);
+  for (int i = 0; i < 8; ++i) wh[i] = kb_hit & 1 ? w[1][i] : w[0][i];
+  draw_class(wh, first8(kb_hit * kLinBlock + tid * 8, V), kb_hit, before, target, V, sh_bw[0],
+             depth < P.out_stride ? P.out_tokens + static_cast<int64_t>(b) * P.out_stride + depth : nullptr);
 }
 
 // Workspace: [row statistics][helper protocol: pass descriptors, hand-back slots (zeroed by the

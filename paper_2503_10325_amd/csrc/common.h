@@ -188,6 +188,18 @@ struct __align__(16) SegStat {
   double z;
 };
 
+// (maximum, sum of 2^((l - max) c)) of a row over a workgroup's classes from those of its NW waves.
+template <int NW>
+__device__ __forceinline__ void merge_waves(const float* sh_m, const double* sh_z, float c, float& M, double& Z) {
+  M = sh_m[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) M = fmaxf(M, sh_m[w]);
+  Z = 0.0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w)
+    if (sh_m[w] != -INFINITY) Z += sh_z[w] * static_cast<double>(fast_exp2((sh_m[w] - M) * c));
+}
+
 // Merged (max, sum) of one logit row from its per-segment records load(0) .. load(nseg - 1), by a group of 16 lanes (lane sl
 // of the group takes segments sl, sl + 16, ...); the result is in every lane of the group.  The arithmetic and its order
 // are the same for every caller, so every caller gets the same bits (accept_walk_kernel merges by itself, in the

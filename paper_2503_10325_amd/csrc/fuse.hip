@@ -176,17 +176,6 @@ __device__ __forceinline__ void once_exponentials(const void* __restrict__ logit
   }
 }
 
-// (maximum, sum) of one row over the workgroup's classes from those of its waves.
-__device__ __forceinline__ void once_merge(const float* sh_m, const double* sh_z, float c, float& M, double& Z) {
-  M = sh_m[0];
-#pragma unroll
-  for (int w = 1; w < kOnceWaves; ++w) M = fmaxf(M, sh_m[w]);
-  Z = 0.0;
-#pragma unroll
-  for (int w = 0; w < kOnceWaves; ++w)
-    if (sh_m[w] != -INFINITY) Z += sh_z[w] * static_cast<double>(fast_exp2((sh_m[w] - M) * c));
-}
-
 // NB: drafters held (N of them exist); G: groups of eight classes per thread.
 template <int DT, int NB, int G>
 __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_once_kernel(
@@ -224,7 +213,7 @@ __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_on
     if (tid < N) {
       float M;
       double Z;
-      once_merge(sh_m[tid], sh_z[tid], c, M, Z);
+      merge_waves<kOnceWaves>(sh_m[tid], sh_z[tid], c, M, Z);
       const int r = tid * S + seg;
       sh_rm[r] = M; sh_rz[r] = Z; sh_have[r] = 1;
       if (S > 1) {
@@ -266,7 +255,7 @@ __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_on
         float e1[1][G][8], m1[1];
         once_exponentials<DT, 1, G>(logits, one, 1, sg * G * kOnceBlock, V, c, sh_m, sh_z, e1, m1, row0 + n);
         __syncthreads();
-        if (tid == 0) once_merge(sh_m[0], sh_z[0], c, sh_rm[r], sh_rz[r]);
+        if (tid == 0) merge_waves<kOnceWaves>(sh_m[0], sh_z[0], c, sh_rm[r], sh_rz[r]);
         __syncthreads();
       }
     }
