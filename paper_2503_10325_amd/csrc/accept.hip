@@ -1666,18 +1666,20 @@ static size_t chain_offset(const AcceptArgs& a) {
 static size_t chain_words(const AcceptArgs& a) {
   return static_cast<size_t>(stats_segments(a.V)) * (static_cast<size_t>(a.total_nodes + a.B) * kChainWords + static_cast<size_t>(a.B) * kChainSumWords);
 }
-// The line: up to five workgroups per four compute units and 64 KB of logits per compute unit.  Beyond, workgroups that wait
+// The line: up to five workgroups with rows per four compute units and 48 KB of logits per compute unit.  Beyond, workgroups that wait
 // share their units with others that work and the two launches are the faster.  Kernel times (the two launches have the
 // gap between them, 1 to 1.5 us, on top), chain / statistics + draw: 1 x 2 drafts x 1000 classes 7.8 / 8.6, 48 x 4 x
 // 2000 9.0 / 11.0, 16 x 16 x 8000 11.1 / 13.2, 4 x 8 x 32000 fp32 11.1 / 12.4, 8 x 8 x 32000 11.7 / 13.4, 32 x 4 x 16000 (320
 // workgroups) 13.2 / 13.5; 12 x 8 x 32000 (432) 13.2 / 13.7 but slower in a step, 3 x 8 x 128256 (432) 13.5 / 13.2, 16 x 8 x
-// 32000 (576) 17.4 / 14.5, 8 x 8 x 32000 fp32 (18 MB) 13.7 / 13.6.
+// 32000 (576) 17.4 / 14.5, 8 x 8 x 32000 fp32 (18 MB) 13.7 / 13.6, 5 x 3 to 9 x 50257 fp32 (245, 14 MB) 13.5 / 13.3 and 1 % behind
+// in a step; ragged drafts, calls in a loop: 12 x 1 to 10 x 32000 12.9 / 13.3, 30 x 1 to 16 x 8000 11.8 / 12.9.
 static bool chain_path(const AcceptArgs& a) {
   if (!linear_path(a) || a.path != 0 || a.max_nodes > kMaxNodes) return false;
   const int64_t S = stats_segments(a.V), levels = a.max_nodes + 1, n_cu = current_device_cus();
   if (levels * S > kChainMaxRecords || S * kChainBlocks > kChainMaxRecords) return false;
-  if (levels * S * a.B * 4 > n_cu * 5) return false;
-  if (levels * a.B * a.V * ((a.t_dtype == kBF16 ? 2 : 4) + (a.q_dtype == kBF16 ? 2 : 4)) > n_cu * 65536) return false;
+  const int64_t rows = static_cast<int64_t>(a.total_nodes) + a.B;       // (workgroups of levels that a request does not have leave at once)
+  if (rows * S * 4 > n_cu * 5 || levels * S * a.B > n_cu * 8) return false;
+  if (rows * a.V * ((a.t_dtype == kBF16 ? 2 : 4) + (a.q_dtype == kBF16 ? 2 : 4)) > n_cu * 49152) return false;
   return chain_offset(a) + chain_words(a) * sizeof(unsigned long long) <= accept_layout(a.B, a.total_nodes, a.n_q_rows, a.V).total;
 }
 
