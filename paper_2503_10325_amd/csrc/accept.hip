@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(
     const void* __restrict__ t_base, int t_dtype, int n_t_rows,
     const void* __restrict__ q_base, int q_dtype, int n_q_rows,
     int V, float c, int nseg, SegStat* __restrict__ stats, unsigned* __restrict__ zero_words, int n_zero,
-    const int32_t* __restrict__ q_row, int n_nodes) {
+    const int32_t* __restrict__ q_row) {
   const int seg = blockIdx.x;
   const int row = blockIdx.y;
   // side job of the first workgroup: clear the flags the walk kernel's workgroups exchange
@@ -135,14 +135,11 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(
   int64_t r = row;
   if (row >= n_t_rows) {
     base = q_base; dtype = q_dtype; r = row - n_t_rows;
-    // With more draft rows than draft nodes (several drafters per position) most rows are nobody's:
-    // a row no node was drawn from (q_row, clamped as the walk clamps it) is not read at all.
-    if (q_row) {
-      int mine = 0;
-      for (int i = threadIdx.x; i < n_nodes; i += kStatThreads)
-        mine |= (min(max(q_row[i], 0), n_q_rows - 1) == static_cast<int>(r));
-      if (!__syncthreads_or(mine)) return;
-    }
+    // With more draft rows than draft nodes (several drafters per position) most rows are nobody's: the grid then has a row
+    // per node, the one it was drawn from (clamped as the walk clamps it; nodes that share one write the same record).
+    // 32 requests x 6 nodes, 4 drafters, 32000 classes: 10.8 us when every draft row had workgroups that looked
+    // for a node of theirs first.
+    if (q_row) r = min(max(q_row[r], 0), n_q_rows - 1);
   }
   const int64_t row_off = r * static_cast<int64_t>(V);
   __shared__ StatScratch sh;
@@ -151,7 +148,7 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(
   if (segment_stats(base, dtype, row_off, seg * kStatSeg, V, c, sh, M, Z)) {
     SegStat st;
     st.m = M; st.pad = 0.f; st.z = Z;
-    stats[static_cast<int64_t>(row) * nseg + seg] = st;
+    stats[(row < n_t_rows ? row : n_t_rows + r) * nseg + seg] = st;
   }
 }
 
@@ -162,12 +159,12 @@ __global__ __launch_bounds__(kStatThreads) void zero_words_kernel(unsigned* __re
 void launch_row_stats(const void* t_base, int t_dtype, int n_t_rows, const void* q_base, int q_dtype,
                       int n_q_rows, int V, float c, SegStat* stats, hipStream_t stream, unsigned* zero_words,
                       int n_zero, const int32_t* q_row, int n_nodes) {
-  const int rows = n_t_rows + n_q_rows;
+  const int rows = n_t_rows + (q_row ? n_nodes : n_q_rows);
   if (rows <= 0 || V <= 0) return;
   const int nseg = stats_segments(V);
   dim3 grid(nseg, rows);
   hipLaunchKernelGGL(row_stats_kernel, grid, dim3(kStatThreads), 0, stream, t_base, t_dtype,
-                     n_t_rows, q_base, q_dtype, n_q_rows, V, c, nseg, stats, zero_words, n_zero, q_row, n_nodes);
+                     n_t_rows, q_base, q_dtype, n_q_rows, V, c, nseg, stats, zero_words, n_zero, q_row);
 }
 
 // ----------------------------------------------------------------------------------
@@ -1762,6 +1759,8 @@ void launch_accept(const AcceptArgs& a, hipStream_t stream) {
     return;
   }
   unsigned* words = reinterpret_cast<unsigned*>(ws + lay.words_off);      // start of the zeroed region
+  // rows nobody was drawn from exist only when there are more draft rows than nodes
+  const bool sparse_q = n_q_stat_rows > a.total_nodes;
   if (progressive_stats(a)) {
     unsigned* node_cnt = reinterpret_cast<unsigned*>(ws + lay.prog_cnt_off);
     int* stop = reinterpret_cast<int*>(ws + lay.prog_stop_off);
@@ -1775,15 +1774,13 @@ void launch_accept(const AcceptArgs& a, hipStream_t stream) {
                        a.draft_q, a.q_dtype, a.n_q_rows, a.V, c, nseg, stats, a.node_offsets, a.q_row, a.draft_tokens,
                        a.u_accept, node_cnt, stop, a.max_nodes);
   } else if (!a.target_stats_ready) {
-    // rows nobody was drawn from exist only when there are more draft rows than nodes
-    const bool sparse_q = n_q_stat_rows > a.total_nodes;
     launch_row_stats(a.target, a.t_dtype, n_t_rows, a.draft_q, a.q_dtype, n_q_stat_rows, a.V, c, stats, stream, words,
                      static_cast<int>(lay.n_zero_words), sparse_q ? a.q_row : nullptr, a.total_nodes);
   } else if (n_q_stat_rows > 0) {
     // the target rows' entries were written by the LM-head kernel; only the draft rows are left
-    launch_row_stats(a.draft_q, a.q_dtype, n_q_stat_rows, nullptr, 0, 0, a.V, c,
+    launch_row_stats(nullptr, 0, 0, a.draft_q, a.q_dtype, n_q_stat_rows, a.V, c,
                      stats + static_cast<size_t>(n_t_rows) * stats_segments(a.V), stream, words,
-                     static_cast<int>(lay.n_zero_words));
+                     static_cast<int>(lay.n_zero_words), sparse_q ? a.q_row : nullptr, a.total_nodes);
   } else {
     hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(kStatThreads), 0, stream, words,
                        static_cast<int>(lay.n_zero_words));
