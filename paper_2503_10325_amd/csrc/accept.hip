@@ -1682,12 +1682,14 @@ static bool chain_path(const AcceptArgs& a) {
 
 // The statistics pass that stops at each request's first rejection pays when the launch is several times what
 // the chip holds at once (about 2048 workgroups): later levels then start after the decisions of earlier ones.
+// The line (workgroups over all rows; whole calls, first rejections / all rows, us): 6528 32.4 / 29.4, 7200 41.2 / 37.9, 8448 40.1
+// / 37.9, 9216 43.1 / 41.3; 10752 41.5 / 42.2, 10880 40.6 / 43.8, 12800 39.7 / 48.2, 14784 42.9 / 48.9.
 // It needs draft logits (their statistics are part of the decision) and computes the target rows itself.
 static bool progressive_stats(const AcceptArgs& a) {
   if (!linear_path(a) || a.q_kind != 0 || a.target_stats_ready || a.total_nodes <= 0) return false;
   if (a.max_nodes > kProgMaxNodes || a.B > 65535) return false;
   const int64_t wgs = (static_cast<int64_t>(a.total_nodes) * 2 + a.B) * stats_segments(a.V);
-  return a.path == 4 || (a.path == 0 && wgs >= 6144);
+  return a.path == 4 || (a.path == 0 && wgs >= 9728);
 }
 
 const char* accept_plan_name(const AcceptArgs& a, int n_cu) {
