@@ -431,11 +431,14 @@ static int lm_tile_rows(const int (&choices)[N], int vb, int rows, int V, int n_
   return best;
 }
 
-// One wave per (row, 8192-class segment): the block statistics of the segment (per_seg <= 64 of them) become the
-// entry the acceptance walk reads.
-__global__ __launch_bounds__(kWave) void lm_stats_merge_kernel(const float2* __restrict__ bstats, int nvb, int per_seg, int nseg,
-                                                               float c, SegStat* __restrict__ stats) {
-  const int seg = blockIdx.x, row = blockIdx.y, lane = threadIdx.x;
+// One wave per (row, 8192-class segment), four to a workgroup: the block statistics of the segment (per_seg <= 64 of them)
+// become the entry the acceptance walk reads.
+constexpr int kMergeWaves = 4;
+__global__ __launch_bounds__(kMergeWaves * kWave) void lm_stats_merge_kernel(const float2* __restrict__ bstats, int nvb, int per_seg, int nseg,
+                                                                             int entries, float c, SegStat* __restrict__ stats) {
+  const int entry = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * kMergeWaves + threadIdx.x / kWave)), lane = threadIdx.x & 63;
+  if (entry >= entries) return;
+  const int row = entry / nseg, seg = entry - row * nseg;
   const int i = seg * per_seg + lane;
   float m = -INFINITY, s = 0.f;
   if (lane < per_seg && i < nvb) {
@@ -449,7 +452,7 @@ __global__ __launch_bounds__(kWave) void lm_stats_merge_kernel(const float2* __r
   if (lane == 0) {
     SegStat st;
     st.m = M; st.pad = 0.f; st.z = z;
-    stats[static_cast<int64_t>(row) * nseg + seg] = st;
+    stats[entry] = st;
   }
 }
 
@@ -520,7 +523,8 @@ int launch_lm_head(const LmHeadArgs& a, hipStream_t stream) {
   }
   if (rc != 0) return rc;
   const int nseg = stats_segments(a.V);
-  hipLaunchKernelGGL(lm_stats_merge_kernel, dim3(nseg, a.rows), dim3(kWave), 0, stream, P.bstats, P.nvb, 8192 / vb, nseg, P.c,
+  hipLaunchKernelGGL(lm_stats_merge_kernel, dim3((a.rows * nseg + kMergeWaves - 1) / kMergeWaves), dim3(kMergeWaves * kWave), 0, stream, P.bstats, P.nvb,
+                     8192 / vb, nseg, a.rows * nseg, P.c,
                      static_cast<SegStat*>(a.stats));
   return 0;
 }
