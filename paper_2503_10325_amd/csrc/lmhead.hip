@@ -432,7 +432,8 @@ static int lm_tile_rows(const int (&choices)[N], int vb, int rows, int V, int n_
 }
 
 // One wave per (row, 8192-class segment), four to a workgroup: the block statistics of the segment (per_seg <= 64 of them)
-// become the entry the acceptance walk reads.
+// become the entry the acceptance walk reads.  (One wave per workgroup, a launch of thousands: 72 rows x 4 segments 4.7 -> 4.4 us,
+// 429 x 16 5.5 -> 5.2, 1040 x 16 7.0 -> 6.2.)
 constexpr int kMergeWaves = 4;
 __global__ __launch_bounds__(kMergeWaves * kWave) void lm_stats_merge_kernel(const float2* __restrict__ bstats, int nvb, int per_seg, int nseg,
                                                                              int entries, float c, SegStat* __restrict__ stats) {
