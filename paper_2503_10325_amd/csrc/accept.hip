@@ -1301,8 +1301,10 @@ __device__ __forceinline__ void chain_weights(const WalkRows& R, const ChainValu
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     if (k == 0 ? !T : (!Q || L == 0)) continue;
-    const float mm = (v.m[k] == -INFINITY) ? 0.f : v.m[k];
-    f[k] = static_cast<float>(exp2(static_cast<double>(mm - (k ? R.q_m : R.t_m)) * static_cast<double>(c)) * (k ? R.q_invz : R.t_invz));
+    // (a thread without a finite logit has exponentials 0 and takes the row's maximum for its own: a factor from any fixed number
+    // overflows where the row lies far below it, and 0 x inf is no weight.  A row of -inf throughout stays NaN)
+    const float row_m = k ? R.q_m : R.t_m, mm = (v.m[k] == -INFINITY) ? row_m : v.m[k];
+    f[k] = static_cast<float>(exp2(static_cast<double>(mm - row_m) * static_cast<double>(c)) * (k ? R.q_invz : R.t_invz));
   }
   const float t_invz = static_cast<float>(R.t_invz);
 #pragma unroll

@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def inputs(V, n, tdt, qdt, probs, seed):
+def inputs(V, n, tdt, qdt, probs, seed, T=1.0):
     g = torch.Generator(device="cuda").manual_seed(seed)
     n = np.asarray(n)
     off = np.concatenate([[0], np.cumsum(n)])
@@ -20,7 +20,7 @@ def inputs(V, n, tdt, qdt, probs, seed):
     rows = torch.from_numpy(np.concatenate([off[b] + b + np.arange(k) for b, k in enumerate(n)] + [[]]).astype(np.int64)).cuda()
     draft = target[rows] + 0.7 * torch.randn((total, V), generator=g, device="cuda")
     e = torch.empty_like(draft).exponential_(generator=g)
-    tokens = (torch.softmax(draft, 1) / e).argmax(1).int()
+    tokens = (torch.softmax(draft / T, 1) / e).argmax(1).int()
     draft = (torch.softmax(draft, 1) if probs else draft).to(qdt).contiguous()
     u = torch.randint(0, 1 << 24, (total + B,), generator=g, device="cuda").float() * 2.0 ** -24
     return dict(B=B, total=total, most=int(n.max()), off=torch.from_numpy(off.astype(np.int32)).cuda(), tokens=tokens,
@@ -130,3 +130,62 @@ def test_chain_replays():
         graph.replay()
         torch.cuda.synchronize()
         same(out, run(sv, s, sv.SpecAcceptTuning(path=3), torch.empty_like(ws)))
+
+
+def given_statistics(d, T, V):
+    """The records that the projection hands over: per 8192-class segment the largest logit m and the sum of 2^((l - m) c)."""
+    c = float(np.float32(1.4426950408889634) / np.float32(T))
+    rec = []
+    for x in d["target"].double().split(8192, 1):
+        m = x.amax(1)
+        z = torch.exp2((x - m.where(m.isfinite(), torch.zeros_like(m))[:, None]) * c).sum(1)
+        rec.append(torch.stack([m.float().view(torch.int32).long(), z.view(torch.int64)], 1))
+    return torch.stack(rec, 1).contiguous().view(torch.uint8).view(-1)
+
+
+@pytest.mark.parametrize("accepted", [True, False])
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("shift,T", [(-200.0, 1.0), (-20.0, 0.1), (90.0, 0.1)])
+@pytest.mark.parametrize("V,dtype", [(1000, torch.bfloat16), (32000, torch.bfloat16), (50257, torch.float32)])
+def test_chain_of_shifted_and_masked_rows(V, dtype, shift, T, masked, accepted):
+    """Acceptance does not depend on where the logits lie, nor on classes without mass: rows far below and above zero, draft rows cut
+    to their 40 best classes and target rows without 64 to 2048 classes in a row (of a thread's classes none, some or all are left),
+    and vocabularies whose last segment leaves threads without classes."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import oracle
+    from gpu_util import compare_accept
+    from paper_2503_10325_amd import binding as sv
+    n = np.asarray([4, 0, 3])
+    d = inputs(V, n, torch.float32, torch.float32, False, 11, T)
+    if masked:
+        least = d["draft"].topk(40, 1).values[:, -1:]
+        held = torch.zeros_like(d["draft"], dtype=torch.bool).scatter_(1, d["tokens"].long()[:, None], True)
+        d["draft"] = d["draft"].masked_fill((d["draft"] < least) & ~held, -float("inf"))
+        run_of = 64 if V < 8192 else 2048
+        gone = torch.arange(V, device="cuda") // run_of % 2 == 1
+        kept = torch.zeros_like(d["target"], dtype=torch.bool).index_fill_(1, d["tokens"].long(), True)
+        d["target"] = d["target"].masked_fill(gone & ~kept, -float("inf"))
+    d["target"], d["draft"] = (d["target"] + shift).to(dtype), (d["draft"] + shift).to(dtype)
+    d["ua"].fill_(0.0 if accepted else 1.0 - 2.0 ** -24)
+    code = sv.SPEC_BF16 if dtype == torch.bfloat16 else sv.SPEC_F32
+    assert sv.spec_describe_accept_plan(3, V, 7, 4, False, target_dtype=code, q_dtype=code).startswith("accept_chain_kernel")
+    ws = torch.randint(0, 256, (sv.spec_accept_workspace_size(3, 7, 7, V),), dtype=torch.uint8, device="cuda")
+    bits = lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16) if dtype == torch.bfloat16 else t.cpu().numpy()
+    for seed in range(8):             # (one set of rows, many draws)
+        g = torch.Generator().manual_seed(seed)
+        d["ur"].copy_(torch.randint(0, 1 << 24, (3,), generator=g).float() * 2.0 ** -24)
+        ref = run(sv, d, sv.SpecAcceptTuning(path=3), ws.clone(), T)
+        got = run(sv, d, None, ws, T)
+        same(got, ref)
+        same(run(sv, d, sv.SpecAcceptTuning(patience=0), ws, T), ref)
+        if dtype == torch.bfloat16:
+            rec = given_statistics(d, T, V)
+            ws[:rec.numel()].copy_(rec)
+            same(run(sv, d, None, ws, T, prestats=True), ref)
+        want = oracle.accept(d["off"].cpu().numpy(), None, d["tokens"].cpu().numpy(), bits(d["target"]), bits(d["draft"]),
+                             d["q_row"].cpu().numpy(), d["ua"].cpu().numpy(), d["ur"].cpu().numpy(), temperature=T)
+        assert (want["accept_len"] == n).all() == accepted
+        bad, ties, _ = compare_accept(dict(accept_len=got["len"].cpu().numpy(), out_tokens=got["tok"].cpu().numpy(),
+                                           stop_node=got["stop"].cpu().numpy()), want, n)
+        assert not bad and ties <= 1

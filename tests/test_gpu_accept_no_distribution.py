@@ -88,3 +88,21 @@ def test_rejected_sibling_leaves_the_target_distribution(vocab, tuning):
     bad, ties, _ = compare_accept(got, ref, ai.st.n)
     assert not bad and ties <= 1
     assert visited_pattern_agrees(got, ref, off)
+
+
+@pytest.mark.parametrize("vocab", [65544, 50257, 4096, 1000])
+def test_chain_accepts_in_one_launch(vocab):
+    """The kernel that a small linear batch takes by itself."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cfg = W.scaled(W.CONFIGS["c2_tree_llama3_8b"], batch=4, vocab=vocab, draft=("linear", 3))
+    assert sv.spec_describe_accept_plan(4, vocab, 12, 3, False).startswith("accept_chain_kernel")
+    ai, target, draft, tokens = spoiled(cfg, seed=4)
+    got, ref = run(cfg, ai, target, draft, tokens, dict(path=0))
+    assert (ref["accept_len"] >= 1).all()
+    bad, ties, _ = compare_accept(got, ref, ai.st.n)
+    assert not bad and ties <= 1
+    ai.u_accept[ai.st.node_offsets[1:] - 1] = 1.0 - 2.0 ** -24        # the last node is rejected where the draft favours its token
+    got, ref = run(cfg, ai, target, draft, tokens, dict(path=0))
+    bad, ties, _ = compare_accept(got, ref, ai.st.n)
+    assert not bad and ties <= 1
