@@ -284,7 +284,10 @@ __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_on
 #pragma unroll
     for (int n = 0; n < NB; ++n)
       if (n < N) {
-        const double f = sh_row_w[n] * exp2(static_cast<double>((m[n] == -INFINITY ? 0.f : m[n]) - sh_row_m[n]) * static_cast<double>(c));
+        // (a thread without a finite logit of this drafter has exponentials 0 and takes the row's maximum for its own: a factor
+        // from any fixed number overflows where the row lies far below it, and 0 x inf is no probability)
+        const float row_m = sh_row_m[n];
+        const double f = sh_row_w[n] * exp2(static_cast<double>((m[n] == -INFINITY ? row_m : m[n]) - row_m) * static_cast<double>(c));
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll

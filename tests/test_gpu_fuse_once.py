@@ -95,3 +95,40 @@ def test_mixture_in_one_launch_replays():
         torch.cuda.synchronize()
         ref, want = call(sv, s, torch.empty_like(ws))
         assert torch.equal(out, want) and all(torch.equal(a, b) for a, b in zip(ints, ref))
+
+
+@pytest.mark.parametrize("T", [1.0, 0.05])
+@pytest.mark.parametrize("B,k,N,V,dtype", [
+    (2, 2, 3, 1000, torch.bfloat16), (2, 3, 4, 32000, torch.bfloat16), (2, 2, 6, 9001, torch.float32), (2, 2, 2, 50264, torch.float32),
+])
+def test_mixture_of_masked_rows_far_below_zero(B, k, N, V, dtype, T):
+    """Drafters cut to a few classes (a thread's classes are all without mass in one drafter, not in another), rows whose largest
+    logit over T overflows an exponential.  Tolerance: an argument of A binary places is rounded twice and the thread's
+    maximum has an argument of its own, 2^-24 A each; 2^-21 is for the exponentials, the sums and the result."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import binding as sv
+    full = sv.spec_fuse_drafts_workspace_size(B, k, N, V, sv.SPEC_FUSE_MIXTURE)
+    least = B * k * N * ((V + 8191) // 8192) * 16 + 256
+    ws = torch.randint(0, 256, (max(full, least),), dtype=torch.uint8, device="cuda")
+    for seed in range(2):
+        d = make(B, k, N, V, dtype, seed)
+        x = d["logits"].float()
+        cut = x.topk(30, 1).values[:, -1:]
+        odd = torch.arange(B * k * N, device="cuda")[:, None] % 2 == 1
+        x = x.masked_fill(odd & (x < cut), -float("inf"))                        # every other drafter: 30 classes
+        x = x.masked_fill(~odd & (torch.arange(V, device="cuda") // 512 % 3 == 0), -float("inf"))      # the others: runs of 512 gone
+        d["logits"] = (x - (1500.0 if T == 1.0 else 60.0)).to(dtype)
+        used = (torch.arange(k, device="cuda")[None] < d["lens"][:, None]).reshape(-1)
+        c = float(np.float32(1.4426950408889634) / np.float32(T))
+        lg = d["logits"].double()
+        A = ((lg.amax(1, keepdim=True) - lg) * c).nan_to_num(0.0, posinf=0.0)
+        w = d["conf"].double()
+        s = w.sum(-1, keepdim=True)
+        w = torch.where(s > 0, w / s, torch.full_like(w, 1.0 / N)).view(-1, N, 1)
+        p = torch.softmax(lg * (c * np.log(2.0)), 1)
+        ref = (w * p.view(-1, N, V)).sum(1)
+        bound = (w * (p * (2.0 ** -21 + A * 2.0 ** -22)).view(-1, N, V)).sum(1) + 2.0 ** -125       # (below: no normal number)
+        for room in (full, least):
+            _, out = call(sv, d, ws[:room], T)
+            assert bool(((out.double() - ref).abs() <= bound)[used].all()), room
