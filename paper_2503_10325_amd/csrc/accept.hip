@@ -1708,6 +1708,10 @@ const char* accept_plan_name(const AcceptArgs& a, int n_cu) {
                 : "accept_cluster_kernel (cluster of workgroups per request, row slices held in registers or LDS)";
 }
 
+// Draft rows whose statistics count.  Without nodes nothing was drawn from any: every request draws from its one target row,
+// and no launch of a row per node is empty.
+static int draft_stat_rows(const AcceptArgs& a) { return a.q_kind == 0 && a.total_nodes > 0 ? a.n_q_rows : 0; }
+
 static AcceptParams accept_params(const AcceptArgs& a, int n_t_rows, float c, const SegStat* stats) {
   AcceptParams P;
   P.B = a.B; P.V = a.V; P.n_t_rows = n_t_rows; P.n_q_rows = a.n_q_rows > 0 ? a.n_q_rows : 1; P.nseg = stats_segments(a.V);
@@ -1732,7 +1736,7 @@ void launch_accept(const AcceptArgs& a, hipStream_t stream) {
   if (a.B <= 0) return;
   const float c = kLog2e / a.temperature;
   const int n_t_rows = a.total_nodes + a.B;
-  const int n_q_stat_rows = (a.q_kind == 0) ? a.n_q_rows : 0;
+  const int n_q_stat_rows = draft_stat_rows(a);
   const AcceptLayout lay = accept_layout(a.B, a.total_nodes, a.n_q_rows, a.V);
   unsigned char* ws = static_cast<unsigned char*>(a.workspace);
   const int n_cu = current_device_cus();

@@ -189,3 +189,37 @@ def test_chain_of_shifted_and_masked_rows(V, dtype, shift, T, masked, accepted):
         bad, ties, _ = compare_accept(dict(accept_len=got["len"].cpu().numpy(), out_tokens=got["tok"].cpu().numpy(),
                                            stop_node=got["stop"].cpu().numpy()), want, n)
         assert not bad and ties <= 1
+
+
+@pytest.mark.parametrize("B,V,dtype,parent", [
+    (4, 1000, torch.bfloat16, False), (4, 7, torch.bfloat16, False), (64, 128256, torch.bfloat16, False), (40, 32000, torch.float32, False),
+    (4, 65545, torch.bfloat16, True), (3, 65544, torch.bfloat16, True),
+])
+def test_no_drafts_beside_draft_rows(B, V, dtype, parent):
+    """No request has drafts, draft rows and a row number are there all the same: one token from every target row, on every path, whatever the workspace held, target statistics from the caller included."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import binding as sv
+    g = torch.Generator(device="cuda").manual_seed(3)
+    target = (torch.randn((B, V), generator=g, device="cuda") * 2).to(dtype)
+    draft = torch.randn((5, V), generator=g, device="cuda").to(dtype)
+    one = torch.zeros(1, dtype=torch.int32, device="cuda")
+    off, ur = torch.zeros(B + 1, dtype=torch.int32, device="cuda"), torch.rand(B, generator=g, device="cuda")
+    ua = torch.zeros(1, device="cuda")
+    # the token: the first class whose running sum passes u, in fp64; the next ones where u is within the sums' rounding of it
+    c = float(np.float32(1.4426950408889634) / np.float32(0.9)) * np.log(2.0)
+    cdf = torch.softmax(target.double() * c, 1).cumsum(1)
+    lo, hi = ((cdf < (ur.double() + e)[:, None]).sum(1).clamp(max=V - 1) for e in (-1e-6, 1e-6))
+    size = sv.spec_accept_workspace_size(B, 0, 5, V)
+    for how in ("plain", "prestats") if dtype == torch.bfloat16 else ("plain",):
+        ws = torch.randint(0, 256, (size,), dtype=torch.uint8, generator=g, device="cuda")
+        if how == "prestats":
+            rec = given_statistics(dict(target=target), 0.9, V)
+            ws[:rec.numel()].copy_(rec)
+        for _ in range(2):
+            length = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+            tok, stop = torch.full((B, 1), -7, dtype=torch.int32, device="cuda"), torch.full((B,), -7, dtype=torch.int32, device="cuda")
+            (sv.spec_accept_prestats if how == "prestats" else sv.spec_accept)(
+                B, 0, 0, off, one if parent else None, one, target, draft, sv.SPEC_Q_LOGITS, one, 0.9, ua, ur, length, tok, stop, None, ws)
+            assert bool((length == 0).all()) and bool((stop == -1).all()), how
+            assert bool(((tok[:, 0] >= lo) & (tok[:, 0] <= hi)).all()), how
