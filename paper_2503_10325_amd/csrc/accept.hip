@@ -1708,8 +1708,8 @@ const char* accept_plan_name(const AcceptArgs& a, int n_cu) {
                 : "accept_cluster_kernel (cluster of workgroups per request, row slices held in registers or LDS)";
 }
 
-// Draft rows whose statistics count.  Without nodes nothing was drawn from any: every request draws from its one target row,
-// and no launch of a row per node is empty.
+// Draft rows whose statistics count.  Without nodes nothing was drawn from any: whatever is handed in (a null pointer
+// among it) is not read, every request draws from its one target row, and no launch of a row per node is empty.
 static int draft_stat_rows(const AcceptArgs& a) { return a.q_kind == 0 && a.total_nodes > 0 ? a.n_q_rows : 0; }
 
 static AcceptParams accept_params(const AcceptArgs& a, int n_t_rows, float c, const SegStat* stats) {
@@ -1727,7 +1727,7 @@ static AcceptParams accept_params(const AcceptArgs& a, int n_t_rows, float c, co
 
 template <int TDT, int QDT>
 static auto chain_kernel(const AcceptArgs& a) {
-  const bool q_stats = a.q_kind == 0 && a.n_q_rows > 0;       // (no draft rows: every request draws from its one target row)
+  const bool q_stats = draft_stat_rows(a) > 0;
   return a.target_stats_ready ? (q_stats ? accept_chain_kernel<TDT, QDT, false, true> : accept_chain_kernel<TDT, QDT, false, false>)
                               : (q_stats ? accept_chain_kernel<TDT, QDT, true, true> : accept_chain_kernel<TDT, QDT, true, false>);
 }

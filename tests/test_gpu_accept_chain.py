@@ -196,7 +196,8 @@ def test_chain_of_shifted_and_masked_rows(V, dtype, shift, T, masked, accepted):
     (4, 65545, torch.bfloat16, True), (3, 65544, torch.bfloat16, True),
 ])
 def test_no_drafts_beside_draft_rows(B, V, dtype, parent):
-    """No request has drafts, draft rows and a row number are there all the same: one token from every target row, on every path, whatever the workspace held, target statistics from the caller included."""
+    """No request has drafts, draft rows and a row number are there all the same (or are announced behind a null pointer): one token
+    from every target row, on every path, whatever the workspace held, target statistics from the caller included."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2503_10325_amd import binding as sv
@@ -211,7 +212,7 @@ def test_no_drafts_beside_draft_rows(B, V, dtype, parent):
     cdf = torch.softmax(target.double() * c, 1).cumsum(1)
     lo, hi = ((cdf < (ur.double() + e)[:, None]).sum(1).clamp(max=V - 1) for e in (-1e-6, 1e-6))
     size = sv.spec_accept_workspace_size(B, 0, 5, V)
-    for how in ("plain", "prestats") if dtype == torch.bfloat16 else ("plain",):
+    for how in ("plain", "prestats", "null") if dtype == torch.bfloat16 else ("plain", "null"):
         ws = torch.randint(0, 256, (size,), dtype=torch.uint8, generator=g, device="cuda")
         if how == "prestats":
             rec = given_statistics(dict(target=target), 0.9, V)
@@ -219,7 +220,14 @@ def test_no_drafts_beside_draft_rows(B, V, dtype, parent):
         for _ in range(2):
             length = torch.full((B,), -7, dtype=torch.int32, device="cuda")
             tok, stop = torch.full((B, 1), -7, dtype=torch.int32, device="cuda"), torch.full((B,), -7, dtype=torch.int32, device="cuda")
-            (sv.spec_accept_prestats if how == "prestats" else sv.spec_accept)(
-                B, 0, 0, off, one if parent else None, one, target, draft, sv.SPEC_Q_LOGITS, one, 0.9, ua, ur, length, tok, stop, None, ws)
+            if how == "null":
+                code = sv.SPEC_BF16 if dtype == torch.bfloat16 else sv.SPEC_F32
+                rc = sv.lib().spec_accept(B, V, 0, 5, 0, off.data_ptr(), one.data_ptr() if parent else None, None, target.data_ptr(), code,
+                                          None, code, sv.SPEC_Q_LOGITS, None, 0.9, None, ur.data_ptr(), length.data_ptr(), tok.data_ptr(), 1,
+                                          stop.data_ptr(), None, ws.data_ptr(), size, torch.cuda.current_stream().cuda_stream)
+                assert rc == sv.SPEC_OK
+            else:
+                (sv.spec_accept_prestats if how == "prestats" else sv.spec_accept)(
+                    B, 0, 0, off, one if parent else None, one, target, draft, sv.SPEC_Q_LOGITS, one, 0.9, ua, ur, length, tok, stop, None, ws)
             assert bool((length == 0).all()) and bool((stop == -1).all()), how
             assert bool(((tok[:, 0] >= lo) & (tok[:, 0] <= hi)).all()), how
