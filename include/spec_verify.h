@@ -229,7 +229,8 @@ int32_t spec_accept_tuned(
  * enqueued; SPEC_ERR_LAUNCH if the array's address cannot be obtained.  Every call on one GPU uses
  * that GPU's one array: calls that may overlap on one GPU (different streams, different threads)
  * race and must be serialised by the caller.  What has to start at zero is cleared by a kernel of
- * the call itself; messages between workgroups carry the call's own tag instead. */
+ * the call itself; messages between workgroups carry a tag instead that no other call of the
+ * process has (calls under capture clear them: their replays repeat it). */
 size_t spec_accept_noalloc_max_workspace(void);
 int32_t spec_accept_noalloc(
     int32_t B, int32_t V, int32_t total_nodes, int32_t n_q_rows, int32_t max_nodes_per_req,

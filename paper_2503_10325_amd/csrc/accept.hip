@@ -30,18 +30,27 @@ namespace specv {
 // ----------------------------------------------------------------------------------
 // messages between the workgroups of one launch
 // ----------------------------------------------------------------------------------
-unsigned next_message_tag() {
-  static std::atomic<unsigned> calls{static_cast<unsigned>(std::chrono::steady_clock::now().time_since_epoch().count() * 2654435761u >> 9)};
-  return calls.fetch_add(1, std::memory_order_relaxed) * kTagsPerCall;
-}
-
-bool stream_captures(hipStream_t stream) {
+static bool stream_captures(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
     (void)hipGetLastError();
     return true;
   }
   return st != hipStreamCaptureStatusNone;
+}
+
+// Tags with rounds are below 2^36, those without have that bit set: whichever of their bits a kernel looks at tells them apart.
+// The count starts somewhere else in every process: what memory held before it was the process's own is no message.
+MessageTag next_message_tag(bool rounds, hipStream_t stream) {
+  static const uint64_t start = static_cast<uint64_t>(std::chrono::steady_clock::now().time_since_epoch().count()) * 0x9E3779B97F4A7C15ull >> 20;
+  static std::atomic<uint64_t> calls[2];
+  const uint64_t n = calls[rounds].fetch_add(1, std::memory_order_relaxed);
+  constexpr uint64_t kBit = 1ull << (kTagBitsRounds - 1), kRoundCalls = kBit / kTagRounds, kCalls = 1ull << (kTagBits - 1);
+  MessageTag t;
+  const uint64_t at = (start + n) % (rounds ? kRoundCalls : kCalls);
+  t.tag = rounds ? at * kTagRounds : (at / kBit * 2 + 1) * kBit + at % kBit;
+  t.clear = n >= (rounds ? kRoundCalls : kCalls) || stream_captures(stream);
+  return t;
 }
 
 __global__ __launch_bounds__(256) void clear_messages_kernel(unsigned long long* __restrict__ words, int64_t n) {
@@ -1208,22 +1217,15 @@ static auto linear_kernel(int blocks) {
 //
 // Messages are 64-bit words {data : tag}, relaxed device-scope accesses; the tag is the call's own number, so that the
 // workspace needs no clearing (a launch that is being captured is preceded by a kernel that clears them: replays repeat the
-// tag).  Waits are bounded: a workgroup that misses a record after `patience` polls works it out itself, with the same
+// tag; see MessageTag).  Waits are bounded: a workgroup that misses a record after `patience` polls works it out itself, with the same
 // arithmetic in the same order, and goes on; nobody's result depends on who came first.
 //
 // What bounds it: latency.  Offsets, draft row numbers, logits, the two exchanges (a trip each way), the class.
 // ----------------------------------------------------------------------------------
 constexpr int kChainMaxRecords = 512;      // (nodes + 1) x segments of a request: a thread gathers one
-constexpr int kChainWords = 6;             // words of a record: (sum, 2; maximum) of the target and of the draft row
-constexpr int kChainSumWords = 4;          // ... of a segment's weights: two blocks, 2 each
 constexpr int kChainBlocks = 2;            // blocks of 4096 classes in a segment
-
-__device__ __forceinline__ unsigned long long chain_word(unsigned data, unsigned tag) {
-  return (static_cast<unsigned long long>(data) << 32) | tag;
-}
-__device__ __forceinline__ double chain_double(unsigned long long hi, unsigned long long lo) {
-  return __hiloint2double(static_cast<int>(hi >> 32), static_cast<int>(lo >> 32));
-}
+constexpr int kChainWords = 2 * kRecordWords;             // words of a record: (sum, maximum) of the target and of the draft row
+constexpr int kChainSumWords = kChainBlocks * kSumWords;  // ... of a segment's weights
 
 struct ChainScratch {
   float m[2][kLinWaves];
@@ -1335,7 +1337,7 @@ __device__ __forceinline__ void chain_weights(const WalkRows& R, const ChainValu
 // T_STATS: the statistics of the target rows are taken here (else they lie in P.stats); Q_STATS: draft rows are logits.
 template <int TDT, int QDT, bool T_STATS, bool Q_STATS>
 __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptParams P, unsigned long long* __restrict__ msg,
-                                                                      unsigned long long* __restrict__ sums, unsigned tag, int levels) {
+                                                                      unsigned long long* __restrict__ sums, unsigned long long tag, int levels) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int S = P.nseg, V = P.V;
   const int seg = blockIdx.x % S, bj = blockIdx.x / S, j = bj % levels, b = bj / levels;
@@ -1413,10 +1415,9 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
       double Z;
       merge_waves<kLinWaves>(sh_stat.m[tid], sh_stat.z[tid], c, M, Z);
       sh_m[tid][own] = M; sh_z[tid][own] = Z;
-      unsigned long long* to = msg + ((trow0 + j) * S + seg) * kChainWords + 3 * tid;
-      st_dev(to, chain_word(static_cast<unsigned>(__double2hiint(Z)), tag));
-      st_dev(to + 1, chain_word(static_cast<unsigned>(__double2loint(Z)), tag));
-      st_dev(to + 2, chain_word(__float_as_uint(M), tag));
+      unsigned long long* to = msg + ((trow0 + j) * S + seg) * kChainWords + kRecordWords * tid;
+#pragma unroll
+      for (int k = 0; k < kRecordWords; ++k) st_dev(to + k, message_word(k, Z, M, tag));
     }
     // ---- gather: thread r the record of segment r % S of rows r / S ----
     bool have = true;
@@ -1433,10 +1434,9 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
         if (mine) {
 #pragma unroll
           for (int k = 0; k < kChainWords; ++k)
-            if (k < 3 ? T_STATS : Q_STATS) w[k] = ld_dev(from + k);
-#pragma unroll
-          for (int k = 0; k < kChainWords; ++k)
-            if (k < 3 ? T_STATS : want_q) have &= static_cast<unsigned>(w[k]) == tag;
+            if (k < kRecordWords ? T_STATS : Q_STATS) w[k] = ld_dev(from + k);
+          if constexpr (T_STATS) have = have_tag<kRecordWords>(w, tag);
+          if constexpr (Q_STATS) have &= !want_q || have_tag<kRecordWords>(w + kRecordWords, tag);
         }
         if (__all(have) || poll >= P.patience) break;
         __builtin_amdgcn_s_sleep(1);
@@ -1444,8 +1444,8 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
       if (tid < n_rec) {
         sh_have[tid] = have;
         if (tid != own) {
-          if constexpr (T_STATS) { sh_m[0][tid] = __uint_as_float(static_cast<unsigned>(w[2] >> 32)); sh_z[0][tid] = chain_double(w[0], w[1]); }
-          if constexpr (Q_STATS) { sh_m[1][tid] = __uint_as_float(static_cast<unsigned>(w[5] >> 32)); sh_z[1][tid] = chain_double(w[3], w[4]); }
+          if constexpr (T_STATS) { sh_m[0][tid] = message_max(w); sh_z[0][tid] = message_sum(w); }
+          if constexpr (Q_STATS) { sh_m[1][tid] = message_max(w + kRecordWords); sh_z[1][tid] = message_sum(w + kRecordWords); }
         }
       }
     }
@@ -1543,26 +1543,26 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
   if (S > 1) {
     unsigned long long* mine = sums + static_cast<int64_t>(b) * S * kChainSumWords;
     if (wave == 0 && lane < kChainSumWords) {
-      const double z = lane >= 2 ? tot[1] : tot[0];
-      st_dev(mine + seg * kChainSumWords + lane, chain_word(static_cast<unsigned>(lane & 1 ? __double2loint(z) : __double2hiint(z)), tag));
+      const int i = lane >= kSumWords;
+      st_dev(mine + seg * kChainSumWords + lane, message_word(lane - i * kSumWords, i ? tot[1] : tot[0], 0.f, tag));
     }
     bool have = true;
     if (tid < (nblocks + kWave - 1) / kWave * kWave) {          // (wave-uniform) thread k gathers block k
       const bool want = tid < nblocks && tid / kChainBlocks != seg;
-      unsigned long long hi = 0ull, lo = 0ull;
+      unsigned long long w[kSumWords] = {0ull, 0ull, 0ull};
       for (int poll = 0;; ++poll) {
         have = true;
         if (want) {
-          hi = ld_dev(mine + tid * 2);
-          lo = ld_dev(mine + tid * 2 + 1);
-          have = static_cast<unsigned>(hi) == tag && static_cast<unsigned>(lo) == tag;
+#pragma unroll
+          for (int k = 0; k < kSumWords; ++k) w[k] = ld_dev(mine + tid * kSumWords + k);
+          have = have_tag<kSumWords>(w, tag);
         }
         if (__all(have) || poll >= P.patience) break;
         __builtin_amdgcn_s_sleep(1);
       }
       if (tid < nblocks) {
         sh_have[tid] = have;
-        sh_part[tid] = want ? chain_double(hi, lo) : (tid & 1 ? tot[1] : tot[0]);
+        sh_part[tid] = want ? message_sum(w) : (tid & 1 ? tot[1] : tot[0]);
       }
     }
     if (__syncthreads_or(!have)) {
@@ -1758,12 +1758,13 @@ void launch_accept(const AcceptArgs& a, hipStream_t stream) {
     P.patience = (a.patience >= 0 && a.patience <= 1000000) ? a.patience : 1000;
     auto* msg = reinterpret_cast<unsigned long long*>(ws + chain_offset(a));
     unsigned long long* sums = msg + static_cast<size_t>(n_t_rows) * P.nseg * kChainWords;
-    if (stream_captures(stream)) clear_messages(msg, static_cast<int64_t>(chain_words(a)), stream);
+    const MessageTag t = next_message_tag(false, stream);
+    if (t.clear) clear_messages(msg, static_cast<int64_t>(chain_words(a)), stream);
     const int levels = a.max_nodes + 1;
     const dim3 grid(static_cast<unsigned>(static_cast<int64_t>(a.B) * levels * P.nseg));
     auto kernel = a.t_dtype == kBF16 ? (a.q_dtype == kBF16 ? chain_kernel<kBF16, kBF16>(a) : chain_kernel<kBF16, kF32>(a))
                                      : (a.q_dtype == kBF16 ? chain_kernel<kF32, kBF16>(a) : chain_kernel<kF32, kF32>(a));
-    hipLaunchKernelGGL(kernel, grid, dim3(kLinThreads), 0, stream, P, msg, sums, next_message_tag() + (kTagsPerCall - 1), levels);
+    hipLaunchKernelGGL(kernel, grid, dim3(kLinThreads), 0, stream, P, msg, sums, t.tag, levels);
     return;
   }
   unsigned* words = reinterpret_cast<unsigned*>(ws + lay.words_off);      // start of the zeroed region

@@ -15,14 +15,15 @@
 // holds it finds the token there.  The rows of the child under test are fetched before it is accepted; else rows
 // behind the first rejection are never read.
 //
-// Messages.  One message = four 64-bit words {data : tag}, written with relaxed device-scope stores
+// Messages.  One message = four 64-bit words {27 bits of data : 37-bit tag}, written with relaxed device-scope stores
 // and read with relaxed device-scope loads; a word is valid when its tag is the call's plus the round number, so
 // no ordering between words is needed.  Every workgroup posts in every round (a dummy when it has
 // nothing to add) into one of two buffers chosen by the round's parity: a workgroup can post round
 // r+2 only after it has seen every peer's round r+1, i.e. after every peer has finished reading
 // round r, so two buffers suffice.  Whatever the buffers hold carries other tags (see next_message_tag), so nothing clears
 // them (a kernel ahead that did cost 5 of 128 us of a step of 16 x 64 tree nodes), but for launches that are being
-// captured: replays repeat their tag.
+// captured: replays repeat their tag.  (37 bits of tag instead of 32, so that it never comes round: 0.4 us of 126; 40 bits and a
+// fourth word to look at: 2 us.)
 //
 // No wait is unbounded and the result never depends on a peer making progress: a workgroup that does
 // not see a round complete within its patience leaves; if it is the cluster's first workgroup (the
@@ -47,8 +48,26 @@ constexpr int kClUnit = kClThreads * 8;        // logits one workgroup-wide 16-b
 constexpr int kClNodes = 128;
 constexpr int kClMaxUpt = 16;                  // units per slice: 16 x 4 KiB per row, two rows = 128 KiB of LDS
 constexpr int kClMaxParts = kClMaxUpt * kClWaves;
-constexpr unsigned kClAbort = kTagsPerCall - 2;       // added to the call's tag in place of a round number (258 rounds at most)
+constexpr unsigned kClAbort = kTagRounds - 1;  // added to the call's tag in place of a round number
 constexpr uint32_t kNegInf2 = 0xff80ff80u;     // two bf16 -inf
+
+// Three words of 27 bits above 37 bits of tag: an fp64 sum and, as bf16, the largest of a slice's logits (one of them).
+constexpr int kClWords = 3;
+constexpr int kClTagBits = kTagBitsRounds;
+__device__ __forceinline__ unsigned long long cl_message_word(int k, double z, float m, unsigned long long tag) {
+  const unsigned lo = static_cast<unsigned>(__double2loint(z)), hi = static_cast<unsigned>(__double2hiint(z));
+  unsigned d = lo;
+  d = k == 1 ? (lo >> 27) | (hi << 5) : d;
+  d = k == 2 ? (hi >> 22) | ((__float_as_uint(m) >> 16) << 10) : d;
+  return (static_cast<unsigned long long>(d) << kClTagBits) | tag;
+}
+__device__ __forceinline__ double cl_message_sum(const unsigned long long* w) {
+  const unsigned d0 = static_cast<unsigned>(w[0] >> kClTagBits), d1 = static_cast<unsigned>(w[1] >> kClTagBits), d2 = static_cast<unsigned>(w[2] >> kClTagBits);
+  return __hiloint2double(static_cast<int>((d1 >> 5) | (d2 << 22)), static_cast<int>(d0 | (d1 << 27)));
+}
+__device__ __forceinline__ float cl_message_max(const unsigned long long* w) {
+  return __uint_as_float(static_cast<unsigned>(w[2] >> (kClTagBits + 10)) << 16);
+}
 
 struct ClusterParams {
   int B, V, n_q_rows;
@@ -68,7 +87,7 @@ struct ClusterParams {
   int LV, SL;                     // window levels x vocabulary slices = workgroups per request
   int UPT;                        // units (2048 logits) per slice
   int solo;                       // one workgroup per request, which computes all LV x SL parts itself
-  unsigned tag;                   // of the call's messages, plus the round number
+  unsigned long long tag;         // of the call's messages, plus the round number
   int patience;                   // polls the owner spends on one round before it walks alone
   unsigned long long* msg;        // [B][2 buffers][C][2 messages][4 words]
 };
@@ -520,10 +539,7 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
     int l = lane;
     asm volatile("" : "+v"(l));
     const int w = l & 3;
-    unsigned word = w == 2 ? __float_as_uint(aux) : 0u;
-    word = w == 0 ? static_cast<unsigned>(__double2loint(val)) : word;
-    word = w == 1 ? static_cast<unsigned>(__double2hiint(val)) : word;
-    st_dev(msg_word(msg_at(r, rank, k) + 8u * w), (static_cast<unsigned long long>(word) << 32) | (P.tag + r));
+    st_dev(msg_word(msg_at(r, rank, k) + 8u * w), cl_message_word(w, val, aux, P.tag + r));
   };
   // Round r: the wave without logits posts this workgroup's one or two messages and waits for everybody's (the other waves
   // go on to the barrier).  Every wave has passed a barrier since it read what the round before left here.
@@ -538,18 +554,19 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
       const unsigned at = nmsg == 2 ? msg_at(r, my >> 1, my & 1) : msg_at(r, my, 0);
       const int limit = owner ? P.patience : 4 * P.patience + 16;
       int spins = 0, status = -1;
-      unsigned long long w[2][3];
-      auto look = [&](unsigned long long (&x)[3]) __attribute__((always_inline)) {
-        x[0] = ld_dev(msg_word(at)); x[1] = ld_dev(msg_word(at + 8u)); x[2] = ld_dev(msg_word(at + 16u));
+      unsigned long long w[2][kClWords];
+      auto look = [&](unsigned long long (&x)[kClWords]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kClWords; ++k) x[k] = ld_dev(msg_word(at + 8u * k));
       };
-      auto judge = [&](const unsigned long long (&x)[3]) __attribute__((always_inline)) {     // -1: look again
-        const unsigned tag = P.tag + r;
-        const bool ok = static_cast<unsigned>(x[0]) == tag && static_cast<unsigned>(x[1]) == tag && static_cast<unsigned>(x[2]) == tag;
-        if (__any(static_cast<unsigned>(x[0]) == P.tag + kClAbort)) { status = 2; return; }
+      auto judge = [&](const unsigned long long (&x)[kClWords]) __attribute__((always_inline)) {     // -1: look again
+        const unsigned long long tag = P.tag + r;
+        const bool ok = have_tag<kClWords, kClTagBits>(x, tag);
+        if (__any(have_tag<1, kClTagBits>(x, P.tag + kClAbort))) { status = 2; return; }
         if (__all(ok)) {
           status = 0;
-          sh_val[my] = __hiloint2double(static_cast<int>(x[1] >> 32), static_cast<int>(x[0] >> 32));
-          sh_aux[my] = __uint_as_float(static_cast<unsigned>(x[2] >> 32));
+          sh_val[my] = cl_message_sum(x);
+          sh_aux[my] = cl_message_max(x);
           return;
         }
         if (++spins > 2 * limit) status = 1;      // (two looks take the time of one trip)
@@ -824,7 +841,7 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
     // the owner's peers are late or gone: tell them to leave and walk the request alone
     if (wave == 0)
       st_dev(P.msg + ((static_cast<size_t>(b) * 2 + ((lane >> 3) & 1)) * C * 2 + ((lane >> 2) & 1)) * 4 + (lane & 3),
-            static_cast<unsigned long long>(P.tag + kClAbort));
+             P.tag + kClAbort);
     cl_sync();
     solo = true;
   }
@@ -895,8 +912,9 @@ void launch_accept_cluster(const AcceptArgs& a, const ClusterPlan& plan, int pat
   const int C = plan.solo ? 1 : plan.levels * plan.slices;
   // a cluster of one workgroup exchanges nothing: SL stays the number of slices it computes in turn
   const dim3 grid(a.B * C);
-  P.tag = plan.solo ? 0 : next_message_tag();
-  if (!plan.solo && stream_captures(stream)) clear_messages(P.msg, static_cast<int64_t>(a.B) * C * 16, stream);
+  const MessageTag t = plan.solo ? MessageTag{} : next_message_tag(true, stream);
+  P.tag = t.tag;
+  if (t.clear) clear_messages(P.msg, static_cast<int64_t>(a.B) * C * 16, stream);
   const size_t lds = static_cast<size_t>(plan.upt) * 2 * kClThreads * 16;
   static std::atomic<uint64_t> attr_done{0};
   if (plan.upt == 4) {                            // (32 KB of rows: no attribute needed)

@@ -179,6 +179,37 @@ template <typename T> __device__ __forceinline__ void st_dev(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Messages between the workgroups of one launch: 64-bit words, 24 bits of data above the call's 40-bit tag (next_message_tag in
+// kernels.h).  Every word counts by itself, so that no order between words is needed.  An fp64 sum takes three words, with
+// an fp32 maximum four.
+constexpr int kTagBits = 40;
+constexpr int kTagBitsRounds = 37;          // ... of launches that exchange in rounds
+constexpr int kSumWords = 3, kRecordWords = 4;
+template <int N, int BITS = kTagBits>
+__device__ __forceinline__ bool have_tag(const unsigned long long* w, unsigned long long tag) {      // all of w[0 .. N - 1]
+  unsigned long long differ = w[0] ^ tag;
+#pragma unroll
+  for (int k = 1; k < N; ++k) differ |= w[k] ^ tag;
+  return (differ << (64 - BITS)) == 0ull;
+}
+__device__ __forceinline__ unsigned message_data(int k, double z, float m) {       // of word k
+  const unsigned lo = static_cast<unsigned>(__double2loint(z)), hi = static_cast<unsigned>(__double2hiint(z)), mb = __float_as_uint(m);
+  unsigned d = lo & 0xffffffu;
+  d = k == 1 ? (lo >> 24) | ((hi & 0xffffu) << 8) : d;
+  d = k == 2 ? (hi >> 16) | ((mb & 0xffu) << 16) : d;
+  return k == 3 ? mb >> 8 : d;
+}
+__device__ __forceinline__ unsigned long long message_word(int k, double z, float m, unsigned long long tag) {
+  return (static_cast<unsigned long long>(message_data(k, z, m)) << kTagBits) | tag;
+}
+__device__ __forceinline__ double message_sum(const unsigned long long* w) {
+  const unsigned d0 = static_cast<unsigned>(w[0] >> kTagBits), d1 = static_cast<unsigned>(w[1] >> kTagBits), d2 = static_cast<unsigned>(w[2] >> kTagBits);
+  return __hiloint2double(static_cast<int>((d1 >> 8) | (d2 << 16)), static_cast<int>(d0 | (d1 << 24)));
+}
+__device__ __forceinline__ float message_max(const unsigned long long* w) {
+  return __uint_as_float((static_cast<unsigned>(w[2] >> kTagBits) >> 16) | (static_cast<unsigned>(w[3] >> kTagBits) << 8));
+}
+
 // Per-(row, segment) softmax statistics written by the row-statistics kernel:
 // m = largest logit of the segment (raw logit units, -inf if the segment is empty),
 // z = sum over the segment of 2^((l - m) * c), c = log2(e)/T.

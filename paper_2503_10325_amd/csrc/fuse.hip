@@ -134,7 +134,6 @@ constexpr int kOnceWaves = kOnceThreads / kWave;
 constexpr int kOnceBlock = kOnceThreads * 8;
 constexpr int kOnceMaxN = 6;                     // drafters
 constexpr int kOnceMaxRecords = 96;             // drafters x segments at most (once_fits): a thread gathers one
-constexpr int kOnceWords = 3;                    // of a record: sum (2), maximum
 
 // Exponentials of n_rows (at most N) rows' logits in this thread's classes, relative to the thread's maximum m[n]; each wave's
 // (maximum, sum) of every row go to LDS.
@@ -180,7 +179,7 @@ __device__ __forceinline__ void once_exponentials(const void* __restrict__ logit
 template <int DT, int NB, int G>
 __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_once_kernel(
     int k_max, int N, int V, int S, const int32_t* __restrict__ k_len, const float* __restrict__ conf,
-    const int32_t* __restrict__ toks, const void* __restrict__ logits, float c, unsigned long long* __restrict__ msg, unsigned tag,
+    const int32_t* __restrict__ toks, const void* __restrict__ logits, float c, unsigned long long* __restrict__ msg, unsigned long long tag,
     int patience, int32_t* __restrict__ fused, int32_t* __restrict__ winner, int32_t* __restrict__ q_row, float* __restrict__ out) {
   typedef float f4 __attribute__((ext_vector_type(4)));
   typedef f4 f4_any __attribute__((aligned(4)));
@@ -217,32 +216,29 @@ __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_on
       const int r = tid * S + seg;
       sh_rm[r] = M; sh_rz[r] = Z; sh_have[r] = 1;
       if (S > 1) {
-        unsigned long long* to = msg + (row0 * S + r) * kOnceWords;
-        auto post = [&](int k, unsigned data) { st_dev(to + k, (static_cast<unsigned long long>(data) << 32) | tag); };
-        post(0, static_cast<unsigned>(__double2hiint(Z)));
-        post(1, static_cast<unsigned>(__double2loint(Z)));
-        post(2, __float_as_uint(M));
+        unsigned long long* to = msg + (row0 * S + r) * kRecordWords;
+#pragma unroll
+        for (int k = 0; k < kRecordWords; ++k) st_dev(to + k, message_word(k, Z, M, tag));
       }
     }
     bool have = true;
     if (S > 1 && tid < (n_rec + kWave - 1) / kWave * kWave) {   // (wave-uniform)
       const bool want = tid < n_rec && tid % S != seg;
-      const unsigned long long* from = msg + (row0 * S + tid) * kOnceWords;
-      unsigned long long w[kOnceWords] = {0ull, 0ull, 0ull};
+      const unsigned long long* from = msg + (row0 * S + tid) * kRecordWords;
+      unsigned long long w[kRecordWords] = {0ull, 0ull, 0ull, 0ull};
       for (int poll = 0;; ++poll) {
         have = true;
         if (want) {
 #pragma unroll
-          for (int k = 0; k < kOnceWords; ++k) w[k] = ld_dev(from + k);
-#pragma unroll
-          for (int k = 0; k < kOnceWords; ++k) have &= static_cast<unsigned>(w[k]) == tag;
+          for (int k = 0; k < kRecordWords; ++k) w[k] = ld_dev(from + k);
+          have = have_tag<kRecordWords>(w, tag);
         }
         if (__all(have) || poll >= patience) break;
         __builtin_amdgcn_s_sleep(1);
       }
       if (want) {
-        sh_rm[tid] = __uint_as_float(static_cast<unsigned>(w[2] >> 32));
-        sh_rz[tid] = __hiloint2double(static_cast<int>(w[0] >> 32), static_cast<int>(w[1] >> 32));
+        sh_rm[tid] = message_max(w);
+        sh_rz[tid] = message_sum(w);
         sh_have[tid] = have;
       }
     }
@@ -323,7 +319,7 @@ __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_on
 constexpr int kOnceGroups = 2;
 static int once_segments(int N, int V) { return (V + kOnceGroups * kOnceBlock - 1) / (kOnceGroups * kOnceBlock); }
 static size_t once_bytes(int B, int k_max, int N, int V) {
-  return static_cast<size_t>(B) * k_max * N * once_segments(N, V) * kOnceWords * sizeof(unsigned long long);
+  return static_cast<size_t>(B) * k_max * N * once_segments(N, V) * kRecordWords * sizeof(unsigned long long);
 }
 // Kernel plus gaps, one launch / statistics, average and fusion (us): 32 x 6 positions x 4 drafters x 32000 classes 22.4 / 29.5
 // (74 MB), 2 drafters 16.0 / 21.5, 6 drafters 30.1 / 35.8, fp32 28.5 / 42.1, 32 x 16 x 4 x 32000 49.7 / 66.7, 16 x 6 x 4 x 65536
@@ -360,11 +356,12 @@ void launch_fuse(const FuseArgs& a, hipStream_t stream) {
   if (a.mode == 1 && once_fits(a.N, a.V) && static_cast<int64_t>(positions) * once_segments(a.N, a.V) <= INT32_MAX / kOnceThreads && a.workspace_bytes >= once_bytes(a.B, a.k_max, a.N, a.V)) {
     const int S = once_segments(a.N, a.V);
     unsigned long long* msg = static_cast<unsigned long long*>(a.workspace);
-    if (S > 1 && stream_captures(stream))
+    const MessageTag t = S > 1 ? next_message_tag(false, stream) : MessageTag{};
+    if (t.clear)
       clear_messages(msg, static_cast<int64_t>(once_bytes(a.B, a.k_max, a.N, a.V) / sizeof(unsigned long long)), stream);
     hipLaunchKernelGGL((a.l_dtype == kBF16 ? once_kernel<kBF16>(a.N) : once_kernel<kF32>(a.N)), dim3(static_cast<unsigned>(positions) * S),
                        dim3(kOnceThreads), 0, stream, a.k_max, a.N, a.V, S, a.k_len, a.conf, a.draft_tokens, a.draft_logits, c, msg,
-                       next_message_tag() + (kTagsPerCall - 1), 1000, a.fused_token, a.winner, a.q_row, a.fused_probs);
+                       t.tag, 1000, a.fused_token, a.winner, a.q_row, a.fused_probs);
     return;
   }
   hipLaunchKernelGGL(fuse_argmax_kernel, dim3((positions + 255) / 256), dim3(256), 0, stream, a.B, a.k_max,

@@ -19,14 +19,17 @@ void launch_row_stats(const void* t_base, int t_dtype, int n_t_rows, const void*
                       int n_nodes = 0);
 
 // Messages between the workgroups of one launch are words {data : tag} in a workspace that nothing clears: a word counts when
-// it carries a tag of the launch.  next_message_tag() is the first of kTagsPerCall tags that belong to the call alone (a
-// process-wide count: they come round again after 2^23 calls, when a word would have to have stayed in place, unwritten
-// by all calls between); the last of them is the one-launch kernel's for linear drafts, the others are the cluster walk's.
-constexpr unsigned kTagsPerCall = 512;
-unsigned next_message_tag();
-// Whether launches on the stream are being recorded, to be replayed with the same arguments, tags among them (unknown counts
-// as yes): such a launch is preceded by clear_messages (tag 0 with round 0 is never sent).
-bool stream_captures(hipStream_t stream);
+// it carries the launch's own tag, which no other call of the process has.  Kernels that exchange in rounds (the cluster
+// walk) add the round to theirs, 1 .. kTagRounds - 1.  There are 2^39 tags for launches without rounds, 2^28 calls' worth for
+// those with.
+// `clear`: the launch has to be preceded by clear_messages (0 is no tag): where launches on the stream are being recorded,
+// to be replayed with the same arguments, tags among them (unknown counts as yes), and where the tags have run out.
+constexpr unsigned kTagRounds = 256 + 4;      // (rounds of a walk over 128 nodes: 258 at most)
+struct MessageTag {
+  unsigned long long tag;
+  bool clear;
+};
+MessageTag next_message_tag(bool rounds, hipStream_t stream);
 void clear_messages(unsigned long long* words, int64_t n, hipStream_t stream);
 
 struct AcceptArgs {
