@@ -139,6 +139,15 @@ int32_t spec_fuse_drafts(
     float* fused_probs,          /* MIXTURE: [B*k_max, V] fp32; else may be NULL       */
     void* workspace, size_t workspace_bytes, void* stream);
 
+/* spec_fuse_drafts with an explicit patience, for tests (same arguments, same results): the number of polls a workgroup
+ * of the one-launch averaging spends waiting for its peers before it does their share itself (0 = one look; < 0 = the
+ * library's choice). */
+int32_t spec_fuse_drafts_tuned(
+    int32_t patience, int32_t B, int32_t k_max, int32_t N, int32_t V, const int32_t* k_len, const float* conf,
+    const int32_t* draft_tokens, const void* draft_logits, int32_t logits_dtype, float temperature, int32_t mode,
+    int32_t* fused_token, int32_t* winner, int32_t* q_row, float* fused_probs, void* workspace, size_t workspace_bytes,
+    void* stream);
+
 /* ------------------------------------------------------------------------------
  * spec_accept
  *

@@ -20,7 +20,7 @@ SPEC_Q_LOGITS, SPEC_Q_PROBS = 0, 1
 
 EXPORTS = [
     "spec_verify_attn_workspace_size", "spec_verify_attn",
-    "spec_fuse_drafts_workspace_size", "spec_fuse_drafts",
+    "spec_fuse_drafts_workspace_size", "spec_fuse_drafts", "spec_fuse_drafts_tuned",
     "spec_accept_workspace_size", "spec_accept", "spec_accept_tuned",
     "spec_describe_attn_plan", "spec_describe_accept_plan",
     "spec_accept_noalloc", "spec_accept_noalloc_max_workspace",
@@ -78,6 +78,8 @@ def lib() -> ctypes.CDLL:
         L.spec_fuse_drafts_workspace_size.argtypes = [i32] * 5
         L.spec_fuse_drafts.restype = i32
         L.spec_fuse_drafts.argtypes = [i32] * 4 + [vp] * 4 + [i32, f32, i32] + [vp] * 5 + [sz, vp]
+        L.spec_fuse_drafts_tuned.restype = i32
+        L.spec_fuse_drafts_tuned.argtypes = [i32] + L.spec_fuse_drafts.argtypes
         L.spec_accept_workspace_size.restype = sz
         L.spec_accept_workspace_size.argtypes = [i32] * 4
         L.spec_accept_greedy_workspace_size.restype = sz
@@ -195,6 +197,18 @@ def spec_fuse_drafts(k_len, conf, draft_tokens, draft_logits, temperature, mode,
                                 _ptr(fused_probs), _ptr(workspace), ws_bytes, _stream(stream))
     if rc != SPEC_OK:
         raise SpecError("spec_fuse_drafts", rc)
+
+
+def spec_fuse_drafts_tuned(patience, k_len, conf, draft_tokens, draft_logits, temperature, mode, fused_token, winner, q_row,
+                           fused_probs=None, workspace=None, stream=None) -> None:
+    """spec_fuse_drafts with logits and an explicit number of polls in the one-launch averaging."""
+    B, k_max, N = conf.shape
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    rc = lib().spec_fuse_drafts_tuned(int(patience), B, k_max, N, draft_logits.shape[1], _ptr(k_len), _ptr(conf), _ptr(draft_tokens),
+                                      _ptr(draft_logits), _dtype_code(draft_logits), float(temperature), int(mode), _ptr(fused_token),
+                                      _ptr(winner), _ptr(q_row), _ptr(fused_probs), _ptr(workspace), ws_bytes, _stream(stream))
+    if rc != SPEC_OK:
+        raise SpecError("spec_fuse_drafts_tuned", rc)
 
 
 def spec_accept_workspace_size(B, total_nodes, n_q_rows, V) -> int:

@@ -118,11 +118,11 @@ size_t spec_fuse_drafts_workspace_size(int32_t B, int32_t k_max, int32_t N, int3
   return fuse_workspace_bytes(B, k_max, N, V, mode);
 }
 
-int32_t spec_fuse_drafts(int32_t B, int32_t k_max, int32_t N, int32_t V, const int32_t* k_len,
-                         const float* conf, const int32_t* draft_tokens, const void* draft_logits,
-                         int32_t logits_dtype, float temperature, int32_t mode, int32_t* fused_token,
-                         int32_t* winner, int32_t* q_row, float* fused_probs, void* workspace,
-                         size_t workspace_bytes, void* stream) {
+int32_t spec_fuse_drafts_tuned(int32_t patience, int32_t B, int32_t k_max, int32_t N, int32_t V, const int32_t* k_len,
+                               const float* conf, const int32_t* draft_tokens, const void* draft_logits,
+                               int32_t logits_dtype, float temperature, int32_t mode, int32_t* fused_token,
+                               int32_t* winner, int32_t* q_row, float* fused_probs, void* workspace,
+                               size_t workspace_bytes, void* stream) {
   if (B < 0 || k_max < 0 || N <= 0) return SPEC_ERR_SHAPE;
   if (mode != SPEC_FUSE_ARGMAX && mode != SPEC_FUSE_MIXTURE) return SPEC_ERR_UNSUPPORTED;
   if (B == 0 || k_max == 0) return SPEC_OK;
@@ -139,9 +139,18 @@ int32_t spec_fuse_drafts(int32_t B, int32_t k_max, int32_t N, int32_t V, const i
   a.B = B; a.k_max = k_max; a.N = N; a.V = V; a.k_len = k_len; a.conf = conf; a.draft_tokens = draft_tokens;
   a.draft_logits = draft_logits; a.l_dtype = logits_dtype; a.temperature = temperature; a.mode = mode;
   a.fused_token = fused_token; a.winner = winner; a.q_row = q_row; a.fused_probs = fused_probs;
-  a.workspace = workspace; a.workspace_bytes = workspace_bytes;
+  a.workspace = workspace; a.workspace_bytes = workspace_bytes; a.patience = patience;
   launch_fuse(a, static_cast<hipStream_t>(stream));
   return hipGetLastError() == hipSuccess ? SPEC_OK : SPEC_ERR_LAUNCH;
+}
+
+int32_t spec_fuse_drafts(int32_t B, int32_t k_max, int32_t N, int32_t V, const int32_t* k_len,
+                         const float* conf, const int32_t* draft_tokens, const void* draft_logits,
+                         int32_t logits_dtype, float temperature, int32_t mode, int32_t* fused_token,
+                         int32_t* winner, int32_t* q_row, float* fused_probs, void* workspace,
+                         size_t workspace_bytes, void* stream) {
+  return spec_fuse_drafts_tuned(-1, B, k_max, N, V, k_len, conf, draft_tokens, draft_logits, logits_dtype, temperature, mode,
+                                fused_token, winner, q_row, fused_probs, workspace, workspace_bytes, stream);
 }
 
 size_t spec_accept_workspace_size(int32_t B, int32_t total_nodes, int32_t n_q_rows, int32_t V) {

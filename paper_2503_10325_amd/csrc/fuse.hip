@@ -361,7 +361,8 @@ void launch_fuse(const FuseArgs& a, hipStream_t stream) {
       clear_messages(msg, static_cast<int64_t>(once_bytes(a.B, a.k_max, a.N, a.V) / sizeof(unsigned long long)), stream);
     hipLaunchKernelGGL((a.l_dtype == kBF16 ? once_kernel<kBF16>(a.N) : once_kernel<kF32>(a.N)), dim3(static_cast<unsigned>(positions) * S),
                        dim3(kOnceThreads), 0, stream, a.k_max, a.N, a.V, S, a.k_len, a.conf, a.draft_tokens, a.draft_logits, c, msg,
-                       t.tag, 1000, a.fused_token, a.winner, a.q_row, a.fused_probs);
+                       t.tag,
+                       a.patience >= 0 && a.patience <= 1000000 ? a.patience : 1000, a.fused_token, a.winner, a.q_row, a.fused_probs);
     return;
   }
   hipLaunchKernelGGL(fuse_argmax_kernel, dim3((positions + 255) / 256), dim3(256), 0, stream, a.B, a.k_max,

@@ -149,6 +149,7 @@ struct FuseArgs {
   int32_t* q_row;
   float* fused_probs;
   void* workspace; size_t workspace_bytes;
+  int patience;                // polls of the one-launch kernel, < 0 = its own choice
 };
 size_t fuse_workspace_bytes(int B, int k_max, int N, int V, int mode);       // what the size query answers
 size_t fuse_workspace_min_bytes(int B, int k_max, int N, int V, int mode);   // the least that is taken

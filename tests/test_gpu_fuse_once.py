@@ -24,12 +24,13 @@ def make(B, k, N, V, dtype, seed):
     return dict(logits=logits, conf=conf, toks=toks, lens=lens)
 
 
-def call(sv, d, ws, T=0.8):
+def call(sv, d, ws, T=0.8, patience=None):
     B, k, N = d["conf"].shape
     V = d["logits"].shape[1]
     got = [torch.full((B, k), -9, dtype=torch.int32, device="cuda") for _ in range(3)]
     out = torch.full((B * k, V), -1.0, device="cuda")
-    sv.spec_fuse_drafts(d["lens"], d["conf"], d["toks"], d["logits"], T, sv.SPEC_FUSE_MIXTURE, *got, out, ws)
+    fuse = sv.spec_fuse_drafts if patience is None else lambda *a: sv.spec_fuse_drafts_tuned(patience, *a)
+    fuse(d["lens"], d["conf"], d["toks"], d["logits"], T, sv.SPEC_FUSE_MIXTURE, *got, out, ws)
     return got, out
 
 
@@ -132,3 +133,25 @@ def test_mixture_of_masked_rows_far_below_zero(B, k, N, V, dtype, T):
         for room in (full, least):
             _, out = call(sv, d, ws[:room], T)
             assert bool(((out.double() - ref).abs() <= bound)[used].all()), room
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("B,k,N,V,dtype", [
+    (2, 2, 2, 4097, torch.bfloat16), (2, 3, 4, 32000, torch.bfloat16), (2, 2, 6, 9001, torch.float32), (2, 2, 5, 12290, torch.bfloat16),
+    (1, 3, 2, 131072, torch.bfloat16), (40, 8, 2, 9001, torch.bfloat16),
+])
+def test_mixture_without_waiting(B, k, N, V, dtype, masked):
+    """Patience 0: a workgroup looks once and works out every record that is not there yet itself, with the same arithmetic in the
+    same order: the same bits as with the records of its peers, a segment without any mass in some drafters among them."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_10325_amd import binding as sv
+    ws = torch.randint(0, 256, (sv.spec_fuse_drafts_workspace_size(B, k, N, V, sv.SPEC_FUSE_MIXTURE),), dtype=torch.uint8, device="cuda")
+    for seed in range(3):
+        d = make(B, k, N, V, dtype, seed)
+        if masked:
+            d["logits"][1::2, :4096] = -float("inf")
+        want, ref = call(sv, d, ws)
+        for _ in range(3):
+            ints, out = call(sv, d, ws, patience=0)
+            assert torch.equal(out, ref) and all(torch.equal(a, b) for a, b in zip(ints, want))
