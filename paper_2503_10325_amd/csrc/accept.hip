@@ -1672,12 +1672,19 @@ static size_t chain_words(const AcceptArgs& a) {
 // workgroups) 13.2 / 13.5; 12 x 8 x 32000 (432) 13.2 / 13.7 but slower in a step, 3 x 8 x 128256 (432) 13.5 / 13.2, 16 x 8 x
 // 32000 (576) 17.4 / 14.5, 8 x 8 x 32000 fp32 (18 MB) 13.7 / 13.6, 5 x 3 to 9 x 50257 fp32 (245, 14 MB) 13.5 / 13.3 and 1 % behind
 // in a step; ragged drafts, calls in a loop: 12 x 1 to 10 x 32000 12.9 / 13.3, 30 x 1 to 16 x 8000 11.8 / 12.9.
+// And where workgroups share units, the more segments a row has the more there is to gather, while the grid's places for levels
+// that a request does not have cost a little each.  Steps of attention and acceptance, workgroups / grid, chain / two launches (us),
+// rows of up to two segments: 274 / 336 24.0 / 25.4, 255 / 2040 26.2 / 29.0; three and four: 270 / 270 26.4 / 27.8, 276 / 352 36.0 /
+// 36.1, 248 / 440 22.9 / 22.5, 204 / 1224 19.2 / 19.0; more: 230 / 270 22.3 / 23.0, 216 / 288 25.4 / 25.5, 253 / 330 25.3 / 24.5, 288
+// / 432 25.9 / 25.1, 308 / 308 28.4 / 27.6.
 static bool chain_path(const AcceptArgs& a) {
   if (!linear_path(a) || a.path != 0 || a.max_nodes > kMaxNodes) return false;
   const int64_t S = stats_segments(a.V), levels = a.max_nodes + 1, n_cu = current_device_cus();
   if (levels * S > kChainMaxRecords || S * kChainBlocks > kChainMaxRecords) return false;
   const int64_t rows = static_cast<int64_t>(a.total_nodes) + a.B;       // (workgroups of levels that a request does not have leave at once)
-  if (rows * S * 4 > n_cu * 5 || levels * S * a.B > n_cu * 8) return false;
+  const int64_t wgs = rows * S, grid = levels * S * a.B;
+  if (wgs * 4 > n_cu * 5 || grid > n_cu * 8) return false;
+  if (S > 2 && (wgs + grid) * 2 > n_cu * (S > 4 ? 4 : 5)) return false;
   if (rows * a.V * ((a.t_dtype == kBF16 ? 2 : 4) + (a.q_dtype == kBF16 ? 2 : 4)) > n_cu * 49152) return false;
   return chain_offset(a) + chain_words(a) * sizeof(unsigned long long) <= accept_layout(a.B, a.total_nodes, a.n_q_rows, a.V).total;
 }
