@@ -1218,7 +1218,10 @@ static auto linear_kernel(int blocks) {
 // Messages are 64-bit words {data : tag}, relaxed device-scope accesses; the tag is the call's own number, so that the
 // workspace needs no clearing (a launch that is being captured is preceded by a kernel that clears them: replays repeat the
 // tag; see MessageTag).  Waits are bounded: a workgroup that misses a record after `patience` polls works it out itself, with the same
-// arithmetic in the same order, and goes on; nobody's result depends on who came first.
+// arithmetic in the same order, and goes on; nobody's result depends on who came first.  What that costs at worst, every record
+// worked out by everybody (patience 0, calls in a loop, us; else 9.5 to 14): 16 x 16 drafts x 8000 classes 41, 8 x 8 x 32000
+// 74, 1 x 7 x 128256 256, 1 x 15 x 131072 444.  Beside another stream whose products fill the chip no record was missed for long:
+// 293 to 296 us per call, in two launches 296 to 297.
 //
 // What bounds it: latency.  Offsets, draft row numbers, logits, the two exchanges (a trip each way), the class.
 // ----------------------------------------------------------------------------------

@@ -16,7 +16,6 @@ namespace specv {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 lm_bf16x8;
 typedef uint32_t lm_u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t lm_u32x2 __attribute__((ext_vector_type(2)));
 
 struct LmParams {
   int rows, K, V;
@@ -414,9 +413,11 @@ static int launch_lm_tile(LmParams P, hipStream_t stream) {
 
 // Row tiles per workgroup: the split of the rows whose rounds over the chip cost least.  A slice costs its matrix work,
 // proportional to the row tiles, plus a part that does not depend on them (weight traffic, barrier), about three tiles'
-// worth.  Measured over all choices, times as multiples of the fastest: 1040 x 4096 x 128256 13 tiles 1, 14 1.05, 12 1.10,
-// 10 1.14, 16 1.15; 429 x 8192 x 128256 14 tiles 1, 15 1.05, 16 1.10, 10 1.13, 13 1.34; 224 x 4096 x 32000 8 tiles 1, 10
-// 1.10, 14 1.14: the rule takes the fastest each time.
+// worth.  Measured over all choices (15 and 16 tiles leave no LDS to run on into the next tile), times as multiples of the
+// fastest: 1040 x 4096 x 128256 13 tiles 1, 14 1.06, 11 1.06, 12 1.11, 16 1.19; 429 x 8192 x 128256 14 tiles 1, 15 1.06, 16 1.11, 10
+// 1.15, 13 1.35; 224 x 4096 x 32000 8 tiles 1, 10 1.06, 13 1.11, 14 1.18; 700 x 4096 x 64000 15 tiles 1, 11 1.01, 16 1.05, 13 1.12;
+// 256 x 4096 x 128256 16 tiles 1, 8 1.16; 200 x 8192 x 128256 13, 900 x 2048 x 100352 12, 300 x 4096 x 50304, 520 x 4096 x
+// 32000 and 320 x 8192 x 32000 10: the rule takes the fastest of all ten.
 constexpr int kTlFixed = 3;
 template <int N>
 static int lm_tile_rows(const int (&choices)[N], int vb, int rows, int V, int n_cu) {
