@@ -1413,14 +1413,13 @@ __global__ __launch_bounds__(kLinThreads, 4) void accept_chain_kernel(AcceptPara
     chain_exponentials<T_STATS, Q_STATS>(R, rt, rq, seg * kChainBlocks * kLinBlock, V, c, val, sum);
     chain_wave_stats<T_STATS, Q_STATS>(val, sum, c, sh_stat);
     __syncthreads();
-    if (tid < 2 && (tid == 0 ? T_STATS : Q_STATS)) {            // thread 0: the target row's record, 1: the draft row's
+    const int kind = tid / kRecordWords;
+    if (tid < kChainWords && (kind == 0 ? T_STATS : Q_STATS)) {  // a thread per word: the target row's record, then the draft row's
       float M;
       double Z;
-      merge_waves<kLinWaves>(sh_stat.m[tid], sh_stat.z[tid], c, M, Z);
-      sh_m[tid][own] = M; sh_z[tid][own] = Z;
-      unsigned long long* to = msg + ((trow0 + j) * S + seg) * kChainWords + kRecordWords * tid;
-#pragma unroll
-      for (int k = 0; k < kRecordWords; ++k) st_dev(to + k, message_word(k, Z, M, tag));
+      merge_waves<kLinWaves>(sh_stat.m[kind], sh_stat.z[kind], c, M, Z);
+      if (tid % kRecordWords == 0) { sh_m[kind][own] = M; sh_z[kind][own] = Z; }
+      st_dev(msg + ((trow0 + j) * S + seg) * kChainWords + tid, message_word(tid % kRecordWords, Z, M, tag));
     }
     // ---- gather: thread r the record of segment r % S of rows r / S ----
     bool have = true;

@@ -209,17 +209,14 @@ __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_on
     __syncthreads();
     // ---- records of this segment out (thread n: drafter n's), those of the others in (thread r: drafter r / S, segment r % S) ----
     const int n_rec = N * S;
-    if (tid < N) {
+    if (tid < N * kRecordWords) {                // (a thread per word of drafter n's)
+      const int n = tid / kRecordWords, k = tid % kRecordWords;
       float M;
       double Z;
-      merge_waves<kOnceWaves>(sh_m[tid], sh_z[tid], c, M, Z);
-      const int r = tid * S + seg;
-      sh_rm[r] = M; sh_rz[r] = Z; sh_have[r] = 1;
-      if (S > 1) {
-        unsigned long long* to = msg + (row0 * S + r) * kRecordWords;
-#pragma unroll
-        for (int k = 0; k < kRecordWords; ++k) st_dev(to + k, message_word(k, Z, M, tag));
-      }
+      merge_waves<kOnceWaves>(sh_m[n], sh_z[n], c, M, Z);
+      const int r = n * S + seg;
+      if (k == 0) { sh_rm[r] = M; sh_rz[r] = Z; sh_have[r] = 1; }
+      if (S > 1) st_dev(msg + (row0 * S + r) * kRecordWords + k, message_word(k, Z, M, tag));
     }
     bool have = true;
     if (S > 1 && tid < (n_rec + kWave - 1) / kWave * kWave) {   // (wave-uniform)
