@@ -187,20 +187,8 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
   // (429 x 8192 x 128256 746-773 -> 740-750 us; in registers alone 1985 -> 2015 TFLOP/s).
   auto step = [&](const lm_u32x4 (&a)[MI], const lm_u32x4 (&b)[NT], lm_u32x4 (&an)[MI], lm_u32x4 (&bn)[NT], int a_at, int b_at,
                   auto&& extra) __attribute__((always_inline)) {
-    auto product = [&](int mi, int ni) __attribute__((always_inline)) {
-      acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lm_bf16x8, a[mi]),
-                                                            __builtin_bit_cast(lm_bf16x8, b[ni]), acc[mi][ni], 0, 0, 0);
-    };
 #pragma unroll
     for (int ni = 0; ni < NT; ++ni) {
-      // One row tile per wave: the first product ahead of the reads (as the compiler placed it before workgroups kept their
-      // compute unit; behind them, 126 x 14336 x 3072 takes 81.5 us instead of 79.6, 126 x 14336 x 6000 86.1 instead of 84.3, 64 x
-      // 14336 x 6000 88.7 instead of 87.8: several workgroups read the same weights side by side and wait for memory).
-      constexpr int kAhead = NT == 1 ? 1 : 0;
-      if constexpr (kAhead) {
-        product(0, ni);
-        __builtin_amdgcn_sched_barrier(0);
-      }
       // the MI + NT operand reads spread over the first NT - 1 groups of MI products
 #pragma unroll
       for (int u = 0; u < MI + NT; ++u)
@@ -210,7 +198,11 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
         }
       extra(ni);
 #pragma unroll
-      for (int m = kAhead; m < MI; ++m) product(ni & 1 ? MI - 1 - m : m, ni);
+      for (int m = 0; m < MI; ++m) {
+        const int mi = ni & 1 ? MI - 1 - m : m;
+        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lm_bf16x8, a[mi]),
+                                                              __builtin_bit_cast(lm_bf16x8, b[ni]), acc[mi][ni], 0, 0, 0);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
