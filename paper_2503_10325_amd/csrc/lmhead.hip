@@ -185,10 +185,22 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
   // One 32-deep step: the products of (a, b) with the reads of the next step's operands (an, bn) between them.  The order
   // turns back at the end of a row of tiles, so that from one product to the next only one operand changes: less power
   // (429 x 8192 x 128256 746-773 -> 740-750 us; in registers alone 1985 -> 2015 TFLOP/s).
+  // With 128 vocabulary entries per workgroup a step waits for memory: the order stays, and what comes first is written
+  // down.  One row tile per wave: a product, then the reads.  Left to the compiler, which took the reads first, 126 x 14336 x
+  // 3072 takes 81.3 us instead of 80.2, 487 x 12288 x 1216 63.4 instead of 62.4 (26 x 4096 x 3136 16.6 either way).
   auto step = [&](const lm_u32x4 (&a)[MI], const lm_u32x4 (&b)[NT], lm_u32x4 (&an)[MI], lm_u32x4 (&bn)[NT], int a_at, int b_at,
                   auto&& extra) __attribute__((always_inline)) {
+    constexpr int kAhead = NT == 1 ? 1 : 0;
+    auto product = [&](int mi, int ni) __attribute__((always_inline)) {
+      acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lm_bf16x8, a[mi]),
+                                                            __builtin_bit_cast(lm_bf16x8, b[ni]), acc[mi][ni], 0, 0, 0);
+    };
 #pragma unroll
     for (int ni = 0; ni < NT; ++ni) {
+      if constexpr (kAhead) {
+        product(0, ni);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       // the MI + NT operand reads spread over the first NT - 1 groups of MI products
 #pragma unroll
       for (int u = 0; u < MI + NT; ++u)
@@ -198,11 +210,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
         }
       extra(ni);
 #pragma unroll
-      for (int m = 0; m < MI; ++m) {
-        const int mi = ni & 1 ? MI - 1 - m : m;
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lm_bf16x8, a[mi]),
-                                                              __builtin_bit_cast(lm_bf16x8, b[ni]), acc[mi][ni], 0, 0, 0);
-      }
+      for (int m = kAhead; m < MI; ++m) product(MI > 2 && (ni & 1) ? MI - 1 - m : m, ni);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -212,6 +220,8 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
   // the first slices, as many as there are buffers; then slice 0 is waited for and its first operands are read
   seek_a(first);
   seek_b(first);
+  const unsigned char *const abase = acur, *const bbase = bcur;
+  auto slice_of = [&](const unsigned char* base, int s) { return base + min(s, nch - 1) * kTlSlice; };      // (one tile)
   auto first_loads = [&](int s) __attribute__((always_inline)) {
     if (s < kBBufs) {
 #pragma unroll
@@ -220,7 +230,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
         bcur += kTlSlice;
         if (--bleft == 0) wrap_b();
       } else {
-        bcur += --bleft > 0 ? kTlSlice : 0;
+        bcur = slice_of(bbase, s + 1);
       }
     }
 #pragma unroll
@@ -229,7 +239,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
       acur += kTlSlice;
       if (--aleft == 0) wrap_a();
     } else {
-      acur += --aleft > 0 ? kTlSlice : 0;
+      acur = slice_of(abase, s + 1);
     }
   };
   if constexpr (kStream) {
@@ -254,8 +264,8 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0.f;
 
-    // One slice i: its two steps, and the loads of slices i + kABufs and i + kBBufs.
-    auto slice = [&](bool behind) __attribute__((always_inline)) {
+    // One slice i (of the one tile; several tiles have cursors): its two steps, and the loads of slices i + kABufs and i + kBBufs.
+    auto slice = [&](int i, bool behind) __attribute__((always_inline)) {
       const int anext = abuf == kABufs - 1 ? 0 : abuf + 1;
       const int bnext = bbuf == kBBufs - 1 ? 0 : bbuf + 1;
       step(a0, b0, a1, b1, (a_lane + abuf * kABuf) ^ 64, (b_lane + bbuf * kBBuf) ^ 64, [](int) {});
@@ -268,6 +278,10 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
       else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kAfter) : "memory");
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!kStream) {
+        acur = slice_of(abase, i + kABufs);
+        bcur = slice_of(bbase, i + kBBufs);
+      }
       step(a1, b1, a0, b0, a_lane + anext * kABuf, b_lane + bnext * kBBuf, [&](int ni) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < MI + kBPer; ++j)
@@ -275,13 +289,13 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
             if (j < kBPer) load_b(bbuf, j);
             else load_a(abuf, j - kBPer);
           }
+        // (several: the first loads ahead of the products, 382 x 28672 x 4544 198.0 -> 192.2 us)
+        if constexpr (MI == 2 && NT > 1)
+          if (ni == 0) __builtin_amdgcn_sched_barrier(0);
       });
       if constexpr (kStream) {
         acur += kTlSlice;
         bcur += kTlSlice;
-      } else {
-        acur += --aleft > 0 ? kTlSlice : 0;
-        bcur += --bleft > 0 ? kTlSlice : 0;
       }
       abuf = anext;
       bbuf = bnext;
@@ -292,16 +306,16 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
         int run = min(left, min(aleft, bleft));
         left -= run; aleft -= run; bleft -= run;
         if (stores_behind) {
-          slice(true);
+          slice(0, true);
           stores_behind = false;
           --run;
         }
-        for (; run > 0; --run) slice(false);
+        for (; run > 0; --run) slice(0, false);
         if (aleft == 0) wrap_a();
         if (bleft == 0) wrap_b();
       }
     } else {
-      for (int left = nch; left > 0; --left) slice(false);
+      for (int i = 0; i < nch; ++i) slice(i, false);
     }
     if constexpr (!kStream) {
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
