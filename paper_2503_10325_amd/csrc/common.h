@@ -182,7 +182,7 @@ template <typename T> __device__ __forceinline__ void st_dev(T* p, T v) {
 // Messages between the workgroups of one launch: 64-bit words, 24 bits of data above the call's 40-bit tag (next_message_tag in
 // kernels.h).  Every word counts by itself, so that no order between words is needed.  An fp64 sum takes three words, with
 // an fp32 maximum four.  A lane posts one word: a record goes out in one store (one after the other by one thread: a step of 1
-// request x 7 drafts x 128256 classes 33.3 us instead of 32.8, averaging and acceptance of 32 x 6 x 4 x 32000 35.9 instead of 35.7).
+// request x 7 drafts x 128256 classes 33.2 us instead of 32.7, averaging and acceptance of 32 x 6 x 4 x 32000 35.9 instead of 35.7).
 constexpr int kTagBits = 40;
 constexpr int kTagBitsRounds = 37;          // ... of launches that exchange in rounds
 constexpr int kSumWords = 3, kRecordWords = 4;
