@@ -22,8 +22,8 @@
 // r+2 only after it has seen every peer's round r+1, i.e. after every peer has finished reading
 // round r, so two buffers suffice.  Whatever the buffers hold carries other tags (see next_message_tag), so nothing clears
 // them (a kernel ahead that did cost 5 of 128 us of a step of 16 x 64 tree nodes), but for launches that are being
-// captured: replays repeat their tag.  (37 bits of tag instead of 32, so that it never comes round: 0.4 us of 126; 40 bits and a
-// fourth word to look at: 2 us.)
+// captured: replays repeat their tag.  (37 bits of tag instead of 32, so that it does not come round: 0.4 us of 126; a fourth word
+// to look at: 2 us.)
 //
 // No wait is unbounded and the result never depends on a peer making progress: a workgroup that does
 // not see a round complete within its patience leaves; if it is the cluster's first workgroup (the
@@ -51,23 +51,8 @@ constexpr int kClMaxParts = kClMaxUpt * kClWaves;
 constexpr unsigned kClAbort = kTagRounds - 1;  // added to the call's tag in place of a round number
 constexpr uint32_t kNegInf2 = 0xff80ff80u;     // two bf16 -inf
 
-// Three words of 27 bits above 37 bits of tag: an fp64 sum and, as bf16, the largest of a slice's logits (one of them).
-constexpr int kClWords = 3;
-constexpr int kClTagBits = kTagBitsRounds;
-__device__ __forceinline__ unsigned long long cl_message_word(int k, double z, float m, unsigned long long tag) {
-  const unsigned lo = static_cast<unsigned>(__double2loint(z)), hi = static_cast<unsigned>(__double2hiint(z));
-  unsigned d = lo;
-  d = k == 1 ? (lo >> 27) | (hi << 5) : d;
-  d = k == 2 ? (hi >> 22) | ((__float_as_uint(m) >> 16) << 10) : d;
-  return (static_cast<unsigned long long>(d) << kClTagBits) | tag;
-}
-__device__ __forceinline__ double cl_message_sum(const unsigned long long* w) {
-  const unsigned d0 = static_cast<unsigned>(w[0] >> kClTagBits), d1 = static_cast<unsigned>(w[1] >> kClTagBits), d2 = static_cast<unsigned>(w[2] >> kClTagBits);
-  return __hiloint2double(static_cast<int>((d1 >> 5) | (d2 << 22)), static_cast<int>(d0 | (d1 << 27)));
-}
-__device__ __forceinline__ float cl_message_max(const unsigned long long* w) {
-  return __uint_as_float(static_cast<unsigned>(w[2] >> (kClTagBits + 10)) << 16);
-}
+// Words of a message that count: the maxima are of bf16 logits (one of them).
+constexpr int kClWords = record_words(kBF16);
 
 struct ClusterParams {
   int B, V, n_q_rows;
@@ -539,7 +524,7 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
     int l = lane;
     asm volatile("" : "+v"(l));
     const int w = l & 3;
-    st_dev(msg_word(msg_at(r, rank, k) + 8u * w), cl_message_word(w, val, aux, P.tag + r));
+    st_dev(msg_word(msg_at(r, rank, k) + 8u * w), message_word(w, val, aux, P.tag + r));
   };
   // Round r: the wave without logits posts this workgroup's one or two messages and waits for everybody's (the other waves
   // go on to the barrier).  Every wave has passed a barrier since it read what the round before left here.
@@ -561,12 +546,12 @@ __global__ __launch_bounds__(kClBlock) void accept_cluster_kernel(ClusterParams 
       };
       auto judge = [&](const unsigned long long (&x)[kClWords]) __attribute__((always_inline)) {     // -1: look again
         const unsigned long long tag = P.tag + r;
-        const bool ok = have_tag<kClWords, kClTagBits>(x, tag);
-        if (__any(have_tag<1, kClTagBits>(x, P.tag + kClAbort))) { status = 2; return; }
+        const bool ok = have_tag<kClWords>(x, tag);
+        if (__any(have_tag<1>(x, P.tag + kClAbort))) { status = 2; return; }
         if (__all(ok)) {
           status = 0;
-          sh_val[my] = cl_message_sum(x);
-          sh_aux[my] = cl_message_max(x);
+          sh_val[my] = message_sum(x);
+          sh_aux[my] = message_max<kClWords>(x);
           return;
         }
         if (++spins > 2 * limit) status = 1;      // (two looks take the time of one trip)

@@ -179,36 +179,38 @@ template <typename T> __device__ __forceinline__ void st_dev(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Messages between the workgroups of one launch: 64-bit words, 24 bits of data above the call's 40-bit tag (next_message_tag in
-// kernels.h).  Every word counts by itself, so that no order between words is needed.  An fp64 sum takes three words, with
-// an fp32 maximum four.  A lane posts one word: a record goes out in one store (one after the other by one thread: a step of 1
-// request x 7 drafts x 128256 classes 33.2 us instead of 32.7, averaging and acceptance of 32 x 6 x 4 x 32000 35.9 instead of 35.7).
-constexpr int kTagBits = 40;
-constexpr int kTagBitsRounds = 37;          // ... of launches that exchange in rounds
+// Messages between the workgroups of one launch: 64-bit words, 27 bits of data above the launch's 37-bit tag (next_message_tag
+// in kernels.h).  Every word counts by itself, so that no order between words is needed.  An fp64 sum takes three words and
+// leaves room for the upper half of an fp32 maximum, which is all of a maximum of bf16 logits; the lower half takes a
+// fourth.  (40 bits of tag and four words whatever the logits, posted by one thread: 1 x 7 drafts x 128256 classes in one launch 12.1
+// us, now 11.6, as with 32 bits of tag and three words, 11.8; 8 x 8 x 32000 behind the projection 11.8, now 11.6.)
+constexpr int kTagBits = 37;
 constexpr int kSumWords = 3, kRecordWords = 4;
-template <int N, int BITS = kTagBits>
+constexpr int record_words(int dtype) { return dtype == kBF16 ? 3 : kRecordWords; }
+template <int N>
 __device__ __forceinline__ bool have_tag(const unsigned long long* w, unsigned long long tag) {      // all of w[0 .. N - 1]
   unsigned long long differ = w[0] ^ tag;
 #pragma unroll
   for (int k = 1; k < N; ++k) differ |= w[k] ^ tag;
-  return (differ << (64 - BITS)) == 0ull;
-}
-__device__ __forceinline__ unsigned message_data(int k, double z, float m) {       // of word k
-  const unsigned lo = static_cast<unsigned>(__double2loint(z)), hi = static_cast<unsigned>(__double2hiint(z)), mb = __float_as_uint(m);
-  unsigned d = lo & 0xffffffu;
-  d = k == 1 ? (lo >> 24) | ((hi & 0xffffu) << 8) : d;
-  d = k == 2 ? (hi >> 16) | ((mb & 0xffu) << 16) : d;
-  return k == 3 ? mb >> 8 : d;
+  return (differ << (64 - kTagBits)) == 0ull;
 }
 __device__ __forceinline__ unsigned long long message_word(int k, double z, float m, unsigned long long tag) {
-  return (static_cast<unsigned long long>(message_data(k, z, m)) << kTagBits) | tag;
+  const unsigned lo = static_cast<unsigned>(__double2loint(z)), hi = static_cast<unsigned>(__double2hiint(z)), mb = __float_as_uint(m);
+  unsigned d = lo;
+  d = k == 1 ? (lo >> 27) | (hi << 5) : d;
+  d = k == 2 ? (hi >> 22) | ((mb >> 16) << 10) : d;
+  d = k == 3 ? mb & 0xffffu : d;
+  return (static_cast<unsigned long long>(d) << kTagBits) | tag;
 }
 __device__ __forceinline__ double message_sum(const unsigned long long* w) {
   const unsigned d0 = static_cast<unsigned>(w[0] >> kTagBits), d1 = static_cast<unsigned>(w[1] >> kTagBits), d2 = static_cast<unsigned>(w[2] >> kTagBits);
-  return __hiloint2double(static_cast<int>((d1 >> 8) | (d2 << 16)), static_cast<int>(d0 | (d1 << 24)));
+  return __hiloint2double(static_cast<int>((d1 >> 5) | (d2 << 22)), static_cast<int>(d0 | (d1 << 27)));
 }
+template <int WORDS>
 __device__ __forceinline__ float message_max(const unsigned long long* w) {
-  return __uint_as_float((static_cast<unsigned>(w[2] >> kTagBits) >> 16) | (static_cast<unsigned>(w[3] >> kTagBits) << 8));
+  unsigned m = static_cast<unsigned>(w[2] >> (kTagBits + 10)) << 16;
+  if constexpr (WORDS > 3) m |= static_cast<unsigned>(w[3] >> kTagBits);
+  return __uint_as_float(m);
 }
 
 // Per-(row, segment) softmax statistics written by the row-statistics kernel:

@@ -227,14 +227,14 @@ __global__ __launch_bounds__(kOnceThreads, NB <= 4 ? 4 : 3) void fuse_mixture_on
         have = true;
         if (want) {
 #pragma unroll
-          for (int k = 0; k < kRecordWords; ++k) w[k] = ld_dev(from + k);
-          have = have_tag<kRecordWords>(w, tag);
+          for (int k = 0; k < record_words(DT); ++k) w[k] = ld_dev(from + k);
+          have = have_tag<record_words(DT)>(w, tag);
         }
         if (__all(have) || poll >= patience) break;
         __builtin_amdgcn_s_sleep(1);
       }
       if (want) {
-        sh_rm[tid] = message_max(w);
+        sh_rm[tid] = message_max<record_words(DT)>(w);
         sh_rz[tid] = message_sum(w);
         sh_have[tid] = have;
       }

@@ -20,7 +20,7 @@ void launch_row_stats(const void* t_base, int t_dtype, int n_t_rows, const void*
 
 // Messages between the workgroups of one launch are words {data : tag} in a workspace that nothing clears: a word counts when
 // it carries the launch's own tag, which no other call of the process has.  Kernels that exchange in rounds (the cluster
-// walk) add the round to theirs, 1 .. kTagRounds - 1.  There are 2^39 tags for launches without rounds, 2^28 calls' worth for
+// walk) add the round to theirs, 1 .. kTagRounds - 1.  There are 2^36 tags for launches without rounds, 2^28 calls' worth for
 // those with.
 // `clear`: the launch has to be preceded by clear_messages (0 is no tag): where launches on the stream are being recorded,
 // to be replayed with the same arguments, tags among them (unknown counts as yes), and where the tags have run out.

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 LOW = (1 << 32) - 1
 
 
-def stale(ws, seen, bits=40):
+def stale(ws, seen, bits=37):
     """Fills the workspace with words of random data whose tags are the next call's but for bits above the 32nd.  seen: a message
     word of each of the two calls before."""
     step = (seen[1] - seen[0]) & LOW
@@ -104,6 +104,6 @@ def test_cluster_walk():
         ref = call()
         seen.append(min(w & (1 << 37) - 1 for w in nonzero(ws)))       # a tag of round 1
     for _ in range(10):
-        stale(ws, seen, 37)
+        stale(ws, seen)
         seen = [seen[1], 2 * seen[1] - seen[0]]
         same(beside_work(call), ref)
