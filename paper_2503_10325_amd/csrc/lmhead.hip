@@ -117,6 +117,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
   constexpr int kABufs = C::kABufs, kBBufs = C::kBBufs;
   constexpr int kABuf = C::kABuf, kBBuf = C::kBBuf;
   constexpr bool kStream = C::kStream;
+  constexpr bool kOrdered = MI == 2 && NT2 == 2;
   constexpr int kBLoads = kRows / 8;                // load instructions per hidden slice (8 rows each), dealt to 8 waves
   constexpr int kBPer = (kBLoads + 7) / 8;          // ... at most per wave
   constexpr int kBMin = kBLoads / 8;                // ... at least
@@ -185,12 +186,13 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
   // One 32-deep step: the products of (a, b) with the reads of the next step's operands (an, bn) between them.  The order
   // turns back at the end of a row of tiles, so that from one product to the next only one operand changes: less power
   // (429 x 8192 x 128256 746-773 -> 740-750 us; in registers alone 1985 -> 2015 TFLOP/s).
-  // With 128 vocabulary entries per workgroup a step waits for memory: the order stays, and what comes first is written
-  // down.  One row tile per wave: a product, then the reads.  Left to the compiler, which took the reads first, 126 x 14336 x
-  // 3072 takes 81.3 us instead of 80.2, 487 x 12288 x 1216 63.4 instead of 62.4 (26 x 4096 x 3136 16.6 either way).
+  // With one row tile in every wave (kOrdered) a step waits for memory, and its order is written down: a product, then the
+  // reads.  Left to the compiler, weights from HBM / from the memory-side cache: 126 x 14336 x 3072 81.5 us instead of 80.2, 487 x
+  // 12288 x 1216 63.6 / 43.6 instead of 62.4 / 43.4, 26 x 4096 x 3136 25.1 / 16.2 and 25.2 / 16.3.  Not with more row tiles, where
+  // the like (loads, then products) is worth 3 % on 382 x 28672 x 4544 and costs 1 to 3 on 128 x 8192 x 16000 and 432 x 4096 x 2432.
   auto step = [&](const lm_u32x4 (&a)[MI], const lm_u32x4 (&b)[NT], lm_u32x4 (&an)[MI], lm_u32x4 (&bn)[NT], int a_at, int b_at,
                   auto&& extra) __attribute__((always_inline)) {
-    constexpr int kAhead = NT == 1 ? 1 : 0;
+    constexpr int kAhead = kOrdered ? 1 : 0;
     auto product = [&](int mi, int ni) __attribute__((always_inline)) {
       acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lm_bf16x8, a[mi]),
                                                             __builtin_bit_cast(lm_bf16x8, b[ni]), acc[mi][ni], 0, 0, 0);
@@ -210,7 +212,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
         }
       extra(ni);
 #pragma unroll
-      for (int m = kAhead; m < MI; ++m) product(MI > 2 && (ni & 1) ? MI - 1 - m : m, ni);
+      for (int m = kAhead; m < MI; ++m) product(ni & 1 ? MI - 1 - m : m, ni);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -221,7 +223,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
   seek_a(first);
   seek_b(first);
   const unsigned char *const abase = acur, *const bbase = bcur;
-  auto slice_of = [&](const unsigned char* base, int s) { return base + min(s, nch - 1) * kTlSlice; };      // (one tile)
+  auto slice_of = [&](const unsigned char* base, int s) { return base + min(s, nch - 1) * kTlSlice; };
   auto first_loads = [&](int s) __attribute__((always_inline)) {
     if (s < kBBufs) {
 #pragma unroll
@@ -230,7 +232,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
         bcur += kTlSlice;
         if (--bleft == 0) wrap_b();
       } else {
-        bcur = slice_of(bbase, s + 1);
+        bcur += --bleft > 0 ? kTlSlice : 0;
       }
     }
 #pragma unroll
@@ -239,7 +241,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
       acur += kTlSlice;
       if (--aleft == 0) wrap_a();
     } else {
-      acur = slice_of(abase, s + 1);
+      acur += --aleft > 0 ? kTlSlice : 0;
     }
   };
   if constexpr (kStream) {
@@ -264,7 +266,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0.f;
 
-    // One slice i (of the one tile; several tiles have cursors): its two steps, and the loads of slices i + kABufs and i + kBBufs.
+    // One slice i: its two steps, and the loads of slices i + kABufs and i + kBBufs (kOrdered: by the number, as there is one tile).
     auto slice = [&](int i, bool behind) __attribute__((always_inline)) {
       const int anext = abuf == kABufs - 1 ? 0 : abuf + 1;
       const int bnext = bbuf == kBBufs - 1 ? 0 : bbuf + 1;
@@ -278,7 +280,7 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
       else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kAfter) : "memory");
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (!kStream) {
+      if constexpr (kOrdered) {
         acur = slice_of(abase, i + kABufs);
         bcur = slice_of(bbase, i + kBBufs);
       }
@@ -289,13 +291,13 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
             if (j < kBPer) load_b(bbuf, j);
             else load_a(abuf, j - kBPer);
           }
-        // (several: the first loads ahead of the products, 382 x 28672 x 4544 198.0 -> 192.2 us)
-        if constexpr (MI == 2 && NT > 1)
-          if (ni == 0) __builtin_amdgcn_sched_barrier(0);
       });
       if constexpr (kStream) {
         acur += kTlSlice;
         bcur += kTlSlice;
+      } else if constexpr (!kOrdered) {
+        acur += --aleft > 0 ? kTlSlice : 0;
+        bcur += --bleft > 0 ? kTlSlice : 0;
       }
       abuf = anext;
       bbuf = bnext;
@@ -314,8 +316,10 @@ __device__ __forceinline__ void lm_tile_wave(const LmParams& P, unsigned char* l
         if (aleft == 0) wrap_a();
         if (bleft == 0) wrap_b();
       }
-    } else {
+    } else if constexpr (kOrdered) {
       for (int i = 0; i < nch; ++i) slice(i, false);
+    } else {
+      for (int left = nch; left > 0; --left) slice(0, false);
     }
     if constexpr (!kStream) {
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
